@@ -784,7 +784,7 @@ def run_helmholtz(wname, args):
             roof["achieved_8flop_equivalent"] = 8.0 * work / t_dom / 1e12
         # redundant rows read once, results written once (complex64)
         alg_bytes = S_red * nrhs * 8 + tree.n * nrhs * 8
-    elif nrhs == 1:
+    else:
         # one right-hand side on the matrix cores, target boxes as the columns; the
         # redundant evaluation call from the plan is the product launch alone
         kern, src, t_dom = "k_helm_mfma_cols_red", "helmholtz_cols.hip", t_red / K
@@ -796,10 +796,6 @@ def run_helmholtz(wname, args):
         roof["achieved_8flop_equivalent"] = 8.0 * work / t_dom / 1e12
         # redundant rows read once, results written once (complex64), G blocks read once
         alg_bytes = S_red * 8 + tree.n * 8 + 27 * 4096 * 8
-    else:
-        kern, src, t_dom = "k_helmholtz_red", "helmholtz.hip", t_red / K
-        roof = {"bound": "alu", "peak": FP32_VALU_PEAK_TFLOPS}
-        alg_bytes = S_red * nrhs * 8 + tree.n * nrhs * 8
     ach = flops / t_dom / 1e12
     traffic = pmc_traffic(kern, wname, src)
     roof.update({"kernel": kern, "achieved": ach, "unit": "TFLOP/s", "frac": ach / roof["peak"],

@@ -86,9 +86,7 @@ typedef enum { P2P_GATHER = 0, P2P_REDUNDANT = 1 } p2p_layout;
  * single once per (target leaf, source)) and for the per-target accumulation
  * of single-precision partial sums (gravity: at most 32 pair terms each;
  * Helmholtz: the 64 terms of one near box, each box's FP32 partial product
- * added into a double sum per target and right-hand side).  Helmholtz
- * blocks run on FP32 matrix cores when there is one right-hand side or a
- * multiple of 32.
+ * added into a double sum per target and right-hand side).
  * P2P_FP32 (Helmholtz only; gravity calls return P2P_EUNSUPPORTED): as
  * FP32_MIXED, but the sums over all near boxes stay in single precision.
  * Layouts built with FP32_MIXED and FP32 hold the same payload and serve
@@ -332,9 +330,10 @@ p2p_status p2p_eval_gravity_noalloc(const p2p_tree *tree, const p2p_nbrs *nbrs, 
  * chunk) items in tree order from eight queues, one per XCD, each over a
  * contiguous eighth of the items, a wave whose own queue is empty taking from
  * the others in turn (neighbouring boxes meet in one XCD's L2); instances whose k h
- * agree to 1e-12 share one set of G blocks.  nrhs == 1 runs on the matrix
- * cores of its precision (v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64) with
- * tiles of 16 target boxes as the columns of the product.  `tile` (host int32[4], may be
+ * agree to 1e-12 share one set of G blocks.  Every other
+ * nrhs, and FP64, runs on the matrix cores of its precision
+ * (v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64) with tiles of 16 (target
+ * box, right-hand side) pairs as the columns of the product.  `tile` (host int32[4], may be
  * NULL = default {4, 2, 64 or 32, 1}) is the launch shape the autotuner picked:
  * tile[0] = waves per workgroup (1, 2 or 4), tile[1] = workgroups per compute
  * unit (1..16), tile[2] = right-hand sides per wave (32 or 64, dividing nrhs),
@@ -352,8 +351,7 @@ p2p_status p2p_eval_helmholtz(const p2p_tree *tree, const p2p_nbrs *nbrs, const 
  * reused by every box and every call).  A plan holds, in a caller-owned device
  * buffer, what p2p_eval_helmholtz otherwise rebuilds on every call: the
  * instances' parameters, the G blocks of every distinct k h built in double
- * precision (rounded to single on the FP32 matrix-core paths) or the G(d^2)
- * tables (vector path).  Host struct. */
+ * precision (rounded to single on the FP32 paths).  Host struct. */
 typedef struct {
     void *buf;            /* in: device buffer, 256-byte aligned; NULL asks for the size */
     size_t bytes;         /* in: size of buf; out (buf == NULL): bytes needed */

@@ -803,29 +803,28 @@ extern "C" p2p_status p2p_eval_gravity_remote(const p2p_tree *tree, const p2p_tr
 namespace {
 
 // Everything a Helmholtz evaluation derives from its arguments on the host:
-// the path (matrix cores multi-RHS or single RHS, or the vector kernel), the
-// launch shape, the distinct k h values (one G table or set of G blocks each),
-// and the layout of the set-up buffer.  The set-up buffer (the plan) holds the
-// instances' parameters and the G tables or blocks; it
-// is filled by helm_fill, either on every call (p2p_eval_helmholtz, in the
+// the path (columns of right-hand sides, or columns of (box, right-hand side)
+// pairs), the launch shape, the distinct k h values (one set of G blocks
+// each), and the layout of the set-up buffer.  The set-up buffer (the plan)
+// holds the instances' parameters and the G blocks; it is filled by helm_fill, either on every call (p2p_eval_helmholtz, in the
 // workspace) or once (p2p_helmholtz_prepare, in a caller buffer).
 struct HelmSetup {
     p2p_precision prec;
     int32_t nrhs;
-    bool fp64, mfma, cols, blk, inline_params;
+    bool fp64, mfma, cols, inline_params;
     int waves_per_wg = 4, wg_per_cu = 2, rhs_tile = 32, copies = 1;
     int32_t n_grids = 0, n_tables = 0, n_tiles = 0;
     std::vector<double> khs;
     std::vector<int32_t> itab;
     std::vector<float> iscale;
-    size_t o_k = 0, o_kh = 0, o_itab = 0, o_isc = 0, o_tiles = 0, param_bytes = 0;
+    std::vector<int32_t> first;   // column path: first tile, then first box, of each instance (and the totals)
+    size_t o_kh = 0, o_itab = 0, o_isc = 0, o_first = 0, param_bytes = 0;
     HelmInline inl{};
 };
 
 // Device arrays of the set-up inside an arena (null pointers when sizing).
 struct HelmSetupBufs {
     char *params = nullptr;
-    char *table = nullptr;
     float2 *blocks = nullptr;
 };
 
@@ -842,11 +841,14 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     h->nrhs = nrhs;
     h->n_grids = n_grids;
     h->fp64 = prec == P2P_FP64;
-    // the matrix-core product addresses a box's 64 source rows with 32-bit byte
-    // offsets (buffer loads), so nrhs above 2^20 takes the vector kernel
+    // the product with right-hand sides as columns addresses a box's 64 source
+    // rows with 32-bit byte offsets (buffer loads), so nrhs above 2^20 takes
+    // the column path
     h->mfma = !h->fp64 && nrhs % 32 == 0 && nrhs <= (1 << 20);
-    // one RHS: matrix cores (FP32, or FP64 on the FP64 matrix instructions) with the target boxes as columns
-    h->cols = nrhs == 1;
+    // every other count, and FP64 (on the FP64 matrix instructions): (box,
+    // right-hand side) pairs as columns, which wastes at most 15 columns per
+    // instance whatever nrhs is
+    h->cols = !h->mfma;
     h->rhs_tile = (nrhs % 64 == 0) ? 64 : 32;
     if (tile) {
         if (!h->mfma) return fail(P2P_EINVAL, "tile applies to the matrix-core path (FP32_MIXED, nrhs % 32 == 0)");
@@ -881,86 +883,78 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
         h->iscale[g] = static_cast<float>(1.0 / grids[g].h);
     }
     h->n_tables = static_cast<int32_t>(h->khs.size());
-    h->blk = h->mfma || h->cols;
-    h->n_tiles = h->cols ? helmholtz_cols_tiles(grids, n_grids, nullptr) : 0;
     if (h->cols) {
         // every box of a grid instance is a leaf, instances in order
-        int64_t boxes = 0;
-        for (int32_t g = 0; g < n_grids; ++g)
-            boxes += static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
+        int64_t boxes = 0, tiles = 0;
+        h->first.assign(2 * static_cast<size_t>(n_grids + 1), 0);
+        for (int32_t g = 0; g < n_grids; ++g) {
+            const int64_t nb = static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
+            boxes += nb;
+            tiles += helmholtz_cols_tiles(nb, nrhs);
+            if (tiles > INT32_MAX) return fail(P2P_EINVAL, "nrhs too large for these grids");
+            h->first[g + 1] = static_cast<int32_t>(tiles);
+            h->first[n_grids + 1 + g + 1] = static_cast<int32_t>(boxes);
+        }
         if (boxes != tree->n_leaves) return fail(P2P_EINVAL, "tree leaves do not match the grids' boxes");
+        h->n_tiles = static_cast<int32_t>(tiles);
     }
-    // the host parameters (h and k per instance, k h per table, the table and
-    // 1/h of each instance, the column tiles) travel in one copy: each small
-    // copy costs a blit launch, a sizeable part of a call on a small grid
-    h->o_k = 8 * static_cast<size_t>(n_grids);
-    h->o_kh = h->o_k + 8 * static_cast<size_t>(n_grids);
+    // the host parameters (h per instance, k h per table, the table and 1/h of
+    // each instance, the column tiles) travel in one copy: each small copy
+    // costs a blit launch, a sizeable part of a call on a small grid
+    h->o_kh = 8 * static_cast<size_t>(n_grids);
     h->o_itab = h->o_kh + 8 * static_cast<size_t>(h->n_tables);
     h->o_isc = h->o_itab + 4 * static_cast<size_t>(n_grids);
-    h->o_tiles = h->o_isc + 4 * static_cast<size_t>(n_grids);
-    h->param_bytes = h->o_tiles + 8 * static_cast<size_t>(h->n_tiles);
-    // a single-RHS call on a grid of few instances takes its parameters in the
-    // kernel arguments; every other call uploads them
+    h->o_first = h->o_isc + 4 * static_cast<size_t>(n_grids);
+    h->param_bytes = h->o_first + 4 * h->first.size();
+    // a column-path call on few instances takes its parameters in the kernel
+    // arguments; every other call uploads them
     h->inline_params = h->cols && n_grids <= kInlineGrids && h->n_tables <= kInlineGrids;
     if (h->inline_params) {
         HelmInline &inl = h->inl;
         inl.n_grids = n_grids;
         inl.n_tables = h->n_tables;
-        int32_t tf = 0, lf = 0;
+        for (int32_t g = 0; g <= n_grids; ++g) {
+            inl.tile_first[g] = h->first[g];
+            inl.leaf_first[g] = h->first[n_grids + 1 + g];
+        }
         for (int32_t g = 0; g < n_grids; ++g) {
-            const int32_t nb = (grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
-            inl.tile_first[g] = tf;
-            inl.leaf_first[g] = lf;
             inl.itab[g] = h->itab[g];
             inl.iscale[g] = h->iscale[g];
             inl.iscale64[g] = 1.0 / grids[g].h;
-            tf += (nb + kHelmColBoxes - 1) / kHelmColBoxes;
-            lf += nb;
         }
-        inl.tile_first[n_grids] = tf;
-        inl.leaf_first[n_grids] = lf;
         for (int32_t t = 0; t < h->n_tables; ++t) inl.kh[t] = h->khs[t];
     }
     return P2P_OK;
 }
 
 HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h) {
-    const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     HelmSetupBufs b;
     b.params = ar.take<char>(h.param_bytes);
-    if (!h.blk) b.table = ar.take<char>(static_cast<size_t>(h.n_grids) * kTableLen * csize);
-    // the G blocks: multi-RHS float4 entries; single RHS float2 (FP64: double2) entries and 64 zero
-    // entries after them
-    if (h.blk)
-        b.blocks = ar.take<float2>(h.cols ? (static_cast<size_t>(h.n_tables) * 27 * 4096 + 64) * (h.fp64 ? 2 : 1)
-                                          : static_cast<size_t>(h.n_tables) * h.copies * 27 * 4096 * 2);
+    // the G blocks: float4 entries, or on the column path float2 (FP64: double2)
+    // entries and 64 zero entries after them
+    b.blocks = ar.take<float2>(h.cols ? (static_cast<size_t>(h.n_tables) * 27 * 4096 + 64) * (h.fp64 ? 2 : 1)
+                                      : static_cast<size_t>(h.n_tables) * h.copies * 27 * 4096 * 2);
     return b;
 }
 
 // Fill the set-up buffer: parameters uploaded (unless they travel inline),
-// the G tables (vector path) or blocks (matrix cores).
-p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_tree *tree, const p2p_nbrs *nbrs,
-                     const p2p_grid *grids, hipStream_t s) {
-    double *d_h = reinterpret_cast<double *>(b.params);
-    double *d_k = reinterpret_cast<double *>(b.params + h.o_k);
+// the G blocks.  A set-up for several right-hand sides or many instances is
+// refused under capture, as the interface states.
+p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid *grids, hipStream_t s) {
     double *d_kh = reinterpret_cast<double *>(b.params + h.o_kh);
+    if (!h.inline_params || h.nrhs > 1)
+        P2P_TRY(no_capture(s, "a Helmholtz set-up for several right-hand sides or many instances"));
     if (!h.inline_params) {
-        P2P_TRY(no_capture(s, "a Helmholtz set-up that uploads its parameters"));
         std::vector<char> hp(h.param_bytes);
-        for (int32_t g = 0; g < h.n_grids; ++g) {
-            std::memcpy(hp.data() + 8 * g, &grids[g].h, 8);
-            std::memcpy(hp.data() + h.o_k + 8 * g, &grids[g].k, 8);
-        }
+        for (int32_t g = 0; g < h.n_grids; ++g) std::memcpy(hp.data() + 8 * g, &grids[g].h, 8);
         std::memcpy(hp.data() + h.o_kh, h.khs.data(), 8 * static_cast<size_t>(h.n_tables));
         std::memcpy(hp.data() + h.o_itab, h.itab.data(), 4 * static_cast<size_t>(h.n_grids));
         std::memcpy(hp.data() + h.o_isc, h.iscale.data(), 4 * static_cast<size_t>(h.n_grids));
-        if (h.cols) helmholtz_cols_tiles(grids, h.n_grids, reinterpret_cast<int32_t *>(hp.data() + h.o_tiles));
+        if (h.cols) std::memcpy(hp.data() + h.o_first, h.first.data(), 4 * h.first.size());
         // a copy from pageable memory has read its source when it returns
         P2P_HIP(hipMemcpyAsync(b.params, hp.data(), h.param_bytes, hipMemcpyHostToDevice, s));
     }
-    if (h.blk) P2P_TRY(launch_green_blocks(d_kh, h.inl, h.n_tables, h.copies, h.cols, h.fp64, b.blocks, s));
-    else P2P_TRY(launch_green_tables(d_h, d_k, h.n_grids, h.fp64, b.table, s));
-    return P2P_OK;
+    return launch_green_blocks(d_kh, h.inl, h.n_tables, h.copies, h.cols, h.fp64, b.blocks, s);
 }
 
 // Argument checks of an evaluation that come after the workspace query.
@@ -988,8 +982,8 @@ p2p_status helm_check_call(const HelmSetup &h, const p2p_tree *tree, const p2p_n
 }
 
 // The evaluation from a filled set-up: the sorted copy of q (GATHER), then one
-// product launch (the matrix-core queues' counters are zeroed first; one RHS on a
-// grid of few tiles adds the join of the two halves of each tile).
+// product launch (the work queues' counters are zeroed first; on the column path
+// few tiles add the join of the two halves of each tile).
 p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter, char *sorted, double2 *parts,
                     const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
                     const void *q, void *u, int32_t conj, hipStream_t s) {
@@ -1008,43 +1002,7 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     }
     const int32_t *d_itab = reinterpret_cast<const int32_t *>(b.params + h.o_itab);
     const float *d_iscale = reinterpret_cast<const float *>(b.params + h.o_isc);
-    const int32_t *d_tiles = reinterpret_cast<const int32_t *>(b.params + h.o_tiles);
-    if (h.cols || h.mfma) {
-        HelmholtzMfmaArgs a{};
-        a.L = L;
-        a.key_bits = tree->key_bits;
-        a.leaf_start = tree->leaf_start;
-        a.leaf_key = tree->leaf_key;
-        a.perm = tree->perm;
-        a.nbr_start = nbrs->nbr_start;
-        a.nbr_idx = nbrs->nbr_idx;
-        a.red_start = redundant ? red->red_start : nullptr;
-        a.red_row = tiled ? red->red_row : nullptr;
-        a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
-        a.blocks = b.blocks;
-        const int64_t nblk = static_cast<int64_t>(h.n_tables) * 27 * 4096;
-        a.zeros = !h.cols ? nullptr
-                  : h.fp64 ? reinterpret_cast<const float2 *>(reinterpret_cast<const double2 *>(b.blocks) + nblk)
-                           : b.blocks + nblk;
-        a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
-        a.n = n;
-        a.parts = parts;
-        a.inst_table = d_itab;
-        a.inst_scale = d_iscale;
-        a.conj = conj;
-        a.comp = h.prec == P2P_FP32_MIXED;
-        a.u = static_cast<float2 *>(u);
-        if (h.cols) {
-            a.copies = 1;
-            a.nrhs = 1;
-            return launch_helmholtz_mfma_cols(a, d_tiles, h.inl, h.n_tiles, redundant, h.fp64, s);
-        }
-        a.copies = h.copies;
-        a.counter = counter;
-        a.nrhs = nrhs;
-        return launch_helmholtz_mfma(a, redundant, h.waves_per_wg, h.wg_per_cu, h.rhs_tile, s);
-    }
-    HelmholtzArgs a{};
+    HelmholtzMfmaArgs a{};
     a.L = L;
     a.key_bits = tree->key_bits;
     a.leaf_start = tree->leaf_start;
@@ -1054,24 +1012,44 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.nbr_idx = nbrs->nbr_idx;
     a.red_start = redundant ? red->red_start : nullptr;
     a.red_row = tiled ? red->red_row : nullptr;
-    a.src = redundant ? red->planes[0] : sorted;
-    a.table = b.table;
+    a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
+    a.blocks = b.blocks;
+    const int64_t nblk = static_cast<int64_t>(h.n_tables) * 27 * 4096;
+    a.zeros = !h.cols ? nullptr
+              : h.fp64 ? reinterpret_cast<const float2 *>(reinterpret_cast<const double2 *>(b.blocks) + nblk)
+                       : b.blocks + nblk;
+    a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
+    a.n = n;
+    a.parts = parts;
+    a.inst_table = d_itab;
+    a.inst_scale = d_iscale;
     a.nrhs = nrhs;
     a.conj = conj;
     a.comp = h.prec == P2P_FP32_MIXED;
-    a.u = u;
-    return launch_helmholtz(a, redundant, h.fp64, s);
+    a.u = static_cast<float2 *>(u);
+    if (h.cols) {
+        a.copies = 1;
+        const int32_t *first = reinterpret_cast<const int32_t *>(b.params + h.o_first);
+        const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids};
+        return launch_helmholtz_mfma_cols(a, ht, h.inl, h.n_tiles, redundant, h.fp64, s);
+    }
+    a.copies = h.copies;
+    a.counter = counter;
+    return launch_helmholtz_mfma(a, redundant, h.waves_per_wg, h.wg_per_cu, h.rhs_tile, s);
 }
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
-// (matrix cores, several RHS), the sorted copy of q (GATHER) and, for one RHS,
-// the two partial results of tiles whose offsets two workgroups share.
+// (right-hand sides as columns), the sorted copy of q (GATHER) and, on the
+// column path, the two partial results of tiles whose offsets two workgroups
+// share: at most half as many tiles as the card has CUs, so no more than
+// kMaxSplitTiles on any card, and larger calls hold none.
+constexpr int32_t kMaxSplitTiles = 256;
 void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, int32_t **counter, char **sorted,
                     double2 **parts) {
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     *counter = h.mfma ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
-    *parts = h.cols ? ar.take<double2>(2 * static_cast<size_t>(n)) : nullptr;
+    *parts = h.cols && h.n_tiles <= kMaxSplitTiles ? ar.take<double2>(2 * static_cast<size_t>(n) * h.nrhs) : nullptr;
 }
 
 p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red,
@@ -1092,7 +1070,7 @@ p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2
     if (ws_query(ws, ws_bytes, ar, &st)) return st;
     // every argument is checked before the set-up is queued
     P2P_TRY(helm_check_call(h, tree, nbrs, red, layout, q, u, conj));
-    P2P_TRY(helm_fill(h, b, tree, nbrs, grids, s));
+    P2P_TRY(helm_fill(h, b, grids, s));
     return helm_run(h, b, counter, sorted, parts, tree, nbrs, red, layout, q, u, conj, s);
 }
 
@@ -1161,7 +1139,7 @@ extern "C" p2p_status p2p_helmholtz_prepare(const p2p_tree *tree, const p2p_nbrs
         return fail(P2P_EINVAL, "plan->bytes too small: need " + std::to_string(ar.used) + ", got " +
                                     std::to_string(plan->bytes));
     if ((reinterpret_cast<uintptr_t>(plan->buf) & 255u) != 0) return fail(P2P_EINVAL, "plan->buf must be 256-byte aligned");
-    P2P_TRY(helm_fill(h, b, tree, nbrs, grids, as_stream(stream)));
+    P2P_TRY(helm_fill(h, b, grids, as_stream(stream)));
     plan->prec = prec;
     plan->nrhs = nrhs;
     plan->tile[0] = h.waves_per_wg;

@@ -1,6 +1,7 @@
-// Single right-hand side of the near-field Helmholtz sum on the matrix cores,
-// FP32 and FP64 (the dense regular case of Sec. 5.1 with one right-hand side),
-// the target boxes taken as the columns of the product.  Kept in a file of its
+// Near-field Helmholtz sum on the matrix cores with the (target box,
+// right-hand side) pairs as the columns of the product, FP32 and FP64 (the
+// dense regular case of Sec. 5.1): one right-hand side, counts that are no
+// multiple of 32, and every count in FP64.  Kept in a file of its
 // own: it is compiled with the matrix accumulators in ordinary vector
 // registers (-amdgpu-mfma-vgpr-form), so the FP32 kernel's per-offset FP64
 // flush reads them without a copy out of the accumulation registers.
@@ -11,19 +12,25 @@
 namespace p2p {
 namespace {
 
-// Single right-hand side on matrix cores: the target boxes become the columns
-// of the product.  For a tile of up to 16 boxes b_0..b_15 of one instance,
+// A column is a (target box, right-hand side) pair: on a regular grid G_o
+// depends only on the box offset o, so boxes and right-hand sides are alike to
+// the product.  For a tile of up to 16 consecutive columns (b_j, r_j) of one
+// instance, numbered box * nrhs + rhs,
 //     U (64 x 16) = sum_o G_o (64 x 64) Q_o (64 x 16),
-// column j of Q_o holding the 64 sources of the box at offset o from b_j (a
-// zero column where b_j has no such neighbour, at the faces of the grid), so
-// every column of an instruction shares the one G_o.  v_mfma_f32_16x16x4f32,
+// column j of Q_o holding right-hand side r_j of the 64 sources of the box at
+// offset o from b_j (a zero column where b_j has no such neighbour, at the
+// faces of the grid), so every column of an instruction shares the one G_o.
+// Bound by the matrix cores.  It replaced a vector kernel (a wave per box, G
+// from a table in LDS, one pass per right-hand side, bound by the LDS reads of
+// G): 32^3 grid, 8 right-hand sides, FP64: 545 to 56 us per product; five
+// grids up to 40^3, 20 right-hand sides, FP32: 3040 to 563 us.  v_mfma_f32_16x16x4f32,
 // complex as three real products; lane l supplies A[l%16][l/16] and
 // B[l/16][l%16], and accumulator register r of lane l holds row 4 (l/16) + r,
 // column l%16.  A workgroup of 4 wavefronts owns a tile; wave w takes the
 // offsets o = w, w + 4, ... for all 64 targets (four row tiles, 12
 // instructions per k-step of 4 sources) with a deep operand prefetch, and the
 // four partial products are summed through LDS at the end.  The workgroup
-// first maps every (offset, column) to the first row of its sources -- the
+// first maps every (offset, box) to the first row of its sources -- the
 // sorted rows of the neighbour box (gather) or its place in the target's
 // segment (redundant) -- from the tile's near lists, which are one contiguous
 // run of the CSR.
@@ -35,44 +42,61 @@ static_assert(kColWaves == 4, "wave w finishes row tile w of the four");
 constexpr int kColPrefG = 3;
 constexpr int kColPrefQ = 7;
 
-// The column tile of workgroup b: its first box A0, box count cnt, G table tab
-// and 1/h of its instance (sc in float; sc64 in double from inl.iscale64 or
-// inst_h, when inst_h or the inline parameters are given).
-__device__ inline void col_tile(int key_bits, const int32_t *__restrict__ tiles, const HelmInline &inl,
-                                const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ inst_table,
-                                const float *__restrict__ inst_scale, const double *__restrict__ inst_h, int32_t b,
-                                int32_t &A0, int32_t &cnt, int32_t &tab, float &sc, double &sc64) {
-    sc64 = 1.0;
+// The column tile of workgroup b: the instance's first leaf, the tile's first
+// column c0 among the instance's columns (column = box * nrhs + right-hand
+// side) and column count cnt, the G table and 1/h of the instance (sc in
+// float; sc64 in double from inl.iscale64 or inst_h, when inst_h or the inline
+// parameters are given).  Called by whole wavefronts: with uploaded parameters
+// the lanes compare b with the instances' first tiles, so the search is one
+// round of loads for up to 64 instances.
+struct ColTile {
+    int32_t leaf0, cnt, tab;
+    int64_t c0;
+    float sc;
+    double sc64;
+};
+__device__ inline ColTile col_tile(const HelmInline &inl, const HelmTiles &ht, int32_t nrhs,
+                                   const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale,
+                                   const double *__restrict__ inst_h, int32_t b) {
+    ColTile t;
+    t.sc = 1.f;
+    t.sc64 = 1.0;
+    t.tab = 0;
+    int32_t tf = 0, lf = 0, lf1 = 0;
     if (inl.n_grids > 0) {
-        int32_t tf = 0, lf = 0, lf1 = 0;
-        tab = 0;
-        sc = 1.f;
 #pragma unroll
         for (int i = 0; i < kInlineGrids; ++i)
             if (i < inl.n_grids && b >= inl.tile_first[i]) {
                 tf = inl.tile_first[i];
                 lf = inl.leaf_first[i];
                 lf1 = inl.leaf_first[i + 1];
-                tab = inl.itab[i];
-                sc = inl.iscale[i];
-                sc64 = inl.iscale64[i];
+                t.tab = inl.itab[i];
+                t.sc = inl.iscale[i];
+                t.sc64 = inl.iscale64[i];
             }
-        A0 = lf + kColBoxes * (b - tf);
-        cnt = min(kColBoxes, lf1 - A0);
     } else {
-        A0 = tiles[2 * b];
-        cnt = tiles[2 * b + 1];
-        const int g = static_cast<int>(leaf_key[A0] >> (3 * key_bits));
-        tab = inst_table ? inst_table[g] : 0;
-        sc = inst_scale ? inst_scale[g] : 1.f;
-        if (inst_h) sc64 = 1.0 / inst_h[g];
+        int g = -1;   // instances whose first tile is at most b, less one
+        for (int32_t i0 = 0; i0 < ht.n_grids; i0 += 64) {
+            const int32_t i = i0 + static_cast<int32_t>(threadIdx.x & 63);
+            g += __popcll(__ballot(i < ht.n_grids && ht.tile_first[min(i, ht.n_grids - 1)] <= b));
+        }
+        tf = ht.tile_first[g];
+        lf = ht.leaf_first[g];
+        lf1 = ht.leaf_first[g + 1];
+        t.tab = inst_table[g];
+        if (inst_scale) t.sc = inst_scale[g];
+        if (inst_h) t.sc64 = 1.0 / inst_h[g];
     }
+    t.leaf0 = lf;
+    t.c0 = static_cast<int64_t>(kColBoxes) * (b - tf);
+    t.cnt = static_cast<int32_t>(min<int64_t>(kColBoxes, static_cast<int64_t>(lf1 - lf) * nrhs - t.c0));
+    return t;
 }
 
-// The (offset, column) map of a tile in LDS: the first source row of every
-// (offset, column) from the tile's near lists (one contiguous run of the CSR;
-// -1 where the column has no such neighbour), and each column's first sorted
-// target row.
+// The (offset, box) map of a tile in LDS: the first source row of every
+// (offset, box) from the near lists of the tile's boxes (one contiguous run of
+// the CSR; -1 where the box has no such neighbour), and each box's first
+// sorted target row.
 struct ColMap {
     int64_t row[27][kColBoxes];
     int64_t nstart[kColBoxes + 1];
@@ -81,7 +105,7 @@ struct ColMap {
     int32_t tstart[kColBoxes];    // its first sorted target row
 };
 
-// Fills m; called by the whole workgroup (64 kColWaves threads), ends with a
+// Fills m for the cnt boxes from leaf A0; called by the whole workgroup (64 kColWaves threads), ends with a
 // barrier.  Each column's list start, key, segment start and first target row
 // come in one round of loads; then the entries, two per thread with their
 // loads issued together: at most 27 per box, so one round covers a tile.
@@ -141,13 +165,38 @@ __device__ void col_map(ColMap &m, int key_bits, int32_t A0, int32_t cnt, const 
     __syncthreads();
 }
 
+// Column li of a tile: its box (an index into the map) and right-hand side,
+// the first leaf A0 of the tile's boxes and their number.
+struct ColLane {
+    int32_t A0, boxes, box, rhs;
+};
+template <bool ONE>
+__device__ inline ColLane col_lane(const ColTile &t, int32_t nrhs, int li) {
+    ColLane l;
+    if constexpr (ONE) {
+        l.A0 = t.leaf0 + static_cast<int32_t>(t.c0);
+        l.boxes = t.cnt;
+        l.box = li;
+        l.rhs = 0;
+    } else {
+        const int64_t b0 = t.c0 / nrhs;
+        const int32_t r0 = static_cast<int32_t>(t.c0 - b0 * nrhs);   // < nrhs; r0 + 15 may pass 2^31
+        l.A0 = t.leaf0 + static_cast<int32_t>(b0);
+        l.boxes = static_cast<int32_t>((static_cast<int64_t>(r0) + t.cnt - 1) / nrhs) + 1;
+        const uint32_t c = static_cast<uint32_t>(r0) + static_cast<uint32_t>(min(li, t.cnt - 1));
+        l.box = static_cast<int32_t>(c / static_cast<uint32_t>(nrhs));
+        l.rhs = static_cast<int32_t>(c - static_cast<uint32_t>(l.box) * static_cast<uint32_t>(nrhs));
+    }
+    return l;
+}
+
 // H workgroups per tile as in k_helm_mfma_cols64 below (H = 2 on grids with at
 // most half as many tiles as CUs): each part then stores its result, the FP64
 // sums or the FP32 tile, in sorted order to parts[p][.] as double2, and
 // k_join_parts adds the two in double and rounds the sum once.
-template <bool RED, bool CONJ, bool COMP, int H>
+template <bool RED, bool CONJ, bool COMP, bool ONE, int H>
 __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
-    int key_bits, const int32_t *__restrict__ tiles, HelmInline inl, const int32_t *__restrict__ leaf_start,
+    int key_bits, HelmTiles ht, HelmInline inl, int32_t nrhs, const int32_t *__restrict__ leaf_start,
     const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ perm,
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
@@ -163,15 +212,14 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
     __shared__ double s_redd[COMP ? kColWaves * 4 * 2 * 4 * 64 : 1];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // the tile: its first box, its box count, the G table and 1/h of its instance
-    int32_t A0, cnt, tab;
-    float sc;
-    double sc64;
     const int32_t b = static_cast<int32_t>(blockIdx.x) / H, part = static_cast<int32_t>(blockIdx.x) % H;
-    col_tile(key_bits, tiles, inl, leaf_key, inst_table, inst_scale, nullptr, b, A0, cnt, tab, sc, sc64);
-    col_map<RED>(sm, key_bits, A0, cnt, leaf_start, leaf_key, nbr_start, nbr_idx, red_start, red_row);
-
+    const ColTile ct = col_tile(inl, ht, nrhs, inst_table, inst_scale, nullptr, b);
+    const int32_t cnt = ct.cnt, tab = ct.tab;
+    const float sc = ct.sc;
     const int li = lane & 15, kq = lane >> 4;
+    const ColLane cl = col_lane<ONE>(ct, nrhs, li);
+    col_map<RED>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start, red_row);
+
     const int vw = part * kColWaves + w;
     const float2 *__restrict__ gbase = blocks + static_cast<int64_t>(tab) * (27 * 4096);
     // Every instruction of the k-step loop that is not a matrix product or a load
@@ -194,11 +242,14 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
     const int goff = (kq * 16 + li) * 4;
     auto ptrs = [&](int idx, const float2 *&Gs, const float2 *&Qp) {
         const int o = vw + VW * idx;
-        const int64_t row = o < 27 ? sm.row[o][li] : int64_t(-1);
+        const int64_t row = o < 27 ? sm.row[o][cl.box] : int64_t(-1);
         Gs = gbase + (o < 27 ? o : 0) * 4096;
-        Qp = (row >= 0 ? src + row : zeros) + kq;
+        if constexpr (ONE)
+            Qp = (row >= 0 ? src + row : zeros) + kq;
+        else
+            Qp = row >= 0 ? src + (row + kq) * nrhs + cl.rhs : zeros;
     };
-    int32_t dst[4] = {0, 0, 0, 0};
+    int64_t dst[4] = {0, 0, 0, 0};
     // The complex product in three real products (the 3M form, as in the
     // multi-RHS kernel): pa = sum Re G Re Q, pb = sum Im G Im Q,
     // pc = sum (Re G + Im G)(Re Q + Im Q); U = G Q: Re = pa - pb,
@@ -254,7 +305,22 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
             gv[2] = make_float2(hi.x, hi.y);
             gv[3] = make_float2(hi.z, hi.w);
         };
-        auto load_q = [&](int st) { qbuf[st % (kColPrefQ + 1)] = Qs[st / 16][(st % 16) * 4]; };
+        // several right-hand sides: a running pointer over the slot's source
+        // rows, 4 rows per k-step (absent neighbours stay on the zero entry)
+        const float2 *qp = nullptr;
+        int64_t qs = 0;
+        auto load_q = [&](int st) {
+            if constexpr (ONE) {
+                qbuf[st % (kColPrefQ + 1)] = Qs[st / 16][(st % 16) * 4];
+            } else {
+                if (st % 16 == 0) {
+                    qp = Qs[st / 16];
+                    qs = qp == zeros ? 0 : 4 * static_cast<int64_t>(nrhs);
+                }
+                qbuf[st % (kColPrefQ + 1)] = *qp;
+                qp += qs;
+            }
+        };
 #pragma unroll
         for (int st = 0; st < kColPrefG; ++st) load_g(st);
 #pragma unroll
@@ -265,8 +331,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
         if (li < cnt) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int32_t sr = sm.tstart[li] + 16 * w + 4 * kq + r;
+                const int32_t sr = sm.tstart[cl.box] + 16 * w + 4 * kq + r;
                 dst[r] = H == 1 ? perm[sr] : sr;
+                if constexpr (!ONE) dst[r] = dst[r] * nrhs + cl.rhs;
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -359,20 +426,19 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols(
 }
 
 
-// FP64 single right-hand side on the FP64 matrix cores: the same product as
-// k_helm_mfma_cols with v_mfma_f64_16x16x4f64 (four real products per
-// complex one, all sums in double; G blocks in double2, same layout).  Lane l
+// FP64 on the FP64 matrix cores: the same product as k_helm_mfma_cols with
+// v_mfma_f64_16x16x4f64 (all sums in double; G blocks in double2, same layout).  Lane l
 // supplies A[l%16][l/16] and B[l/16][l%16] as in FP32, but accumulator
 // register r of lane l holds row l/16 + 4 r (rows interleaved), column l%16.
 // A tile's 27 offsets may be shared by H workgroups (H = 2 on grids with at
 // most half as many tiles as CUs, so that twice the CUs work): wave w of part
 // p takes offsets o = 4 p + w + 4 H idx.  With H = 2 each part stores its
-// result in sorted order to parts[p][.] (coalesced), and k_join_parts64 adds
+// result in sorted order to parts[p][.] (coalesced), and k_join_parts adds
 // part 0 and part 1 and scatters the sum to the caller's order (FP64 atomic
 // additions at the scattered caller rows took 7 us more on a 48^3 grid).
-template <bool RED, bool CONJ, int H>
+template <bool RED, bool CONJ, bool ONE, int H>
 __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
-    int key_bits, const int32_t *__restrict__ tiles, HelmInline inl, const int32_t *__restrict__ leaf_start,
+    int key_bits, HelmTiles ht, HelmInline inl, int32_t nrhs, const int32_t *__restrict__ leaf_start,
     const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ perm,
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const double2 *__restrict__ src,
@@ -386,13 +452,13 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t b = static_cast<int32_t>(blockIdx.x) / H, part = static_cast<int32_t>(blockIdx.x) % H;
-    int32_t A0, cnt, tab;
-    float sc;
-    double sc64;
-    col_tile(key_bits, tiles, inl, leaf_key, inst_table, nullptr, inst_h, b, A0, cnt, tab, sc, sc64);
-    col_map<RED>(sm, key_bits, A0, cnt, leaf_start, leaf_key, nbr_start, nbr_idx, red_start, red_row);
-
+    const ColTile ct = col_tile(inl, ht, nrhs, inst_table, nullptr, inst_h, b);
+    const int32_t cnt = ct.cnt, tab = ct.tab;
+    const double sc64 = ct.sc64;
     const int li = lane & 15, kq = lane >> 4;
+    const ColLane cl = col_lane<ONE>(ct, nrhs, li);
+    col_map<RED>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start, red_row);
+
     const double2 *__restrict__ gbase = blocks + static_cast<int64_t>(tab) * (27 * 4096);
     // lane (kq, li) reads, at k-step kk, G_o[source 4 kk + kq][targets li, 16 + li, 32 + li, 48 + li]
     // (one 64-byte run) and Q[source 4 kk + kq] of column li; the slots past the 27
@@ -401,11 +467,14 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     const int vw = part * kColWaves + w;
     auto ptrs = [&](int idx, const double2 *&Gs, const double2 *&Qp) {
         const int o = vw + VW * idx;
-        const int64_t row = o < 27 ? sm.row[o][li] : int64_t(-1);
+        const int64_t row = o < 27 ? sm.row[o][cl.box] : int64_t(-1);
         Gs = gbase + (o < 27 ? o : 0) * 4096;
-        Qp = (row >= 0 ? src + row : zeros) + kq;
+        if constexpr (ONE)
+            Qp = (row >= 0 ? src + row : zeros) + kq;
+        else
+            Qp = row >= 0 ? src + (row + kq) * nrhs + cl.rhs : zeros;
     };
-    int32_t dst[4] = {0, 0, 0, 0};
+    int64_t dst[4] = {0, 0, 0, 0};
     // three real products per complex one, as in the FP32 kernel: pa = sum Re G Re Q,
     // pb = sum Im G Im Q, pc = sum (Re G +- Im G)(Re Q + Im Q), the sums formed per k-step
     f64x4 pa[4], pb[4], pc[4];
@@ -423,7 +492,20 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
 #pragma unroll
             for (int rt = 0; rt < 4; ++rt) gv[rt] = g[rt];
         };
-        auto load_q = [&](int st) { qbuf[st % (kColPrefQ + 1)] = Qs[st / 16][(st % 16) * 4]; };
+        const double2 *qp = nullptr;
+        int64_t qs = 0;
+        auto load_q = [&](int st) {
+            if constexpr (ONE) {
+                qbuf[st % (kColPrefQ + 1)] = Qs[st / 16][(st % 16) * 4];
+            } else {
+                if (st % 16 == 0) {
+                    qp = Qs[st / 16];
+                    qs = qp == zeros ? 0 : 4 * static_cast<int64_t>(nrhs);
+                }
+                qbuf[st % (kColPrefQ + 1)] = *qp;
+                qp += qs;
+            }
+        };
 #pragma unroll
         for (int st = 0; st < kColPrefG; ++st) load_g(st);
 #pragma unroll
@@ -433,8 +515,9 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
         if (li < cnt) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int32_t sr = sm.tstart[li] + 16 * w + kq + 4 * r;
+                const int32_t sr = sm.tstart[cl.box] + 16 * w + kq + 4 * r;
                 dst[r] = H == 1 ? perm[sr] : sr;
+                if constexpr (!ONE) dst[r] = dst[r] * nrhs + cl.rhs;
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -488,95 +571,92 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     }
 }
 
-// u[perm[s]] = parts[0][s] + parts[1][s] for every sorted row s, added in
-// double and rounded once.
-__global__ void k_join_parts(const double2 *__restrict__ parts, const int32_t *__restrict__ perm, int64_t n,
-                             float2 *__restrict__ u) {
+// u[perm[s]][r] = parts[0][s][r] + parts[1][s][r] for every sorted row s and
+// right-hand side r, added in double and rounded once (m = rows times
+// right-hand sides).
+template <class C>
+__global__ void k_join_parts(const double2 *__restrict__ parts, const int32_t *__restrict__ perm, int64_t m,
+                             int32_t nrhs, C *__restrict__ u) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double2 a = parts[i], b = parts[n + i];
-    u[perm[i]] = make_float2(static_cast<float>(a.x + b.x), static_cast<float>(a.y + b.y));
-}
-
-// u[perm[s]] = parts[0][s] + parts[1][s] for every sorted row s.
-__global__ void k_join_parts64(const double2 *__restrict__ parts, const int32_t *__restrict__ perm, int64_t n,
-                               double2 *__restrict__ u) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double2 a = parts[i], b = parts[n + i];
-    u[perm[i]] = make_double2(a.x + b.x, a.y + b.y);
+    if (i >= m) return;
+    const double2 a = parts[i], b = parts[m + i];
+    C v;
+    v.x = static_cast<decltype(v.x)>(a.x + b.x);
+    v.y = static_cast<decltype(v.y)>(a.y + b.y);
+    if (nrhs == 1) {
+        u[perm[i]] = v;
+    } else {
+        const int64_t s = i / nrhs;
+        u[static_cast<int64_t>(perm[s]) * nrhs + (i - s * nrhs)] = v;
+    }
 }
 
 }  // namespace
 
-int32_t helmholtz_cols_tiles(const p2p_grid *grids, int32_t n_grids, int32_t *tiles) {
-    int64_t first = 0;
-    int32_t t = 0;
-    for (int32_t g = 0; g < n_grids; ++g) {
-        const int64_t nb = static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
-        for (int64_t b = 0; b < nb; b += kColBoxes, ++t) {
-            if (tiles) {
-                tiles[2 * t] = static_cast<int32_t>(first + b);
-                tiles[2 * t + 1] = static_cast<int32_t>(std::min<int64_t>(kColBoxes, nb - b));
-            }
-        }
-        first += nb;
-    }
-    return t;
+int64_t helmholtz_cols_tiles(int64_t boxes, int32_t nrhs) { return (boxes * nrhs + kColBoxes - 1) / kColBoxes; }
+
+template <bool R, bool C, bool O, int H>
+static void launch_cols64(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                          hipStream_t s) {
+    k_helm_mfma_cols64<R, C, O, H><<<static_cast<unsigned>(n_tiles) * H, 64 * kColWaves, 0, s>>>(
+        a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start, a.red_row,
+        reinterpret_cast<const double2 *>(a.src), reinterpret_cast<const double2 *>(a.blocks),
+        reinterpret_cast<const double2 *>(a.zeros), a.inst_table, a.inst_h, reinterpret_cast<double2 *>(a.u), a.parts,
+        a.n * a.nrhs);
+}
+
+template <bool R, bool C, bool O, int H>
+static void launch_cols32(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                          hipStream_t s) {
+    const unsigned g = static_cast<unsigned>(n_tiles) * H;
+#define P2P_COLS32(M)                                                                                             \
+    k_helm_mfma_cols<R, C, M, O, H><<<g, 64 * kColWaves, 0, s>>>(                                                 \
+        a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start,       \
+        a.red_row, a.src, a.blocks, a.zeros, a.inst_table, a.inst_scale, a.u, a.parts, a.n * a.nrhs)
+    if (a.comp) P2P_COLS32(true); else P2P_COLS32(false);
+#undef P2P_COLS32
 }
 
 template <bool R, bool C, int H>
-static void launch_cols64(const HelmholtzMfmaArgs &a, const int32_t *tiles, const HelmInline &inl, int32_t n_tiles,
-                          hipStream_t s) {
-    k_helm_mfma_cols64<R, C, H><<<static_cast<unsigned>(n_tiles) * H, 64 * kColWaves, 0, s>>>(
-        a.key_bits, tiles, inl, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start, a.red_row,
-        reinterpret_cast<const double2 *>(a.src), reinterpret_cast<const double2 *>(a.blocks),
-        reinterpret_cast<const double2 *>(a.zeros), a.inst_table, a.inst_h, reinterpret_cast<double2 *>(a.u), a.parts,
-        a.n);
+static void launch_cols_h(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                          bool fp64, hipStream_t s) {
+    if (fp64) {
+        if (a.nrhs == 1) launch_cols64<R, C, true, H>(a, ht, inl, n_tiles, s);
+        else launch_cols64<R, C, false, H>(a, ht, inl, n_tiles, s);
+    } else {
+        if (a.nrhs == 1) launch_cols32<R, C, true, H>(a, ht, inl, n_tiles, s);
+        else launch_cols32<R, C, false, H>(a, ht, inl, n_tiles, s);
+    }
 }
 
-p2p_status launch_helmholtz_mfma_cols(const HelmholtzMfmaArgs &a, const int32_t *tiles, const HelmInline &inl,
+template <bool R, bool C>
+static void launch_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                        bool fp64, bool split, hipStream_t s) {
+    if (split) launch_cols_h<R, C, 2>(a, ht, inl, n_tiles, fp64, s);
+    else launch_cols_h<R, C, 1>(a, ht, inl, n_tiles, fp64, s);
+}
+
+p2p_status launch_helmholtz_mfma_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
                                       int32_t n_tiles, bool redundant, bool fp64, hipStream_t s) {
     if (n_tiles <= 0) return P2P_OK;
-    if (fp64) {
-        int dev = 0, cus = 0;
-        P2P_HIP(hipGetDevice(&dev));
-        P2P_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        const bool split = 2 * static_cast<int64_t>(n_tiles) <= cus && a.parts;
-        const bool cj = a.conj != 0;
-#define P2P_MF64(H)                                                                  \
-    if (redundant) { if (cj) launch_cols64<true, true, H>(a, tiles, inl, n_tiles, s);    \
-                     else launch_cols64<true, false, H>(a, tiles, inl, n_tiles, s); }    \
-    else { if (cj) launch_cols64<false, true, H>(a, tiles, inl, n_tiles, s);             \
-           else launch_cols64<false, false, H>(a, tiles, inl, n_tiles, s); }
-        if (split) { P2P_MF64(2) } else { P2P_MF64(1) }
-#undef P2P_MF64
-        P2P_LAUNCH_CHECK();
-        if (split) {
-            k_join_parts64<<<grid_for(a.n, 256), 256, 0, s>>>(a.parts, a.perm, a.n, reinterpret_cast<double2 *>(a.u));
-            P2P_LAUNCH_CHECK();
-        }
-        return P2P_OK;
-    }
     int dev = 0, cus = 0;
     P2P_HIP(hipGetDevice(&dev));
     P2P_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    // two workgroups per tile while that still fits on the card's CUs
     const bool split = 2 * static_cast<int64_t>(n_tiles) <= cus && a.parts;
-#define P2P_MFC3(R, C, M, H)                                                                            \
-    k_helm_mfma_cols<R, C, M, H><<<static_cast<unsigned>(n_tiles) * H, 64 * kColWaves, 0, s>>>(        \
-        a.key_bits, tiles, inl, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start, a.red_row, a.src, \
-        a.blocks, a.zeros, a.inst_table, a.inst_scale, a.u, a.parts, a.n)
-#define P2P_MFC2(R, C, M) if (split) P2P_MFC3(R, C, M, 2); else P2P_MFC3(R, C, M, 1)
-#define P2P_MFC(R, C) if (a.comp) { P2P_MFC2(R, C, true); } else { P2P_MFC2(R, C, false); }
     const bool cj = a.conj != 0;
-    if (redundant) { if (cj) { P2P_MFC(true, true); } else { P2P_MFC(true, false); } }
-    else { if (cj) { P2P_MFC(false, true); } else { P2P_MFC(false, false); } }
-#undef P2P_MFC
-#undef P2P_MFC2
-#undef P2P_MFC3
+    if (redundant) { if (cj) launch_cols<true, true>(a, ht, inl, n_tiles, fp64, split, s);
+                     else launch_cols<true, false>(a, ht, inl, n_tiles, fp64, split, s); }
+    else { if (cj) launch_cols<false, true>(a, ht, inl, n_tiles, fp64, split, s);
+           else launch_cols<false, false>(a, ht, inl, n_tiles, fp64, split, s); }
     P2P_LAUNCH_CHECK();
     if (split) {
-        k_join_parts<<<grid_for(a.n, 256), 256, 0, s>>>(a.parts, a.perm, a.n, a.u);
+        const int64_t m = a.n * a.nrhs;
+        if (fp64)
+            k_join_parts<double2><<<grid_for(m, 256), 256, 0, s>>>(a.parts, a.perm, m, a.nrhs,
+                                                                   reinterpret_cast<double2 *>(a.u));
+        else
+            k_join_parts<float2><<<grid_for(m, 256), 256, 0, s>>>(a.parts, a.perm, m, a.nrhs, a.u);
         P2P_LAUNCH_CHECK();
     }
     return P2P_OK;

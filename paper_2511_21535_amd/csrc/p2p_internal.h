@@ -263,29 +263,6 @@ struct GravityAdjointArgs {
 };
 p2p_status launch_gravity_adjoint(const GravityAdjointArgs &a, bool mixed, hipStream_t s);
 
-// Helmholtz (helmholtz.hip).
-struct HelmholtzArgs {
-    int64_t L;
-    int key_bits;
-    const int32_t *leaf_start;
-    const uint64_t *leaf_key;
-    const int32_t *perm;
-    const int64_t *nbr_start;
-    const int32_t *nbr_idx;
-    const int64_t *red_start;
-    const int64_t *red_row;  // tile-grain layout: first row of each entry's source box (else null)
-    const void *src;       // sorted q rows (gather) or redundant rows
-    const void *table;     // per-instance G(dd) tables, [n_grids][kTableLen] complex
-    int32_t nrhs;
-    int32_t conj;          // 1: conj(q) in, conj(u) out
-    int32_t comp;          // FP32 payload: 1 = each near box's partial sum added into FP64 per target
-    void *u;               // caller order
-};
-constexpr int kTableLen = 148;   // dd = 0..147 inside a 3x3x3-box neighbourhood of 4^3 boxes
-p2p_status launch_green_tables(const double *d_h, const double *d_k, int32_t n_grids, bool fp64,
-                               void *table, hipStream_t s);
-p2p_status launch_helmholtz(const HelmholtzArgs &a, bool redundant, bool fp64, hipStream_t s);
-
 // Multi-RHS Helmholtz on FP32 matrix cores (helmholtz_mfma.hip).
 struct HelmholtzMfmaArgs {
     int64_t L;
@@ -299,12 +276,12 @@ struct HelmholtzMfmaArgs {
     const int64_t *red_row;    // tile-grain layout: first row of each entry's source box (else null)
     const float2 *src;         // sorted q rows (gather) or redundant rows, [.][nrhs]
     const float2 *blocks;      // multi-RHS: float4 (Re, Im, Re + Im, Re - Im) G at [n_tables][copies][27][64 src]
-                               // [64 tgt] (unit spacing); single RHS: float2 (double2 on the FP64 path) at
+                               // [64 tgt] (unit spacing); column path: float2 (double2 in FP64) at
                                // [n_tables][27][64 src][16][4] (target 16 r + c at [c][r])
-    const float2 *zeros;       // 64 zero rows (an absent neighbour's sources, single RHS; double2 on FP64)
-    const double *inst_h;      // per instance: h (FP64 single-RHS path with uploaded parameters)
+    const float2 *zeros;       // column path: 64 zero entries (an absent neighbour's sources; double2 in FP64)
+    const double *inst_h;      // per instance: h (FP64 column path with uploaded parameters)
     int64_t n;                 // points
-    double2 *parts;            // single RHS: [2][n] partial results in sorted order (tiles split in two)
+    double2 *parts;            // column path: [2][n][nrhs] partial results in sorted order (tiles split in two)
     int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies
     const int32_t *inst_table; // per instance: table index
     const float *inst_scale;   // per instance: 1/h
@@ -314,11 +291,16 @@ struct HelmholtzMfmaArgs {
     int32_t comp;              // 1: each near box's FP32 partial product summed into FP64 per target
     float2 *u;                 // caller order [n][nrhs]
 };
-// Per-call parameters of a grid with at most kInlineGrids instances, passed by
-// value in the kernel arguments (no upload, no extra launch): n_grids = 0
-// means the device arrays are used instead.
+// Per-call parameters of a column-path call with at most kInlineGrids
+// instances, passed by value in the kernel arguments (no upload, no extra
+// launch): n_grids = 0 means the device arrays are used instead.
 constexpr int kInlineGrids = 8;
-constexpr int kHelmColBoxes = 16;           // target boxes (columns) per tile of the single-RHS path
+constexpr int kHelmColBoxes = 16;           // columns (target box, right-hand side) per tile of the column path
+struct HelmTiles {
+    const int32_t *tile_first;              // first column tile of each instance, [n_grids + 1]
+    const int32_t *leaf_first;              // first box (leaf) of each instance, [n_grids + 1]
+    int32_t n_grids;
+};
 struct HelmInline {
     int32_t n_grids;
     int32_t n_tables;
@@ -330,18 +312,17 @@ struct HelmInline {
     double iscale64[kInlineGrids];          // 1/h of each instance in double (FP64 path)
 };
 // G blocks for the k h values of d_kh, or of inl.kh when inl.n_grids > 0, in the
-// multi-RHS or (cols) the single-RHS layout, followed by 64 zero entries; with
-// f64 (single-RHS layout only) the entries are double2.
+// multi-RHS or (cols) the column layout, followed by 64 zero entries; with
+// f64 (column layout only) the entries are double2.
 p2p_status launch_green_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
                                bool cols, bool f64, void *blocks, hipStream_t s);
 p2p_status launch_helmholtz_mfma(const HelmholtzMfmaArgs &a, bool redundant, int waves_per_wg,
                                  int wg_per_cu, int rhs_tile, hipStream_t s);
-// Single RHS on matrix cores, target boxes as the columns: tiles of up to 16
-// consecutive boxes of one instance, (first leaf, count) pairs; returns their
-// number (tiles may be null to count).  Uses blocks, inst_table, inst_scale,
-// conj and u of the arguments (copies 1, no work queue).
-int32_t helmholtz_cols_tiles(const p2p_grid *grids, int32_t n_grids, int32_t *tiles);
-p2p_status launch_helmholtz_mfma_cols(const HelmholtzMfmaArgs &a, const int32_t *tiles, const HelmInline &inl,
+// Column path: the columns of an instance are its (box, right-hand side)
+// pairs, cut into tiles of kHelmColBoxes; the number of tiles of an instance
+// of `boxes` boxes.
+int64_t helmholtz_cols_tiles(int64_t boxes, int32_t nrhs);
+p2p_status launch_helmholtz_mfma_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
                                       int32_t n_tiles, bool redundant, bool fp64, hipStream_t s);
 
 // Locality (locality.hip).
