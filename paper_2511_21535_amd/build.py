@@ -34,10 +34,10 @@ FLAGS = [
 ]
 
 
-# flags of single sources: the single-RHS matrix-core kernel keeps its
-# accumulators in ordinary vector registers, so its per-offset FP64 flush needs
-# no copies out of the accumulation registers
-FILE_FLAGS = {"helmholtz_cols.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# flags of single sources: the matrix accumulators of these products stay in
+# ordinary vector registers, so the per-offset FP64 sums need no copies out of
+# the accumulation registers
+FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("helmholtz_cols.hip", "helmholtz_split.hip")}
 
 
 def _compile(src: str) -> str:

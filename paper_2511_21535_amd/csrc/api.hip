@@ -812,7 +812,7 @@ struct HelmSetup {
     p2p_precision prec;
     int32_t nrhs;
     bool fp64, mfma, cols, inline_params;
-    int waves_per_wg = 4, wg_per_cu = 2, rhs_tile = 32, copies = 1;
+    int waves_per_wg = 4, wg_per_cu = 2, rhs_tile = 32, copies = 1, planes = 6;
     int32_t n_grids = 0, n_tables = 0, n_tiles = 0;
     std::vector<double> khs;
     std::vector<int32_t> itab;
@@ -886,11 +886,12 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     if (h->cols) {
         // every box of a grid instance is a leaf, instances in order
         int64_t boxes = 0, tiles = 0;
+        const int64_t cb = h->fp64 ? kHelmColBoxes : kHelmSplitCols;
         h->first.assign(2 * static_cast<size_t>(n_grids + 1), 0);
         for (int32_t g = 0; g < n_grids; ++g) {
             const int64_t nb = static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
             boxes += nb;
-            tiles += helmholtz_cols_tiles(nb, nrhs);
+            tiles += (nb * nrhs + cb - 1) / cb;
             if (tiles > INT32_MAX) return fail(P2P_EINVAL, "nrhs too large for these grids");
             h->first[g + 1] = static_cast<int32_t>(tiles);
             h->first[n_grids + 1 + g + 1] = static_cast<int32_t>(boxes);
@@ -927,13 +928,18 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     return P2P_OK;
 }
 
+// Size of the G blocks in float2.
+size_t helm_block_elems(const HelmSetup &h) {
+    const size_t sets = static_cast<size_t>(h.n_tables) * h.copies * 27;
+    if (!h.cols || h.fp64) return sets * 4096 * 2;                      // float4, double2
+    return sets * 8 * static_cast<size_t>(h.planes) * 64 * 2;           // 16-byte operands
+}
+
 HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h) {
     HelmSetupBufs b;
     b.params = ar.take<char>(h.param_bytes);
-    // the G blocks: float4 entries, or on the column path float2 (FP64: double2)
-    // entries and 64 zero entries after them
-    b.blocks = ar.take<float2>(h.cols ? (static_cast<size_t>(h.n_tables) * 27 * 4096 + 64) * (h.fp64 ? 2 : 1)
-                                      : static_cast<size_t>(h.n_tables) * h.copies * 27 * 4096 * 2);
+    // the G blocks, and on the column path 64 zero entries after them
+    b.blocks = ar.take<float2>(helm_block_elems(h) + (h.cols ? (h.fp64 ? 128 : 64) : 0));
     return b;
 }
 
@@ -954,7 +960,9 @@ p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid 
         // a copy from pageable memory has read its source when it returns
         P2P_HIP(hipMemcpyAsync(b.params, hp.data(), h.param_bytes, hipMemcpyHostToDevice, s));
     }
-    return launch_green_blocks(d_kh, h.inl, h.n_tables, h.copies, h.cols, h.fp64, b.blocks, s);
+    if (!h.cols) return launch_green_blocks(d_kh, h.inl, h.n_tables, h.copies, b.blocks, s);
+    if (h.fp64) return launch_green_blocks64(d_kh, h.inl, h.n_tables, b.blocks, s);
+    return launch_split_blocks(d_kh, h.inl, h.n_tables, h.copies, h.planes, b.blocks, s);
 }
 
 // Argument checks of an evaluation that come after the workspace query.
@@ -982,8 +990,8 @@ p2p_status helm_check_call(const HelmSetup &h, const p2p_tree *tree, const p2p_n
 }
 
 // The evaluation from a filled set-up: the sorted copy of q (GATHER), then one
-// product launch (the work queues' counters are zeroed first; on the column path
-// few tiles add the join of the two halves of each tile).
+// product launch (the work queues' counters are zeroed first; in FP64 few tiles
+// add the join of the two halves of each tile).
 p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter, char *sorted, double2 *parts,
                     const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
                     const void *q, void *u, int32_t conj, hipStream_t s) {
@@ -1014,10 +1022,8 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.red_row = tiled ? red->red_row : nullptr;
     a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
     a.blocks = b.blocks;
-    const int64_t nblk = static_cast<int64_t>(h.n_tables) * 27 * 4096;
-    a.zeros = !h.cols ? nullptr
-              : h.fp64 ? reinterpret_cast<const float2 *>(reinterpret_cast<const double2 *>(b.blocks) + nblk)
-                       : b.blocks + nblk;
+    a.planes = h.planes;
+    a.zeros = h.cols ? b.blocks + helm_block_elems(h) : nullptr;
     a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
     a.n = n;
     a.parts = parts;
@@ -1027,20 +1033,19 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.conj = conj;
     a.comp = h.prec == P2P_FP32_MIXED;
     a.u = static_cast<float2 *>(u);
+    a.copies = h.copies;
     if (h.cols) {
-        a.copies = 1;
         const int32_t *first = reinterpret_cast<const int32_t *>(b.params + h.o_first);
         const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids};
-        return launch_helmholtz_mfma_cols(a, ht, h.inl, h.n_tiles, redundant, h.fp64, s);
+        return h.fp64 ? launch_helmholtz_cols64(a, ht, h.inl, h.n_tiles, redundant, s)
+                      : launch_helmholtz_split_cols(a, ht, h.inl, h.n_tiles, redundant, s);
     }
-    a.copies = h.copies;
     a.counter = counter;
     return launch_helmholtz_mfma(a, redundant, h.waves_per_wg, h.wg_per_cu, h.rhs_tile, s);
 }
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
-// (right-hand sides as columns), the sorted copy of q (GATHER) and, on the
-// column path, the two partial results of tiles whose offsets two workgroups
+// (right-hand sides as columns), the sorted copy of q (GATHER) and, in FP64, the two partial results of tiles whose offsets two workgroups
 // share: at most half as many tiles as the card has CUs, so no more than
 // kMaxSplitTiles on any card, and larger calls hold none.
 constexpr int32_t kMaxSplitTiles = 256;
@@ -1049,7 +1054,7 @@ void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, in
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     *counter = h.mfma ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
-    *parts = h.cols && h.n_tiles <= kMaxSplitTiles ? ar.take<double2>(2 * static_cast<size_t>(n) * h.nrhs) : nullptr;
+    *parts = h.fp64 && h.n_tiles <= kMaxSplitTiles ? ar.take<double2>(2 * static_cast<size_t>(n) * h.nrhs) : nullptr;
 }
 
 p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red,

@@ -29,7 +29,7 @@
 // copies, spreading the pattern loads over more L2 lines and channels.
 #include <algorithm>
 
-#include "p2p_internal.h"
+#include "helm_columns.h"
 
 namespace p2p {
 namespace {
@@ -42,67 +42,20 @@ __device__ inline Rsrc buffer_rsrc(const void *p, int bytes) {
 }
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-constexpr double kPi = 3.14159265358979323846;
 
-// G(t, o, s, i) = e^{i kh sqrt(dd)} / (4 pi sqrt(dd)), dd = |l_i - (l_s + 4 o)|^2, zero for
-// dd = 0, for table t, offset o = (ox+1) + 3 (oy+1) + 9 (oz+1), source s and target i (l_*
-// are local Morton coordinates).  Multi-RHS layout: float4 (Re G, Im G, Re G + Im G,
-// Re G - Im G) at [t][c][o][s][i], identical for every copy c (the three-product form of
-// the complex product reads the sum, its conjugate the difference; both are formed in
-// double and rounded once).  Single-RHS (COLS) layout: float2 at [t][o][s][i % 16][i / 16],
-// the four row tiles of a target column next to each other, so a lane reads the four it
-// needs in one 32-byte run, followed by 64 zero entries (the source rows of an absent
-// neighbour); the FP64 single-RHS path keeps the same layout in double2.
+// G(t, o, s, i) of table t, offset o, source s and target i: float4 (Re G, Im G,
+// Re G + Im G, Re G - Im G) at [t][c][o][s][i], identical for every copy c
+// (the three-product form of the complex product reads the sum, its conjugate
+// the difference; both are formed in double and rounded once).
 __global__ void k_green_blocks(const double *__restrict__ kh_dev, HelmInline inl, int32_t n_tables,
-                               int32_t copies, bool cols, bool f64, void *__restrict__ out) {
+                               int32_t copies, float4 *__restrict__ out) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t per = 27 * 64 * 64, total = per * n_tables * copies;
-    if (t >= total + (cols ? 64 : 0)) return;
-    if (t >= total) {
-        if (f64)
-            static_cast<double2 *>(out)[t] = make_double2(0.0, 0.0);
-        else
-            static_cast<float2 *>(out)[t] = make_float2(0.f, 0.f);
-        return;
-    }
-    const int tab = static_cast<int>(t / (per * copies));
-    double khv = 0.0;
-    if (inl.n_grids > 0) {
-        // compile-time indices only, so the argument array stays in the kernel arguments
-#pragma unroll
-        for (int i = 0; i < kInlineGrids; ++i)
-            if (i == tab) khv = inl.kh[i];
-    } else {
-        khv = kh_dev[tab];
-    }
-    const int rem = static_cast<int>(t % per);
-    const int o = rem / 4096, s = (rem / 64) % 64, i = rem % 64;
-    const int od[3] = {o % 3 - 1, (o / 3) % 3 - 1, o / 9 - 1};
-    int dd = 0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int li = ((i >> d) & 1) | (((i >> (d + 3)) & 1) << 1);
-        const int ls = ((s >> d) & 1) | (((s >> (d + 3)) & 1) << 1);
-        const int diff = li - (ls + 4 * od[d]);
-        dd += diff * diff;
-    }
-    double gr = 0.0, gi = 0.0;
-    if (dd > 0) {
-        const double r = sqrt(static_cast<double>(dd));
-        const double a = 1.0 / (4.0 * kPi * r);
-        double sn, cs;
-        sincos(khv * r, &sn, &cs);
-        gr = cs * a;
-        gi = sn * a;
-    }
-    const int64_t at = static_cast<int64_t>(tab) * per + o * 4096 + s * 64 + (i % 16) * 4 + i / 16;
-    if (cols && f64)
-        static_cast<double2 *>(out)[at] = make_double2(gr, gi);
-    else if (cols)
-        static_cast<float2 *>(out)[at] = make_float2(static_cast<float>(gr), static_cast<float>(gi));
-    else
-        static_cast<float4 *>(out)[t] = make_float4(static_cast<float>(gr), static_cast<float>(gi),
-                                                    static_cast<float>(gr + gi), static_cast<float>(gr - gi));
+    if (t >= total) return;
+    const int tab = static_cast<int>(t / (per * copies)), rem = static_cast<int>(t % per);
+    const double2 g = green(table_kh(inl, kh_dev, tab), near_distance(rem / 4096, (rem / 64) % 64, rem % 64));
+    out[t] = make_float4(static_cast<float>(g.x), static_cast<float>(g.y), static_cast<float>(g.x + g.y),
+                         static_cast<float>(g.x - g.y));
 }
 
 __global__ void k_zero_counter(int32_t *c, int n) {
@@ -372,15 +325,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1))) void k
 }  // namespace
 
 p2p_status launch_green_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               bool cols, bool f64, void *blocks, hipStream_t s) {
-    if (cols && copies != 1) return fail(P2P_EINVAL, "internal: the single-RHS G layout has one copy");
-    if (f64 && !cols) return fail(P2P_EINVAL, "internal: FP64 G blocks exist in the single-RHS layout only");
-    const int64_t n = static_cast<int64_t>(n_tables) * copies * 27 * 4096 + (cols ? 64 : 0);
-    k_green_blocks<<<grid_for(n, 256), 256, 0, s>>>(d_kh, inl, n_tables, copies, cols, f64, blocks);
+                               void *blocks, hipStream_t s) {
+    const int64_t n = static_cast<int64_t>(n_tables) * copies * 27 * 4096;
+    k_green_blocks<<<grid_for(n, 256), 256, 0, s>>>(d_kh, inl, n_tables, copies, static_cast<float4 *>(blocks));
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
-
 
 template <bool RED, bool CONJ, int TJ, bool COMP>
 static void launch_mfma_t(const HelmholtzMfmaArgs &a, unsigned grid, unsigned block, hipStream_t s) {

@@ -276,8 +276,10 @@ struct HelmholtzMfmaArgs {
     const int64_t *red_row;    // tile-grain layout: first row of each entry's source box (else null)
     const float2 *src;         // sorted q rows (gather) or redundant rows, [.][nrhs]
     const float2 *blocks;      // multi-RHS: float4 (Re, Im, Re + Im, Re - Im) G at [n_tables][copies][27][64 src]
-                               // [64 tgt] (unit spacing); column path: float2 (double2 in FP64) at
-                               // [n_tables][27][64 src][16][4] (target 16 r + c at [c][r])
+                               // [64 tgt] (unit spacing); FP64: double2 at [n_tables][27][64 src][16][4]
+                               // (target 16 r + c at [c][r]); split path: `planes` planes of 16-byte operands
+                               // at [n_tables][copies][27][4 k-steps][2 row tiles][planes][64 lanes]
+    int32_t planes;            // split path: 6 (h, m, l of Re G and Im G) or 9 (and of Re G + Im G)
     const float2 *zeros;       // column path: 64 zero entries (an absent neighbour's sources; double2 in FP64)
     const double *inst_h;      // per instance: h (FP64 column path with uploaded parameters)
     int64_t n;                 // points
@@ -295,7 +297,8 @@ struct HelmholtzMfmaArgs {
 // instances, passed by value in the kernel arguments (no upload, no extra
 // launch): n_grids = 0 means the device arrays are used instead.
 constexpr int kInlineGrids = 8;
-constexpr int kHelmColBoxes = 16;           // columns (target box, right-hand side) per tile of the column path
+constexpr int kHelmColBoxes = 16;           // columns (target box, right-hand side) per tile in FP64
+constexpr int kHelmSplitCols = 32;          // ... and of the split product (single precision)
 struct HelmTiles {
     const int32_t *tile_first;              // first column tile of each instance, [n_grids + 1]
     const int32_t *leaf_first;              // first box (leaf) of each instance, [n_grids + 1]
@@ -312,18 +315,21 @@ struct HelmInline {
     double iscale64[kInlineGrids];          // 1/h of each instance in double (FP64 path)
 };
 // G blocks for the k h values of d_kh, or of inl.kh when inl.n_grids > 0, in the
-// multi-RHS or (cols) the column layout, followed by 64 zero entries; with
-// f64 (column layout only) the entries are double2.
+// layouts above (the column layouts with their 64 zero entries behind them).
 p2p_status launch_green_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               bool cols, bool f64, void *blocks, hipStream_t s);
+                               void *blocks, hipStream_t s);
+p2p_status launch_green_blocks64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks,
+                                 hipStream_t s);
+p2p_status launch_split_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
+                               int32_t planes, void *blocks, hipStream_t s);
 p2p_status launch_helmholtz_mfma(const HelmholtzMfmaArgs &a, bool redundant, int waves_per_wg,
                                  int wg_per_cu, int rhs_tile, hipStream_t s);
 // Column path: the columns of an instance are its (box, right-hand side)
-// pairs, cut into tiles of kHelmColBoxes; the number of tiles of an instance
-// of `boxes` boxes.
-int64_t helmholtz_cols_tiles(int64_t boxes, int32_t nrhs);
-p2p_status launch_helmholtz_mfma_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
-                                      int32_t n_tiles, bool redundant, bool fp64, hipStream_t s);
+// pairs, cut into tiles of kHelmColBoxes (FP64) or kHelmSplitCols.
+p2p_status launch_helmholtz_cols64(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                   int32_t n_tiles, bool redundant, hipStream_t s);
+p2p_status launch_helmholtz_split_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                       int32_t n_tiles, bool redundant, hipStream_t s);
 
 // Locality (locality.hip).
 p2p_status launch_locality_stats(const int32_t *leaf_start, const int64_t *nbr_start,
