@@ -4,7 +4,7 @@
 Default workload (the largest configuration): 128 independent grid instances
 of edge 16..48 points (leaf boxes of 4^3 points, k at 10 points per
 wavelength), 64 complex right-hand sides each, evaluated in one persistent
-launch on the FP32 matrix cores with autotuned tiles.  One step is one pass of
+launch on the matrix cores in single precision with autotuned tiles.  One step is one pass of
 the whole path over the resident inputs: tree binning, near lists,
 restructure to the redundant layout, redundant evaluation, gather evaluation
 (the update into caller order is fused into both evaluations).  Every
@@ -28,10 +28,10 @@ afterwards) on the same tree and lists, the same tree on the unit torus
 one half of the domain, all outside the timed steps.
 
 --workload selects one configuration on its own:
-  helmholtz_batched_128x64  (default) 128 grids 16^3..48^3, 64 RHS, FP32 matrix cores
+  helmholtz_batched_128x64  (default) 128 grids 16^3..48^3, 64 RHS, single precision
   gravity_plummer_2m        2^21 Plummer-mixture particles, leaf cap 64, FP32-mixed
   gravity_uniform_4096      4096 uniform particles, uniform depth 3, FP64
-  helmholtz_grid_64         64^3 grid, 1 RHS, FP32 matrix cores (target boxes as columns)
+  helmholtz_grid_64         64^3 grid, 1 RHS, single precision (target boxes as columns)
   adjoint_gravity_256k      2^18 Plummer particles, forward + adjoint, FP64 and FP32-mixed
   adjoint_helmholtz_48      48^3 grid, forward + adjoint (A^T g), FP64
 
@@ -79,11 +79,16 @@ SLOTS_PER_PAIR_FP64 = 3 + 3 + 3 + 1 + 3 + 6         # = 19
 # 41 and 42 instructions a per-pair difference needed.
 SLOTS_PER_PAIR_ADJ_FP64 = 33 + 6                     # = 39
 SLOTS_PER_PAIR_ADJ_MIXED = 34 + 1                    # = 35
-# FP32 vector FMA without packed issue: 256 CUs x 64 lanes x 2 flop x 2.4 GHz
-FP32_VALU_PEAK_TFLOPS = 256 * 64 * 2 * 2.4e9 / 1e12  # = 78.6
 FP32_MFMA_PEAK_TFLOPS = 157.3                        # dense FP32 matrix (published)
 FP64_VALU_PEAK_TFLOPS = 78.6                         # FP64 vector (published)
 FP64_MFMA_PEAK_TFLOPS = 78.6                         # dense FP64 matrix (published)
+BF16_MFMA_PEAK_TFLOPS = 2500.0                       # dense BF16 matrix (published)
+# The single-precision Helmholtz products run on the BF16 matrix cores, every
+# operand split exactly into three BF16 parts: four real products per complex
+# multiply-add, six partial products each, 2 flop.
+SPLIT_FLOP_PER_PAIR = 4 * 6 * 2                      # = 48
+SPLIT_PER_PAIR = ("48 BF16 flop per pair (x RHS): the complex multiply-add as four real products of operands "
+                  "split exactly into three BF16 parts, six partial products each")
 CACHE_BYTES = 32.0 * 2 ** 20                         # C of the Locality metric: 8 XCDs x 4 MB L2
 
 
@@ -769,33 +774,23 @@ def run_helmholtz(wname, args):
 
     wall, (t_tree, t_nbr, t_res, t_red, t_gat) = _timed_steps(step, K, args.warmup)
     value = work * K / (t_res + t_red)
-    flops = 8.0 * work
-    per_pair = "8 flop per complex multiply-add (x RHS)"
+    flops, per_pair = SPLIT_FLOP_PER_PAIR * work, SPLIT_PER_PAIR
+    src, t_dom = "helmholtz_split.hip", t_red / K
+    roof = {"bound": "mfma", "peak": BF16_MFMA_PEAK_TFLOPS, "achieved_8flop_equivalent": 8.0 * work / t_dom / 1e12}
     if mfma:
-        kern, src, t_dom = "k_helm_mfma_red", "helmholtz_mfma.hip", t_red / K
-        roof = {"bound": "mfma", "peak": FP32_MFMA_PEAK_TFLOPS, "instruction": "v_mfma_f32_32x32x2f32",
-                "timed": "the redundant evaluation call from the prepared plan (queue counter reset, product)"}
-        # the product form the kernel runs: 64 RHS per wave with the FP64 sums take four
-        # real products per complex one, every other multi-RHS shape three (3M)
-        if not (tile and tile[2] == 64):
-            flops = 6.0 * work
-            per_pair = ("6 flop per pair x RHS: the complex multiply-add as three real products "
-                        "(Re G Re Q, Im G Im Q, (Re G + Im G)(Re Q + Im Q))")
-            roof["achieved_8flop_equivalent"] = 8.0 * work / t_dom / 1e12
+        kern = "k_helm_split_red"
+        roof.update(instruction="v_mfma_f32_16x16x32_bf16",
+                    timed="the redundant evaluation call from the prepared plan (queue counter reset, product)")
         # redundant rows read once, results written once (complex64)
         alg_bytes = S_red * nrhs * 8 + tree.n * nrhs * 8
     else:
-        # one right-hand side on the matrix cores, target boxes as the columns; the
-        # redundant evaluation call from the plan is the product launch alone
-        kern, src, t_dom = "k_helm_mfma_cols_red", "helmholtz_cols.hip", t_red / K
-        roof = {"bound": "mfma", "peak": FP32_MFMA_PEAK_TFLOPS, "instruction": "v_mfma_f32_16x16x4f32",
-                "timed": "the redundant evaluation call from the prepared plan (one product launch)"}
-        flops = 6.0 * work
-        per_pair = ("6 flop per pair: the complex multiply-add as three real products "
-                    "(Re G Re Q, Im G Im Q, (Re G + Im G)(Re Q + Im Q))")
-        roof["achieved_8flop_equivalent"] = 8.0 * work / t_dom / 1e12
-        # redundant rows read once, results written once (complex64), G blocks read once
-        alg_bytes = S_red * 8 + tree.n * 8 + 27 * 4096 * 8
+        # one right-hand side, target boxes as the columns; the redundant evaluation
+        # call from the plan is the product launch alone
+        kern = "k_helm_split_cols_red"
+        roof.update(instruction="v_mfma_f32_32x32x16_bf16",
+                    timed="the redundant evaluation call from the prepared plan (one product launch)")
+        # redundant rows read once, results written once (complex64), G operands read once
+        alg_bytes = S_red * 8 + tree.n * 8 + 27 * 4096 * 12
     ach = flops / t_dom / 1e12
     traffic = pmc_traffic(kern, wname, src)
     roof.update({"kernel": kern, "achieved": ach, "unit": "TFLOP/s", "frac": ach / roof["peak"],
@@ -806,7 +801,7 @@ def run_helmholtz(wname, args):
     desc = ("64^3 grid, leaf boxes of 4^3 points, 1 complex RHS, k at 10 points per wavelength"
             if wname == "helmholtz_grid_64" else
             f"{len(sides)} grids of edge 16..48 (leaf boxes of 4^3 points, k at 10 points per wavelength), "
-            f"{nrhs} complex RHS each, one persistent launch on the FP32 matrix cores")
+            f"{nrhs} complex RHS each, one persistent launch on the matrix cores in single precision")
     cfg = {"workload": f"{wname}: {desc}", "grids": len(sides), "points": tree.n, "boxes": tree.n_leaves,
            "nrhs": nrhs, "near_entries": nbrs.count, "redundant_entries": S_red, "box_grain_entries": S,
            "grain": grain, "pairs": pairs, "precision": "FP32_MIXED",
@@ -826,7 +821,7 @@ def run_helmholtz(wname, args):
         "locality": {k: loc[k] for k in ("d_mean", "d_ratio", "v_ratio", "locality")},
         "speedup_model": speedup_model.evaluate({"compute": t_gat}, {"collect": t_res, "compute": t_red},
                                                 loc["d_ratio"], loc["v_ratio"], S * 8.0 * nrhs, CACHE_BYTES),
-        "roofline": with_measured_peak(roof, "mfma_f32_TFLOPs") if roof["bound"] == "mfma" else roof,
+        "roofline": roof,
     })
     line["locality"]["note"] = "box grain (V = S x 8 x RHS bytes), as Definition 1 states it"
     # FP32 throughout: the same layouts and kernels without the FP64 sums
@@ -855,7 +850,7 @@ def run_helmholtz(wname, args):
                                                        plan=plan),
             "eval_gather_us": lambda: api.helmholtz(tree, nbrs, gq, layout="gather", out=out, plan=plan)})
         line["back_to_back"] = dict(b2b, calls=B2B_CALLS)
-        if kern == "k_helm_mfma_cols_red":
+        if kern == "k_helm_split_cols_red":
             # a launch of tens of microseconds: its average duration is taken over
             # B2B_CALLS launches issued back to back between two HIP events on the
             # library's stream (a single timed call also holds the host's launch gap)
@@ -864,8 +859,6 @@ def run_helmholtz(wname, args):
             rl["achieved"] = flops / (b2b["eval_redundant_us"] * 1e-6) / 1e12
             rl["achieved_8flop_equivalent"] = 8.0 * work / (b2b["eval_redundant_us"] * 1e-6) / 1e12
             rl["frac"] = rl["achieved"] / rl["peak"]
-            if "peak_measured" in rl:
-                rl["frac_of_measured_peak"] = rl["achieved"] / rl["peak_measured"]
             rl["timed"] = (f"the redundant evaluation call from the prepared plan (one product launch), mean of "
                            f"{B2B_CALLS} launches back to back")
     if tile:
@@ -884,10 +877,10 @@ def run_helmholtz(wname, args):
                           nrhs=nrhs, tile=t_[1], out=o)
             err[f"{p_}_{layout}"] = helmholtz_error(o, ref)
             del o
-    form = ("three real products" if not (tile and tile[2] == 64) else "four real products")
     line["error_vs_oracle"] = dict(
-        err, precision=f"fp32_mixed: FP32 matrix cores (complex as {form}), each near box's 64-term "
-                       "partial product added into FP64 sums per target; fp32_plain: all 27 boxes summed in FP32")
+        err, precision="fp32_mixed: FP32 operands split exactly into three BF16 parts on the BF16 matrix cores, FP32 "
+                       "accumulation, each near box's 64-term partial product added into FP64 sums per target; "
+                       "fp32_plain: all 27 boxes summed in FP32")
     if base is not None:
         line["cpu_baseline"] = base
     return line
@@ -1018,7 +1011,7 @@ def run_adjoint_helmholtz(wname, args):
     # the four-product form beside it): FP64 on the FP64 matrix instructions, FP32
     # on the FP32 ones (a tile's offsets shared by two workgroups on this grid)
     a64 = 6.0 * pairs / (t_adj / K) / 1e12
-    a32 = 6.0 * pairs / (t_adj32 / K) / 1e12
+    a32 = SPLIT_FLOP_PER_PAIR * pairs / (t_adj32 / K) / 1e12
     per_pair = ("6 flop per pair: the complex multiply-add as three real products "
                 "(Re G Re Q, Im G Im Q, (Re G + Im G)(Re Q + Im Q))")
     line["roofline"] = {"bound": "mfma", "kernel": "k_helm_mfma_cols64", "achieved": a64,
@@ -1026,11 +1019,11 @@ def run_adjoint_helmholtz(wname, args):
                         "traffic": None, "algorithmic_per_pair": per_pair,
                         "achieved_8flop_equivalent": a64 * 8.0 / 6.0,
                         "timed": "the whole adjoint call (sorted copy, G blocks, cleared output, product)"}
-    line["roofline_fp32"] = with_measured_peak(
-        {"bound": "mfma", "kernel": "k_helm_mfma_cols", "achieved": a32, "peak": FP32_MFMA_PEAK_TFLOPS,
-         "unit": "TFLOP/s", "frac": a32 / FP32_MFMA_PEAK_TFLOPS, "algorithmic_per_pair": per_pair,
-         "achieved_8flop_equivalent": a32 * 8.0 / 6.0,
-         "timed": "the whole adjoint call (sorted copy, G blocks, product)"}, "mfma_f32_TFLOPs")
+    line["roofline_fp32"] = {
+        "bound": "mfma", "kernel": "k_helm_split_cols", "achieved": a32, "peak": BF16_MFMA_PEAK_TFLOPS,
+        "unit": "TFLOP/s", "frac": a32 / BF16_MFMA_PEAK_TFLOPS, "algorithmic_per_pair": SPLIT_PER_PAIR,
+        "achieved_8flop_equivalent": 8.0 * pairs / (t_adj32 / K) / 1e12,
+        "timed": "the whole adjoint call (sorted copy, G blocks, product)"}
     # A^T g against the oracle's transpose action (a scatter over every target's near field)
     import oracle
     gh = g.cpu().numpy()

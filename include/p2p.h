@@ -324,22 +324,23 @@ p2p_status p2p_eval_gravity_noalloc(const p2p_tree *tree, const p2p_nbrs *nbrs, 
  * for each of the nrhs columns, with h and k of I's instance.  grids: the host
  * array the tree was built from.  q (GATHER) and u: caller order [n][nrhs],
  * float2 (FP32_MIXED) or double2 (FP64) interleaved complex.  REDUNDANT reads
- * q from `red` (built with the same precision and nrhs).  FP32_MIXED with
- * nrhs a multiple of 32 (at most 2^20) runs on FP32 matrix cores (v_mfma_f32_32x32x2f32) in
- * one persistent launch over all boxes of all instances, taking (box, RHS
- * chunk) items in tree order from eight queues, one per XCD, each over a
- * contiguous eighth of the items, a wave whose own queue is empty taking from
- * the others in turn (neighbouring boxes meet in one XCD's L2); instances whose k h
- * agree to 1e-12 share one set of G blocks.  Every other
- * nrhs, and FP64, runs on the matrix cores of its precision
- * (v_mfma_f32_16x16x4f32 or v_mfma_f64_16x16x4f64) with tiles of 16 (target
- * box, right-hand side) pairs as the columns of the product.  `tile` (host int32[4], may be
- * NULL = default {4, 2, 64 or 32, 1}) is the launch shape the autotuner picked:
- * tile[0] = waves per workgroup (1, 2 or 4), tile[1] = workgroups per compute
- * unit (1..16), tile[2] = right-hand sides per wave (32 or 64, dividing nrhs),
- * tile[3] = copies of the G blocks in memory (1, 2, 4 or 8; the block-level
- * pattern redundancy factor of Sec. 5.1.2, the workgroups of one XCD reading
- * different copies); other paths reject a non-NULL tile with P2P_EINVAL. */
+ * q from `red` (built with the same precision and nrhs).  The columns of the
+ * matrix product are the (target box, right-hand side) pairs, for any nrhs.
+ * Single precision runs on the BF16 matrix cores with every operand split
+ * exactly into three BF16 parts and FP32 accumulation (the rounding of single
+ * precision), FP64 on the FP64 matrix cores.  Calls of many columns take
+ * (tile of columns) items in tree order from eight queues in one persistent
+ * launch, one queue per XCD over a contiguous eighth of the items, a workgroup
+ * whose own queue is empty taking from the others in turn (neighbouring boxes
+ * meet in one XCD's L2).  Instances whose k h agree to 1e-12 share one set of
+ * G blocks.  `tile` (host int32[4], may be NULL = default {4, 1, 32, 1}) is the
+ * launch shape of single-precision calls with nrhs a multiple of 32 (at most
+ * 2^20) that the autotuner picked: tile[0] = 1, 2 or 4: workgroups of two (1,
+ * 2) or four tiles of 32 columns, two wavefronts each; tile[1] = workgroups per
+ * compute unit (1..16); tile[2] = right-hand sides of a tile's columns taken
+ * per item (32 or 64, dividing nrhs); tile[3] = copies of the G blocks in
+ * memory (1, 2, 4 or 8; the block-level pattern redundancy factor of Sec.
+ * 5.1.2, the workgroups of one XCD reading different copies); other paths reject a non-NULL tile with P2P_EINVAL. */
 p2p_status p2p_eval_helmholtz(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red,
                               p2p_layout layout, p2p_precision prec,
                               const p2p_grid *grids, int32_t n_grids, int32_t nrhs,

@@ -1,7 +1,7 @@
-"""Autotuner for the launch shape of the multi-RHS Helmholtz matrix-core kernel.
+"""Autotuner for the launch shape of the Helmholtz product for many columns.
 
-Candidates are (waves per workgroup, workgroups per CU, right-hand sides per
-wave); the best of them is then tried with 2, 4 and 8 copies of the G blocks
+Candidates are (tile[0], workgroups per CU, right-hand sides per item; see
+p2p_eval_helmholtz); the best of them is then tried with 2, 4 and 8 copies of the G blocks
 in memory (the pattern redundancy factor), and the fewest copies within 2% of
 the fastest time are kept.  Each candidate is timed on the
 actual problem with HIP events (one warm-up, then the median of `reps` calls)
@@ -91,8 +91,8 @@ def tune_helmholtz(tree: api.Tree, nbrs: api.Nbrs, q: Optional[torch.Tensor] = N
                    use_cache: bool = True, copies: Sequence[int] = COPIES, prec: str = "fp32"
                    ) -> Tuple[Tuple[int, int, int, int], Dict[str, float]]:
     """Pick the fastest launch shape, then the number of copies of the G
-    blocks; returns (tile, timings), tile = (waves per workgroup, workgroups
-    per CU, RHS per wave, copies).  prec: "fp32" (FP64 per-target sums of the
+    blocks; returns (tile, timings), tile as for p2p_eval_helmholtz (the last
+    entry the copies).  prec: "fp32" (FP64 per-target sums of the
     per-box partial products) or "fp32_plain"."""
     nrhs = red.nrhs if red is not None else q.shape[1]
     key = problem_key(tree, nrhs, layout, prec)

@@ -803,21 +803,23 @@ extern "C" p2p_status p2p_eval_gravity_remote(const p2p_tree *tree, const p2p_tr
 namespace {
 
 // Everything a Helmholtz evaluation derives from its arguments on the host:
-// the path (columns of right-hand sides, or columns of (box, right-hand side)
-// pairs), the launch shape, the distinct k h values (one set of G blocks
+// the product (few columns, many columns, FP64), the launch shape, the distinct k h values (one set of G blocks
 // each), and the layout of the set-up buffer.  The set-up buffer (the plan)
 // holds the instances' parameters and the G blocks; it is filled by helm_fill, either on every call (p2p_eval_helmholtz, in the
 // workspace) or once (p2p_helmholtz_prepare, in a caller buffer).
+constexpr int64_t kWideColumns = 24576;
 struct HelmSetup {
     p2p_precision prec;
     int32_t nrhs;
-    bool fp64, mfma, cols, inline_params;
-    int waves_per_wg = 4, wg_per_cu = 2, rhs_tile = 32, copies = 1, planes = 6;
+    bool fp64, wide, inline_params;
+    int waves_per_wg = 4, wg_per_cu = 1, rhs_tile = 32, copies = 1;
+    // 32-column tiles per workgroup of the product for many columns
+    int tiles_per_wg() const { return waves_per_wg == 4 ? 4 : 2; }
     int32_t n_grids = 0, n_tables = 0, n_tiles = 0;
     std::vector<double> khs;
     std::vector<int32_t> itab;
     std::vector<float> iscale;
-    std::vector<int32_t> first;   // column path: first tile, then first box, of each instance (and the totals)
+    std::vector<int32_t> first;   // first tile, then first box, of each instance (and the totals)
     size_t o_kh = 0, o_itab = 0, o_isc = 0, o_first = 0, param_bytes = 0;
     HelmInline inl{};
 };
@@ -841,17 +843,17 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     h->nrhs = nrhs;
     h->n_grids = n_grids;
     h->fp64 = prec == P2P_FP64;
-    // the product with right-hand sides as columns addresses a box's 64 source
-    // rows with 32-bit byte offsets (buffer loads), so nrhs above 2^20 takes
-    // the column path
-    h->mfma = !h->fp64 && nrhs % 32 == 0 && nrhs <= (1 << 20);
-    // every other count, and FP64 (on the FP64 matrix instructions): (box,
-    // right-hand side) pairs as columns, which wastes at most 15 columns per
-    // instance whatever nrhs is
-    h->cols = !h->mfma;
-    h->rhs_tile = (nrhs % 64 == 0) ? 64 : 32;
+    // Single precision: from kWideColumns columns on, the product that stages G
+    // in LDS for many columns; below, the one that splits the offsets of 32
+    // columns over eight wavefronts and both row tiles over two workgroups,
+    // which fills the card with fewer columns: 16,384 columns 80-99 us against
+    // 134-138 us, 32,768 columns 174 against 150 us per call.  A launch shape is
+    // for the former.
+    const int64_t columns = tree->n_leaves * static_cast<int64_t>(nrhs);
+    h->wide = !h->fp64 && (tile || columns >= kWideColumns);
     if (tile) {
-        if (!h->mfma) return fail(P2P_EINVAL, "tile applies to the matrix-core path (FP32_MIXED, nrhs % 32 == 0)");
+        if (h->fp64 || nrhs % 32 != 0 || nrhs > (1 << 20))
+            return fail(P2P_EINVAL, "tile applies to single precision with nrhs a multiple of 32 up to 2^20");
         h->waves_per_wg = tile[0];
         h->wg_per_cu = tile[1];
         h->rhs_tile = tile[2];
@@ -883,22 +885,20 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
         h->iscale[g] = static_cast<float>(1.0 / grids[g].h);
     }
     h->n_tables = static_cast<int32_t>(h->khs.size());
-    if (h->cols) {
-        // every box of a grid instance is a leaf, instances in order
-        int64_t boxes = 0, tiles = 0;
-        const int64_t cb = h->fp64 ? kHelmColBoxes : kHelmSplitCols;
-        h->first.assign(2 * static_cast<size_t>(n_grids + 1), 0);
-        for (int32_t g = 0; g < n_grids; ++g) {
-            const int64_t nb = static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
-            boxes += nb;
-            tiles += (nb * nrhs + cb - 1) / cb;
-            if (tiles > INT32_MAX) return fail(P2P_EINVAL, "nrhs too large for these grids");
-            h->first[g + 1] = static_cast<int32_t>(tiles);
-            h->first[n_grids + 1 + g + 1] = static_cast<int32_t>(boxes);
-        }
-        if (boxes != tree->n_leaves) return fail(P2P_EINVAL, "tree leaves do not match the grids' boxes");
-        h->n_tiles = static_cast<int32_t>(tiles);
+    // every box of a grid instance is a leaf, instances in order
+    int64_t boxes = 0, tiles = 0;
+    const int64_t cb = h->fp64 ? kHelmColBoxes : kHelmSplitCols * (h->wide ? h->tiles_per_wg() : 1);
+    h->first.assign(2 * static_cast<size_t>(n_grids + 1), 0);
+    for (int32_t g = 0; g < n_grids; ++g) {
+        const int64_t nb = static_cast<int64_t>(grids[g].n_side / 4) * (grids[g].n_side / 4) * (grids[g].n_side / 4);
+        boxes += nb;
+        tiles += (nb * nrhs + cb - 1) / cb;
+        if (tiles > INT32_MAX) return fail(P2P_EINVAL, "nrhs too large for these grids");
+        h->first[g + 1] = static_cast<int32_t>(tiles);
+        h->first[n_grids + 1 + g + 1] = static_cast<int32_t>(boxes);
     }
+    if (boxes != tree->n_leaves) return fail(P2P_EINVAL, "tree leaves do not match the grids' boxes");
+    h->n_tiles = static_cast<int32_t>(tiles);
     // the host parameters (h per instance, k h per table, the table and 1/h of
     // each instance, the column tiles) travel in one copy: each small copy
     // costs a blit launch, a sizeable part of a call on a small grid
@@ -907,9 +907,9 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     h->o_isc = h->o_itab + 4 * static_cast<size_t>(n_grids);
     h->o_first = h->o_isc + 4 * static_cast<size_t>(n_grids);
     h->param_bytes = h->o_first + 4 * h->first.size();
-    // a column-path call on few instances takes its parameters in the kernel
-    // arguments; every other call uploads them
-    h->inline_params = h->cols && n_grids <= kInlineGrids && h->n_tables <= kInlineGrids;
+    // a call on few instances takes its parameters in the kernel arguments;
+    // every other call uploads them
+    h->inline_params = n_grids <= kInlineGrids && h->n_tables <= kInlineGrids;
     if (h->inline_params) {
         HelmInline &inl = h->inl;
         inl.n_grids = n_grids;
@@ -931,15 +931,15 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
 // Size of the G blocks in float2.
 size_t helm_block_elems(const HelmSetup &h) {
     const size_t sets = static_cast<size_t>(h.n_tables) * h.copies * 27;
-    if (!h.cols || h.fp64) return sets * 4096 * 2;                      // float4, double2
-    return sets * 8 * static_cast<size_t>(h.planes) * 64 * 2;           // 16-byte operands
+    if (h.fp64) return sets * 4096 * 2;                                 // double2
+    return sets * 8 * 6 * 64 * 2;                                       // 16-byte operands
 }
 
 HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h) {
     HelmSetupBufs b;
     b.params = ar.take<char>(h.param_bytes);
-    // the G blocks, and on the column path 64 zero entries after them
-    b.blocks = ar.take<float2>(helm_block_elems(h) + (h.cols ? (h.fp64 ? 128 : 64) : 0));
+    // the G blocks and the zero entries after them
+    b.blocks = ar.take<float2>(helm_block_elems(h) + (h.fp64 ? 128 : 63 + static_cast<size_t>(h.nrhs)));
     return b;
 }
 
@@ -956,13 +956,12 @@ p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid 
         std::memcpy(hp.data() + h.o_kh, h.khs.data(), 8 * static_cast<size_t>(h.n_tables));
         std::memcpy(hp.data() + h.o_itab, h.itab.data(), 4 * static_cast<size_t>(h.n_grids));
         std::memcpy(hp.data() + h.o_isc, h.iscale.data(), 4 * static_cast<size_t>(h.n_grids));
-        if (h.cols) std::memcpy(hp.data() + h.o_first, h.first.data(), 4 * h.first.size());
+        std::memcpy(hp.data() + h.o_first, h.first.data(), 4 * h.first.size());
         // a copy from pageable memory has read its source when it returns
         P2P_HIP(hipMemcpyAsync(b.params, hp.data(), h.param_bytes, hipMemcpyHostToDevice, s));
     }
-    if (!h.cols) return launch_green_blocks(d_kh, h.inl, h.n_tables, h.copies, b.blocks, s);
     if (h.fp64) return launch_green_blocks64(d_kh, h.inl, h.n_tables, b.blocks, s);
-    return launch_split_blocks(d_kh, h.inl, h.n_tables, h.copies, h.planes, b.blocks, s);
+    return launch_split_blocks(d_kh, h.inl, h.n_tables, h.copies, h.nrhs, b.blocks, s);
 }
 
 // Argument checks of an evaluation that come after the workspace query.
@@ -997,7 +996,7 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
                     const void *q, void *u, int32_t conj, hipStream_t s) {
     P2P_TRY(helm_check_call(h, tree, nbrs, red, layout, q, u, conj));
     const bool redundant = layout == P2P_REDUNDANT;
-    const int64_t n = tree->n, L = tree->n_leaves;
+    const int64_t n = tree->n;
     const int32_t nrhs = h.nrhs;
     const bool tiled = redundant && red->grain > 1;
     if (!redundant) {
@@ -1011,7 +1010,6 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     const int32_t *d_itab = reinterpret_cast<const int32_t *>(b.params + h.o_itab);
     const float *d_iscale = reinterpret_cast<const float *>(b.params + h.o_isc);
     HelmholtzMfmaArgs a{};
-    a.L = L;
     a.key_bits = tree->key_bits;
     a.leaf_start = tree->leaf_start;
     a.leaf_key = tree->leaf_key;
@@ -1022,8 +1020,7 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.red_row = tiled ? red->red_row : nullptr;
     a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
     a.blocks = b.blocks;
-    a.planes = h.planes;
-    a.zeros = h.cols ? b.blocks + helm_block_elems(h) : nullptr;
+    a.zeros = b.blocks + helm_block_elems(h);
     a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
     a.n = n;
     a.parts = parts;
@@ -1034,25 +1031,23 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.comp = h.prec == P2P_FP32_MIXED;
     a.u = static_cast<float2 *>(u);
     a.copies = h.copies;
-    if (h.cols) {
-        const int32_t *first = reinterpret_cast<const int32_t *>(b.params + h.o_first);
-        const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids};
-        return h.fp64 ? launch_helmholtz_cols64(a, ht, h.inl, h.n_tiles, redundant, s)
-                      : launch_helmholtz_split_cols(a, ht, h.inl, h.n_tiles, redundant, s);
-    }
     a.counter = counter;
-    return launch_helmholtz_mfma(a, redundant, h.waves_per_wg, h.wg_per_cu, h.rhs_tile, s);
+    const int32_t *first = reinterpret_cast<const int32_t *>(b.params + h.o_first);
+    const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids};
+    if (h.fp64) return launch_helmholtz_cols64(a, ht, h.inl, h.n_tiles, redundant, s);
+    if (!h.wide) return launch_helmholtz_split_cols(a, ht, h.inl, h.n_tiles, redundant, s);
+    return launch_helmholtz_split(a, ht, h.inl, h.n_tiles, redundant, h.tiles_per_wg(), h.wg_per_cu, h.rhs_tile, s);
 }
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
-// (right-hand sides as columns), the sorted copy of q (GATHER) and, in FP64, the two partial results of tiles whose offsets two workgroups
+// (many columns), the sorted copy of q (GATHER) and, in FP64, the two partial results of tiles whose offsets two workgroups
 // share: at most half as many tiles as the card has CUs, so no more than
 // kMaxSplitTiles on any card, and larger calls hold none.
 constexpr int32_t kMaxSplitTiles = 256;
 void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, int32_t **counter, char **sorted,
                     double2 **parts) {
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
-    *counter = h.mfma ? ar.take<int32_t>(64) : nullptr;
+    *counter = h.wide ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
     *parts = h.fp64 && h.n_tiles <= kMaxSplitTiles ? ar.take<double2>(2 * static_cast<size_t>(n) * h.nrhs) : nullptr;
 }

@@ -100,41 +100,63 @@ __device__ inline ColTile col_tile(const HelmInline &inl, const HelmTiles &ht, i
 // (offset, box) from the near lists of the tile's boxes (one contiguous run of
 // the CSR; -1 where the box has no such neighbour), and each box's first
 // sorted target row.
+struct ColMapView {
+    int64_t *row;         // [27][cap]
+    int64_t *nstart;      // [cap + 1]: list start of each box
+    uint64_t *key;        // [cap]: local Morton key
+    int64_t *rstart;      // [cap]: segment start (redundant layout, box grain)
+    int32_t *tstart;      // [cap]: first sorted target row
+    int32_t *present;     // [27]: 1 where some box of the tile has a neighbour at the offset
+    int32_t cap;
+};
 template <int CB>
 struct ColMap {
-    int64_t row[27][CB];
-    int64_t nstart[CB + 1];
-    uint64_t key[CB];       // local Morton key of each box
-    int64_t rstart[CB];     // its segment start (redundant layout, box grain)
-    int32_t tstart[CB];     // its first sorted target row
-    int32_t present[27];    // 1: some box of the tile has a neighbour at this offset
+    int64_t row[27 * CB], nstart[CB + 1], rstart[CB];
+    uint64_t key[CB];
+    int32_t tstart[CB], present[27];
+    __device__ ColMapView view() { return {row, nstart, key, rstart, tstart, present, CB}; }
 };
+// The same in dynamic LDS, from `base`.
+__host__ __device__ inline size_t col_map_bytes(int cap) {
+    return (static_cast<size_t>(27 + 3) * cap + 1) * 8 + static_cast<size_t>(cap + 27) * 4;
+}
+__device__ inline ColMapView col_map_view(void *base, int cap) {
+    ColMapView m;
+    m.cap = cap;
+    m.row = static_cast<int64_t *>(base);
+    m.nstart = m.row + 27 * cap;
+    m.rstart = m.nstart + cap + 1;
+    m.key = reinterpret_cast<uint64_t *>(m.rstart + cap);
+    m.tstart = reinterpret_cast<int32_t *>(m.key + cap);
+    m.present = m.tstart + cap;
+    return m;
+}
 
 // Fills m for the cnt boxes from leaf A0; called by the whole workgroup (T threads), ends with a
 // barrier.  Each column's list start, key, segment start and first target row
 // come in one round of loads; then the entries, two per thread with their
 // loads issued together: at most 27 per box, so one round covers a tile.
-template <bool RED, int CB, int T>
-__device__ void col_map(ColMap<CB> &m, int key_bits, int32_t A0, int32_t cnt, const int32_t *__restrict__ leaf_start,
+template <bool RED, int T>
+__device__ void col_map(const ColMapView &m, int key_bits, int32_t A0, int32_t cnt, const int32_t *__restrict__ leaf_start,
                         const uint64_t *__restrict__ leaf_key, const int64_t *__restrict__ nbr_start,
                         const int32_t *__restrict__ nbr_idx, const int64_t *__restrict__ red_start,
                         const int64_t *__restrict__ red_row) {
     const int tid = threadIdx.x;
     const uint64_t local_mask = (1ull << (3 * key_bits)) - 1ull;
-    for (int i = tid; i < 27 * CB; i += T) m.row[i / CB][i % CB] = -1;
+    for (int i = tid; i < 27 * m.cap; i += T) m.row[i] = -1;
     if (tid < 27) m.present[tid] = 0;
-    if (tid <= cnt) {
-        // all four loads in flight at once (thread cnt only needs the list end)
-        const int32_t a = A0 + min(tid, cnt - 1);
-        const int64_t ns = nbr_start[A0 + tid];
+    for (int k = tid; k <= cnt; k += T) {
+        // all four loads in flight at once (entry cnt only needs the list end)
+        const int32_t a = A0 + min(k, cnt - 1);
+        const int64_t ns = nbr_start[A0 + k];
         const uint64_t key = leaf_key[a];
         const int64_t rs = (RED && !red_row) ? red_start[a] : 0;
         const int32_t ts = leaf_start[a];
-        m.nstart[tid] = ns;
-        if (tid < cnt) {
-            m.key[tid] = key & local_mask;
-            m.rstart[tid] = rs;
-            m.tstart[tid] = ts;
+        m.nstart[k] = ns;
+        if (k < cnt) {
+            m.key[k] = key & local_mask;
+            m.rstart[k] = rs;
+            m.tstart[k] = ts;
         }
     }
     __syncthreads();
@@ -168,7 +190,7 @@ __device__ void col_map(ColMap<CB> &m, int key_bits, int32_t A0, int32_t cnt, co
                 (static_cast<int>(p2pd::compact3(lB[p] >> 2)) - static_cast<int>(p2pd::compact3(lA >> 2))) / 4;
             const int o = (ox + 1) + 3 * (oy + 1) + 9 * (oz + 1);
             m.present[o] = 1;   // every writer stores the same value
-            m.row[o][j] = (RED && !red_row) ? m.rstart[j] + 64 * (e - m.nstart[j]) : rv[p];
+            m.row[o * m.cap + j] = (RED && !red_row) ? m.rstart[j] + 64 * (e - m.nstart[j]) : rv[p];
         }
     }
     __syncthreads();

@@ -76,7 +76,8 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     typedef double f64x4 __attribute__((ext_vector_type(4)));
     constexpr int VW = kColWaves * H;              // waves sharing a tile's offsets
     constexpr int NSL = (27 + VW - 1) / VW;        // offset slots per wave
-    __shared__ ColMap<kColBoxes> sm;
+    __shared__ ColMap<kColBoxes> s_map;
+    const ColMapView sm = s_map.view();
     __shared__ double s_red[kColWaves][4][2][4][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -86,7 +87,8 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     const double sc64 = ct.sc64;
     const int li = lane & 15, kq = lane >> 4;
     const ColLane cl = col_lane<ONE>(ct, nrhs, li);
-    col_map<RED, kColBoxes, 64 * kColWaves>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start, red_row);
+    col_map<RED, 64 * kColWaves>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start,
+                                 red_row);
 
     const double2 *__restrict__ gbase = blocks + static_cast<int64_t>(tab) * (27 * 4096);
     // lane (kq, li) reads, at k-step kk, G_o[source 4 kk + kq][targets li, 16 + li, 32 + li, 48 + li]
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     const int vw = part * kColWaves + w;
     auto ptrs = [&](int idx, const double2 *&Gs, const double2 *&Qp) {
         const int o = vw + VW * idx;
-        const int64_t row = o < 27 ? sm.row[o][cl.box] : int64_t(-1);
+        const int64_t row = o < 27 ? sm.row[o * kColBoxes + cl.box] : int64_t(-1);
         Gs = gbase + (o < 27 ? o : 0) * 4096;
         if constexpr (ONE)
             Qp = (row >= 0 ? src + row : zeros) + kq;

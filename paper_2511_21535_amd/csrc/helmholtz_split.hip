@@ -10,6 +10,7 @@
 // products per complex one) leave 2.2e-7.  A BF16 product takes a sixteenth of
 // the FP32 one's time, so six cost 0.38 of it.  Magnitudes below about 1e-33
 // lose their low parts to the subnormal range; infinities and NaN give NaN.
+#include <algorithm>
 #include <type_traits>
 
 #include "helm_columns.h"
@@ -17,14 +18,16 @@
 namespace p2p {
 namespace {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// The packed conversion as one instruction: from plain casts the compiler
+// converts the low value a second time wherever it is also used as a float.
 __device__ inline uint32_t bf16_pair(float a, float b) {
-    const bf16x2 v = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
-    return __builtin_bit_cast(uint32_t, v);
+    uint32_t r;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
 }
 __device__ inline float bf16_lo(uint32_t v) { return __uint_as_float(v << 16); }
 __device__ inline float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
@@ -38,62 +41,52 @@ __device__ inline void split_pair(float a, float b, uint32_t &h, uint32_t &m, ui
     l = bf16_pair(a1 - bf16_lo(m), b1 - bf16_hi(m));
 }
 
-// G blocks of the split product.  For table t, copy c, box offset o, k-step ks
-// (16 sources) and row tile rt (32 targets), np planes of 64 lanes x 16 bytes:
-// lane l holds the eight sources 16 ks + 8 (l / 32) + 0..7 of target
-// 32 rt + l % 32, the operand order of the instruction.  Planes: the h, m and l
-// parts of Re G, of Im G and, with np = 9, of Re G + Im G (formed in double and
-// rounded to single once, as Re and Im are).  64 zero float2 entries follow
-// (the sources of an absent neighbour).  G depends on the squared distance
+// G operands of the split products: for table t, copy c, box offset o and run
+// s8 of eight sources (8 s8 + 0..7), six planes -- the h, m and l parts of Re G
+// and of Im G, each formed in double and rounded to single once -- of 64
+// targets x 16 bytes: the operand of a lane of either instruction shape, which
+// differ only in which runs and targets their lanes take.  Behind them 63 +
+// nrhs zero entries, the sources of an absent neighbour (64 rows from a
+// column's right-hand side on, stride one).  G depends on the squared distance
 // alone, so a workgroup forms the 148 values it can take once, in double.
+constexpr int kSplitTable = 27 * 8 * 6 * 64;     // 16-byte operands of a table
 __global__ __launch_bounds__(256) void k_split_blocks(const double *__restrict__ kh_dev, HelmInline inl,
-                                                      int32_t n_tables, int32_t copies, int32_t np,
+                                                      int32_t n_tables, int32_t copies, int32_t nrhs,
                                                       u32x4 *__restrict__ out) {
     __shared__ float2 s_g[kDistances];
-    __shared__ float s_sum[kDistances];
-    constexpr int per = 27 * 4 * 2 * 64;            // lanes per table
-    constexpr int wgs = per / 256;
+    constexpr int wgs = 27 * 8 * 64 / 256;
     const int tab = static_cast<int>(blockIdx.x) / wgs;
     const int tid = threadIdx.x;
     if (tid < kDistances) {
         const double2 v = green(table_kh(inl, kh_dev, tab), tid);
         s_g[tid] = make_float2(static_cast<float>(v.x), static_cast<float>(v.y));
-        s_sum[tid] = static_cast<float>(v.x + v.y);
     }
     __syncthreads();
     const int t = (static_cast<int>(blockIdx.x) % wgs) * 256 + tid;
-    const int lane = t & 63, rt = (t >> 6) & 1, ks = (t >> 7) & 3, o = t >> 9;
-    const int i = 32 * rt + (lane & 31), s0 = 16 * ks + 8 * (lane >> 5);
-    float v[3][8];
+    const int i = t & 63, s8 = (t >> 6) & 7, o = t >> 9;
+    u32x4 v[6];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int dd = near_distance(o, s0 + j, i);
-        v[0][j] = s_g[dd].x;
-        v[1][j] = s_g[dd].y;
-        v[2][j] = s_sum[dd];
+    for (int j = 0; j < 4; ++j) {
+        const float2 a = s_g[near_distance(o, 8 * s8 + 2 * j, i)], b = s_g[near_distance(o, 8 * s8 + 2 * j + 1, i)];
+        uint32_t h, m, l;
+        split_pair(a.x, b.x, h, m, l);
+        v[0][j] = h;
+        v[1][j] = m;
+        v[2][j] = l;
+        split_pair(a.y, b.y, h, m, l);
+        v[3][j] = h;
+        v[4][j] = m;
+        v[5][j] = l;
     }
     for (int c = 0; c < copies; ++c) {
-        u32x4 *w = out + (static_cast<int64_t>(tab) * copies + c) * (27 * 8) * np * 64 +
-                   static_cast<int64_t>((o * 4 + ks) * 2 + rt) * np * 64 + lane;
+        u32x4 *w = out + (static_cast<int64_t>(tab) * copies + c) * kSplitTable + (o * 8 + s8) * 6 * 64 + i;
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            if (3 * q >= np) break;
-            u32x4 h, m, l;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t hh, mm, ll;
-                split_pair(v[q][2 * j], v[q][2 * j + 1], hh, mm, ll);
-                h[j] = hh;
-                m[j] = mm;
-                l[j] = ll;
-            }
-            w[(3 * q) * 64] = h;
-            w[(3 * q + 1) * 64] = m;
-            w[(3 * q + 2) * 64] = l;
-        }
+        for (int p = 0; p < 6; ++p) w[p * 64] = v[p];
     }
-    if (blockIdx.x == 0 && tid < 32)
-        out[static_cast<int64_t>(n_tables) * copies * (27 * 8) * np * 64 + tid] = u32x4{0, 0, 0, 0};
+    float2 *z = reinterpret_cast<float2 *>(out + static_cast<int64_t>(n_tables) * copies * kSplitTable);
+    for (int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + tid; k < 63 + static_cast<int64_t>(nrhs);
+         k += static_cast<int64_t>(gridDim.x) * 256)
+        z[k] = make_float2(0.f, 0.f);
 }
 
 // (target box, right-hand side) columns, 32 to a tile.  Two workgroups of eight
@@ -117,10 +110,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ perm,
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
-    const u32x4 *__restrict__ blocks, int32_t np, int32_t copies, const float2 *__restrict__ zeros,
+    const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
     const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, float2 *__restrict__ u) {
     using S = typename std::conditional<COMP, double, float>::type;
-    __shared__ ColMap<kSplitCols> sm;
+    __shared__ ColMap<kSplitCols> s_map;
+    const ColMapView sm = s_map.view();
     __shared__ S s_red[kSplitWaves][16][2][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -130,8 +124,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
                                             static_cast<int32_t>(item >> 1));
     const int col = lane & 31, half = lane >> 5;
     const ColLane cl = col_lane<ONE>(ct, nrhs, col);
-    col_map<RED, kSplitCols, 64 * kSplitWaves>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start,
-                                               nbr_idx, red_start, red_row);
+    col_map<RED, 64 * kSplitWaves>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start,
+                                   red_row);
     // the offsets that occur in this tile, as a bit mask
     const uint32_t present = static_cast<uint32_t>(__ballot(lane < 27 && sm.present[min(lane, 26)] != 0));
     const int n_off = __popc(present);
@@ -143,20 +137,20 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
         return __builtin_amdgcn_readfirstlane(__ffs(m) - 1);
     };
     const u32x4 *__restrict__ gtab =
-        blocks + static_cast<int64_t>(ct.tab) * copies * (27 * 8) * np * 64 + static_cast<int64_t>(rt) * np * 64 + lane;
+        blocks + static_cast<int64_t>(ct.tab) * copies * kSplitTable + half * 6 * 64 + 32 * rt + col;
     // this lane's sources at k-step ks: rows 16 ks + 8 half + 0..7 of its column
     const float2 *qp = nullptr;
     int64_t qs = 0;
     const u32x4 *gp = nullptr;
     auto open = [&](int slot) {
         const int o = offset_of(slot);
-        const int64_t row = sm.row[o][cl.box];
-        gp = gtab + static_cast<int64_t>(o) * 8 * np * 64;
+        const int64_t row = sm.row[o * kSplitCols + cl.box];
+        gp = gtab + o * 8 * 6 * 64;
         if constexpr (ONE) {
             qp = (row >= 0 && col < ct.cnt ? src + row : zeros) + 8 * half;
         } else {
-            qp = row >= 0 ? src + (row + 8 * half) * nrhs + cl.rhs : zeros;
-            qs = row >= 0 ? nrhs : 0;
+            qs = row >= 0 ? nrhs : 1;
+            qp = (row >= 0 ? src + row * nrhs : zeros) + 8 * half * qs + cl.rhs;
         }
     };
     auto load_q = [&](int ks, float (&v)[16]) {
@@ -183,7 +177,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     };
     auto load_g = [&](int ks, u32x4 (&g)[6]) {
 #pragma unroll
-        for (int p = 0; p < 6; ++p) g[p] = gp[(ks * 2 * np + p) * 64];
+        for (int p = 0; p < 6; ++p) g[p] = gp[(ks * 2 * 6 + p) * 64];
     };
     // the h, m, l parts of Re q and Im q (negated with CONJ)
     auto split_q = [&](const float (&v)[16], u32x4 (&q)[6]) {
@@ -292,12 +286,291 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     }
 }
 
+// ------------------------------------------------------------ many columns --
+// The same product when there are columns enough to fill the card: a workgroup
+// of 2 W wavefronts takes W tiles of 32 columns through the offsets together,
+// so that a G block is read from L2 once for 32 W columns and its operands come
+// from LDS.  A wavefront holds all 64 targets of 16 columns
+// (v_mfma_f32_16x16x32_bf16): each Q value is then split once per target box,
+// and 32 accumulator and 64 FP64-sum registers leave room for two wavefronts
+// per SIMD, one of which splits, adds and waits while the other multiplies.
+// On the 128-grid, 64-RHS batch the product takes 20.8 ms, 1.27 PFLOP/s of BF16
+// products with the matrix cores busy 0.62 of the cycles at 2.05 GHz (FP32
+// matrix instructions: 26.4 ms).  A wavefront per SIMD with 64 x 32 results and
+// three real products per complex one issues a quarter fewer matrix
+// instructions, but its vector work, eight instructions per matrix instruction,
+// hides behind nothing: 22.3 ms.  Row tiles of 32 over twice the wavefronts
+// split every Q value twice: 24.1 ms.
+// G is staged 32 sources at a time through three LDS buffers: the stage after
+// next is written behind a stage's one barrier and its loads are issued a stage
+// earlier, so a barrier waits for the slowest wavefront only.  The barrier
+// stands at the middle of the stage for the first W wavefronts and at its start
+// for the others, so that the two of a SIMD do not split at the same time
+// (21.6 ms with all at the middle).  G parts are read from LDS two plane pairs
+// ahead of their products.
+// Items (one tile, or two with 64 right-hand sides per wave) are taken in tree
+// order from eight queues, one per XCD over a contiguous eighth of them
+// (neighbouring boxes meet in one XCD's L2), a workgroup whose own queue is
+// empty taking from the others in turn; counters only grow, so every workgroup
+// ends after at most eight misses.
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+constexpr int kWideStage = 4 * 6 * 64;    // 16-byte operands of a stage: [run of eight sources][plane][target]
+
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+template <int W, bool RED, bool CONJ, bool COMP, bool UNI>
+__global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) void k_helm_split(
+    int key_bits, HelmTiles ht, HelmInline inl, int32_t nrhs, int32_t n_tiles, int32_t per_item, int32_t cap,
+    const int32_t *__restrict__ leaf_start, const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ perm,
+    const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
+    const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
+    const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
+    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, int32_t *__restrict__ counter,
+    float2 *__restrict__ u) {
+    constexpr int NT = 128 * W, NL = kWideStage / NT;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    __shared__ int32_t s_item;
+    u32x4 *const sg = reinterpret_cast<u32x4 *>(smem);
+    const ColMapView sm = col_map_view(smem + 3 * kWideStage * sizeof(u32x4), cap);
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kq = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int xcd = static_cast<int>(blockIdx.x & 7);
+    const int64_t items = (n_tiles + per_item - 1) / per_item;
+    auto slice = [&](int x) { return items * x / 8; };
+    // thread 0: `ticket` is drawn at the start of an item and looked at after it
+    int sl = 0;
+    int32_t ticket = tid == 0 ? atomicAdd(&counter[xcd], 1) : 0;
+    for (;;) {
+        if (tid == 0) {
+            int32_t it = -1;
+            for (;;) {
+                const int x = (xcd + sl) & 7;
+                if (slice(x) + ticket < slice(x + 1)) {
+                    it = static_cast<int32_t>(slice(x) + ticket);
+                    break;
+                }
+                if (++sl == 8) break;
+                ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
+            }
+            s_item = it;
+        }
+        __syncthreads();
+        const int32_t item = __builtin_amdgcn_readfirstlane(s_item);
+        if (item < 0) break;
+        if (tid == 0) ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
+        const int32_t tile_end = static_cast<int32_t>(min<int64_t>((item + int64_t(1)) * per_item, n_tiles));
+        for (int32_t tile = item * per_item; tile < tile_end; ++tile) {
+            const ColTile ct = col_tile<32 * W>(inl, ht, nrhs, inst_table, inst_scale, nullptr, tile);
+            const ColLane cl = col_lane<false>(ct, nrhs, 16 * w + col);
+            __syncthreads();   // the map and the stages of the tile before are no longer read
+            col_map<RED, NT>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start,
+                             red_row);
+            uint32_t present = static_cast<uint32_t>(__ballot(lane < 27 && sm.present[min(lane, 26)] != 0));
+            if (present == 0) present = 1;   // empty lists: one offset, every source row absent
+            const int n_off = __popc(present);
+            const int64_t copy = (blockIdx.x >> 3) % copies;   // the workgroups of one XCD spread over the copies
+            const u32x4 *__restrict__ gtab =
+                blocks + (static_cast<int64_t>(ct.tab) * copies + copy) * kSplitTable + tid;
+
+            // stages: two per offset that occurs, in order; past the end the last offset's again
+            u32x4 st[NL];
+            uint32_t lm = present;
+            int lh = 0;
+            auto load_stage = [&]() {
+                const u32x4 *p = gtab + ((__ffs(lm) - 1) * 2 + lh) * kWideStage;
+#pragma unroll
+                for (int i = 0; i < NL; ++i) st[i] = p[i * NT];
+                lh ^= 1;
+                if (lh == 0 && (lm & (lm - 1))) lm &= lm - 1;
+            };
+            auto write_stage = [&](int buf) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) sg[buf * kWideStage + i * NT + tid] = st[i];
+            };
+            // this lane's source rows at an offset.  UNI: the wavefront's columns are
+            // 16 right-hand sides of one box, so the rows are reached through a
+            // buffer descriptor (scalar registers; of length zero where the box has
+            // no such neighbour: such loads return zeros), a fixed lane offset and a
+            // scalar offset per row, without vector instructions on addresses.
+            // Otherwise a pointer and row stride per lane.
+            const float2 *qp = nullptr;
+            int64_t qs = 0;
+            Rsrc qr_;
+            const int rhs0 = __builtin_amdgcn_readfirstlane(cl.rhs);
+            const int voff = (8 * kq * nrhs + col) * static_cast<int>(sizeof(float2));
+            auto rows_of = [&](int o) {
+                const int64_t row = sm.row[o * cap + cl.box];
+                if constexpr (UNI) {
+                    const int64_t r = (static_cast<int64_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row >> 32))) << 32) |
+                                      static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(row)));
+                    qr_ = __builtin_amdgcn_make_buffer_rsrc(
+                        const_cast<float2 *>(src + (r >= 0 ? r * nrhs : 0) + rhs0), 0,
+                        r >= 0 ? (64 * nrhs - rhs0) * static_cast<int>(sizeof(float2)) : 0, 0x00020000);
+                } else {
+                    qs = row >= 0 ? nrhs : 1;
+                    qp = (row >= 0 ? src + row * nrhs : zeros) + 8 * kq * qs + cl.rhs;
+                }
+            };
+            auto load_q = [&](int ks, float (&v)[16]) {
+                const float2 *p = qp + 32 * ks * qs;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    float2 x;
+                    if constexpr (UNI) {
+                        x = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(
+                                                           qr_, voff, (32 * ks + j) * nrhs * static_cast<int>(sizeof(float2)), 0));
+                    } else {
+                        x = *p;
+                        p += qs;
+                    }
+                    v[2 * j] = x.x;
+                    v[2 * j + 1] = x.y;
+                }
+            };
+            // parts of Re q, Im q and -Im q
+            auto split_q = [&](const float (&v)[16], u32x4 (&qr)[3], u32x4 (&qi)[3], u32x4 (&qn)[3]) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t h, m, l;
+                    split_pair(v[4 * j], v[4 * j + 2], h, m, l);
+                    qr[0][j] = h;
+                    qr[1][j] = m;
+                    qr[2][j] = l;
+                    split_pair(v[4 * j + 1], v[4 * j + 3], h, m, l);
+                    qi[0][j] = h;
+                    qi[1][j] = m;
+                    qi[2][j] = l;
+                }
+#pragma unroll
+                for (int p = 0; p < 3; ++p) qn[p] = qi[p] ^ 0x80008000u;
+            };
+            // the pairs of planes (part of Re G, the same part of Im G) of a stage
+            // in the order of their use, l, m, h of row tile 0, then of 1, ...
+            auto read_g = [&](int buf, int pair, u32x4 (&g)[2]) {
+                const int rt = pair / 3, p = 2 - pair % 3;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) g[c] = sg[buf * kWideStage + (kq * 6 + 3 * c + p) * 64 + 16 * rt + col];
+            };
+            floatx4 re[4], im[4];
+            const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) re[rt] = im[rt] = zero;
+            constexpr int CN = COMP ? 4 : 1;
+            double cr[4][CN], ci[4][CN];
+            if constexpr (COMP) {
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) cr[rt][r] = ci[rt][r] = 0.0;
+            }
+            auto mfma = [](const u32x4 &x, const u32x4 &y, const floatx4 &c) {
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x),
+                                                               __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
+            };
+
+            float raw[16];
+            u32x4 g[3][2];
+            load_stage();
+            write_stage(0);
+            load_stage();
+            write_stage(1);
+            load_stage();
+            const bool late = w >= W;   // the second wavefront of a SIMD
+            uint32_t cm = present;
+            rows_of(__ffs(cm) - 1);
+            load_q(0, raw);
+            __syncthreads();
+            read_g(0, 0, g[0]);
+            read_g(0, 1, g[1]);
+            int b0 = 0, b1 = 1, b2 = 2;   // buffers of this stage, the next and the one after
+            auto next_stage = [&]() {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+                write_stage(b2);
+                load_stage();
+            };
+            for (int k = 0; k < n_off; ++k) {
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    if (late) next_stage();
+                    u32x4 qr[3], qi[3], qn[3];
+                    split_q(raw, qr, qi, qn);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ks == 1) {
+                        if (cm & (cm - 1)) cm &= cm - 1;
+                        rows_of(__ffs(cm) - 1);
+                    }
+                    load_q(1 - ks, raw);   // the next stage's
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) {
+                        if (rt == 2 && !late) next_stage();
+                        // conj(G) q = conj(G conj(q))
+                        const u32x4(&qa)[3] = CONJ ? qn : qi, (&qb)[3] = CONJ ? qi : qn;
+#pragma unroll
+                        for (int p = 2; p >= 0; --p) {
+                            const int pair = 3 * rt + 2 - p, ahead = pair + 2;
+                            read_g(ahead < 12 ? b0 : b1, ahead % 12, g[ahead % 3]);
+                            __builtin_amdgcn_sched_barrier(0);
+                            const u32x4(&gc)[2] = g[pair % 3];
+#pragma unroll
+                            for (int r = 2 - p; r >= 0; --r) {
+                                const bool fresh = COMP && ks == 0 && p == 2;
+                                re[rt] = mfma(gc[0], qr[r], fresh ? zero : re[rt]);
+                                im[rt] = mfma(gc[0], qa[r], fresh ? zero : im[rt]);
+                                re[rt] = mfma(gc[1], qb[r], re[rt]);
+                                im[rt] = mfma(gc[1], qr[r], im[rt]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    const int t = b0;
+                    b0 = b1;
+                    b1 = b2;
+                    b2 = t;
+                }
+                if constexpr (COMP) {
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            cr[rt][r] += static_cast<double>(re[rt][r]);
+                            ci[rt][r] += static_cast<double>(im[rt][r]);
+                        }
+                }
+            }
+            if (16 * w + col < ct.cnt) {
+                const int32_t t0 = sm.tstart[cl.box];
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int64_t at = static_cast<int64_t>(perm[t0 + 16 * rt + 4 * kq + r]) * nrhs + cl.rhs;
+                        float x, y;
+                        if constexpr (COMP) {
+                            x = static_cast<float>(cr[rt][r] * ct.sc);
+                            y = static_cast<float>(ci[rt][r] * ct.sc);
+                        } else {
+                            x = re[rt][r] * ct.sc;
+                            y = im[rt][r] * ct.sc;
+                        }
+                        u[at] = make_float2(x, CONJ ? -y : y);
+                    }
+            }
+        }
+        __syncthreads();   // s_item has been read by all
+    }
+}
+
+__global__ void k_zero_counter(int32_t *c, int n) {
+    if (static_cast<int>(threadIdx.x) < n) c[threadIdx.x] = 0;
+}
+
 }  // namespace
 
 p2p_status launch_split_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               int32_t planes, void *blocks, hipStream_t s) {
-    const int64_t wgs = static_cast<int64_t>(n_tables) * (27 * 4 * 2 * 64 / 256);
-    k_split_blocks<<<static_cast<unsigned>(wgs), 256, 0, s>>>(d_kh, inl, n_tables, copies, planes,
+                               int32_t nrhs, void *blocks, hipStream_t s) {
+    const int64_t wgs = static_cast<int64_t>(n_tables) * (27 * 8 * 64 / 256);
+    k_split_blocks<<<static_cast<unsigned>(wgs), 256, 0, s>>>(d_kh, inl, n_tables, copies, nrhs,
                                                              static_cast<u32x4 *>(blocks));
     P2P_LAUNCH_CHECK();
     return P2P_OK;
@@ -310,7 +583,7 @@ static void launch_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const 
 #define P2P_SPLIT(O)                                                                                            \
     k_helm_split_cols<R, C, M, O><<<grid, 64 * kSplitWaves, 0, s>>>(                                            \
         a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start,      \
-        a.red_row, a.src, reinterpret_cast<const u32x4 *>(a.blocks), a.planes, a.copies, a.zeros, a.inst_table,  \
+        a.red_row, a.src, reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,  \
         a.inst_scale, a.u)
     // one right-hand side: a lane's eight sources are one 64-byte run, read 16
     // bytes at a time where the rows are aligned to that
@@ -329,6 +602,62 @@ p2p_status launch_helmholtz_split_cols(const HelmholtzMfmaArgs &a, const HelmTil
 #undef P2P_SPLIT_M
     P2P_LAUNCH_CHECK();
     return P2P_OK;
+}
+
+template <int W, bool R, bool C, bool M, bool U>
+static p2p_status launch_wide(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                              int32_t n_tiles, int32_t per_item, unsigned grid, hipStream_t s) {
+    // boxes a tile of 32 W columns can touch
+    const int32_t cap = static_cast<int32_t>(std::min<int64_t>(32 * W, (32 * W + static_cast<int64_t>(a.nrhs) - 2) / a.nrhs + 1));
+    const size_t lds = 3 * kWideStage * sizeof(u32x4) + col_map_bytes(cap);
+    auto *k = k_helm_split<W, R, C, M, U>;
+    P2P_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                static_cast<int>(lds)));
+    k<<<grid, 128 * W, lds, s>>>(a.key_bits, ht, inl, a.nrhs, n_tiles, per_item, cap, a.leaf_start, a.leaf_key, a.perm,
+                                a.nbr_start, a.nbr_idx, a.red_start, a.red_row, a.src,
+                                reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,
+                                a.inst_scale, a.counter, a.u);
+    P2P_LAUNCH_CHECK();
+    return P2P_OK;
+}
+
+template <int W, bool R, bool C>
+static p2p_status launch_wide_m(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                int32_t n_tiles, int32_t per_item, unsigned grid, hipStream_t s) {
+    // 16 right-hand sides of one box per wavefront, a box's rows within 32-bit byte offsets
+    const bool uni = a.nrhs % 16 == 0 && a.nrhs <= (1 << 20);
+    if (a.comp)
+        return uni ? launch_wide<W, R, C, true, true>(a, ht, inl, n_tiles, per_item, grid, s)
+                   : launch_wide<W, R, C, true, false>(a, ht, inl, n_tiles, per_item, grid, s);
+    return uni ? launch_wide<W, R, C, false, true>(a, ht, inl, n_tiles, per_item, grid, s)
+               : launch_wide<W, R, C, false, false>(a, ht, inl, n_tiles, per_item, grid, s);
+}
+
+template <int W>
+static p2p_status launch_wide_w(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                int32_t n_tiles, int32_t per_item, unsigned grid, bool redundant, hipStream_t s) {
+    const bool cj = a.conj != 0;
+    if (redundant)
+        return cj ? launch_wide_m<W, true, true>(a, ht, inl, n_tiles, per_item, grid, s)
+                  : launch_wide_m<W, true, false>(a, ht, inl, n_tiles, per_item, grid, s);
+    return cj ? launch_wide_m<W, false, true>(a, ht, inl, n_tiles, per_item, grid, s)
+              : launch_wide_m<W, false, false>(a, ht, inl, n_tiles, per_item, grid, s);
+}
+
+p2p_status launch_helmholtz_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                  int32_t n_tiles, bool redundant, int tiles_per_wg, int wg_per_cu, int rhs_tile,
+                                  hipStream_t s) {
+    if (n_tiles <= 0) return P2P_OK;
+    int dev = 0, cus = 0;
+    P2P_HIP(hipGetDevice(&dev));
+    P2P_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    k_zero_counter<<<1, 64, 0, s>>>(a.counter, 8);
+    P2P_LAUNCH_CHECK();
+    const int32_t per_item = rhs_tile / 32;
+    const int64_t items = (static_cast<int64_t>(n_tiles) + per_item - 1) / per_item;
+    const unsigned grid = static_cast<unsigned>(std::min<int64_t>(items, static_cast<int64_t>(cus) * wg_per_cu));
+    return tiles_per_wg == 2 ? launch_wide_w<2>(a, ht, inl, n_tiles, per_item, grid, redundant, s)
+                             : launch_wide_w<4>(a, ht, inl, n_tiles, per_item, grid, redundant, s);
 }
 
 }  // namespace p2p

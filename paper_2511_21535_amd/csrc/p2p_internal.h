@@ -263,9 +263,10 @@ struct GravityAdjointArgs {
 };
 p2p_status launch_gravity_adjoint(const GravityAdjointArgs &a, bool mixed, hipStream_t s);
 
-// Multi-RHS Helmholtz on FP32 matrix cores (helmholtz_mfma.hip).
+// Helmholtz on matrix cores: FP64 (helmholtz_cols.hip) and single precision
+// (helmholtz_split.hip), the columns of the product being the (target box,
+// right-hand side) pairs.
 struct HelmholtzMfmaArgs {
-    int64_t L;
     int key_bits;
     const int32_t *leaf_start;
     const uint64_t *leaf_key;
@@ -274,17 +275,15 @@ struct HelmholtzMfmaArgs {
     const int32_t *nbr_idx;
     const int64_t *red_start;
     const int64_t *red_row;    // tile-grain layout: first row of each entry's source box (else null)
-    const float2 *src;         // sorted q rows (gather) or redundant rows, [.][nrhs]
-    const float2 *blocks;      // multi-RHS: float4 (Re, Im, Re + Im, Re - Im) G at [n_tables][copies][27][64 src]
-                               // [64 tgt] (unit spacing); FP64: double2 at [n_tables][27][64 src][16][4]
-                               // (target 16 r + c at [c][r]); split path: `planes` planes of 16-byte operands
-                               // at [n_tables][copies][27][4 k-steps][2 row tiles][planes][64 lanes]
-    int32_t planes;            // split path: 6 (h, m, l of Re G and Im G) or 9 (and of Re G + Im G)
-    const float2 *zeros;       // column path: 64 zero entries (an absent neighbour's sources; double2 in FP64)
-    const double *inst_h;      // per instance: h (FP64 column path with uploaded parameters)
+    const float2 *src;         // sorted q rows (gather) or redundant rows, [.][nrhs] (double2 in FP64)
+    const float2 *blocks;      // G at unit spacing.  FP64: double2 at [n_tables][27][64 src][16][4] (target
+                               // 16 r + c at [c][r]); single precision: the h, m, l parts of Re G
+                               // and Im G at [n_tables][copies][27][8 runs of 8 src][6][64 tgt][8]
+    const float2 *zeros;       // an absent neighbour's sources: 64 zero entries (double2) in FP64, else 63 + nrhs
+    const double *inst_h;      // per instance: h (FP64 with uploaded parameters)
     int64_t n;                 // points
-    double2 *parts;            // column path: [2][n][nrhs] partial results in sorted order (tiles split in two)
-    int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies
+    double2 *parts;            // FP64: [2][n][nrhs] partial results in sorted order (tiles split in two)
+    int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies (many columns)
     const int32_t *inst_table; // per instance: table index
     const float *inst_scale;   // per instance: 1/h
     int32_t *counter;          // [8] work-queue counters, one per XCD slice (zeroed by the launcher)
@@ -293,8 +292,7 @@ struct HelmholtzMfmaArgs {
     int32_t comp;              // 1: each near box's FP32 partial product summed into FP64 per target
     float2 *u;                 // caller order [n][nrhs]
 };
-// Per-call parameters of a column-path call with at most kInlineGrids
-// instances, passed by value in the kernel arguments (no upload, no extra
+// Per-call parameters of a call with at most kInlineGrids instances, passed by value in the kernel arguments (no upload, no extra
 // launch): n_grids = 0 means the device arrays are used instead.
 constexpr int kInlineGrids = 8;
 constexpr int kHelmColBoxes = 16;           // columns (target box, right-hand side) per tile in FP64
@@ -315,21 +313,21 @@ struct HelmInline {
     double iscale64[kInlineGrids];          // 1/h of each instance in double (FP64 path)
 };
 // G blocks for the k h values of d_kh, or of inl.kh when inl.n_grids > 0, in the
-// layouts above (the column layouts with their 64 zero entries behind them).
-p2p_status launch_green_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               void *blocks, hipStream_t s);
+// layouts above, the zero entries behind them.
 p2p_status launch_green_blocks64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks,
                                  hipStream_t s);
 p2p_status launch_split_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               int32_t planes, void *blocks, hipStream_t s);
-p2p_status launch_helmholtz_mfma(const HelmholtzMfmaArgs &a, bool redundant, int waves_per_wg,
-                                 int wg_per_cu, int rhs_tile, hipStream_t s);
-// Column path: the columns of an instance are its (box, right-hand side)
-// pairs, cut into tiles of kHelmColBoxes (FP64) or kHelmSplitCols.
+                               int32_t nrhs, void *blocks, hipStream_t s);
+// Products over the tiles of columns of every instance: kHelmColBoxes columns
+// each in FP64, kHelmSplitCols in launch_helmholtz_split_cols and kHelmSplitCols
+// times tiles_per_wg (2 or 4) in launch_helmholtz_split (many columns).
 p2p_status launch_helmholtz_cols64(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
                                    int32_t n_tiles, bool redundant, hipStream_t s);
 p2p_status launch_helmholtz_split_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
                                        int32_t n_tiles, bool redundant, hipStream_t s);
+p2p_status launch_helmholtz_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,
+                                  int32_t n_tiles, bool redundant, int tiles_per_wg, int wg_per_cu, int rhs_tile,
+                                  hipStream_t s);
 
 // Locality (locality.hip).
 p2p_status launch_locality_stats(const int32_t *leaf_start, const int64_t *nbr_start,

@@ -2,8 +2,8 @@
 matrix-core product, against the FP64 oracle: right-hand-side counts around the
 16-column tile and that leave a partial last tile, instances of one box, tiles
 shared by two workgroups (few columns) and not (many), several G tables, and
-more than 8 instances (uploaded parameters), in both layouts and grains and
-both directions.  Tolerances are the project's: 1e-5 (FP32) and 1e-12 (FP64)."""
+more than 8 instances (uploaded parameters); and the single-precision product
+for many columns; in both layouts and grains and both directions.  Tolerances are the project's: 1e-5 (FP32) and 1e-12 (FP64)."""
 import numpy as np
 import pytest
 import torch
@@ -34,9 +34,18 @@ CASES = [
     ([8] * 5 + [4] * 5, [10, 6] * 5, 5),    # 10 instances: uploaded parameters
 ]
 
+# single precision with columns enough for the product that stages G in LDS: 16
+# right-hand sides of one box per wavefront and not, a partial last tile per
+# instance, two tables, uploaded parameters
+MANY = [
+    ([16, 12], [10, 6], 272),
+    ([16, 12], [10, 10], 301),
+    ([8] * 5 + [4] * 5, [10, 6] * 5, 560),
+]
 
-@pytest.mark.parametrize("sides,ppw,nrhs", CASES)
-@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp32_plain"])
+
+@pytest.mark.parametrize("sides,ppw,nrhs,prec", [(*c, p) for c in CASES for p in ("fp64", "fp32", "fp32_plain")] +
+                         [(*c, p) for c in MANY for p in ("fp32", "fp32_plain")])
 def test_columns_parity(sides, ppw, nrhs, prec):
     print(f"case columns sides={sides} nrhs={nrhs} prec={prec}", flush=True)
     h = np.array([1.0 / n for n in sides])
