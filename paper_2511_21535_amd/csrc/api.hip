@@ -213,11 +213,9 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
     int32_t *vals_tmp = ar.take<int32_t>(n);
     uint32_t *hist = ar.take<uint32_t>(radix_hist_elems(n));
     uint8_t *pair_common = ar.take<uint8_t>(n);
-    int8_t *level = ar.take<int8_t>(n);
-    int32_t *flags = ar.take<int32_t>(n);
-    int32_t *flag_scan = ar.take<int32_t>(n + 1);
-    int32_t *scan_tmp = ar.take<int32_t>(scan_ws_elems(n));
-    int32_t *counters = ar.take<int32_t>(2);   // [0] domain flag, [1] max level
+    uint8_t *mark = ar.take<uint8_t>(n);
+    int32_t *leaf_counts = ar.take<int32_t>(leaf_count_elems(n) + 1);
+    TreeCounts *tc = ar.take<TreeCounts>(1);
     int32_t *d_nside = ar.take<int32_t>(particles ? 1 : n_grids);
     int64_t *d_off = ar.take<int64_t>(particles ? 1 : n_grids);
     p2p_status st;
@@ -239,9 +237,9 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
         tree->max_level = 0;
         return P2P_OK;
     }
-    P2P_HIP(hipMemsetAsync(counters, 0, 2 * sizeof(int32_t), s));
+    P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
     if (particles) {
-        P2P_TRY(launch_particle_keys(x, y, z, n, keys, vals, &counters[0], s));
+        P2P_TRY(launch_particle_keys(x, y, z, n, keys, &tc->bad, s));
     } else {
         std::vector<int32_t> ns(n_grids);
         std::vector<int64_t> off(n_grids);
@@ -251,33 +249,44 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
         }
         P2P_HIP(hipMemcpyAsync(d_nside, ns.data(), n_grids * sizeof(int32_t), hipMemcpyHostToDevice, s));
         P2P_HIP(hipMemcpyAsync(d_off, off.data(), n_grids * sizeof(int64_t), hipMemcpyHostToDevice, s));
-        P2P_TRY(launch_grid_keys(d_nside, d_off, n_grids, key_bits, n, keys, vals, s));
+        P2P_TRY(launch_grid_keys(d_nside, d_off, n_grids, key_bits, n, keys, s));
     }
-    P2P_TRY(radix_sort_pairs(keys, vals, keys_tmp, vals_tmp, n, sort_bits, hist, s));
-    P2P_TRY(launch_leaf_levels(keys, n, tree->kind, leaf_depth, particles ? leaf_cap : 0, pair_common,
-                               level, flags, s));
-    P2P_TRY((exclusive_scan<int32_t, int32_t>(flags, flag_scan, n, scan_tmp, s)));
-    int32_t host[2] = {0, 0};
-    P2P_HIP(hipMemcpyAsync(&host[0], &flag_scan[n], sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    P2P_HIP(hipMemcpyAsync(&host[1], &counters[0], sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    P2P_HIP(hipStreamSynchronize(s));
-    const int64_t L = host[0];
-    if (host[1] != 0) {
+    // Few keys are placed by counting.  More are sorted by the top kSortTop
+    // bits, then every run of equal top bits by a count of its keys: four
+    // passes instead of eight for 60-bit keys.  Points so close that more than
+    // kRunMax share their top bits (a cell of 2^-32 of the domain) set
+    // long_run, and the keys take all their passes.
+    constexpr int kSortTop = 32;
+    const int lo = sort_bits > kSortTop && !rank_sort_fits(n) ? sort_bits - kSortTop : 0;
+    SortBufs sb{keys, keys_tmp, nullptr, vals, vals_tmp};
+    if (rank_sort_fits(n))
+        P2P_TRY(rank_sort_pairs(sb, n, s));
+    else
+        P2P_TRY(radix_sort_pairs(sb, n, lo, sort_bits, hist, s));
+    if (lo > 0) P2P_TRY(sort_runs(sb, n, lo, &tc->long_run, s));
+    TreeCounts host{};
+    for (bool full = lo == 0;; full = true) {
+        P2P_TRY(launch_leaf_levels(sb.keys, n, tree->kind, leaf_depth, particles ? leaf_cap : 0, pair_common, mark,
+                                   leaf_counts, s));
+        P2P_TRY(launch_leaf_write(sb.keys, sb.vals, mark, n, tree->kind, tree->cap_leaves, leaf_counts, tc,
+                                  tree->leaf_start, tree->leaf_key, tree->leaf_level, tree->perm, tree->iperm, s));
+        P2P_HIP(hipMemcpyAsync(&host, tc, sizeof(host), hipMemcpyDeviceToHost, s));
+        P2P_HIP(hipStreamSynchronize(s));
+        if (host.long_run == 0 || host.bad != 0 || full) break;
+        // equal keys are still in caller order: a full sort from here is stable
+        P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
+        P2P_TRY(radix_sort_pairs(sb, n, 0, lo, hist, s));
+        P2P_TRY(radix_sort_pairs(sb, n, lo, sort_bits, hist, s));
+    }
+    const int64_t L = host.n_leaves;
+    if (host.bad != 0) {
         tree->n_leaves = 0;
         return fail(P2P_EDOMAIN, "a particle coordinate lies outside [0,1) or is NaN");
     }
-    if (L > tree->cap_leaves) {
-        tree->n_leaves = L;
-        return fail(P2P_ECAPACITY, "cap_leaves " + std::to_string(tree->cap_leaves) + " < " + std::to_string(L) + " leaves");
-    }
-    P2P_TRY(launch_leaf_write(keys, level, flags, flag_scan, n, tree->kind, tree->leaf_start,
-                              tree->leaf_key, tree->leaf_level, &counters[1], s));
-    P2P_TRY(launch_perm_and_inverse(vals, n, tree->perm, tree->iperm, s));
-    int32_t maxl = 0;
-    P2P_HIP(hipMemcpyAsync(&maxl, &counters[1], sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    P2P_HIP(hipStreamSynchronize(s));
     tree->n_leaves = L;
-    tree->max_level = maxl;
+    if (L > tree->cap_leaves)
+        return fail(P2P_ECAPACITY, "cap_leaves " + std::to_string(tree->cap_leaves) + " < " + std::to_string(L) + " leaves");
+    tree->max_level = host.max_level;
     return P2P_OK;
 }
 

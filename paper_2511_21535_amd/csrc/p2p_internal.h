@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <utility>
 
 #include "p2p.h"
 
@@ -68,27 +69,55 @@ size_t scan_ws_elems(int64_t n);
 template <class TI, class TO>
 p2p_status exclusive_scan(const TI *in, TO *out, int64_t n, TO *scratch, hipStream_t s);
 
-// Sort (key, value) pairs by key, stably, over the low `key_bits` bits.
-// keys/vals are sorted in place; tmp buffers of the same sizes are needed.
-p2p_status radix_sort_pairs(uint64_t *keys, int32_t *vals, uint64_t *keys_tmp, int32_t *vals_tmp,
-                            int64_t n, int key_bits, uint32_t *hist_scratch, hipStream_t s);
+// Pairs to be sorted: keys/vals hold them, tmp buffers of the same sizes take
+// the passes in turn (vals == nullptr at first: the values are 0..n-1, and
+// vals_tmp, vals_alt the two value buffers).
+struct SortBufs {
+    uint64_t *keys, *keys_tmp;
+    int32_t *vals, *vals_tmp, *vals_alt;
+    void swap() {
+        std::swap(keys, keys_tmp);
+        int32_t *old = vals ? vals : vals_alt;
+        vals = vals_tmp;
+        vals_tmp = old;
+    }
+};
+// Sorts by the key bits [lo, hi), stably.  Scratch: radix_hist_elems(n).
+p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s);
 size_t radix_hist_elems(int64_t n);
+// The same by whole keys, one launch, for as many pairs as fit.
+bool rank_sort_fits(int64_t n);
+p2p_status rank_sort_pairs(SortBufs &b, int64_t n, hipStream_t s);
+// After a sort by the bits from lo up: runs of at most kRunMax equal upper
+// parts into the order of the whole key; a longer run is left and sets
+// *long_run.
+constexpr int kRunMax = 64;
+p2p_status sort_runs(SortBufs &b, int64_t n, int lo, int32_t *long_run, hipStream_t s);
 
 // Tree construction steps (tree.hip).
 p2p_status launch_particle_keys(const double *x, const double *y, const double *z, int64_t n,
-                                uint64_t *keys, int32_t *vals, int32_t *bad_flag, hipStream_t s);
+                                uint64_t *keys, int32_t *bad_flag, hipStream_t s);
 p2p_status launch_grid_keys(const int32_t *d_n_side, const int64_t *d_point_off, int32_t n_grids,
-                            int bits, int64_t n, uint64_t *keys, int32_t *vals, hipStream_t s);
+                            int bits, int64_t n, uint64_t *keys, hipStream_t s);
+// What the tree steps find, cleared before them; max_level and n_leaves are
+// written by launch_leaf_write.
+struct TreeCounts {
+    int32_t bad, long_run, max_level, n_leaves;
+};
+// Leaf level of every slot, kLeafFirst added where a leaf starts.  For each
+// kMarkBlock slots, leaf_counts receives the leaves that start in them and,
+// from kDeepShift up, their deepest level (one more entry for the total).
+constexpr uint8_t kLeafFirst = 0x80;
+constexpr int kMarkBlock = 256, kDeepShift = 16;
+inline int64_t leaf_count_elems(int64_t n) { return (n + kMarkBlock - 1) / kMarkBlock; }
 p2p_status launch_leaf_levels(const uint64_t *skeys, int64_t n, int kind, int depth, int leaf_cap,
-                              uint8_t *pair_common, int8_t *level, int32_t *flags, hipStream_t s);
-p2p_status launch_perm_and_inverse(const int32_t *vals, int64_t n, int32_t *perm, int32_t *iperm,
-                                   hipStream_t s);
-// Leaf arrays from the start flags and their scan, then the deepest level into
-// *max_level.
-p2p_status launch_leaf_write(const uint64_t *skeys, const int8_t *level, const int32_t *flags,
-                             const int32_t *flag_scan, int64_t n, int kind, int32_t *leaf_start,
-                             uint64_t *leaf_key, int8_t *leaf_level, int32_t *max_level,
-                             hipStream_t s);
+                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, hipStream_t s);
+// Leaf arrays, perm and its inverse, unless the points are bad, a long run was
+// left or there are more than cap_leaves leaves; the number of leaves in any
+// case.
+p2p_status launch_leaf_write(const uint64_t *skeys, const int32_t *vals, const uint8_t *mark, int64_t n, int kind,
+                             int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
+                             uint64_t *leaf_key, int8_t *leaf_level, int32_t *perm, int32_t *iperm, hipStream_t s);
 
 // Near lists (nbrs.hip).  Directory over the top bits of the leaf keys (dir:
 // (1 << neighbor_dir_bits) + 1 entries); it also clears the overflow counter.

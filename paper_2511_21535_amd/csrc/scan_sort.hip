@@ -157,163 +157,344 @@ template p2p_status exclusive_scan<int32_t, int64_t>(const int32_t *, int64_t *,
                                                      hipStream_t);
 template p2p_status exclusive_scan<int64_t, int64_t>(const int64_t *, int64_t *, int64_t, int64_t *,
                                                      hipStream_t);
-template p2p_status exclusive_scan<uint32_t, uint32_t>(const uint32_t *, uint32_t *, int64_t,
-                                                       uint32_t *, hipStream_t);
 
 // ------------------------------------------------------------------ sort --
+// Stable LSD radix sort of (uint64 key, int32 value) pairs, 8 bits per pass.
+// The passes are short, so what bounds them is the chain of launches and, in
+// a tile, of the ranks: a tile is ranked by 16 wavefronts of one or four
+// chunks of 64 keys each.  2^21 keys: scatter 15.6 us, counts 5.6, scan 4.7 a
+// pass (four wavefronts of 16 chunks, and the generic scan of the counts,
+// took 21.5, 7.8 and 9.4); 60-bit keys in four passes and sort_runs (15 us)
+// instead of eight passes, 118 us instead of 310.
 namespace {
 
-constexpr int kSortBlock = 256;                 // 4 waves
-constexpr int kSortChunks = 16;                 // chunks of 64 keys per wave
-constexpr int kSortWaveKeys = 64 * kSortChunks; // 1024
-constexpr int kSortTile = 4 * kSortWaveKeys;    // 4096 keys per block
+constexpr int kSortThreads = 1024;
+constexpr int kSortWaves = kSortThreads / 64;
 
-__global__ __launch_bounds__(kSortBlock) void k_radix_hist(const uint64_t *__restrict__ keys,
-                                                           int64_t n, int shift,
-                                                           uint32_t *__restrict__ hist,
-                                                           int64_t ntiles) {
-    __shared__ uint32_t h[256];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    int64_t base = static_cast<int64_t>(blockIdx.x) * kSortTile;
-#pragma unroll 4
-    for (int i = 0; i < kSortTile / kSortBlock; ++i) {
-        int64_t idx = base + i * kSortBlock + threadIdx.x;
-        if (idx < n) atomicAdd(&h[(keys[idx] >> shift) & 255u], 1u);
+// Lanes of the wavefront that hold the same digit, among the valid ones.
+__device__ inline uint64_t digit_peers(uint32_t d, bool valid) {
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const uint64_t bal = __ballot((d >> b) & 1u);
+        peers &= ((d >> b) & 1u) ? bal : ~bal;
     }
-    __syncthreads();
-    hist[static_cast<int64_t>(threadIdx.x) * ntiles + blockIdx.x] = h[threadIdx.x];
+    return peers;
 }
+__device__ inline uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
 
-// Stable scatter of one 8-bit digit.  Each wave ranks its 1024 keys in order,
-// chunk by chunk: lanes holding the same digit are found with 8 ballots, the
-// lane's rank among them is a popcount below its lane, and a per-wave digit
-// counter in LDS carries the running count from chunk to chunk.  Wave
-// counters are then scanned across the 4 waves and across the 256 digits,
-// which gives every key its position in the tile sorted by digit (stable).
-// The tile is rearranged in LDS into that order and written out in order, so
-// the keys of one digit leave as one contiguous, coalesced run.
-__global__ __launch_bounds__(kSortBlock) void k_radix_scatter(
-    const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin, uint64_t *__restrict__ kout,
-    int32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ offs,
-    int64_t ntiles) {
-    __shared__ uint32_t cnt[4][256];
-    __shared__ uint32_t dstart[256];     // first tile position of each digit
-    __shared__ uint32_t s_w[4];
-    __shared__ uint64_t s_key[kSortTile];
-    __shared__ int32_t s_val[kSortTile];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < 4 * 256; i += kSortBlock) (&cnt[0][0])[i] = 0;
-    __syncthreads();
-    const int64_t tbase = static_cast<int64_t>(blockIdx.x) * kSortTile;
-    const int64_t wbase = tbase + wave * kSortWaveKeys;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    uint64_t key[kSortChunks];
-    int32_t val[kSortChunks];
-    uint32_t loc[kSortChunks];
+// Exclusive prefix over the 256 digits, by the first four wavefronts (thread =
+// digit); the other wavefronts pass through its barriers.
+__device__ inline uint32_t digit_scan(uint32_t v, uint32_t *s_w) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t inc = v;
+    if (tid < 256) {
 #pragma unroll
-    for (int c = 0; c < kSortChunks; ++c) {
-        const int64_t idx = wbase + c * 64 + lane;
-        const bool valid = idx < n;
-        key[c] = valid ? kin[idx] : 0ull;
-        val[c] = valid ? vin[idx] : 0;
-        const uint32_t d = static_cast<uint32_t>(key[c] >> shift) & 255u;
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t bal = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? bal : ~bal;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
         }
-        const uint32_t rank = __popcll(peers & below);
-        const uint32_t base = valid ? cnt[wave][d] : 0u;
-        if (valid && rank == 0) cnt[wave][d] = base + static_cast<uint32_t>(__popcll(peers));
-        loc[c] = base + rank;
+        if (lane == 63) s_w[wave] = inc;
     }
-    __syncthreads();
-    // per digit (thread = digit): exclusive scan over the waves, and the digit's total
-    uint32_t tot = 0;
-    for (int w = 0; w < 4; ++w) {
-        const uint32_t t = cnt[w][threadIdx.x];
-        cnt[w][threadIdx.x] = tot;
-        tot += t;
-    }
-    // exclusive scan of the digit totals across the 256 threads
-    uint32_t inc = tot;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) s_w[wave] = inc;
     __syncthreads();
     uint32_t woff = 0;
-    for (int w = 0; w < wave; ++w) woff += s_w[w];
-    dstart[threadIdx.x] = woff + inc - tot;
+    if (tid < 256)
+        for (int w = 0; w < wave; ++w) woff += s_w[w];
     __syncthreads();
-    // rearrange the tile in LDS by digit
+    return woff + inc - v;
+}
+
+// Digit counts of a tile: hist[tile][digit] (SUM) or hist[digit][tile].
+template <int K, bool SUM>
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint64_t *__restrict__ keys, int64_t n, int shift,
+                                                             uint32_t *__restrict__ hist, int64_t ntiles) {
+    __shared__ uint32_t h[4][256];
+    const int tid = threadIdx.x;
+    (&h[0][0])[tid] = 0;
+    __syncthreads();
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * (kSortThreads * K);
 #pragma unroll
-    for (int c = 0; c < kSortChunks; ++c) {
-        const int64_t idx = wbase + c * 64 + lane;
-        if (idx < n) {
-            const uint32_t d = static_cast<uint32_t>(key[c] >> shift) & 255u;
-            const uint32_t pos = dstart[d] + cnt[wave][d] + loc[c];
-            s_key[pos] = key[c];
-            s_val[pos] = val[c];
-        }
+    for (int c = 0; c < K; ++c) {
+        const int64_t i = base + c * kSortThreads + tid;
+        if (i < n) atomicAdd(&h[tid & 3][static_cast<uint32_t>(keys[i] >> shift) & 255u], 1u);
     }
     __syncthreads();
-    // write out in tile order: position i of digit d goes to offs[d] + (i - dstart[d])
-    const int tile_n = static_cast<int>(min<int64_t>(kSortTile, n - tbase));
-    for (int i = threadIdx.x; i < tile_n; i += kSortBlock) {
+    if (tid < 256)
+        hist[SUM ? static_cast<int64_t>(blockIdx.x) * 256 + tid : static_cast<int64_t>(tid) * ntiles + blockIdx.x] =
+            h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+}
+
+// Exclusive scan of each digit's counts over the tiles, in place, and the
+// digit's total: one workgroup per digit.
+__global__ __launch_bounds__(kScanBlock) void k_radix_scan(uint32_t *__restrict__ hist, int64_t ntiles,
+                                                           uint32_t *__restrict__ totals) {
+    __shared__ uint32_t lds[kScanBlock / 64];
+    uint32_t *__restrict__ h = hist + static_cast<int64_t>(blockIdx.x) * ntiles;
+    uint32_t carry = 0;
+    for (int64_t c = 0; c < ntiles; c += kScanTile) {
+        const int64_t base = c + threadIdx.x * kScanItems;
+        uint32_t v[kScanItems], s = 0;
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            v[i] = base + i < ntiles ? h[base + i] : 0u;
+            s += v[i];
+        }
+        uint32_t tot;
+        uint32_t pre = block_exclusive_scan<uint32_t>(s, lds, &tot) + carry;
+#pragma unroll
+        for (int i = 0; i < kScanItems; ++i) {
+            if (base + i < ntiles) h[base + i] = pre;
+            pre += v[i];
+        }
+        carry += tot;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+}
+
+// The ranks of a tile's keys by one digit, called by kSortThreads threads: K
+// chunks of 64 keys per wavefront in order.  Lanes holding the same digit are
+// found with 8 ballots, the rank among them is a popcount, and a per-wave digit
+// counter in LDS carries the running count from chunk to chunk; the counters
+// are then scanned across the wavefronts and the digits.  pos[c] = the key's
+// position in the tile sorted by the digit; dstart[d] = first position of digit
+// d.
+template <int K>
+__device__ void tile_ranks(const uint64_t (&key)[K], const bool (&valid)[K], int shift, uint32_t (*cnt)[256],
+                           uint32_t *dstart, uint32_t *s_w, uint32_t (&pos)[K]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < kSortWaves * 256; i += kSortThreads) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    uint32_t dig[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        const uint32_t d = static_cast<uint32_t>(key[c] >> shift) & 255u;
+        const uint64_t peers = digit_peers(d, valid[c]);
+        const uint32_t rank = static_cast<uint32_t>(__popcll(peers & lanes_below(lane)));
+        const uint32_t base = valid[c] ? cnt[wave][d] : 0u;
+        if (valid[c] && rank == 0) cnt[wave][d] = base + static_cast<uint32_t>(__popcll(peers));
+        dig[c] = d;
+        pos[c] = base + rank;
+    }
+    __syncthreads();
+    uint32_t tot = 0;   // thread = digit: exclusive scan over the wavefronts
+    if (tid < 256) {
+#pragma unroll
+        for (int w = 0; w < kSortWaves; ++w) {
+            const uint32_t t = cnt[w][tid];
+            cnt[w][tid] = tot;
+            tot += t;
+        }
+    }
+    const uint32_t first = digit_scan(tot, s_w);
+    if (tid < 256) dstart[tid] = first;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < K; ++c) pos[c] += dstart[dig[c]] + cnt[wave][dig[c]];
+}
+
+// The tile is rearranged in LDS by digit and written out in that order, so the
+// keys of one digit leave as one contiguous, coalesced run.  With SUM every
+// workgroup adds the counts of the tiles before it itself; otherwise they were
+// scanned, and totals holds the digit totals.  FIRST: the values are the
+// positions (vin is not read).
+template <int K, bool SUM, bool FIRST>
+__global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
+    const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin, uint64_t *__restrict__ kout,
+    int32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ hist,
+    const uint32_t *__restrict__ totals, int64_t ntiles) {
+    constexpr int T = kSortThreads * K;
+    __shared__ uint32_t cnt[kSortWaves][256];
+    __shared__ uint32_t dstart[256], dbase[256], s_w[4];
+    __shared__ uint64_t s_key[T];
+    __shared__ int32_t s_val[T];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t tbase = static_cast<int64_t>(blockIdx.x) * T;
+    uint64_t key[K];
+    int32_t val[K];
+    bool valid[K];
+    uint32_t pos[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+        const int64_t i = tbase + wave * (64 * K) + c * 64 + lane;
+        valid[c] = i < n;
+        key[c] = valid[c] ? kin[i] : 0ull;
+        val[c] = FIRST ? static_cast<int32_t>(i) : (valid[c] ? vin[i] : 0);
+    }
+    // first output position of each digit of this tile: the digits before it, then the tiles before this one
+    uint32_t tot = 0, off = 0;
+    if (SUM) {
+        uint32_t *sb = &cnt[0][0], *st = &cnt[4][0];   // four partial sums per digit
+        uint32_t o = 0, a = 0;
+        for (int64_t t = tid >> 8; t < ntiles; t += 4) {
+            const uint32_t c = hist[t * 256 + (tid & 255)];
+            a += c;
+            if (t < blockIdx.x) o += c;
+        }
+        sb[tid] = o;
+        st[tid] = a;
+        __syncthreads();
+        if (tid < 256) {
+            off = sb[tid] + sb[tid + 256] + sb[tid + 512] + sb[tid + 768];
+            tot = st[tid] + st[tid + 256] + st[tid + 512] + st[tid + 768];
+        }
+    } else if (tid < 256) {
+        tot = totals[tid];
+        off = hist[static_cast<int64_t>(tid) * ntiles + blockIdx.x];
+    }
+    off += digit_scan(tot, s_w);
+    tile_ranks<K>(key, valid, shift, cnt, dstart, s_w, pos);
+    if (tid < 256) dbase[tid] = off - dstart[tid];
+#pragma unroll
+    for (int c = 0; c < K; ++c)
+        if (valid[c]) {
+            s_key[pos[c]] = key[c];
+            s_val[pos[c]] = val[c];
+        }
+    __syncthreads();
+    const int tile_n = static_cast<int>(min<int64_t>(T, n - tbase));
+    for (int i = tid; i < tile_n; i += kSortThreads) {
         const uint64_t k = s_key[i];
-        const uint32_t d = static_cast<uint32_t>(k >> shift) & 255u;
-        const int64_t pos = static_cast<int64_t>(offs[static_cast<int64_t>(d) * ntiles + blockIdx.x]) +
-                            (i - static_cast<int64_t>(dstart[d]));
-        kout[pos] = k;
-        vout[pos] = s_val[i];
+        const uint32_t p = dbase[static_cast<uint32_t>(k >> shift) & 255u] + static_cast<uint32_t>(i);
+        kout[p] = k;
+        vout[p] = s_val[i];
     }
 }
 
-__global__ void k_copy_pairs(const uint64_t *__restrict__ ks, const int32_t *__restrict__ vs,
-                             uint64_t *__restrict__ kd, int32_t *__restrict__ vd, int64_t n) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) {
-        kd[i] = ks[i];
-        vd[i] = vs[i];
+// Few pairs: every key's place is the number of keys before it (smaller, or
+// equal and earlier).  A workgroup holds all keys in LDS and places 16 of
+// them, 64 threads counting for each; n <= kRankSortMax.  4096 keys: 9 us; one
+// workgroup sorting them in LDS by four passes and their runs took 23 us, the
+// 24 launches of eight radix passes 170 us.
+constexpr int kRankKeys = 16;
+constexpr int64_t kRankSortMax = 8192;
+__global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__restrict__ kin,
+                                                            const int32_t *__restrict__ vin,
+                                                            uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
+                                                            int n) {
+    __shared__ uint64_t s_key[kRankSortMax];
+    __shared__ int s_cnt[kSortWaves][kRankKeys];
+    const int tid = threadIdx.x, q = tid & (kRankKeys - 1), seg = tid / kRankKeys;
+    for (int j = tid; j < n; j += kSortThreads) s_key[j] = kin[j];
+    __syncthreads();
+    const int i = blockIdx.x * kRankKeys + q;
+    const uint64_t key = i < n ? s_key[i] : 0ull;
+    int cnt = 0;
+    for (int j = seg; j < n; j += kSortThreads / kRankKeys) {
+        const uint64_t k = s_key[j];
+        cnt += k < key || (k == key && j < i) ? 1 : 0;
     }
+    cnt += __shfl_xor(cnt, 16, 64);
+    cnt += __shfl_xor(cnt, 32, 64);
+    if ((tid & 63) < kRankKeys) s_cnt[tid >> 6][q] = cnt;
+    __syncthreads();
+    if (tid < kRankKeys && i < n) {
+        int p = 0;
+        for (int w = 0; w < kSortWaves; ++w) p += s_cnt[w][q];
+        kout[p] = key;
+        vout[p] = vin ? vin[i] : i;
+    }
+}
+
+// Keys sorted by their bits from lo up: puts every run of equal upper bits in
+// order of the whole key, ties in their present order.  A slot finds its run
+// in a window of kRunMax keys on either side, held in LDS, and counts its
+// place.  A run over kRunMax keys is left as it is, and *long_run is set.
+constexpr int kRunBlock = 256;
+__global__ __launch_bounds__(kRunBlock) void k_sort_runs(const uint64_t *__restrict__ kin,
+                                                         const int32_t *__restrict__ vin,
+                                                         uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
+                                                         int64_t n, int lo, int32_t *__restrict__ long_run) {
+    __shared__ uint64_t w[kRunBlock + 2 * kRunMax];
+    const int64_t b = static_cast<int64_t>(blockIdx.x) * kRunBlock;
+    const int t = threadIdx.x;
+    for (int k = t; k < kRunBlock + 2 * kRunMax; k += kRunBlock) {
+        const int64_t j = b - kRunMax + k;
+        w[k] = j >= 0 && j < n ? kin[j] : ~0ull;   // no key has its top bit set
+    }
+    __syncthreads();
+    const int64_t i = b + t;
+    if (i >= n) return;
+    const int me = t + kRunMax;
+    const uint64_t key = w[me], top = key >> lo;
+    int a = me, e = me + 1;
+    while (a > me - kRunMax && (w[a - 1] >> lo) == top) --a;
+    while (e <= me + kRunMax && (w[e] >> lo) == top) ++e;   // one key past the longest run on either side
+    int64_t p = i;
+    if (e - a <= kRunMax) {
+        int r = a - me;
+        for (int j = a; j < e; ++j) r += w[j] < key || (w[j] == key && j < me) ? 1 : 0;
+        p = i + r;
+    } else if (*long_run == 0) {
+        *long_run = 1;   // every writer writes the same
+    }
+    kout[p] = key;
+    vout[p] = vin[i];
+}
+
+// Three launches a pass (counts, scan, scatter), or two where the scatter's
+// workgroups can add the counts of at most kSumTiles tiles themselves: 64 KB
+// from L2 beside a launch of 4.7 us.
+constexpr int64_t kSumTiles = 64;
+constexpr int64_t kSmallTileMax = kSumTiles * kSortThreads;
+int64_t sort_tiles(int64_t n) {
+    const int64_t tile = n <= kSmallTileMax ? kSortThreads : 4 * kSortThreads;
+    return (n + tile - 1) / tile;
+}
+
+template <int K, bool SUM>
+p2p_status radix_pass(SortBufs &b, int64_t n, int shift, uint32_t *hist, hipStream_t s) {
+    const int64_t ntiles = sort_tiles(n);
+    const unsigned g = static_cast<unsigned>(ntiles);
+    uint32_t *totals = hist + 256 * ntiles;
+    k_radix_hist<K, SUM><<<g, kSortThreads, 0, s>>>(b.keys, n, shift, hist, ntiles);
+    P2P_LAUNCH_CHECK();
+    if (!SUM) {
+        k_radix_scan<<<256, kScanBlock, 0, s>>>(hist, ntiles, totals);
+        P2P_LAUNCH_CHECK();
+    }
+    if (b.vals)
+        k_radix_scatter<K, SUM, false><<<g, kSortThreads, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp, n, shift,
+                                                                  hist, totals, ntiles);
+    else
+        k_radix_scatter<K, SUM, true><<<g, kSortThreads, 0, s>>>(b.keys, nullptr, b.keys_tmp, b.vals_tmp, n, shift,
+                                                                 hist, totals, ntiles);
+    P2P_LAUNCH_CHECK();
+    return P2P_OK;
 }
 
 }  // namespace
 
-size_t radix_hist_elems(int64_t n) {
-    int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    int64_t m = 256 * (ntiles > 0 ? ntiles : 1);
-    return static_cast<size_t>(m + 1) + scan_ws_elems(m);
+size_t radix_hist_elems(int64_t n) { return static_cast<size_t>(256 * (n > 0 ? sort_tiles(n) : 1) + 256); }
+
+p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s) {
+    if (n <= 0) return P2P_OK;
+    const bool sum = sort_tiles(n) <= kSumTiles;
+    for (int shift = lo; shift < hi; shift += 8) {
+        P2P_TRY(n <= kSmallTileMax ? (radix_pass<1, true>(b, n, shift, hist, s))
+                : sum              ? (radix_pass<4, true>(b, n, shift, hist, s))
+                                   : (radix_pass<4, false>(b, n, shift, hist, s)));
+        b.swap();
+    }
+    return P2P_OK;
 }
 
-p2p_status radix_sort_pairs(uint64_t *keys, int32_t *vals, uint64_t *keys_tmp, int32_t *vals_tmp,
-                            int64_t n, int key_bits, uint32_t *hist_scratch, hipStream_t s) {
-    if (n <= 1) return P2P_OK;
-    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    const int64_t m = 256 * ntiles;
-    uint32_t *hist = hist_scratch;
-    uint32_t *scan_tmp = hist_scratch + m + 1;
-    uint64_t *ka = keys, *kb = keys_tmp;
-    int32_t *va = vals, *vb = vals_tmp;
-    for (int shift = 0; shift < key_bits; shift += 8) {
-        k_radix_hist<<<static_cast<unsigned>(ntiles), kSortBlock, 0, s>>>(ka, n, shift, hist, ntiles);
-        P2P_LAUNCH_CHECK();
-        P2P_TRY((exclusive_scan<uint32_t, uint32_t>(hist, hist, m, scan_tmp, s)));
-        k_radix_scatter<<<static_cast<unsigned>(ntiles), kSortBlock, 0, s>>>(ka, va, kb, vb, n, shift,
-                                                                            hist, ntiles);
-        P2P_LAUNCH_CHECK();
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    if (ka != keys) {
-        k_copy_pairs<<<grid_for(n, 256), 256, 0, s>>>(ka, va, keys, vals, n);
-        P2P_LAUNCH_CHECK();
-    }
+bool rank_sort_fits(int64_t n) { return n <= kRankSortMax; }
+
+p2p_status rank_sort_pairs(SortBufs &b, int64_t n, hipStream_t s) {
+    if (n <= 0) return P2P_OK;
+    if (!rank_sort_fits(n)) return fail(P2P_EINVAL, "rank sort: too many keys");
+    k_rank_sort<<<grid_for(n, kRankKeys), kSortThreads, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp,
+                                                               static_cast<int>(n));
+    P2P_LAUNCH_CHECK();
+    b.swap();
+    return P2P_OK;
+}
+
+p2p_status sort_runs(SortBufs &b, int64_t n, int lo, int32_t *long_run, hipStream_t s) {
+    if (n <= 0) return P2P_OK;
+    k_sort_runs<<<grid_for(n, kRunBlock), kRunBlock, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp, n, lo, long_run);
+    P2P_LAUNCH_CHECK();
+    b.swap();
     return P2P_OK;
 }
 

@@ -19,8 +19,7 @@ namespace {
 
 __global__ void k_particle_keys(const double *__restrict__ x, const double *__restrict__ y,
                                 const double *__restrict__ z, int64_t n,
-                                uint64_t *__restrict__ keys, int32_t *__restrict__ vals,
-                                int32_t *__restrict__ bad) {
+                                uint64_t *__restrict__ keys, int32_t *__restrict__ bad) {
     int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double p[3] = {x[i], y[i], z[i]};
@@ -34,12 +33,10 @@ __global__ void k_particle_keys(const double *__restrict__ x, const double *__re
     }
     if (!ok) atomicOr(bad, 1);
     keys[i] = p2pd::morton3(c[0], c[1], c[2]);
-    vals[i] = static_cast<int32_t>(i);
 }
 
 __global__ void k_grid_keys(const int32_t *__restrict__ n_side, const int64_t *__restrict__ off,
-                            int32_t n_grids, int bits, int64_t n, uint64_t *__restrict__ keys,
-                            int32_t *__restrict__ vals) {
+                            int32_t n_grids, int bits, int64_t n, uint64_t *__restrict__ keys) {
     int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (p >= n) return;
     // binary search of the instance: last g with off[g] <= p
@@ -52,7 +49,6 @@ __global__ void k_grid_keys(const int32_t *__restrict__ n_side, const int64_t *_
     const uint32_t i = static_cast<uint32_t>(loc % ns), j = static_cast<uint32_t>((loc / ns) % ns),
                    k = static_cast<uint32_t>(loc / (ns * ns));
     keys[p] = (static_cast<uint64_t>(lo) << (3 * bits)) | p2pd::morton3(i, j, k);
-    vals[p] = static_cast<int32_t>(p);
 }
 
 // Leading octal digits shared by two depth-20 keys (60-bit keys in 64-bit words).
@@ -66,16 +62,38 @@ __global__ void k_pair_common(const uint64_t *__restrict__ sk, int64_t n, uint8_
     if (i + 1 < n) c[i] = static_cast<uint8_t>(common_digits(sk[i], sk[i + 1]));
 }
 
-// kind 0, leaf_cap > 0: adaptive level; kind 0, leaf_cap == 0: uniform depth.
+// Ends every leaf-level kernel, called by all kMarkBlock threads of a workgroup:
+// slot i's mark, and the workgroup's leaf starts and deepest level.
+__device__ inline void leaf_mark(int64_t i, int64_t n, int l, bool first, uint8_t *__restrict__ mark,
+                                 int32_t *__restrict__ leaf_counts) {
+    __shared__ int s_cnt[kMarkBlock / 64], s_lev[kMarkBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (i < n) mark[i] = static_cast<uint8_t>(l) | (first ? kLeafFirst : 0);
+    const int cnt = __popcll(__ballot(i < n && first));
+    int m = i < n ? l : 0;
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if (lane == 0) {
+        s_cnt[w] = cnt;
+        s_lev[w] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int c = 0;
+        for (int q = 0; q < kMarkBlock / 64; ++q) {
+            c += s_cnt[q];
+            m = max(m, s_lev[q]);
+        }
+        leaf_counts[blockIdx.x] = c | (m << kDeepShift);
+    }
+}
+
+// Adaptive levels for any leaf_cap > 0.
 __global__ void k_leaf_level_particles(const uint8_t *__restrict__ c, int64_t n, int depth,
-                                       int leaf_cap, int8_t *__restrict__ level,
-                                       int32_t *__restrict__ flag) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    int l;
-    if (leaf_cap == 0) {
-        l = depth;
-    } else {
+                                       int leaf_cap, uint8_t *__restrict__ mark,
+                                       int32_t *__restrict__ leaf_counts) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kMarkBlock + threadIdx.x;
+    int l = depth;
+    if (i < n) {
         // merge the running minima to the left (pairs i-1, i-2, ...) and to the
         // right (pairs i, i+1, ...); -1 marks an exhausted side
         int64_t left = i - 1, right = i;
@@ -97,9 +115,8 @@ __global__ void k_leaf_level_particles(const uint8_t *__restrict__ c, int64_t n,
         }
         l = min(depth, v + 1);
     }
-    level[i] = static_cast<int8_t>(l);
     // a new leaf starts at i unless slot i-1 shares i's level-l node
-    flag[i] = (i == 0 || static_cast<int>(c[i - 1]) < l) ? 1 : 0;
+    leaf_mark(i, n, l, i < n && (i == 0 || static_cast<int>(c[i - 1]) < l), mark, leaf_counts);
 }
 
 // The same leaf levels for leaf_cap <= 64 without the merge: slot i's leaf
@@ -110,10 +127,12 @@ __global__ void k_leaf_level_particles(const uint8_t *__restrict__ c, int64_t n,
 // run longer than 64 matters, so a wave of 64 slots reads the counts of
 // slots -64..127 around it as three ballots per level, and each lane measures
 // its run with one leading- and one trailing-ones count.  Levels are tried
-// from the root down until every lane has its answer.
-__global__ __launch_bounds__(256) void k_leaf_level_ballot(const uint64_t *__restrict__ sk, int64_t n, int depth,
-                                                           int leaf_cap, int8_t *__restrict__ level,
-                                                           int32_t *__restrict__ flag) {
+// from the root down until every lane has its answer.  leaf_cap == 0: the
+// uniform tree, every leaf at `depth`.
+__global__ __launch_bounds__(kMarkBlock) void k_leaf_level_ballot(const uint64_t *__restrict__ sk, int64_t n,
+                                                                  int depth, int leaf_cap,
+                                                                  uint8_t *__restrict__ mark,
+                                                                  int32_t *__restrict__ leaf_counts) {
     __shared__ int8_t cs[256 + 128];   // cs[k] = c[b - 64 + k], -1 past either end
     const int64_t b = static_cast<int64_t>(blockIdx.x) * 256;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
@@ -126,7 +145,7 @@ __global__ __launch_bounds__(256) void k_leaf_level_ballot(const uint64_t *__res
     const int c0 = cs[64 * wv + lane], c1 = cs[64 * wv + 64 + lane], c2 = cs[64 * wv + 128 + lane];
     const int sh = lane;   // the lane's own count c[i] sits at window bit 64 + lane
     int lev = -1;
-    for (int l = 0; l <= 21; ++l) {
+    for (int l = 0; l <= 21 && leaf_cap > 0; ++l) {
         const uint64_t W0 = __ballot(c0 >= l), W1 = __ballot(c1 >= l), W2 = __ballot(c2 >= l);
         // right: window bits 64 + lane .. 127 + lane; left: bits lane .. 63 + lane (top bit: c[i - 1])
         const uint64_t R = sh == 0 ? W1 : (W1 >> sh) | (W2 << (64 - sh));
@@ -137,10 +156,8 @@ __global__ __launch_bounds__(256) void k_leaf_level_ballot(const uint64_t *__res
         if (__ballot(lev < 0) == 0) break;
     }
     const int64_t i = b + 64 * wv + lane;
-    if (i >= n) return;
-    const int l = min(depth, lev);
-    level[i] = static_cast<int8_t>(l);
-    flag[i] = (i == 0 || static_cast<int>(cs[64 * wv + 63 + lane]) < l) ? 1 : 0;
+    const int l = leaf_cap > 0 ? min(depth, lev) : depth;
+    leaf_mark(i, n, l, i == 0 || static_cast<int>(cs[64 * wv + 63 + lane]) < l, mark, leaf_counts);
 }
 
 // The same leaf levels for leaf_cap <= kTileCap, a block of 256 slots at a
@@ -149,11 +166,11 @@ __global__ __launch_bounds__(256) void k_leaf_level_ballot(const uint64_t *__res
 // sorted keys into LDS, -1 past either end of the sequence, so the merge loop
 // reads LDS instead of issuing a scattered byte load per step.
 constexpr int kTileCap = 2048;
-constexpr int kTileSlots = 256;
+constexpr int kTileSlots = kMarkBlock;
 __global__ __launch_bounds__(kTileSlots) void k_leaf_level_tile(const uint64_t *__restrict__ sk, int64_t n,
                                                                   int depth, int leaf_cap,
-                                                                  int8_t *__restrict__ level,
-                                                                  int32_t *__restrict__ flag) {
+                                                                  uint8_t *__restrict__ mark,
+                                                                  int32_t *__restrict__ leaf_counts) {
     extern __shared__ int8_t cs[];   // cs[k] = c[b - leaf_cap + k], k < kTileSlots + 2 leaf_cap
     const int64_t b = static_cast<int64_t>(blockIdx.x) * kTileSlots;
     const int t = threadIdx.x, w = kTileSlots + 2 * leaf_cap;
@@ -163,7 +180,6 @@ __global__ __launch_bounds__(kTileSlots) void k_leaf_level_tile(const uint64_t *
     }
     __syncthreads();
     const int64_t i = b + t;
-    if (i >= n) return;
     // left slot i - 1 - dl at cs[t + leaf_cap - 1 - dl], right slot i + dr at cs[t + leaf_cap + dr]
     int kl = t + leaf_cap - 1, kr = t + leaf_cap;
     int mL = 127, mR = 127, v = -1;
@@ -182,134 +198,205 @@ __global__ __launch_bounds__(kTileSlots) void k_leaf_level_tile(const uint64_t *
         }
     }
     const int l = min(depth, v + 1);
-    level[i] = static_cast<int8_t>(l);
-    flag[i] = (i == 0 || static_cast<int>(cs[t + leaf_cap - 1]) < l) ? 1 : 0;
+    leaf_mark(i, n, l, i == 0 || static_cast<int>(cs[t + leaf_cap - 1]) < l, mark, leaf_counts);
 }
 
-__global__ void k_leaf_flag_grids(const uint64_t *__restrict__ sk, int64_t n,
-                                  int32_t *__restrict__ flag, int8_t *__restrict__ level,
-                                  int box_level) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    flag[i] = (i == 0 || (sk[i] >> 6) != (sk[i - 1] >> 6)) ? 1 : 0;
-    level[i] = static_cast<int8_t>(box_level);
+__global__ __launch_bounds__(kMarkBlock) void k_leaf_flag_grids(const uint64_t *__restrict__ sk, int64_t n,
+                                                                uint8_t *__restrict__ mark, int box_level,
+                                                                int32_t *__restrict__ leaf_counts) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kMarkBlock + threadIdx.x;
+    leaf_mark(i, n, box_level, i < n && (i == 0 || (sk[i] >> 6) != (sk[i - 1] >> 6)), mark, leaf_counts);
 }
 
-__global__ void k_leaf_write(const uint64_t *__restrict__ sk, const int8_t *__restrict__ level,
-                             const int32_t *__restrict__ flag, const int32_t *__restrict__ fscan,
-                             int64_t n, int kind, int32_t *__restrict__ leaf_start,
-                             uint64_t *__restrict__ leaf_key, int8_t *__restrict__ leaf_level) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) {
-        if (i == 0) leaf_start[fscan[n]] = static_cast<int32_t>(n);
-        if (flag[i]) {
-            const int32_t L = fscan[i];
-            const int l = level[i];
-            leaf_start[L] = static_cast<int32_t>(i);
-            leaf_level[L] = static_cast<int8_t>(l);
-            const uint64_t low_bits = (kind == P2P_TREE_PARTICLES) ? 3ull * (20 - l) : 6ull;
-            const uint64_t mask = (low_bits >= 64) ? 0ull : ~((1ull << low_bits) - 1ull);
-            leaf_key[L] = sk[i] & mask;
+// The counts of more slots than k_leaf_write sums: prefix sums of the leaf
+// starts in place, their total and the deepest level (one workgroup).
+__global__ __launch_bounds__(1024) void k_leaf_scan(int32_t *__restrict__ leaf_counts, int64_t nb,
+                                                    TreeCounts *__restrict__ tc) {
+    __shared__ int s_w[16], s_m[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int carry = 0, m = 0;
+    for (int64_t c0 = 0; c0 < nb; c0 += 1024) {
+        const int64_t q = c0 + t;
+        const int c = q < nb ? leaf_counts[q] : 0, v = c & ((1 << kDeepShift) - 1);
+        m = max(m, c >> kDeepShift);
+        int inc = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        if (lane == 63) s_w[w] = inc;
+        __syncthreads();
+        int off = carry;
+        for (int k = 0; k < 16; ++k) {
+            if (k < w) off += s_w[k];
+            carry += s_w[k];
+        }
+        if (q < nb) leaf_counts[q] = off + inc - v;
+        __syncthreads();
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if (lane == 0) s_m[w] = m;
+    __syncthreads();
+    if (t == 0) {
+        for (int k = 0; k < 16; ++k) m = max(m, s_m[k]);
+        tc->max_level = m;
+        leaf_counts[nb] = carry;
+    }
+}
+
+// One workgroup per kLeafTile slots: the leaves that start before them are the
+// sum of leaf_counts (SCANNED: its prefix, already formed), a block scan gives
+// each thread's slots their leaf ids, and the same workgroup writes perm and
+// its inverse for its slots.  It stands for a scan of flags, the leaf writes,
+// their maximum and the permutation, launches that each re-read the slots.
+constexpr int kWriteBlock = 1024;
+constexpr int kWriteItems = 2;
+constexpr int kLeafTile = kWriteBlock * kWriteItems;
+template <bool SCANNED>
+__global__ __launch_bounds__(kWriteBlock) void k_leaf_write(
+    const uint64_t *__restrict__ sk, const int32_t *__restrict__ vals, const uint8_t *__restrict__ mark, int64_t n,
+    int kind, int64_t cap_leaves, const int32_t *__restrict__ leaf_counts, int64_t nb, TreeCounts *__restrict__ tc,
+    int32_t *__restrict__ leaf_start, uint64_t *__restrict__ leaf_key, int8_t *__restrict__ leaf_level,
+    int32_t *__restrict__ perm, int32_t *__restrict__ iperm) {
+    constexpr int W = kWriteBlock / 64;
+    __shared__ int32_t s_w[4][W];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kLeafTile;
+    const int64_t b = i0 / kMarkBlock;   // the first count of this workgroup's slots
+    // this thread's slots are consecutive
+    const int64_t it = i0 + t * kWriteItems;
+    uint8_t mk[kWriteItems];
+    int cnt = 0;
+#pragma unroll
+    for (int k = 0; k < kWriteItems; ++k) {
+        mk[k] = it + k < n ? mark[it + k] : 0;
+        cnt += mk[k] >> 7;
+    }
+    int32_t before = 0, total = 0, deep = 0;
+    if (!SCANNED)
+        for (int64_t q = t; q < nb; q += kWriteBlock) {
+            const int32_t c = leaf_counts[q], v = c & ((1 << kDeepShift) - 1);
+            deep = max(deep, c >> kDeepShift);
+            total += v;
+            if (q < b) before += v;
+        }
+    int inc = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    if (!SCANNED) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            before += __shfl_xor(before, o, 64);
+            total += __shfl_xor(total, o, 64);
+            deep = max(deep, __shfl_xor(deep, o, 64));
         }
     }
-}
-
-// Deepest leaf level: one workgroup strides over the levels (no atomics).
-__global__ __launch_bounds__(1024) void k_max_level(const int8_t *__restrict__ leaf_level,
-                                                    const int32_t *__restrict__ fscan, int64_t n,
-                                                    int32_t *__restrict__ out) {
-    __shared__ int s_m[16];
-    const int64_t L = fscan[n];
-    // eight independent loads in flight per thread
-    int mm[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int64_t step = 8 * static_cast<int64_t>(blockDim.x);
-    int64_t i0 = threadIdx.x;
-    for (; i0 + 7 * static_cast<int64_t>(blockDim.x) < L; i0 += step) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) mm[k] = max(mm[k], static_cast<int>(leaf_level[i0 + k * blockDim.x]));
+    if (lane == 63) {
+        s_w[0][w] = inc;
+        s_w[1][w] = before;
+        s_w[2][w] = total;
+        s_w[3][w] = deep;
     }
-    for (int64_t i = i0; i < L; i += blockDim.x) mm[0] = max(mm[0], static_cast<int>(leaf_level[i]));
-    int m = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m = max(m, mm[k]);
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int r = 0;
-        for (int w = 0; w < static_cast<int>(blockDim.x >> 6); ++w) r = max(r, s_m[w]);
-        *out = r;
+    int32_t id = inc - cnt, L = 0;
+    for (int q = 0; q < W; ++q) {
+        if (q < w) id += s_w[0][q];
+        if (!SCANNED) {
+            id += s_w[1][q];
+            L += s_w[2][q];
+            deep = max(deep, s_w[3][q]);
+        }
     }
-}
-
-// perm[s] = caller index of sorted slot s, and its inverse.
-__global__ void k_perm_and_inverse(const int32_t *__restrict__ vals, int64_t n,
-                                   int32_t *__restrict__ perm, int32_t *__restrict__ iperm) {
-    const int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const int32_t i = vals[s];
-    perm[s] = i;
-    iperm[i] = static_cast<int32_t>(s);
+    if (SCANNED) {
+        id += leaf_counts[b];
+        L = leaf_counts[nb];
+    }
+    if (blockIdx.x == 0 && t == 0) {
+        tc->n_leaves = L;
+        if (!SCANNED) tc->max_level = deep;
+    }
+    if (tc->bad != 0 || tc->long_run != 0 || L > cap_leaves) return;
+    if (blockIdx.x == 0 && t == 0) leaf_start[L] = static_cast<int32_t>(n);
+#pragma unroll
+    for (int k = 0; k < kWriteItems; ++k)
+        if (mk[k] & kLeafFirst) {
+            const int l = mk[k] & (kLeafFirst - 1);
+            leaf_start[id] = static_cast<int32_t>(it + k);
+            leaf_level[id] = static_cast<int8_t>(l);
+            const uint64_t low_bits = (kind == P2P_TREE_PARTICLES) ? 3ull * (20 - l) : 6ull;
+            const uint64_t mask = (low_bits >= 64) ? 0ull : ~((1ull << low_bits) - 1ull);
+            leaf_key[id] = sk[it + k] & mask;
+            ++id;
+        }
+    const int64_t i1 = min(n, i0 + kLeafTile);
+    for (int64_t i = i0 + t; i < i1; i += kWriteBlock) {
+        const int32_t v = vals[i];
+        perm[i] = v;
+        iperm[v] = static_cast<int32_t>(i);
+    }
 }
 
 }  // namespace
 
-p2p_status launch_perm_and_inverse(const int32_t *vals, int64_t n, int32_t *perm, int32_t *iperm,
-                                   hipStream_t s) {
-    if (n <= 0) return P2P_OK;
-    k_perm_and_inverse<<<grid_for(n, 256), 256, 0, s>>>(vals, n, perm, iperm);
-    P2P_LAUNCH_CHECK();
-    return P2P_OK;
-}
-
-
 p2p_status launch_particle_keys(const double *x, const double *y, const double *z, int64_t n,
-                                uint64_t *keys, int32_t *vals, int32_t *bad_flag, hipStream_t s) {
+                                uint64_t *keys, int32_t *bad_flag, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    k_particle_keys<<<grid_for(n, 256), 256, 0, s>>>(x, y, z, n, keys, vals, bad_flag);
+    k_particle_keys<<<grid_for(n, 256), 256, 0, s>>>(x, y, z, n, keys, bad_flag);
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 
 p2p_status launch_grid_keys(const int32_t *d_n_side, const int64_t *d_point_off, int32_t n_grids,
-                            int bits, int64_t n, uint64_t *keys, int32_t *vals, hipStream_t s) {
+                            int bits, int64_t n, uint64_t *keys, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    k_grid_keys<<<grid_for(n, 256), 256, 0, s>>>(d_n_side, d_point_off, n_grids, bits, n, keys, vals);
+    k_grid_keys<<<grid_for(n, 256), 256, 0, s>>>(d_n_side, d_point_off, n_grids, bits, n, keys);
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 
 p2p_status launch_leaf_levels(const uint64_t *skeys, int64_t n, int kind, int depth, int leaf_cap,
-                              uint8_t *pair_common, int8_t *level, int32_t *flags, hipStream_t s) {
+                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    if (kind == P2P_TREE_PARTICLES && leaf_cap > 0 && leaf_cap <= 64) {
-        k_leaf_level_ballot<<<grid_for(n, 256), 256, 0, s>>>(skeys, n, depth, leaf_cap, level, flags);
-    } else if (kind == P2P_TREE_PARTICLES && leaf_cap > 0 && leaf_cap <= kTileCap) {
-        k_leaf_level_tile<<<grid_for(n, kTileSlots), kTileSlots, kTileSlots + 2 * leaf_cap, s>>>(
-            skeys, n, depth, leaf_cap, level, flags);
+    const unsigned g = grid_for(n, kMarkBlock);
+    if (kind == P2P_TREE_PARTICLES && leaf_cap <= 64) {
+        k_leaf_level_ballot<<<g, kMarkBlock, 0, s>>>(skeys, n, depth, leaf_cap, mark, leaf_counts);
+    } else if (kind == P2P_TREE_PARTICLES && leaf_cap <= kTileCap) {
+        k_leaf_level_tile<<<g, kMarkBlock, kTileSlots + 2 * leaf_cap, s>>>(skeys, n, depth, leaf_cap, mark,
+                                                                           leaf_counts);
     } else if (kind == P2P_TREE_PARTICLES) {
         if (n > 1) {
             k_pair_common<<<grid_for(n - 1, 256), 256, 0, s>>>(skeys, n, pair_common);
             P2P_LAUNCH_CHECK();
         }
-        k_leaf_level_particles<<<grid_for(n, 256), 256, 0, s>>>(pair_common, n, depth, leaf_cap,
-                                                                level, flags);
+        k_leaf_level_particles<<<g, kMarkBlock, 0, s>>>(pair_common, n, depth, leaf_cap, mark, leaf_counts);
     } else {
-        k_leaf_flag_grids<<<grid_for(n, 256), 256, 0, s>>>(skeys, n, flags, level, depth);
+        k_leaf_flag_grids<<<g, kMarkBlock, 0, s>>>(skeys, n, mark, depth, leaf_counts);
     }
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 
-p2p_status launch_leaf_write(const uint64_t *skeys, const int8_t *level, const int32_t *flags,
-                             const int32_t *flag_scan, int64_t n, int kind, int32_t *leaf_start,
-                             uint64_t *leaf_key, int8_t *leaf_level, int32_t *max_level,
-                             hipStream_t s) {
+p2p_status launch_leaf_write(const uint64_t *skeys, const int32_t *vals, const uint8_t *mark, int64_t n, int kind,
+                             int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
+                             uint64_t *leaf_key, int8_t *leaf_level, int32_t *perm, int32_t *iperm, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    k_leaf_write<<<grid_for(n, 256), 256, 0, s>>>(skeys, level, flags, flag_scan, n, kind,
-                                                  leaf_start, leaf_key, leaf_level);
-    P2P_LAUNCH_CHECK();
-    k_max_level<<<1, 1024, 0, s>>>(leaf_level, flag_scan, n, max_level);
+    // beyond this many counts (4M slots) their sum in every workgroup costs more than one launch that scans them
+    constexpr int64_t kSumCounts = 16384;
+    const int64_t nb = leaf_count_elems(n);
+    const unsigned g = grid_for(n, kLeafTile);
+    if (nb <= kSumCounts) {
+        k_leaf_write<false><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, cap_leaves, leaf_counts, nb, tc,
+                                                      leaf_start, leaf_key, leaf_level, perm, iperm);
+    } else {
+        k_leaf_scan<<<1, 1024, 0, s>>>(leaf_counts, nb, tc);
+        P2P_LAUNCH_CHECK();
+        k_leaf_write<true><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, cap_leaves, leaf_counts, nb, tc,
+                                                     leaf_start, leaf_key, leaf_level, perm, iperm);
+    }
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
