@@ -314,17 +314,17 @@ p2p_status neighbors_common(const p2p_tree *tree, const p2p_tree *src, p2p_nbrs 
     // total key bits: 3 per axis, plus the instance index for grids
     const int total_bits = 3 * src->key_bits + (src->kind == P2P_TREE_GRIDS ? bits_for(src->n_grids) : 0);
     Arena ar(ws);
-    int32_t *counts = ar.take<int32_t>(L);
-    int64_t *start = ar.take<int64_t>(L + 1);
-    int64_t *scan_tmp = ar.take<int64_t>(scan_ws_elems(L));
     int32_t *dir = ar.take<int32_t>((size_t(1) << neighbor_dir_bits(total_bits)) + 1);
-    int32_t *segs = ar.take<int32_t>(L);
-    int64_t *seg_scan = ar.take<int64_t>(L + 1);
-    int32_t *slots = ar.take<int32_t>(static_cast<size_t>(L) * kNbrSlotsPerLeaf);
-    int8_t *slot_code = ar.take<int8_t>(per ? static_cast<size_t>(L) * kNbrSlotsPerLeaf : 0);
-    int32_t *counters = ar.take<int32_t>(2);
-    int32_t *heavy = ar.take<int32_t>(L);
-    int64_t *totals = ar.take<int64_t>(3);
+    NbrScratch sc;
+    sc.counts = ar.take<int32_t>(L);
+    sc.segs = ar.take<int32_t>(L);
+    sc.slots = ar.take<int32_t>(static_cast<size_t>(L) * kNbrSlotsPerLeaf);
+    sc.slot_code = ar.take<int8_t>(per ? static_cast<size_t>(L) * kNbrSlotsPerLeaf : 0);
+    if (!per) sc.slot_code = nullptr;
+    sc.counters = ar.take<int32_t>(2);
+    sc.heavy = ar.take<int32_t>(L);
+    sc.sums = ar.take<int64_t>(neighbor_sum_elems());
+    sc.totals = ar.take<int64_t>(2);
     p2p_status st;
     if (ws_query(ws, ws_bytes, ar, &st)) return st;
     if (!nbrs->nbr_start) return fail(P2P_EINVAL, "nbrs->nbr_start must not be NULL");
@@ -332,15 +332,14 @@ p2p_status neighbors_common(const p2p_tree *tree, const p2p_tree *src, p2p_nbrs 
     const int inst_shift = 3 * src->key_bits;
     const NbrTargets tg{tree->leaf_key, tree->leaf_level, L};
     const NbrTargets *tgp = remote ? &tg : nullptr;
-    P2P_TRY(launch_key_directory(src->leaf_key, Ls, total_bits, dir, counters, s));
-    P2P_TRY(launch_neighbors_count(src->leaf_key, src->leaf_level, Ls, src->key_bits, inst_shift, dir,
-                                   total_bits, src->leaf_start, counts, segs, slots,
-                                   per ? slot_code : nullptr, counters, heavy, s, tgp));
-    P2P_TRY((exclusive_scan<int32_t, int64_t>(counts, start, L, scan_tmp, s)));
-    P2P_TRY((exclusive_scan<int32_t, int64_t>(segs, seg_scan, L, scan_tmp, s)));
-    P2P_TRY(launch_nbr_totals(start, seg_scan, counters, L, totals, s));
-    int64_t host[3] = {0, 0, 0};
-    P2P_HIP(hipMemcpyAsync(host, totals, sizeof(host), hipMemcpyDeviceToHost, s));
+    // lists that find no array to go to count as not fitting
+    const bool no_array = !nbrs->nbr_idx || (per && !nbrs->nbr_shift);
+    P2P_TRY(launch_key_directory(src->leaf_key, Ls, total_bits, dir, sc.counters, s));
+    P2P_TRY(launch_neighbors(src->leaf_key, src->leaf_level, Ls, src->key_bits, inst_shift, dir, total_bits,
+                             src->leaf_start, sc, no_array ? 0 : nbrs->cap, nbrs->nbr_start, nbrs->nbr_idx,
+                             per ? nbrs->nbr_shift : nullptr, s, tgp));
+    int64_t host[2] = {0, 0};
+    P2P_HIP(hipMemcpyAsync(host, sc.totals, sizeof(host), hipMemcpyDeviceToHost, s));
     P2P_HIP(hipStreamSynchronize(s));
     const int64_t E = host[0];
     nbrs->red_entries = host[1];
@@ -350,11 +349,6 @@ p2p_status neighbors_common(const p2p_tree *tree, const p2p_tree *src, p2p_nbrs 
     }
     if (E > 0 && !nbrs->nbr_idx) return fail(P2P_EINVAL, "nbrs->nbr_idx must not be NULL");
     if (E > 0 && per && !nbrs->nbr_shift) return fail(P2P_EINVAL, "nbrs->nbr_shift must not be NULL for periodic lists");
-    P2P_HIP(hipMemcpyAsync(nbrs->nbr_start, start, (L + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice, s));
-    P2P_TRY(launch_neighbors_fill(src->leaf_key, src->leaf_level, Ls, src->key_bits, inst_shift, dir,
-                                  total_bits, counts, slots, per ? slot_code : nullptr, counters, heavy, host[2] > 0,
-                                  nbrs->nbr_start, nbrs->nbr_idx, per ? nbrs->nbr_shift : nullptr, s, tgp));
-    P2P_HIP(hipStreamSynchronize(s));
     nbrs->count = E;
     return P2P_OK;
 }

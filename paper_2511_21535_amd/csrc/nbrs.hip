@@ -1,17 +1,24 @@
 // Near-field lists (the E2 neighbourhood, Sec. 5.1): for every leaf A, every leaf B whose closed cube
 // touches A's, A included, in ascending leaf id.
 //
-// One wavefront per leaf.  Lanes 0..26 each take one of the 27 cells of A's
-// size around A (A itself in the middle).  A leaf touching A either covers
-// such a cell (it is at least as large as A) or lies inside one.  Each lane
-// finds, by binary search over the sorted leaf keys, the contiguous range of
-// leaves that meet its cell.  The ranges of different cells are disjoint,
-// except that one large leaf may cover several cells; those duplicates are
-// dropped and the ranges are put in key order, which is leaf-id order.  The
-// candidates are then tested in parallel, 64 per step, and the adjacent ones
-// written with a ballot prefix, so the list comes out ascending.
+// A leaf touching A either covers one of the 27 cells of A's size around A (A
+// itself in the middle) or lies inside one.  One lane per cell finds, by binary
+// search over the sorted leaf keys, the contiguous range of leaves that meet
+// its cell.  The ranges of different cells are disjoint, except that one large
+// leaf may cover several cells; those duplicates are dropped and the ranges are
+// put in key order, which is leaf-id order.  The candidates are then tested in
+// parallel, 64 per step, and the adjacent ones written with a ballot prefix, so
+// the list comes out ascending.  Where there are many, the cell that encloses
+// 64 successive candidates is tested first, one such chunk per lane, and only
+// the chunks whose cell touches A are read.
 //
-// The counting pass (counts != NULL) also sums, per leaf A, the points of the
+// The first pass takes successive leaves of one size and one parent together,
+// up to 8 to a wavefront: their cells are the 64 of the 4^3 block around the
+// parent, one per lane, and every candidate is read once and tested against
+// each of them.  A candidate that reaches a leaf only through another's cell
+// does not touch it, so the lists are the same.
+//
+// The counting pass also sums, per leaf A, the points of the
 // leaves in nbr(A): the length of A's segment in the redundant layout.
 //
 // The searches start from a directory over the top bits of the key: dir[p]
@@ -32,21 +39,13 @@ namespace {
 constexpr int kNbrWaves = 4;
 constexpr int kNbrSlots = kNbrSlotsPerLeaf;
 
-// First index in [lo, hi) with a[i] > v (upper) or a[i] >= v (lower).
-__device__ inline int64_t bound_in(const uint64_t *__restrict__ a, int64_t lo, int64_t hi, uint64_t v,
-                                   bool upper) {
+// First index in [lo, hi) with a[i] >= v.
+__device__ inline int64_t bound_in(const uint64_t *__restrict__ a, int64_t lo, int64_t hi, uint64_t v) {
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
-        if (upper ? (a[mid] <= v) : (a[mid] < v)) lo = mid + 1; else hi = mid;
+        if (a[mid] < v) lo = mid + 1; else hi = mid;
     }
     return lo;
-}
-
-__device__ inline int64_t dir_bound(const uint64_t *__restrict__ a, const int32_t *__restrict__ dir,
-                                    int dir_bits, int shift, uint64_t v, bool upper) {
-    const uint64_t p = v >> shift;
-    if (p >= (1ull << dir_bits)) return dir[1ull << dir_bits];
-    return bound_in(a, dir[p], dir[p + 1], v, upper);
 }
 
 // Also clears the two counters of the counting pass that follows (lists over
@@ -61,7 +60,7 @@ __global__ void k_key_directory(const uint64_t *__restrict__ leaf_key, int64_t L
     }
     if (p >= nb) return;
     dir[p] = (p == nb - 1) ? static_cast<int32_t>(L)
-                           : static_cast<int32_t>(bound_in(leaf_key, 0, L, static_cast<uint64_t>(p) << shift, false));
+                           : static_cast<int32_t>(bound_in(leaf_key, 0, L, static_cast<uint64_t>(p) << shift));
 }
 
 __device__ inline void wave_sync() {
@@ -69,18 +68,22 @@ __device__ inline void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// COUNT: counts[A], segs[A], the first kNbrSlots entries of nbr(A) into
-// slots[A * kNbrSlots ...], and +1 on counters[0] for a longer list.
-// FILL: nbr(A) into nbr_idx[nbr_start[A] ...], only for leaves whose list
-// did not fit its slots (counts[A] > kNbrSlots).
+// Count: counts[A], segs[A] and the first kNbrSlots entries of nbr(A) into
+// slots[A * kNbrSlots ...]; a longer list is appended to the end of heavy[].
+// Fill: those lists into nbr_idx[nbr_start[A] ...].
 enum { kNbrCount = 0, kNbrFill = 1 };
 
 // A leaf with more candidates than this (a large leaf beside a finely split
 // region) is left to k_neighbors_heavy, which spreads its candidates over a
 // whole workgroup; in one wavefront it would set the time of the whole pass.
-constexpr int32_t kHeavyCands = 1024;
+// 700,001 periodic points, 512: 43 us and 39 us for the heavy leaves of both
+// passes; 256: 41 and 52.
+constexpr int32_t kHeavyCands = 512;
 constexpr int kHeavyWaves = 16;
 constexpr unsigned kHeavyGrid = 512;
+constexpr unsigned kFillGrid = 1024;
+constexpr int kChunk = 64;          // candidates tested in one step
+constexpr int kSegChunks = 4096;    // chunks a heavy leaf's workgroup holds at a time
 
 // What one leaf's search needs: the candidate (source) tree's arrays and key
 // directory, the target leaves' keys and levels (the same tree for plain
@@ -99,8 +102,8 @@ struct NbrTree {
 
 // Leaf A's geometry in key units: anchor a, edge sA.
 struct NbrLeaf {
-    int64_t a[3];
-    int64_t sA, dim;
+    int32_t a[3];
+    int32_t sA, dim;
     uint64_t local_mask, inst_bits;
     int lA;
 };
@@ -109,313 +112,644 @@ __device__ inline NbrLeaf nbr_leaf(const NbrTree &t, int64_t A) {
     NbrLeaf f;
     const uint64_t kA = t.tkey[A];
     f.lA = t.tlevel[A];
-    f.dim = int64_t(1) << t.key_bits;
-    f.sA = int64_t(1) << (t.key_bits - f.lA);
+    f.dim = int32_t(1) << t.key_bits;   // key_bits <= 20
+    f.sA = int32_t(1) << (t.key_bits - f.lA);
     f.local_mask = (3 * t.key_bits >= 64) ? ~0ull : ((1ull << (3 * t.key_bits)) - 1ull);
     f.inst_bits = (t.inst_shift >= 64) ? 0ull : (kA >> t.inst_shift) << t.inst_shift;
     const uint64_t local = kA & f.local_mask;
-    f.a[0] = p2pd::compact3(local);
-    f.a[1] = p2pd::compact3(local >> 1);
-    f.a[2] = p2pd::compact3(local >> 2);
+    f.a[0] = static_cast<int32_t>(p2pd::compact3(local));
+    f.a[1] = static_cast<int32_t>(p2pd::compact3(local >> 1));
+    f.a[2] = static_cast<int32_t>(p2pd::compact3(local >> 2));
     return f;
 }
 
-// Called by one whole wavefront: the candidate ranges of leaf A in (code, lo)
-// order into s_lo[0..K), their exclusive prefix into s_pre[0..K] and, with
-// PER, their image codes into s_code.  Returns the candidate total; K in *Kout.
+// Candidate ranges in (code, lo) order, range r held by lane r: its first leaf,
+// the candidates of the ranges before it, its image code (PER).
+struct NbrRanges {
+    int32_t lo, pre, code;
+    int K;           // ranges, the same in every lane
+    int32_t total;   // candidates, the same in every lane
+};
+
+// The leaves [lo, hi) that meet the cell at c (may lie past the domain's faces
+// by one cell) of the size of leaf f.  False if there is none; with PER the
+// cell wraps, and its image code goes to `code`.
 template <bool PER>
-__device__ int32_t nbr_ranges(const NbrTree &t, const NbrLeaf &f, int32_t *s_lo, int32_t *s_pre,
-                              int32_t *s_code, int *Kout) {
-    const int lane = threadIdx.x & 63;
-    // ---- one cell per lane
-    int64_t lo = 0, hi = 0;
-    bool valid = false;
-    int code = 13;
-    if (lane < 27) {
-        int64_t c[3] = {f.a[0] + (lane % 3 - 1) * f.sA, f.a[1] + ((lane / 3) % 3 - 1) * f.sA,
-                        f.a[2] + (lane / 9 - 1) * f.sA};
-        bool inside = c[0] >= 0 && c[1] >= 0 && c[2] >= 0 && c[0] < f.dim && c[1] < f.dim && c[2] < f.dim;
-        if constexpr (PER) {
-            // c lies in [-sA, dim + sA) with sA <= dim: one wrap per axis
-            int wrap[3];
+__device__ inline bool cell_range(const NbrTree &t, const NbrLeaf &f, int32_t (&c)[3], int32_t &lo, int32_t &hi,
+                                  int &code) {
+    const int32_t dim = f.dim;
+    if constexpr (PER) {
+        // c lies in [-sA, dim + sA) with sA <= dim: one wrap per axis
+        int wrap[3];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                wrap[d] = c[d] < 0 ? -1 : (c[d] >= f.dim ? 1 : 0);
-                c[d] -= wrap[d] * f.dim;
-            }
-            code = (wrap[0] + 1) + 3 * (wrap[1] + 1) + 9 * (wrap[2] + 1);
-            inside = true;
+        for (int d = 0; d < 3; ++d) {
+            wrap[d] = c[d] < 0 ? -1 : (c[d] >= dim ? 1 : 0);
+            c[d] -= wrap[d] * dim;
         }
-        if (inside) {
-            const uint64_t kC = f.inst_bits | p2pd::morton3(static_cast<uint32_t>(c[0]),
-                                                            static_cast<uint32_t>(c[1]),
-                                                            static_cast<uint32_t>(c[2]));
-            const uint64_t sizeC = 1ull << (3 * (t.key_bits - f.lA));
-            const int64_t j = dir_bound(t.leaf_key, t.dir, t.dir_bits, t.dir_shift, kC, true) - 1;
-            bool covers = false;
-            if (j >= 0) {
-                const uint64_t sj = 1ull << (3 * (t.key_bits - t.leaf_level[j]));
-                covers = kC < t.leaf_key[j] + sj;   // leaf_key[j] <= kC by construction
-            }
-            lo = covers ? j : j + 1;
-            // a covering leaf at least as large as the cell holds all of it
-            // (aligned cubes); only a cell split into smaller leaves needs
-            // the search for its end
-            if (covers && t.leaf_level[j] <= f.lA)
-                hi = j + 1;
-            else
-                hi = dir_bound(t.leaf_key, t.dir, t.dir_bits, t.dir_shift, kC + sizeC, false);
-            valid = lo < hi;
+        code = (wrap[0] + 1) + 3 * (wrap[1] + 1) + 9 * (wrap[2] + 1);
+    } else if (c[0] < 0 || c[1] < 0 || c[2] < 0 || c[0] >= dim || c[1] >= dim || c[2] >= dim) {
+        return false;
+    }
+    const uint64_t kC = f.inst_bits | p2pd::morton3(static_cast<uint32_t>(c[0]), static_cast<uint32_t>(c[1]),
+                                                    static_cast<uint32_t>(c[2]));
+    // both ends of the cell, searched together: first leaf past kC, first leaf past the cell
+    const uint64_t kE = kC + (1ull << (3 * (t.key_bits - f.lA))), top = 1ull << t.dir_bits;
+    const uint64_t p0 = kC >> t.dir_shift, p1 = kE >> t.dir_shift;
+    int32_t l0 = t.dir[min(p0, top)], h0 = t.dir[min(p0 + 1, top)];
+    int32_t l1 = t.dir[min(p1, top)], h1 = t.dir[min(p1 + 1, top)];
+    while (l0 < h0 || l1 < h1) {
+        const int32_t m0 = (l0 + h0) >> 1, m1 = (l1 + h1) >> 1;
+        const bool go0 = l0 < h0, go1 = l1 < h1;
+        const uint64_t v0 = go0 ? t.leaf_key[m0] : 0ull, v1 = go1 ? t.leaf_key[m1] : 0ull;
+        if (go0) {
+            if (v0 <= kC) l0 = m0 + 1; else h0 = m0;
+        }
+        if (go1) {
+            if (v1 < kE) l1 = m1 + 1; else h1 = m1;
         }
     }
-    // ---- drop duplicate ranges (one large leaf covering several cells of
-    // one image), rank by (code, lo); the loops stay rolled (fully unrolled,
-    // their shuffles would hold enough registers to halve the occupancy of a
-    // search that is bound by load latency)
-    bool first = valid;
-#pragma unroll 1
-    for (int q = 0; q < 27; ++q) {
-        const int64_t loq = __shfl(lo, q, 64);
-        const int vq = __shfl(static_cast<int>(valid), q, 64);
-        const int cq = PER ? __shfl(code, q, 64) : 13;
-        if (vq && q < lane && loq == lo && cq == code) first = false;
+    const int32_t j = l0 - 1;
+    bool covers = false;
+    int lj = 0;
+    if (j >= 0) {
+        lj = t.leaf_level[j];
+        covers = kC < t.leaf_key[j] + (1ull << (3 * (t.key_bits - lj)));   // leaf_key[j] <= kC by construction
     }
-    int rank = 0;
-#pragma unroll 1
-    for (int q = 0; q < 27; ++q) {
-        const int64_t loq = __shfl(lo, q, 64);
-        const int fq = __shfl(static_cast<int>(first), q, 64);
-        const int cq = PER ? __shfl(code, q, 64) : 13;
-        if (fq && (cq < code || (cq == code && loq < lo))) ++rank;
-    }
-    const int K = __popcll(__ballot(first));
-    if (first) {
-        s_lo[rank] = static_cast<int32_t>(lo);
-        s_pre[rank] = static_cast<int32_t>(hi - lo);
-        if constexpr (PER) s_code[rank] = code;
-    }
-    wave_sync();
-    // exclusive prefix of the range lengths in sorted order
-    int32_t len = (lane < K) ? s_pre[lane] : 0;
-    int32_t inc = len;
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-        int32_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    wave_sync();
-    if (lane < K) s_pre[lane] = inc - len;
-    const int32_t total = __shfl(inc, K > 0 ? K - 1 : 0, 64);
-    if (lane == 0) s_pre[K] = total;
-    wave_sync();
-    *Kout = K;
-    return total;
+    lo = covers ? j : j + 1;
+    // a covering leaf at least as large as the cell holds all of it (aligned cubes)
+    hi = covers && lj <= f.lA ? j + 1 : l1;
+    return lo < hi;
 }
 
-// Candidate cidx (< total) of the ranges: leaf B, image code cB, and whether
-// B (shifted by its image) touches A.
-template <bool PER>
-__device__ inline bool nbr_candidate(const NbrTree &t, const NbrLeaf &f, int32_t cidx, int K,
-                                     const int32_t *s_lo, const int32_t *s_pre, const int32_t *s_code,
-                                     int64_t &B, int &cB) {
-    int r = 0;
-    while (r + 1 < K && s_pre[r + 1] <= cidx) ++r;
-    B = s_lo[r] + (cidx - s_pre[r]);
-    cB = PER ? s_code[r] : 13;
-    const uint64_t kB = t.leaf_key[B] & f.local_mask;
-    const int64_t sB = int64_t(1) << (t.key_bits - t.leaf_level[B]);
-    int64_t b[3] = {p2pd::compact3(kB), p2pd::compact3(kB >> 1), p2pd::compact3(kB >> 2)};
-    if constexpr (PER) {
-        b[0] += (cB % 3 - 1) * f.dim;
-        b[1] += ((cB / 3) % 3 - 1) * f.dim;
-        b[2] += (cB / 9 - 1) * f.dim;
+// Called by one whole wavefront: the ranges [lo, hi) of the first N lanes in
+// (code, lo) order.  Ranges are disjoint or the same (one large leaf covering
+// several cells of one image), so with the sorted ones side by side a duplicate
+// is dropped and successive ranges are joined.  s: 3 x 64 words of LDS, this
+// wavefront's own.  The values that every lane compares come by readlane: as
+// shuffles they cost their LDS latency one after the other, more than the
+// searches.
+template <int N, bool PER>
+__device__ NbrRanges order_ranges(bool valid, int32_t lo, int32_t hi, int code, int32_t (&s)[3][64]) {
+    const int lane = threadIdx.x & 63;
+    if (!valid) lo = INT32_MAX;   // behind every leaf
+    if (PER && !valid) code = 27;
+    int rank = 0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int32_t loq = __builtin_amdgcn_readlane(lo, q);
+        bool less = loq < lo || (loq == lo && q < lane);
+        if constexpr (PER) {
+            const int cq = __builtin_amdgcn_readlane(code, q);
+            less = cq < code || (cq == code && less);
+        }
+        rank += less ? 1 : 0;
     }
+    const int nv = __popcll(__ballot(valid));
+    if (valid) {
+        s[0][rank] = lo;
+        s[1][rank] = hi;
+        if constexpr (PER) s[2][rank] = code;
+    }
+    wave_sync();
+    const bool has = lane < nv;
+    lo = has ? s[0][lane] : INT32_MAX;
+    hi = has ? s[1][lane] : 0;
+    code = PER && has ? s[2][lane] : 13;
+    const int32_t hi_prev = __shfl_up(hi, 1, 64);
+    const int code_prev = PER ? __shfl_up(code, 1, 64) : 13;
+    const bool head = has && (lane == 0 || lo > hi_prev || code != code_prev);
+    const uint64_t heads = __ballot(head);
+    const uint64_t after = lane == 63 ? 0ull : heads >> (lane + 1);
+    const bool tail = has && (lane + 1 == nv || (after & 1));
+    const int at = __popcll(heads & (lane == 63 ? ~0ull : (2ull << lane) - 1)) - 1;
+    wave_sync();
+    if (head) {
+        s[0][at] = lo;
+        if constexpr (PER) s[2][at] = code;
+    }
+    if (tail) s[1][at] = hi;
+    wave_sync();
+    NbrRanges r;
+    r.K = __popcll(heads);
+    const bool in = lane < r.K;
+    r.lo = in ? s[0][lane] : 0;
+    r.code = PER && in ? s[2][lane] : 13;
+    const int32_t len = in ? s[1][lane] - r.lo : 0;
+    int32_t inc = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    r.total = __builtin_amdgcn_readlane(inc, 63);
+    r.pre = in ? inc - len : INT32_MAX;
+    wave_sync();   // the LDS words may be rewritten
+    return r;
+}
+
+// The candidate ranges of one leaf, called by one whole wavefront.
+template <bool PER>
+__device__ NbrRanges nbr_ranges(const NbrTree &t, const NbrLeaf &f, int32_t (&s)[3][64]) {
+    const int lane = threadIdx.x & 63;
+    int32_t lo = 0, hi = 0;
+    int code = 13;
+    bool valid = false;
+    if (lane < 27) {
+        int32_t c[3] = {f.a[0] + (lane % 3 - 1) * f.sA, f.a[1] + ((lane / 3) % 3 - 1) * f.sA,
+                        f.a[2] + (lane / 9 - 1) * f.sA};
+        valid = cell_range<PER>(t, f, c, lo, hi, code);
+    }
+    return order_ranges<27, PER>(valid, lo, hi, code, s);
+}
+
+// Where candidate cidx (< total) lies: leaf cidx + off, image code `code`.
+// Called by whole wavefronts, cidx any value >= 0.
+template <bool PER>
+__device__ inline void nbr_place(const NbrRanges &r, int32_t cidx, int32_t &off, int &code) {
+    int q = 0;   // last range with pre <= cidx
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1)
+        if (__shfl(r.pre, q + step, 64) <= cidx) q += step;
+    off = __shfl(r.lo - r.pre, q, 64);
+    code = PER ? __shfl(r.code, q, 64) : 13;
+}
+
+// The same for the chunk of candidates c0 + lane: the ranges that begin in the
+// chunk mark their place in 64 words of LDS, and a lane's range is the count of
+// the places up to its own.
+template <bool PER>
+__device__ inline void chunk_place(const NbrRanges &r, int32_t c0, int32_t (&s)[64], int32_t &off, int &code) {
+    const int lane = threadIdx.x & 63;
+    s[lane] = 0;
+    wave_sync();
+    if (r.pre > c0 && r.pre - c0 < kChunk) s[r.pre - c0] = 1;
+    wave_sync();
+    const uint64_t begins = __ballot(s[lane] != 0);
+    wave_sync();
+    const int q = __popcll(__ballot(r.pre <= c0)) - 1 + __popcll(begins & (lane == 63 ? ~0ull : (2ull << lane) - 1));
+    off = __shfl(r.lo - r.pre, q, 64);
+    code = PER ? __shfl(r.code, q, 64) : 13;
+}
+
+// The corner of a cube by its key, moved to image `code`.
+template <bool PER>
+__device__ inline void corner(const NbrLeaf &f, uint64_t key, int code, int32_t (&b)[3]) {
+    b[0] = static_cast<int32_t>(p2pd::compact3(key));
+    b[1] = static_cast<int32_t>(p2pd::compact3(key >> 1));
+    b[2] = static_cast<int32_t>(p2pd::compact3(key >> 2));
+    if constexpr (PER) {
+        b[0] += (code % 3 - 1) * f.dim;
+        b[1] += ((code / 3) % 3 - 1) * f.dim;
+        b[2] += (code / 9 - 1) * f.dim;
+    }
+}
+
+// Candidate `lane` of chunk ch: leaf B, image code cB, and whether there is one
+// and it touches A.
+template <bool PER>
+__device__ inline bool nbr_candidate(const NbrTree &t, const NbrLeaf &f, const NbrRanges &r, int32_t ch,
+                                     int32_t (&s_mark)[64], int32_t &B, int &cB) {
+    const int32_t cidx = ch * kChunk + static_cast<int32_t>(threadIdx.x & 63);
+    int32_t off;
+    chunk_place<PER>(r, ch * kChunk, s_mark, off, cB);
+    if (cidx >= r.total) return false;
+    B = cidx + off;
+    const int32_t s = int32_t(1) << (t.key_bits - t.leaf_level[B]);
+    int32_t b[3];
+    corner<PER>(f, t.leaf_key[B] & f.local_mask, cB, b);
     bool adj = true;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) adj = adj && (f.a[d] <= b[d] + sB) && (b[d] <= f.a[d] + f.sA);
+    for (int d = 0; d < 3; ++d) adj = adj && f.a[d] <= b[d] + s && b[d] <= f.a[d] + f.sA;
     return adj;
 }
 
-// Writes one adjacent candidate at list position pos (COUNT: into the slots if
-// it is among the first kNbrSlots; FILL: into the CSR list).
-template <int MODE, bool PER>
-__device__ inline void nbr_put(int64_t A, int64_t pos, int64_t out0, int64_t B, int cB, int32_t *slots,
-                               int8_t *slot_code, int32_t *nbr_idx, int8_t *nbr_shift) {
-    if (MODE == kNbrFill) {
-        nbr_idx[out0 + pos] = static_cast<int32_t>(B);
-        if constexpr (PER) nbr_shift[out0 + pos] = static_cast<int8_t>(cB);
-    } else if (pos < kNbrSlots) {
-        slots[A * kNbrSlots + pos] = static_cast<int32_t>(B);
-        if constexpr (PER) slot_code[A * kNbrSlots + pos] = static_cast<int8_t>(cB);
-    }
+// Whether chunk ch of the candidates may hold one that touches the cube at f.a
+// of edge `edge`: false if the chunk lies in one run of successive leaves and
+// the smallest cell around its first and last leaf does not touch the cube.
+// All of a chunk's leaves lie inside that cell: they are disjoint aligned cubes
+// between two whose corners it holds.  Called by whole wavefronts, ch any value.
+template <bool PER>
+__device__ inline bool chunk_near(const NbrTree &t, const NbrLeaf &f, int32_t edge, const NbrRanges &r, int32_t ch) {
+    const int64_t c0 = static_cast<int64_t>(ch) * kChunk;
+    const bool in = c0 < r.total;
+    const int32_t i0 = in ? static_cast<int32_t>(c0) : 0;
+    const int32_t i1 = in ? min(r.total, i0 + kChunk) - 1 : 0;
+    int32_t o0, o1;
+    int code0, code1;
+    nbr_place<PER>(r, i0, o0, code0);
+    nbr_place<PER>(r, i1, o1, code1);
+    if (!in) return false;
+    if (o0 != o1 || code0 != code1 || i0 == i1) return true;
+    const uint64_t k0 = t.leaf_key[i0 + o0] & f.local_mask, k1 = t.leaf_key[i1 + o1] & f.local_mask;
+    const int m = (64 - __clzll(static_cast<long long>(k0 ^ k1)) + 2) / 3;
+    int32_t b[3];
+    corner<PER>(f, (k0 >> (3 * m)) << (3 * m), code0, b);
+    bool near = true;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) near = near && f.a[d] <= b[d] + (int32_t(1) << m) && b[d] <= f.a[d] + edge;
+    return near;
 }
 
-// One wavefront per leaf; a leaf with more than kHeavyCands candidates is
-// appended to heavy[] (COUNT) or skipped (FILL) for k_neighbors_heavy.
-// PER: periodic lists; slot_code / nbr_shift receive the image codes.
-template <int MODE, bool PER>
-__global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors(
+// The counting pass: one wavefront per run of successive leaves of one size and
+// one parent, found from the keys beside them; the wavefronts of the other
+// leaves of a run have nothing to do.  Runs with more than kHeavyCands
+// candidates go to k_neighbors_heavy leaf by leaf, at the front of heavy[].
+// Bound by the latency of a wavefront's chain (searches, ordering, chunks) and
+// by the lines that the searches touch, one per lane and step, so what counts
+// is how few searches there are and how short the chain is.  2^21 clustered
+// points: a wavefront per leaf took 231 us, 192 us with both ends of a cell
+// searched together and the ranges compared by readlane, 128 us with the leaves
+// of a parent taken together, 73 us with successive ranges joined and a
+// candidate's range found by marks instead of a loop over the ranges.
+template <bool PER>
+__global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors_count(
     NbrTree t, int32_t *__restrict__ counts, int32_t *__restrict__ segs, int32_t *__restrict__ slots,
-    int8_t *__restrict__ slot_code, int32_t *__restrict__ counters, int32_t *__restrict__ heavy,
-    const int64_t *__restrict__ nbr_start, int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
-    __shared__ int32_t s_lo[kNbrWaves][32];
-    __shared__ int32_t s_pre[kNbrWaves][33];
-    __shared__ int32_t s_code[kNbrWaves][32];
+    int8_t *__restrict__ slot_code, int32_t *__restrict__ counters, int32_t *__restrict__ heavy) {
+    __shared__ int32_t s_w[kNbrWaves][3][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t A = static_cast<int64_t>(blockIdx.x) * kNbrWaves + w;
     if (A >= t.Lt) return;
-    if (MODE == kNbrFill && counts[A] <= kNbrSlots) return;
-    const NbrLeaf f = nbr_leaf(t, A);
-    int K = 0;
-    const int32_t total = nbr_ranges<PER>(t, f, s_lo[w], s_pre[w], s_code[w], &K);
-    if (total > kHeavyCands) {
-        if (MODE == kNbrCount && lane == 0) heavy[atomicAdd(&counters[1], 1)] = static_cast<int32_t>(A);
+    // ---- the run: lane i holds leaf A - 1 + i
+    const int64_t i = A - 1 + lane;
+    uint64_t ki = 0;
+    int li = -1;
+    if (lane < 9 && i >= 0 && i < t.Lt) {
+        ki = t.tkey[i];
+        li = t.tlevel[i];
+    }
+    const uint64_t kA = __shfl(ki, 1, 64);
+    const int lA = __builtin_amdgcn_readlane(li, 1);
+    // key bits below the parent's; a root has no parent (the next bits may number grid instances)
+    const int up = 3 * (t.key_bits - lA) + 3;
+    const bool same = lA > 0 ? li == lA && (ki >> up) == (kA >> up) : lane == 1;
+    const uint32_t run = static_cast<uint32_t>(__ballot(same)) & 0x1ff;
+    if (run & 1) return;                                       // leaf A - 1 leads it
+    const int members = __builtin_ctz(~(run >> 1));            // leaves A .. A + members - 1
+    // their octants of the parent, and the parent's block of cells
+    const int oct = lA > 0 ? static_cast<int>(ki >> (up - 3)) & 7 : 0;
+    uint32_t present = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if (q < members) present |= 1u << __builtin_amdgcn_readlane(oct, q + 1);
+    NbrLeaf f = nbr_leaf(t, A);
+    const int32_t sA = f.sA;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) f.a[d] &= ~(2 * sA - 1);
+    const int cx = (lane & 3) - 1, cy = ((lane >> 2) & 3) - 1, cz = (lane >> 4) - 1;
+    const uint32_t reach = (cx < 0 ? 0x55u : cx > 1 ? 0xaau : 0xffu) & (cy < 0 ? 0x33u : cy > 1 ? 0xccu : 0xffu) &
+                           (cz < 0 ? 0x0fu : cz > 1 ? 0xf0u : 0xffu);   // octants this cell is beside
+    int32_t lo = 0, hi = 0;
+    int code = 13;
+    bool valid = false;
+    if (reach & present) {
+        int32_t c[3] = {f.a[0] + cx * sA, f.a[1] + cy * sA, f.a[2] + cz * sA};
+        valid = cell_range<PER>(t, f, c, lo, hi, code);
+    }
+    const NbrRanges r = order_ranges<64, PER>(valid, lo, hi, code, s_w[w]);
+    if (r.total > kHeavyCands) {
+        int32_t at = 0;
+        if (lane == 0) at = atomicAdd(&counters[1], members);
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (lane < members) heavy[at + lane] = static_cast<int32_t>(A + lane);
         return;
     }
-
     // ---- test candidates, 64 at a time, in ascending (code, leaf id)
-    const int64_t out0 = (MODE == kNbrFill) ? nbr_start[A] : 0;
-    int64_t written = 0;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int32_t occ_sum = 0;     // points of this lane's adjacent candidates (count pass)
-    for (int32_t base = 0; base < total; base += 64) {
-        const int32_t cidx = base + lane;
-        bool adj = false;
-        int64_t B = 0;
-        int cB = 13;
-        if (cidx < total) adj = nbr_candidate<PER>(t, f, cidx, K, s_lo[w], s_pre[w], s_code[w], B, cB);
-        const uint64_t bal = __ballot(adj);
-        const int64_t pos = written + __popcll(bal & below);
-        if (adj) {
-            nbr_put<MODE, PER>(A, pos, out0, B, cB, slots, slot_code, nbr_idx, nbr_shift);
-            if (MODE == kNbrCount) occ_sum += t.leaf_start[B + 1] - t.leaf_start[B];
-        }
-        written += __popcll(bal);
-    }
-    if (MODE == kNbrCount) {
+    const int32_t nch = (r.total + kChunk - 1) / kChunk;   // at most kHeavyCands / kChunk
+    uint64_t todo = nch > 3 ? __ballot(chunk_near<PER>(t, f, 2 * sA, r, lane)) : (1ull << nch) - 1;
+    int32_t written[8], occ[8];   // per octant: entries (the same in every lane), points of this lane's entries
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) occ_sum += __shfl_xor(occ_sum, o, 64);
+    for (int q = 0; q < 8; ++q) written[q] = occ[q] = 0;
+    while (todo != 0) {
+        const int32_t c0 = __builtin_ctzll(todo) * kChunk, cidx = c0 + lane;
+        todo &= todo - 1;
+        int32_t off;
+        int cB;
+        chunk_place<PER>(r, c0, s_w[w][0], off, cB);
+        const bool in = cidx < r.total;
+        const int32_t B = in ? cidx + off : 0;
+        const int32_t s = int32_t(1) << (t.key_bits - t.leaf_level[B]);
+        const int32_t pts = t.leaf_start[B + 1] - t.leaf_start[B];
+        int32_t b[3];
+        corner<PER>(f, t.leaf_key[B] & f.local_mask, cB, b);
+        bool ok[3][2];
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                ok[d][h] = in && f.a[d] + h * sA <= b[d] + s && b[d] <= f.a[d] + (h + 1) * sA;
+        int32_t m = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (!((present >> q) & 1)) continue;
+            const bool adj = ok[0][q & 1] && ok[1][(q >> 1) & 1] && ok[2][q >> 2];
+            const uint64_t bal = __ballot(adj);
+            const int32_t pos = written[q] + __popcll(bal & below);
+            if (adj) {
+                occ[q] += pts;
+                if (pos < kNbrSlots) {
+                    slots[(A + m) * kNbrSlots + pos] = B;
+                    if constexpr (PER) slot_code[(A + m) * kNbrSlots + pos] = static_cast<int8_t>(cB);
+                }
+            }
+            written[q] += __popcll(bal);
+            ++m;
+        }
+    }
+    int32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (!((present >> q) & 1)) continue;
+        int32_t sum = occ[q];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
         if (lane == 0) {
-            counts[A] = static_cast<int32_t>(written);
-            segs[A] = occ_sum;
-            if (written > kNbrSlots) atomicAdd(&counters[0], 1);
+            counts[A + m] = written[q];
+            segs[A + m] = sum;
+            if (written[q] > kNbrSlots) heavy[t.Lt - 1 - atomicAdd(&counters[0], 1)] = static_cast<int32_t>(A + m);
+        }
+        ++m;
+    }
+}
+
+// The lists over kNbrSlots entries, one wavefront each (grid-stride).
+template <bool PER>
+__global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors_fill(
+    NbrTree t, const int32_t *__restrict__ counters, const int32_t *__restrict__ heavy,
+    const int64_t *__restrict__ totals, int64_t cap, const int64_t *__restrict__ nbr_start,
+    int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
+    __shared__ int32_t s_w[kNbrWaves][3][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    if (totals[0] > cap) return;
+    const int64_t work = counters[0];
+    for (int64_t h = static_cast<int64_t>(blockIdx.x) * kNbrWaves + w; h < work;
+         h += static_cast<int64_t>(gridDim.x) * kNbrWaves) {
+        const int64_t A = heavy[t.Lt - 1 - h];
+        const NbrLeaf f = nbr_leaf(t, A);
+        const NbrRanges r = nbr_ranges<PER>(t, f, s_w[w]);
+        const int32_t nch = (r.total + kChunk - 1) / kChunk;   // at most kHeavyCands / kChunk
+        uint64_t todo = nch > 2 ? __ballot(chunk_near<PER>(t, f, f.sA, r, lane)) : (1ull << nch) - 1;
+        int64_t out = nbr_start[A];
+        while (todo != 0) {
+            const int32_t ch = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            int32_t B = 0;
+            int cB = 13;
+            const bool adj = nbr_candidate<PER>(t, f, r, ch, s_w[w][0], B, cB);
+            const uint64_t bal = __ballot(adj);
+            if (adj) {
+                const int64_t p = out + __popcll(bal & below);
+                nbr_idx[p] = B;
+                if constexpr (PER) nbr_shift[p] = static_cast<int8_t>(cB);
+            }
+            out += __popcll(bal);
         }
     }
 }
 
-// The leaves heavy[0 .. counters[1]), one workgroup each (grid-stride): the
-// first wavefront finds the ranges, the candidates are split into
-// kHeavyWaves contiguous runs, one per wavefront; a first sweep counts each
-// run's adjacent candidates, their prefix gives each run its first list
-// position, and a second sweep writes the entries (COUNT: only runs that
-// reach into the first kNbrSlots positions).
+// The leaves heavy[0 .. counters[1]), one workgroup each (grid-stride).  The
+// first wavefront finds the ranges; the chunks of candidates that may touch A
+// are listed in order, kSegChunks at a time, and shared out evenly; each
+// chunk's adjacent candidates are kept as a mask, whose counts give every
+// wavefront its first list position, and FILL writes the entries from the
+// masks.  What it costs follows the surface of A, not the volume around it:
+// 700,001 periodic points 19 us counting and 20 us filling (113 and 80 us with
+// every candidate tested twice).
 template <int MODE, bool PER>
 __global__ __launch_bounds__(64 * kHeavyWaves) void k_neighbors_heavy(
-    NbrTree t, int32_t *__restrict__ counts, int32_t *__restrict__ segs, int32_t *__restrict__ slots,
-    int8_t *__restrict__ slot_code, int32_t *__restrict__ counters, const int32_t *__restrict__ heavy,
+    NbrTree t, int32_t *__restrict__ counts, int32_t *__restrict__ segs, const int32_t *__restrict__ counters,
+    const int32_t *__restrict__ heavy, const int64_t *__restrict__ totals, int64_t cap,
     const int64_t *__restrict__ nbr_start, int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
-    __shared__ int32_t s_lo[32];
-    __shared__ int32_t s_pre[33];
-    __shared__ int32_t s_code[32];
+    __shared__ int32_t s_r[3][64];                // the ranges: first leaf, prefix, image code
+    __shared__ int32_t s_mark[kHeavyWaves][64];
     __shared__ int32_t s_meta[2];                 // K, total
-    __shared__ int32_t s_cnt[kHeavyWaves];        // adjacent candidates per run
-    __shared__ int32_t s_occ[kHeavyWaves];        // their points (COUNT)
+    __shared__ int32_t s_cnt[kHeavyWaves];        // listed chunks, then adjacent candidates, per wavefront
+    __shared__ int32_t s_occ[kHeavyWaves];        // points of the adjacent candidates (COUNT)
+    __shared__ int32_t s_chunk[kSegChunks];
+    __shared__ uint64_t s_mask[MODE == kNbrFill ? kSegChunks : 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (MODE == kNbrFill && totals[0] > cap) return;
     const int32_t nh = counters[1];
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     for (int32_t h = blockIdx.x; h < nh; h += gridDim.x) {
         const int64_t A = heavy[h];
-        if (MODE == kNbrFill && counts[A] <= kNbrSlots) continue;   // uniform over the block
         const NbrLeaf f = nbr_leaf(t, A);
         if (w == 0) {
-            int K = 0;
-            const int32_t total = nbr_ranges<PER>(t, f, s_lo, s_pre, s_code, &K);
+            const NbrRanges r0 = nbr_ranges<PER>(t, f, s_r);
+            s_r[0][lane] = r0.lo;
+            s_r[1][lane] = r0.pre;
+            s_r[2][lane] = r0.code;
             if (lane == 0) {
-                s_meta[0] = K;
-                s_meta[1] = total;
+                s_meta[0] = r0.K;
+                s_meta[1] = r0.total;
             }
         }
         __syncthreads();
-        const int K = s_meta[0];
-        const int32_t total = s_meta[1];
-        const int32_t run = (total + kHeavyWaves - 1) / kHeavyWaves;
-        const int32_t c0 = min(total, w * run), c1 = min(total, c0 + run);
-        // first sweep: count
-        int32_t cnt = 0, occ_sum = 0;
-        for (int32_t base = c0; base < c1; base += 64) {
-            const int32_t cidx = base + lane;
-            bool adj = false;
-            int64_t B = 0;
-            int cB = 13;
-            if (cidx < c1) adj = nbr_candidate<PER>(t, f, cidx, K, s_lo, s_pre, s_code, B, cB);
-            cnt += __popcll(__ballot(adj));
-            if (MODE == kNbrCount && adj) occ_sum += t.leaf_start[B + 1] - t.leaf_start[B];
+        NbrRanges r;
+        r.lo = s_r[0][lane];
+        r.pre = s_r[1][lane];
+        r.code = s_r[2][lane];
+        r.K = __builtin_amdgcn_readfirstlane(s_meta[0]);
+        r.total = __builtin_amdgcn_readfirstlane(s_meta[1]);
+        const int32_t nch = (r.total + kChunk - 1) / kChunk;
+        const int64_t out0 = MODE == kNbrFill ? nbr_start[A] : 0;
+        int32_t written = 0, occ_sum = 0;
+        for (int32_t seg = 0; seg < nch; seg += kSegChunks) {
+            // ---- the chunks that may touch A, in order
+            int32_t M = 0;
+            const int32_t seg_end = min(nch, seg + kSegChunks);
+            for (int32_t c = seg; c < seg_end; c += 64 * kHeavyWaves) {
+                const int32_t ch = c + static_cast<int32_t>(threadIdx.x);
+                const bool near = chunk_near<PER>(t, f, f.sA, r, ch) && ch < seg_end;
+                const uint64_t bal = __ballot(near);
+                if (lane == 0) s_cnt[w] = __popcll(bal);
+                __syncthreads();
+                int32_t at = M + __popcll(bal & below);
+                for (int q = 0; q < kHeavyWaves; ++q) {
+                    if (q < w) at += s_cnt[q];
+                    M += s_cnt[q];
+                }
+                if (near) s_chunk[at] = ch;
+                __syncthreads();
+            }
+            // ---- their adjacent candidates
+            const int32_t per = (M + kHeavyWaves - 1) / kHeavyWaves;
+            const int32_t j0 = min(M, w * per), j1 = min(M, j0 + per);
+            int32_t cnt = 0;
+            for (int32_t j = j0; j < j1; ++j) {
+                const int32_t ch = __builtin_amdgcn_readfirstlane(s_chunk[j]);
+                int32_t B = 0;
+                int cB = 13;
+                const bool adj = nbr_candidate<PER>(t, f, r, ch, s_mark[w], B, cB);
+                const uint64_t bal = __ballot(adj);
+                cnt += __popcll(bal);
+                if (MODE == kNbrCount) {
+                    if (adj) occ_sum += t.leaf_start[B + 1] - t.leaf_start[B];
+                } else if (lane == 0) {
+                    s_mask[j] = bal;
+                }
+            }
+            if (lane == 0) s_cnt[w] = cnt;
+            __syncthreads();
+            int32_t pos = written;
+            for (int q = 0; q < kHeavyWaves; ++q) {
+                if (q < w) pos += s_cnt[q];
+                written += s_cnt[q];
+            }
+            if (MODE == kNbrFill) {
+                for (int32_t j = j0; j < j1; ++j) {
+                    const int32_t ch = __builtin_amdgcn_readfirstlane(s_chunk[j]);
+                    const uint64_t bal = s_mask[j];
+                    const int32_t cidx = ch * kChunk + lane;
+                    int32_t off;
+                    int cB;
+                    chunk_place<PER>(r, ch * kChunk, s_mark[w], off, cB);
+                    if ((bal >> lane) & 1) {
+                        const int64_t p = out0 + pos + __popcll(bal & below);
+                        nbr_idx[p] = cidx + off;
+                        if constexpr (PER) nbr_shift[p] = static_cast<int8_t>(cB);
+                    }
+                    pos += __popcll(bal);
+                }
+            }
+            __syncthreads();   // s_cnt, s_chunk and s_mask are rewritten
         }
         if (MODE == kNbrCount) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) occ_sum += __shfl_xor(occ_sum, o, 64);
-        }
-        if (lane == 0) {
-            s_cnt[w] = cnt;
-            s_occ[w] = occ_sum;
-        }
-        __syncthreads();
-        int64_t first = 0, all = 0, occ_all = 0;
-        for (int q = 0; q < kHeavyWaves; ++q) {
-            if (q < w) first += s_cnt[q];
-            all += s_cnt[q];
-            occ_all += s_occ[q];
-        }
-        // second sweep: write
-        if (MODE == kNbrFill || first < kNbrSlots) {
-            const int64_t out0 = (MODE == kNbrFill) ? nbr_start[A] : 0;
-            int64_t written = first;
-            for (int32_t base = c0; base < c1; base += 64) {
-                if (MODE == kNbrCount && written >= kNbrSlots) break;   // uniform
-                const int32_t cidx = base + lane;
-                bool adj = false;
-                int64_t B = 0;
-                int cB = 13;
-                if (cidx < c1) adj = nbr_candidate<PER>(t, f, cidx, K, s_lo, s_pre, s_code, B, cB);
-                const uint64_t bal = __ballot(adj);
-                const int64_t pos = written + __popcll(bal & below);
-                if (adj) nbr_put<MODE, PER>(A, pos, out0, B, cB, slots, slot_code, nbr_idx, nbr_shift);
-                written += __popcll(bal);
+            if (lane == 0) s_occ[w] = occ_sum;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int32_t all = 0;
+                for (int q = 0; q < kHeavyWaves; ++q) all += s_occ[q];
+                counts[A] = written;
+                segs[A] = all;
             }
-        }
-        if (MODE == kNbrCount && threadIdx.x == 0) {
-            counts[A] = static_cast<int32_t>(all);
-            segs[A] = static_cast<int32_t>(occ_all);
-            if (all > kNbrSlots) atomicAdd(&counters[0], 1);
         }
         __syncthreads();   // the LDS ranges are rewritten for the next leaf
     }
 }
 
+// List starts: at most kStartGrid workgroups each sum the counts and segment
+// lengths of `span` leaves, a multiple of kStartTile (k_nbr_sums), then scan
+// their own span behind the sums before it (k_nbr_starts).  The starts are
+// written only if all lists fit `cap` entries.
+constexpr int kStartBlock = 256, kStartItems = 8, kStartTile = kStartBlock * kStartItems;
+constexpr unsigned kStartGrid = 1024;
+
+__device__ inline int64_t wave_sum(int64_t v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+__global__ __launch_bounds__(kStartBlock) void k_nbr_sums(const int32_t *__restrict__ counts,
+                                                          const int32_t *__restrict__ segs, int64_t L, int64_t span,
+                                                          int64_t *__restrict__ sums) {
+    __shared__ int64_t s_w[2][kStartBlock / 64];
+    const int64_t i0 = blockIdx.x * span, i1 = min(L, i0 + span);
+    int64_t c = 0, g = 0;
+    for (int64_t i = i0 + threadIdx.x; i < i1; i += kStartBlock) {
+        c += counts[i];
+        g += segs[i];
+    }
+    c = wave_sum(c);
+    g = wave_sum(g);
+    if ((threadIdx.x & 63) == 0) {
+        s_w[0][threadIdx.x >> 6] = c;
+        s_w[1][threadIdx.x >> 6] = g;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        int64_t v = 0;
+        for (int q = 0; q < kStartBlock / 64; ++q) v += s_w[threadIdx.x][q];
+        sums[threadIdx.x * kStartGrid + blockIdx.x] = v;
+    }
+}
+
+__global__ __launch_bounds__(kStartBlock) void k_nbr_starts(const int32_t *__restrict__ counts, int64_t L,
+                                                            int64_t span, const int64_t *__restrict__ sums,
+                                                            int64_t cap, int64_t *__restrict__ nbr_start,
+                                                            int64_t *__restrict__ totals) {
+    constexpr int W = kStartBlock / 64;
+    __shared__ int64_t s_w[3][W];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int64_t before = 0, all = 0, seg = 0;
+    for (unsigned q = t; q < gridDim.x; q += kStartBlock) {
+        const int64_t v = sums[q];
+        all += v;
+        if (q < blockIdx.x) before += v;
+        seg += sums[kStartGrid + q];
+    }
+    before = wave_sum(before);
+    all = wave_sum(all);
+    seg = wave_sum(seg);
+    if (lane == 0) {
+        s_w[0][w] = before;
+        s_w[1][w] = all;
+        s_w[2][w] = seg;
+    }
+    __syncthreads();
+    before = all = seg = 0;
+    for (int q = 0; q < W; ++q) {
+        before += s_w[0][q];
+        all += s_w[1][q];
+        seg += s_w[2][q];
+    }
+    if (blockIdx.x == 0 && t == 0) {
+        totals[0] = all;
+        totals[1] = seg;
+    }
+    if (all > cap) return;
+    if (blockIdx.x == 0 && t == 0) nbr_start[L] = all;
+    const int64_t i1 = min(L, blockIdx.x * span + span);
+    for (int64_t i0 = blockIdx.x * span; i0 < i1; i0 += kStartTile) {
+        const int64_t base = i0 + t * kStartItems;
+        int32_t v[kStartItems];
+        int64_t s = 0;
+#pragma unroll
+        for (int k = 0; k < kStartItems; ++k) {
+            v[k] = base + k < i1 ? counts[base + k] : 0;
+            s += v[k];
+        }
+        int64_t inc = s;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        __syncthreads();
+        if (lane == 63) s_w[0][w] = inc;
+        __syncthreads();
+        int64_t p = before + inc - s;
+        for (int q = 0; q < W; ++q) {
+            if (q < w) p += s_w[0][q];
+            before += s_w[0][q];
+        }
+#pragma unroll
+        for (int k = 0; k < kStartItems; ++k) {
+            if (base + k < i1) nbr_start[base + k] = p;
+            p += v[k];
+        }
+    }
+}
+
 // Slots into the CSR lists: thread (A, s) moves entry s of a list that fit
-// (and its image code, if slot_code is not null).
+// (and its image code, if slot_code is not null).  A heavy leaf's short list
+// is not in its slots; the fill writes it afterwards.
 __global__ void k_compact_slots(const int32_t *__restrict__ counts, const int32_t *__restrict__ slots,
-                                const int8_t *__restrict__ slot_code,
-                                const int64_t *__restrict__ nbr_start, int64_t L,
+                                const int8_t *__restrict__ slot_code, const int64_t *__restrict__ totals,
+                                int64_t cap, const int64_t *__restrict__ nbr_start, int64_t L,
                                 int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int64_t A = t / kNbrSlots;
     const int sidx = static_cast<int>(t % kNbrSlots);
-    if (A >= L) return;
+    if (A >= L || totals[0] > cap) return;
     const int32_t c = counts[A];
     if (c <= kNbrSlots && sidx < c) {
         nbr_idx[nbr_start[A] + sidx] = slots[t];
         if (slot_code) nbr_shift[nbr_start[A] + sidx] = slot_code[t];
     }
-}
-
-// The list totals E and S and the number of overflowing lists, gathered for
-// one read-back.
-__global__ void k_nbr_totals(const int64_t *__restrict__ start, const int64_t *__restrict__ seg_scan,
-                             const int32_t *__restrict__ counters, int64_t L, int64_t *__restrict__ out) {
-    out[0] = L > 0 ? start[L] : 0;
-    out[1] = L > 0 ? seg_scan[L] : 0;
-    out[2] = counters[0];
 }
 
 }  // namespace
@@ -451,55 +785,46 @@ NbrTree make_tree(const uint64_t *leaf_key, const int8_t *leaf_level, const int3
 }
 }  // namespace
 
-p2p_status launch_neighbors_count(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L,
-                                  int key_bits, int inst_shift, const int32_t *dir, int total_key_bits,
-                                  const int32_t *leaf_start, int32_t *counts, int32_t *segs,
-                                  int32_t *slots, int8_t *slot_code, int32_t *counters, int32_t *heavy,
-                                  hipStream_t s, const NbrTargets *tg) {
+size_t neighbor_sum_elems() { return 2 * kStartGrid; }
+
+p2p_status launch_neighbors(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L, int key_bits,
+                            int inst_shift, const int32_t *dir, int total_key_bits, const int32_t *leaf_start,
+                            const NbrScratch &ws, int64_t cap, int64_t *nbr_start, int32_t *nbr_idx,
+                            int8_t *nbr_shift, hipStream_t s, const NbrTargets *tg) {
     const NbrTree t = make_tree(leaf_key, leaf_level, leaf_start, L, key_bits, inst_shift, dir, total_key_bits, tg);
-    if (t.Lt <= 0) return P2P_OK;
-#define P2P_NBR_COUNT(PER)                                                                             \
-    k_neighbors<kNbrCount, PER><<<grid_for(t.Lt, kNbrWaves), 64 * kNbrWaves, 0, s>>>(                 \
-        t, counts, segs, slots, slot_code, counters, heavy, nullptr, nullptr, nullptr);                 \
-    P2P_LAUNCH_CHECK();                                                                                \
-    k_neighbors_heavy<kNbrCount, PER><<<kHeavyGrid, 64 * kHeavyWaves, 0, s>>>(                        \
-        t, counts, segs, slots, slot_code, counters, heavy, nullptr, nullptr, nullptr)
-    if (slot_code) { P2P_NBR_COUNT(true); } else { P2P_NBR_COUNT(false); }
-#undef P2P_NBR_COUNT
-    P2P_LAUNCH_CHECK();
-    return P2P_OK;
-}
-
-p2p_status launch_nbr_totals(const int64_t *start, const int64_t *seg_scan, const int32_t *counters,
-                             int64_t L, int64_t *out, hipStream_t s) {
-    k_nbr_totals<<<1, 1, 0, s>>>(start, seg_scan, counters, L, out);
-    P2P_LAUNCH_CHECK();
-    return P2P_OK;
-}
-
-p2p_status launch_neighbors_fill(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L,
-                                 int key_bits, int inst_shift, const int32_t *dir, int total_key_bits,
-                                 const int32_t *counts, const int32_t *slots, const int8_t *slot_code,
-                                 int32_t *counters, const int32_t *heavy, bool any_overflow,
-                                 const int64_t *nbr_start, int32_t *nbr_idx, int8_t *nbr_shift, hipStream_t s,
-                                 const NbrTargets *tg) {
-    const NbrTree t = make_tree(leaf_key, leaf_level, nullptr, L, key_bits, inst_shift, dir, total_key_bits, tg);
-    if (t.Lt <= 0) return P2P_OK;
-    k_compact_slots<<<grid_for(t.Lt * kNbrSlots, 256), 256, 0, s>>>(counts, slots, slot_code, nbr_start, t.Lt,
-                                                                    nbr_idx, nbr_shift);
-    P2P_LAUNCH_CHECK();
-    if (any_overflow) {
-        int32_t *cn = const_cast<int32_t *>(counts);
-#define P2P_NBR_FILL(PER)                                                                              \
-        k_neighbors<kNbrFill, PER><<<grid_for(t.Lt, kNbrWaves), 64 * kNbrWaves, 0, s>>>(              \
-            t, cn, nullptr, nullptr, nullptr, counters, nullptr, nbr_start, nbr_idx, nbr_shift);       \
-        P2P_LAUNCH_CHECK();                                                                            \
-        k_neighbors_heavy<kNbrFill, PER><<<kHeavyGrid, 64 * kHeavyWaves, 0, s>>>(                     \
-            t, cn, nullptr, nullptr, nullptr, counters, heavy, nbr_start, nbr_idx, nbr_shift)
-        if (slot_code) { P2P_NBR_FILL(true); } else { P2P_NBR_FILL(false); }
-#undef P2P_NBR_FILL
+    const int64_t tiles = t.Lt > 0 ? (t.Lt + kStartTile - 1) / kStartTile : 1;
+    const int64_t span = (tiles + kStartGrid - 1) / kStartGrid * kStartTile;
+    const unsigned g_start = grid_for(t.Lt, static_cast<int>(span));
+    const unsigned g_leaf = grid_for(t.Lt, kNbrWaves), g_fill = g_leaf < kFillGrid ? g_leaf : kFillGrid;
+    const unsigned g_heavy = t.Lt < kHeavyGrid ? static_cast<unsigned>(t.Lt) : kHeavyGrid;
+#define P2P_NBR(PER)                                                                                              \
+    k_neighbors_count<PER><<<g_leaf, 64 * kNbrWaves, 0, s>>>(t, ws.counts, ws.segs, ws.slots, ws.slot_code,      \
+                                                             ws.counters, ws.heavy);                             \
+    P2P_LAUNCH_CHECK();                                                                                           \
+    k_neighbors_heavy<kNbrCount, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                       \
+        t, ws.counts, ws.segs, ws.counters, ws.heavy, nullptr, 0, nullptr, nullptr, nullptr)
+    if (t.Lt > 0) {
+        if (ws.slot_code) { P2P_NBR(true); } else { P2P_NBR(false); }
         P2P_LAUNCH_CHECK();
     }
+#undef P2P_NBR
+    k_nbr_sums<<<g_start, kStartBlock, 0, s>>>(ws.counts, ws.segs, t.Lt, span, ws.sums);
+    P2P_LAUNCH_CHECK();
+    k_nbr_starts<<<g_start, kStartBlock, 0, s>>>(ws.counts, t.Lt, span, ws.sums, cap, nbr_start, ws.totals);
+    P2P_LAUNCH_CHECK();
+    if (t.Lt <= 0) return P2P_OK;
+    k_compact_slots<<<grid_for(t.Lt * kNbrSlots, 256), 256, 0, s>>>(ws.counts, ws.slots, ws.slot_code, ws.totals, cap,
+                                                                    nbr_start, t.Lt, nbr_idx, nbr_shift);
+    P2P_LAUNCH_CHECK();
+#define P2P_NBR(PER)                                                                                            \
+    k_neighbors_fill<PER><<<g_fill, 64 * kNbrWaves, 0, s>>>(t, ws.counters, ws.heavy, ws.totals, cap, nbr_start, \
+                                                            nbr_idx, nbr_shift);                                \
+    P2P_LAUNCH_CHECK();                                                                                         \
+    k_neighbors_heavy<kNbrFill, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                      \
+        t, nullptr, nullptr, ws.counters, ws.heavy, ws.totals, cap, nbr_start, nbr_idx, nbr_shift)
+    if (ws.slot_code) { P2P_NBR(true); } else { P2P_NBR(false); }
+#undef P2P_NBR
+    P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 

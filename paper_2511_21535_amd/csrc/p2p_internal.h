@@ -127,33 +127,30 @@ p2p_status launch_key_directory(const uint64_t *leaf_key, int64_t L, int total_k
                                 int32_t *counters, hipStream_t s);
 // Near lists in two passes.  The counting pass writes per-leaf counts, segment
 // lengths (points of the leaves in the list) and the first 64 entries of each
-// list into slots[L][64]; after the scan of the counts, the fill moves the
-// slots into the CSR and searches again only for the lists longer than 64.
-// Leaves with many candidates are listed in heavy[L] and searched by a whole
-// workgroup each.  With tg set, the lists belong to tg's leaves (counts, segs,
-// slots, heavy, nbr_start sized by tg->L) and the candidates are the leaves of
-// the tree passed as leaf_key/leaf_level/leaf_start/L (remote lists).
+// list into slots[L][64]; after the scan of the counts, the slots move into the
+// CSR and a second search fills the lists longer than 64.  Leaves with many
+// candidates are searched by a whole workgroup each, in both passes.  Nothing
+// is written to nbr_start, nbr_idx and nbr_shift unless the lists fit `cap`
+// entries.  With tg set, the lists belong to tg's leaves (scratch and nbr_start
+// sized by tg->L) and the candidates are the leaves of the tree passed as
+// leaf_key/leaf_level/leaf_start/L (remote lists).
 struct NbrTargets {
     const uint64_t *leaf_key;
     const int8_t *leaf_level;
     int64_t L;
 };
-// A non-null slot_code selects periodic lists (particles on the unit torus):
-// slot_code[L][64] and nbr_shift then receive the image codes.
 constexpr int kNbrSlotsPerLeaf = 64;
-p2p_status launch_neighbors_count(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L,
-                                  int key_bits, int inst_shift, const int32_t *dir, int total_key_bits,
-                                  const int32_t *leaf_start, int32_t *counts, int32_t *segs,
-                                  int32_t *slots, int8_t *slot_code, int32_t *counters, int32_t *heavy,
-                                  hipStream_t s, const NbrTargets *tg = nullptr);
-p2p_status launch_nbr_totals(const int64_t *start, const int64_t *seg_scan, const int32_t *counters,
-                             int64_t L, int64_t *out, hipStream_t s);
-p2p_status launch_neighbors_fill(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L,
-                                 int key_bits, int inst_shift, const int32_t *dir, int total_key_bits,
-                                 const int32_t *counts, const int32_t *slots, const int8_t *slot_code,
-                                 int32_t *counters, const int32_t *heavy, bool any_overflow,
-                                 const int64_t *nbr_start, int32_t *nbr_idx, int8_t *nbr_shift, hipStream_t s,
-                                 const NbrTargets *tg = nullptr);
+struct NbrScratch {
+    int32_t *counts, *segs, *slots;   // [L], [L], [L][64]
+    int8_t *slot_code;                // [L][64], or null; not null selects periodic lists (image codes to nbr_shift)
+    int32_t *counters, *heavy;        // [2] (lists over 64 entries, heavy leaves), [L]
+    int64_t *sums, *totals;           // [neighbor_sum_elems()], [2]: entries, points of all segments
+};
+size_t neighbor_sum_elems();
+p2p_status launch_neighbors(const uint64_t *leaf_key, const int8_t *leaf_level, int64_t L, int key_bits,
+                            int inst_shift, const int32_t *dir, int total_key_bits, const int32_t *leaf_start,
+                            const NbrScratch &ws, int64_t cap, int64_t *nbr_start, int32_t *nbr_idx,
+                            int8_t *nbr_shift, hipStream_t s, const NbrTargets *tg = nullptr);
 
 // Restructure (restructure.hip).
 // Segment lengths of L target leaves over the source leaves of leaf_start.
