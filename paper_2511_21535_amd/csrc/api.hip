@@ -806,10 +806,11 @@ extern "C" p2p_status p2p_eval_gravity_remote(const p2p_tree *tree, const p2p_tr
 namespace {
 
 // Everything a Helmholtz evaluation derives from its arguments on the host:
-// the product (few columns, many columns, FP64), the launch shape, the distinct k h values (one set of G blocks
-// each), and the layout of the set-up buffer.  The set-up buffer (the plan)
-// holds the instances' parameters and the G blocks; it is filled by helm_fill, either on every call (p2p_eval_helmholtz, in the
-// workspace) or once (p2p_helmholtz_prepare, in a caller buffer).
+// the product (few columns, many columns, FP64), the launch shape, the distinct
+// k h values (one set of G blocks each), and the layout of the set-up buffer.  The set-up buffer (the plan)
+// holds the instances' parameters and the G blocks; helm_upload and helm_prep
+// fill it, either on every call (p2p_eval_helmholtz, in the workspace) or once
+// (p2p_helmholtz_prepare, in a caller buffer).
 constexpr int64_t kWideColumns = 24576;
 struct HelmSetup {
     p2p_precision prec;
@@ -946,11 +947,10 @@ HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h) {
     return b;
 }
 
-// Fill the set-up buffer: parameters uploaded (unless they travel inline),
-// the G blocks.  A set-up for several right-hand sides or many instances is
-// refused under capture, as the interface states.
-p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid *grids, hipStream_t s) {
-    double *d_kh = reinterpret_cast<double *>(b.params + h.o_kh);
+// The parameters of the set-up buffer, uploaded unless they travel inline.  A
+// set-up for several right-hand sides or many instances is refused under
+// capture, as the interface states.
+p2p_status helm_upload(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid *grids, hipStream_t s) {
     if (!h.inline_params || h.nrhs > 1)
         P2P_TRY(no_capture(s, "a Helmholtz set-up for several right-hand sides or many instances"));
     if (!h.inline_params) {
@@ -963,8 +963,22 @@ p2p_status helm_fill(const HelmSetup &h, const HelmSetupBufs &b, const p2p_grid 
         // a copy from pageable memory has read its source when it returns
         P2P_HIP(hipMemcpyAsync(b.params, hp.data(), h.param_bytes, hipMemcpyHostToDevice, s));
     }
-    if (h.fp64) return launch_green_blocks64(d_kh, h.inl, h.n_tables, b.blocks, s);
-    return launch_split_blocks(d_kh, h.inl, h.n_tables, h.copies, h.nrhs, b.blocks, s);
+    return P2P_OK;
+}
+
+// The launch before the product: the G blocks if `fill` (else the plan holds
+// them), and q into sorted order unless `sorted` is null.
+p2p_status helm_prep(const HelmSetup &h, const HelmSetupBufs &b, bool fill, const p2p_tree *tree, const void *q,
+                     char *sorted, hipStream_t s) {
+    const double *d_kh = reinterpret_cast<const double *>(b.params + h.o_kh);
+    const int32_t n_tables = fill ? h.n_tables : 0;
+    if (h.fp64) return launch_prep64(d_kh, h.inl, n_tables, b.blocks, q, tree->perm, tree->n, h.nrhs, sorted, s);
+    // many columns: the copy is large enough for a launch of its own with the widest units
+    P2P_TRY(launch_split_prep(d_kh, h.inl, n_tables, h.copies, h.nrhs, b.blocks, q, tree->perm, tree->n,
+                              h.wide ? nullptr : sorted, s));
+    if (!h.wide || !sorted) return P2P_OK;
+    return launch_permute_rows<float2>(static_cast<const float2 *>(q), tree->perm, tree->n, h.nrhs,
+                                       reinterpret_cast<float2 *>(sorted), s);
 }
 
 // Argument checks of an evaluation that come after the workspace query.
@@ -991,25 +1005,18 @@ p2p_status helm_check_call(const HelmSetup &h, const p2p_tree *tree, const p2p_n
     return P2P_OK;
 }
 
-// The evaluation from a filled set-up: the sorted copy of q (GATHER), then one
-// product launch (the work queues' counters are zeroed first; in FP64 few tiles
+// The evaluation: one launch for the G blocks (`fill`, else the set-up is a
+// filled plan) and the sorted copy of q (GATHER), then one product launch (the work queues' counters are zeroed first; in FP64 few tiles
 // add the join of the two halves of each tile).
 p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter, char *sorted, double2 *parts,
-                    const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
+                    bool fill, const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
                     const void *q, void *u, int32_t conj, hipStream_t s) {
     P2P_TRY(helm_check_call(h, tree, nbrs, red, layout, q, u, conj));
     const bool redundant = layout == P2P_REDUNDANT;
     const int64_t n = tree->n;
     const int32_t nrhs = h.nrhs;
     const bool tiled = redundant && red->grain > 1;
-    if (!redundant) {
-        if (h.fp64)
-            P2P_TRY(launch_permute_rows<double2>(static_cast<const double2 *>(q), tree->perm, n, nrhs,
-                                                 reinterpret_cast<double2 *>(sorted), s));
-        else
-            P2P_TRY(launch_permute_rows<float2>(static_cast<const float2 *>(q), tree->perm, n, nrhs,
-                                                reinterpret_cast<float2 *>(sorted), s));
-    }
+    P2P_TRY(helm_prep(h, b, fill, tree, q, redundant ? nullptr : sorted, s));
     const int32_t *d_itab = reinterpret_cast<const int32_t *>(b.params + h.o_itab);
     const float *d_iscale = reinterpret_cast<const float *>(b.params + h.o_isc);
     HelmholtzMfmaArgs a{};
@@ -1043,16 +1050,18 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
 }
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
-// (many columns), the sorted copy of q (GATHER) and, in FP64, the two partial results of tiles whose offsets two workgroups
-// share: at most half as many tiles as the card has CUs, so no more than
-// kMaxSplitTiles on any card, and larger calls hold none.
+// (many columns), the sorted copy of q (GATHER) and the partial results of
+// tiles whose offsets several workgroups share: only while the card has CUs to
+// spare (in FP64 at most half as many tiles as CUs, so no more than
+// kMaxSplitTiles on any card), so larger calls hold none.
 constexpr int32_t kMaxSplitTiles = 256;
 void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, int32_t **counter, char **sorted,
                     double2 **parts) {
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     *counter = h.wide ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
-    *parts = h.fp64 && h.n_tiles <= kMaxSplitTiles ? ar.take<double2>(2 * static_cast<size_t>(n) * h.nrhs) : nullptr;
+    const int32_t share = h.fp64 ? (h.n_tiles <= kMaxSplitTiles ? 2 : 1) : h.wide ? 1 : helm_split_share(h.n_tiles);
+    *parts = share > 1 ? ar.take<double2>(static_cast<size_t>(share) * n * h.nrhs) : nullptr;
 }
 
 p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red,
@@ -1073,8 +1082,8 @@ p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2
     if (ws_query(ws, ws_bytes, ar, &st)) return st;
     // every argument is checked before the set-up is queued
     P2P_TRY(helm_check_call(h, tree, nbrs, red, layout, q, u, conj));
-    P2P_TRY(helm_fill(h, b, grids, s));
-    return helm_run(h, b, counter, sorted, parts, tree, nbrs, red, layout, q, u, conj, s);
+    P2P_TRY(helm_upload(h, b, grids, s));
+    return helm_run(h, b, counter, sorted, parts, true, tree, nbrs, red, layout, q, u, conj, s);
 }
 
 // FNV-1a over the arguments a set-up depends on.
@@ -1142,7 +1151,8 @@ extern "C" p2p_status p2p_helmholtz_prepare(const p2p_tree *tree, const p2p_nbrs
         return fail(P2P_EINVAL, "plan->bytes too small: need " + std::to_string(ar.used) + ", got " +
                                     std::to_string(plan->bytes));
     if ((reinterpret_cast<uintptr_t>(plan->buf) & 255u) != 0) return fail(P2P_EINVAL, "plan->buf must be 256-byte aligned");
-    P2P_TRY(helm_fill(h, b, grids, as_stream(stream)));
+    P2P_TRY(helm_upload(h, b, grids, as_stream(stream)));
+    P2P_TRY(helm_prep(h, b, true, tree, nullptr, nullptr, as_stream(stream)));
     plan->prec = prec;
     plan->nrhs = nrhs;
     plan->tile[0] = h.waves_per_wg;
@@ -1178,7 +1188,7 @@ extern "C" p2p_status p2p_eval_helmholtz_prepared(const p2p_tree *tree, const p2
     helm_take_call(ar, h, tree->n, layout == P2P_REDUNDANT, &counter, &sorted, &parts);
     p2p_status st;
     if (ws_query(ws, ws_bytes, ar, &st)) return st;
-    return helm_run(h, b, counter, sorted, parts, tree, nbrs, red, layout, q, u, 0, as_stream(stream));
+    return helm_run(h, b, counter, sorted, parts, false, tree, nbrs, red, layout, q, u, 0, as_stream(stream));
 }
 
 // ------------------------------------------------------------- adjoint ----

@@ -44,6 +44,24 @@ __device__ inline int near_distance(int o, int s, int i) {
     return dd;
 }
 
+// Rows of nrhs entries into sorted order, sorted[s] = q[perm[s]], by workgroup b
+// of 256 threads: four entries a thread, in flight together.  I holds the entry
+// indices; entries past the end repeat the last (same bytes, same place).
+constexpr int kPermuteEntries = 4 * 256;
+template <class T, class I>
+__device__ inline void permute_entries(const T *__restrict__ q, const int32_t *__restrict__ perm, I entries, I nrhs,
+                                       T *__restrict__ sorted, I b) {
+    const I base = b * kPermuteEntries + threadIdx.x;
+    T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const I e = min(base + 256 * k, entries - 1), row = e / nrhs;
+        v[k] = q[static_cast<uint64_t>(perm[row]) * nrhs + (e - row * nrhs)];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sorted[min(base + 256 * k, entries - 1)] = v[k];
+}
+
 // The column tile of workgroup b: the instance's first leaf, the tile's first
 // column c0 among the instance's columns (column = box * nrhs + right-hand
 // side) and column count cnt, the G table and 1/h of the instance (sc in

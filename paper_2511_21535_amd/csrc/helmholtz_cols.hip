@@ -39,12 +39,22 @@ constexpr int kColPrefQ = 7;
 // G blocks: double2 at [table][offset][source][target % 16][target / 16], the
 // four row tiles of a target column next to each other, so a lane reads the
 // four it needs in one 64-byte run; 64 zero entries follow (the sources of an
-// absent neighbour).  A workgroup forms the 148 values G can take once.
+// absent neighbour).  A workgroup forms the 148 values G can take once.  The
+// workgroups past the first g_wgs (all of them with a prepared plan) copy q
+// into sorted order: one launch for what the product needs beforehand.
 constexpr int kGreenEntries = 1024;
-__global__ __launch_bounds__(256) void k_green_blocks64(const double *__restrict__ kh_dev, HelmInline inl,
-                                                        int32_t n_tables, double2 *__restrict__ out) {
+constexpr int kGreenWgs = 27 * 4096 / kGreenEntries;
+template <class I>
+__global__ __launch_bounds__(256) void k_prep64(const double *__restrict__ kh_dev, HelmInline inl,
+                                                int32_t n_tables, double2 *__restrict__ out, int32_t g_wgs,
+                                                const double2 *__restrict__ q, const int32_t *__restrict__ perm,
+                                                I units, I nrhs, double2 *__restrict__ sorted) {
     __shared__ double2 s_g[kDistances];
-    constexpr int per = 27 * 4096, wgs = per / kGreenEntries;
+    if (static_cast<int32_t>(blockIdx.x) >= g_wgs) {
+        permute_entries(q, perm, units, nrhs, sorted, static_cast<I>(blockIdx.x) - static_cast<I>(g_wgs));
+        return;
+    }
+    constexpr int per = 27 * 4096, wgs = kGreenWgs;
     const int tab = static_cast<int>(blockIdx.x) / wgs, e0 = (static_cast<int>(blockIdx.x) % wgs) * kGreenEntries;
     if (threadIdx.x < kDistances) s_g[threadIdx.x] = green(table_kh(inl, kh_dev, tab), threadIdx.x);
     __syncthreads();
@@ -242,10 +252,20 @@ static void launch_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const H
     }
 }
 
-p2p_status launch_green_blocks64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks,
-                                 hipStream_t s) {
-    const int64_t wgs = static_cast<int64_t>(n_tables) * (27 * 4096 / kGreenEntries);
-    k_green_blocks64<<<static_cast<unsigned>(wgs), 256, 0, s>>>(d_kh, inl, n_tables, static_cast<double2 *>(blocks));
+p2p_status launch_prep64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks, const void *q,
+                         const int32_t *perm, int64_t n, int32_t nrhs, void *sorted, hipStream_t s) {
+    const int64_t g_wgs = static_cast<int64_t>(n_tables) * kGreenWgs;
+    const uint64_t units = sorted ? static_cast<uint64_t>(n) * static_cast<uint64_t>(nrhs) : 0;
+    const int64_t wgs = g_wgs + static_cast<int64_t>((units + kPermuteEntries - 1) / kPermuteEntries);
+    if (wgs == 0) return P2P_OK;
+#define P2P_PREP64(I)                                                                                             \
+    k_prep64<I><<<static_cast<unsigned>(wgs), 256, 0, s>>>(                                                       \
+        d_kh, inl, n_tables, static_cast<double2 *>(blocks), static_cast<int32_t>(g_wgs),                         \
+        static_cast<const double2 *>(q), perm, static_cast<I>(units), static_cast<I>(nrhs),                       \
+        static_cast<double2 *>(sorted))
+    // 32-bit entry indices while they fit (with room for the last workgroup's overshoot)
+    if (units + kPermuteEntries < (uint64_t(1) << 32)) P2P_PREP64(uint32_t); else P2P_PREP64(uint64_t);
+#undef P2P_PREP64
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }

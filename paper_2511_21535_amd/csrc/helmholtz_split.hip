@@ -48,15 +48,24 @@ __device__ inline void split_pair(float a, float b, uint32_t &h, uint32_t &m, ui
 // differ only in which runs and targets their lanes take.  Behind them 63 +
 // nrhs zero entries, the sources of an absent neighbour (64 rows from a
 // column's right-hand side on, stride one).  G depends on the squared distance
-// alone, so a workgroup forms the 148 values it can take once, in double.
+// alone, so a workgroup forms the 148 values it can take once, in double.  The
+// workgroups past the first g_wgs (all of them with a prepared plan) copy q into
+// sorted order: one launch for what a product needs beforehand.
 constexpr int kSplitTable = 27 * 8 * 6 * 64;     // 16-byte operands of a table
-__global__ __launch_bounds__(256) void k_split_blocks(const double *__restrict__ kh_dev, HelmInline inl,
-                                                      int32_t n_tables, int32_t copies, int32_t nrhs,
-                                                      u32x4 *__restrict__ out) {
+constexpr int kSplitTableWgs = 27 * 8 * 64 / 256;
+__global__ __launch_bounds__(256) void k_split_prep(const double *__restrict__ kh_dev, HelmInline inl,
+                                                    int32_t n_tables, int32_t copies, int32_t nrhs,
+                                                    u32x4 *__restrict__ out, int32_t g_wgs,
+                                                    const float2 *__restrict__ q, const int32_t *__restrict__ perm,
+                                                    uint32_t units, float2 *__restrict__ sorted) {
     __shared__ float2 s_g[kDistances];
-    constexpr int wgs = 27 * 8 * 64 / 256;
-    const int tab = static_cast<int>(blockIdx.x) / wgs;
     const int tid = threadIdx.x;
+    if (static_cast<int32_t>(blockIdx.x) >= g_wgs) {
+        permute_entries(q, perm, units, static_cast<uint32_t>(nrhs), sorted, blockIdx.x - static_cast<uint32_t>(g_wgs));
+        return;
+    }
+    constexpr int wgs = kSplitTableWgs;
+    const int tab = static_cast<int>(blockIdx.x) / wgs;
     if (tid < kDistances) {
         const double2 v = green(table_kh(inl, kh_dev, tab), tid);
         s_g[tid] = make_float2(static_cast<float>(v.x), static_cast<float>(v.y));
@@ -85,7 +94,7 @@ __global__ __launch_bounds__(256) void k_split_blocks(const double *__restrict__
     }
     float2 *z = reinterpret_cast<float2 *>(out + static_cast<int64_t>(n_tables) * copies * kSplitTable);
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + tid; k < 63 + static_cast<int64_t>(nrhs);
-         k += static_cast<int64_t>(gridDim.x) * 256)
+         k += static_cast<int64_t>(g_wgs) * 256)
         z[k] = make_float2(0.f, 0.f);
 }
 
@@ -101,24 +110,38 @@ __global__ __launch_bounds__(256) void k_split_blocks(const double *__restrict__
 // instructions but need a third set of G planes, and L2 bounds the kernel as
 // much as the matrix cores do.
 // conj(G) q is formed as conj(G conj(q)).
+// SHARE: where the tiles would leave much of the card idle, `share` workgroups
+// take the offsets of each half tile and store their sums in sorted order, and
+// k_join_split adds them: a wavefront's offset takes 4 us, and one with four of
+// them set the time of a 16^3 grid (product 22 us; with four workgroups 13 us
+// and 4 us of join; the last workgroup adding the sums behind agent-scope fences
+// instead took 21 us).
 constexpr int kSplitWaves = 8;
 constexpr int kSplitCols = kHelmSplitCols;
 
-template <bool RED, bool CONJ, bool COMP, bool ONE>
+template <bool RED, bool CONJ, bool COMP, bool ONE, bool SHARE>
 __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_helm_split_cols(
     int key_bits, HelmTiles ht, HelmInline inl, int32_t nrhs, const int32_t *__restrict__ leaf_start,
     const uint64_t *__restrict__ leaf_key, const int32_t *__restrict__ perm,
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
     const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
-    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, float2 *__restrict__ u) {
+    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, float2 *__restrict__ u,
+    int32_t share, double2 *__restrict__ parts, int64_t entries) {
     using S = typename std::conditional<COMP, double, float>::type;
     __shared__ ColMap<kSplitCols> s_map;
     const ColMapView sm = s_map.view();
-    __shared__ S s_red[kSplitWaves][16][2][64];
+    // one right-hand side: until the sums, two tiles of Q rows in a wavefront's part
+    __shared__ __attribute__((aligned(16))) S s_red[kSplitWaves][16][2][64];
+    static_assert(sizeof(s_red[0]) >= 2 * 32 * 16 * sizeof(float2), "Q tiles do not fit");
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t item = p2pd::xcd_contiguous(blockIdx.x, gridDim.x);
+    int64_t item = p2pd::xcd_contiguous(blockIdx.x, gridDim.x);
+    int part = 0;
+    if constexpr (SHARE) {
+        part = static_cast<int>(item % share);
+        item /= share;
+    }
     const int rt = static_cast<int>(item & 1);
     const ColTile ct = col_tile<kSplitCols>(inl, ht, nrhs, inst_table, inst_scale, nullptr,
                                             static_cast<int32_t>(item >> 1));
@@ -129,49 +152,84 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     // the offsets that occur in this tile, as a bit mask
     const uint32_t present = static_cast<uint32_t>(__ballot(lane < 27 && sm.present[min(lane, 26)] != 0));
     const int n_off = __popc(present);
-    const int n_slots = (n_off - w + kSplitWaves - 1) / kSplitWaves;   // this wave's offsets (n_off >= 1)
-    auto offset_of = [&](int slot) {   // the (w + 8 slot)-th set bit, the last one past the end
+    // this wave's offsets: from the w0-th on every n_waves-th (n_off >= 1)
+    const int n_waves = SHARE ? kSplitWaves * share : kSplitWaves, w0 = SHARE ? kSplitWaves * part + w : w;
+    const int n_slots = n_off > w0 ? (n_off - w0 + n_waves - 1) / n_waves : 0;
+    auto offset_of = [&](int slot) {   // the (w0 + n_waves slot)-th set bit, the last one past the end
         uint32_t m = present;
-        const int k = min(w + kSplitWaves * slot, n_off - 1);
+        const int k = min(w0 + n_waves * slot, n_off - 1);
         for (int i = 0; i < k; ++i) m &= m - 1;
         return __builtin_amdgcn_readfirstlane(__ffs(m) - 1);
     };
     const u32x4 *__restrict__ gtab =
         blocks + static_cast<int64_t>(ct.tab) * copies * kSplitTable + half * 6 * 64 + 32 * rt + col;
-    // this lane's sources at k-step ks: rows 16 ks + 8 half + 0..7 of its column
-    const float2 *qp = nullptr;
+    // Sources at k-step ks: rows 16 ks + 8 half + 0..7 of this lane's column.  With
+    // one right-hand side they are 64 bytes of a box's run, which lanes of
+    // neighbouring columns would read at a stride of 512, a cache-line lookup
+    // for every lane and 16 bytes; instead eight lanes read the 128 bytes of a
+    // k-step of one column (lane / 8 of each of four groups of columns), and
+    // the rows change lanes through LDS, 16-byte pieces of column c in the
+    // order of the exclusive or with c / 2 (no bank conflicts).
+    const float2 *qp[ONE ? 4 : 1];
     int64_t qs = 0;
     const u32x4 *gp = nullptr;
+    float4 *const s_q = reinterpret_cast<float4 *>(&s_red[w][0][0][0]);   // [2][32 columns][8 pieces]
+    const int piece = lane & 7;
     auto open = [&](int slot) {
         const int o = offset_of(slot);
-        const int64_t row = sm.row[o * kSplitCols + cl.box];
         gp = gtab + o * 8 * 6 * 64;
         if constexpr (ONE) {
-            qp = (row >= 0 && col < ct.cnt ? src + row : zeros) + 8 * half;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = 8 * i + (lane >> 3);
+                const int64_t row = sm.row[o * kSplitCols + c];
+                qp[i] = (row >= 0 && c < ct.cnt ? src + row : zeros) + 2 * piece;
+            }
         } else {
+            const int64_t row = sm.row[o * kSplitCols + cl.box];
             qs = row >= 0 ? nrhs : 1;
-            qp = (row >= 0 ? src + row * nrhs : zeros) + 8 * half * qs + cl.rhs;
+            qp[0] = (row >= 0 ? src + row * nrhs : zeros) + 8 * half * qs + cl.rhs;
         }
     };
     auto load_q = [&](int ks, float (&v)[16]) {
         if constexpr (ONE) {
-            const float4 *q4 = reinterpret_cast<const float4 *>(qp + 16 * ks);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float4 x = q4[j];
-                v[4 * j] = x.x;
-                v[4 * j + 1] = x.y;
-                v[4 * j + 2] = x.z;
-                v[4 * j + 3] = x.w;
+            for (int i = 0; i < 4; ++i) {
+                const float4 x = *reinterpret_cast<const float4 *>(qp[i] + 16 * ks);
+                v[4 * i] = x.x;
+                v[4 * i + 1] = x.y;
+                v[4 * i + 2] = x.z;
+                v[4 * i + 3] = x.w;
             }
         } else {
-            const float2 *q = qp + 16 * ks * qs;
+            const float2 *q = qp[0] + 16 * ks * qs;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const float2 x = *q;
                 v[2 * j] = x.x;
                 v[2 * j + 1] = x.y;
                 q += qs;
+            }
+        }
+    };
+    // one right-hand side: the loaded pieces to the lanes of their columns
+    auto swap_q = [&](int buf, float (&v)[16]) {
+        if constexpr (ONE) {
+            float4 *d = s_q + buf * 256;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = 8 * i + (lane >> 3);
+                d[c * 8 + (piece ^ ((c >> 1) & 7))] = make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 x = d[col * 8 + ((4 * half + j) ^ ((col >> 1) & 7))];
+                v[4 * j] = x.x;
+                v[4 * j + 1] = x.y;
+                v[4 * j + 2] = x.z;
+                v[4 * j + 3] = x.w;
             }
         }
     };
@@ -234,7 +292,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             const int r = 2 * w + k;
-            dst[k] = perm[sm.tstart[cl.box] + 32 * rt + 8 * (r / 4) + 4 * half + r % 4];
+            const int32_t row = sm.tstart[cl.box] + 32 * rt + 8 * (r / 4) + 4 * half + r % 4;
+            dst[k] = SHARE ? part * (entries / nrhs) + row : static_cast<int64_t>(perm[row]);
             if constexpr (!ONE) dst[k] = dst[k] * nrhs + cl.rhs;
         }
     }
@@ -247,6 +306,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
             load_g((ks + 1) & 3, g[(ks + 1) & 1]);
             // without the barriers the scheduler sinks the loads to their uses
             __builtin_amdgcn_sched_barrier(0);
+            swap_q(ks & 1, raw[ks & 1]);
             split_q(raw[ks & 1], q);
             mma(g[ks & 1], q, COMP && ks == 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -281,9 +341,29 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
                 ti += s_red[v][r][1][lane];
             }
             if (CONJ) ti = -ti;
-            u[dst[k]] = make_float2(static_cast<float>(tr * ct.sc), static_cast<float>(ti * ct.sc));
+            if constexpr (SHARE)
+                parts[dst[k]] = make_double2(static_cast<double>(tr * ct.sc), static_cast<double>(ti * ct.sc));
+            else
+                u[dst[k]] = make_float2(static_cast<float>(tr * ct.sc), static_cast<float>(ti * ct.sc));
         }
     }
+}
+
+// The sums of the workgroups that share a half tile, in order, to caller order.
+__global__ __launch_bounds__(256) void k_join_split(const double2 *__restrict__ parts, int32_t share,
+                                                    const int32_t *__restrict__ perm, int64_t entries, int32_t nrhs,
+                                                    float2 *__restrict__ u) {
+    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= entries) return;
+    const int64_t row = e / nrhs;
+    const int64_t d = static_cast<int64_t>(perm[row]) * nrhs + (e - row * nrhs);
+    double2 s = parts[e];
+    for (int p = 1; p < share; ++p) {
+        const double2 v = parts[p * entries + e];
+        s.x += v.x;
+        s.y += v.y;
+    }
+    u[d] = make_float2(static_cast<float>(s.x), static_cast<float>(s.y));
 }
 
 // ------------------------------------------------------------ many columns --
@@ -567,28 +647,49 @@ __global__ void k_zero_counter(int32_t *c, int n) {
 
 }  // namespace
 
-p2p_status launch_split_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               int32_t nrhs, void *blocks, hipStream_t s) {
-    const int64_t wgs = static_cast<int64_t>(n_tables) * (27 * 8 * 64 / 256);
-    k_split_blocks<<<static_cast<unsigned>(wgs), 256, 0, s>>>(d_kh, inl, n_tables, copies, nrhs,
-                                                             static_cast<u32x4 *>(blocks));
+p2p_status launch_split_prep(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
+                             int32_t nrhs, void *blocks, const void *q, const int32_t *perm, int64_t n, void *sorted,
+                             hipStream_t s) {
+    const int64_t g_wgs = static_cast<int64_t>(n_tables) * kSplitTableWgs;
+    const uint64_t units = sorted ? static_cast<uint64_t>(n) * static_cast<uint64_t>(nrhs) : 0;
+    if (units > INT32_MAX) return fail(P2P_EINVAL, "too many entries for the product of few columns");
+    const int64_t wgs = g_wgs + static_cast<int64_t>((units + kPermuteEntries - 1) / kPermuteEntries);
+    if (wgs == 0) return P2P_OK;
+    k_split_prep<<<static_cast<unsigned>(wgs), 256, 0, s>>>(
+        d_kh, inl, n_tables, copies, nrhs, static_cast<u32x4 *>(blocks), static_cast<int32_t>(g_wgs),
+        static_cast<const float2 *>(q), perm, static_cast<uint32_t>(units), static_cast<float2 *>(sorted));
     P2P_LAUNCH_CHECK();
     return P2P_OK;
+}
+
+template <bool R, bool C, bool M, bool O>
+static void launch_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                         hipStream_t s) {
+    const int32_t share = helm_split_share(n_tiles);
+    const int64_t entries = a.n * a.nrhs;
+    const unsigned grid = 2u * static_cast<unsigned>(n_tiles) * static_cast<unsigned>(share);
+#define P2P_SPLIT(SH)                                                                                           \
+    k_helm_split_cols<R, C, M, O, SH><<<grid, 64 * kSplitWaves, 0, s>>>(                                        \
+        a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start,     \
+        a.red_row, a.src, reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,           \
+        a.inst_scale, a.u, share, a.parts, entries)
+    if (share > 1) {
+        P2P_SPLIT(true);
+        k_join_split<<<grid_for(entries, 256), 256, 0, s>>>(a.parts, share, a.perm, entries, a.nrhs, a.u);
+    } else {
+        P2P_SPLIT(false);
+    }
+#undef P2P_SPLIT
 }
 
 template <bool R, bool C, bool M>
 static void launch_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
                          hipStream_t s) {
-    const unsigned grid = 2u * static_cast<unsigned>(n_tiles);
-#define P2P_SPLIT(O)                                                                                            \
-    k_helm_split_cols<R, C, M, O><<<grid, 64 * kSplitWaves, 0, s>>>(                                            \
-        a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start,      \
-        a.red_row, a.src, reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,  \
-        a.inst_scale, a.u)
-    // one right-hand side: a lane's eight sources are one 64-byte run, read 16
-    // bytes at a time where the rows are aligned to that
-    if (a.nrhs == 1 && (reinterpret_cast<uintptr_t>(a.src) & 15) == 0) P2P_SPLIT(true); else P2P_SPLIT(false);
-#undef P2P_SPLIT
+    // one right-hand side: a box's rows are read 16 bytes at a time where they are aligned to that
+    if (a.nrhs == 1 && (reinterpret_cast<uintptr_t>(a.src) & 15) == 0)
+        launch_split<R, C, M, true>(a, ht, inl, n_tiles, s);
+    else
+        launch_split<R, C, M, false>(a, ht, inl, n_tiles, s);
 }
 
 p2p_status launch_helmholtz_split_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl,

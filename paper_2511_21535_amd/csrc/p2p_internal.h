@@ -308,7 +308,8 @@ struct HelmholtzMfmaArgs {
     const float2 *zeros;       // an absent neighbour's sources: 64 zero entries (double2) in FP64, else 63 + nrhs
     const double *inst_h;      // per instance: h (FP64 with uploaded parameters)
     int64_t n;                 // points
-    double2 *parts;            // FP64: [2][n][nrhs] partial results in sorted order (tiles split in two)
+    double2 *parts;            // [share][n][nrhs] partial results in sorted order of tiles whose offsets
+                               // several workgroups share (two in FP64, helm_split_share in single precision)
     int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies (many columns)
     const int32_t *inst_table; // per instance: table index
     const float *inst_scale;   // per instance: 1/h
@@ -338,12 +339,20 @@ struct HelmInline {
     double kh[kInlineGrids];                // k h of each table
     double iscale64[kInlineGrids];          // 1/h of each instance in double (FP64 path)
 };
-// G blocks for the k h values of d_kh, or of inl.kh when inl.n_grids > 0, in the
-// layouts above, the zero entries behind them.
-p2p_status launch_green_blocks64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks,
-                                 hipStream_t s);
-p2p_status launch_split_blocks(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
-                               int32_t nrhs, void *blocks, hipStream_t s);
+// What a product needs beforehand, in one launch: the G blocks for the k h values
+// of d_kh, or of inl.kh when inl.n_grids > 0, in the layouts above, the zero
+// entries behind them (n_tables = 0: none, a plan holds them); and, unless
+// sorted is null, q from caller order into sorted order.
+p2p_status launch_prep64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks, const void *q,
+                         const int32_t *perm, int64_t n, int32_t nrhs, void *sorted, hipStream_t s);
+p2p_status launch_split_prep(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
+                             int32_t nrhs, void *blocks, const void *q, const int32_t *perm, int64_t n, void *sorted,
+                             hipStream_t s);
+// Workgroups that share the offsets of a half tile of the product for few
+// columns: as many as leave every CU of the card (256) at most one workgroup, up
+// to 4 (27 offsets over eight wavefronts each).  16^3 grid, 2 tiles: product 22
+// us alone, 13 us shared by four and 4 us of join.
+inline int32_t helm_split_share(int64_t n_tiles) { return 8 * n_tiles <= 256 ? 4 : 4 * n_tiles <= 256 ? 2 : 1; }
 // Products over the tiles of columns of every instance: kHelmColBoxes columns
 // each in FP64, kHelmSplitCols in launch_helmholtz_split_cols and kHelmSplitCols
 // times tiles_per_wg (2 or 4) in launch_helmholtz_split (many columns).

@@ -32,6 +32,14 @@ CASES = [
     ([12, 8, 4], [10, 6, 10], 31),
     ([16], [10], 33),                       # 2112 columns: one workgroup per tile
     ([8] * 5 + [4] * 5, [10, 6] * 5, 5),    # 10 instances: uploaded parameters
+    # single precision: half tiles shared by four workgroups (up to 32 tiles), by
+    # two (up to 64) and not, one right-hand side and several
+    ([16], [10], 1),
+    ([48], [10], 1),
+    ([32], [10], 2),
+    ([32], [10], 3),
+    ([32], [10], 4),
+    ([32], [10], 5),
 ]
 
 # single precision with columns enough for the product that stages G in LDS: 16
@@ -55,13 +63,13 @@ def test_columns_parity(sides, ppw, nrhs, prec):
     cd = np.complex128 if prec == "fp64" else np.complex64
     q = W.grid_rhs(gt.n, nrhs, seed=81).astype(cd)
     gq = torch.as_tensor(q, device=DEV)
-    ref = oracle.helmholtz(sides, q, h=h, kw=kw)
+    ref = oracle.helmholtz(sides, q, h=h, kw=kw).reshape(q.shape)
     got = {"gather": api.helmholtz(gt, gn, gq, prec=prec)}
     for grain in (1, 2):
         red = api.restructure(gt, gn, [gq], prec=prec, nrhs=nrhs, grain=grain)
         got[f"redundant, grain {grain}"] = api.helmholtz(gt, gn, None, layout="redundant", prec=prec, red=red)
     for name, u in got.items():
-        u = u.cpu().numpy()
+        u = u.cpu().numpy().reshape(q.shape)
         err, col = _rel(u, ref), max(_rel(u[:, r], ref[:, r]) for r in range(nrhs))
         print(f"  {name}: {err:.2e} (worst column {col:.2e})", flush=True)
         assert err <= TOL[prec] and col <= TOL[prec]
