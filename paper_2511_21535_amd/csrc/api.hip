@@ -237,9 +237,10 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
         tree->max_level = 0;
         return P2P_OK;
     }
-    P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
+    const bool few = rank_sort_fits(n);   // the sort by counting writes the counts
+    if (!few) P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
     if (particles) {
-        P2P_TRY(launch_particle_keys(x, y, z, n, keys, &tc->bad, s));
+        P2P_TRY(launch_particle_keys(x, y, z, n, keys, few ? nullptr : &tc->bad, s));
     } else {
         std::vector<int32_t> ns(n_grids);
         std::vector<int64_t> off(n_grids);
@@ -257,10 +258,10 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
     // kRunMax share their top bits (a cell of 2^-32 of the domain) set
     // long_run, and the keys take all their passes.
     constexpr int kSortTop = 32;
-    const int lo = sort_bits > kSortTop && !rank_sort_fits(n) ? sort_bits - kSortTop : 0;
+    const int lo = sort_bits > kSortTop && !few ? sort_bits - kSortTop : 0;
     SortBufs sb{keys, keys_tmp, nullptr, vals, vals_tmp};
-    if (rank_sort_fits(n))
-        P2P_TRY(rank_sort_pairs(sb, n, s));
+    if (few)
+        P2P_TRY(rank_sort_pairs(sb, n, tc, s));
     else
         P2P_TRY(radix_sort_pairs(sb, n, lo, sort_bits, hist, s));
     if (lo > 0) P2P_TRY(sort_runs(sb, n, lo, &tc->long_run, s));

@@ -472,19 +472,16 @@ __global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors_count(
     }
 }
 
-// The lists over kNbrSlots entries, one wavefront each (grid-stride).
+// The lists over kNbrSlots entries, one wavefront each, by workgroup b of nb.
 template <bool PER>
-__global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors_fill(
-    NbrTree t, const int32_t *__restrict__ counters, const int32_t *__restrict__ heavy,
-    const int64_t *__restrict__ totals, int64_t cap, const int64_t *__restrict__ nbr_start,
-    int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
+__device__ inline void fill_long_lists(const NbrTree &t, uint32_t b, uint32_t nb, const int32_t *__restrict__ counters,
+                                       const int32_t *__restrict__ heavy, const int64_t *__restrict__ nbr_start,
+                                       int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
     __shared__ int32_t s_w[kNbrWaves][3][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    if (totals[0] > cap) return;
     const int64_t work = counters[0];
-    for (int64_t h = static_cast<int64_t>(blockIdx.x) * kNbrWaves + w; h < work;
-         h += static_cast<int64_t>(gridDim.x) * kNbrWaves) {
+    for (int64_t h = static_cast<int64_t>(b) * kNbrWaves + w; h < work; h += static_cast<int64_t>(nb) * kNbrWaves) {
         const int64_t A = heavy[t.Lt - 1 - h];
         const NbrLeaf f = nbr_leaf(t, A);
         const NbrRanges r = nbr_ranges<PER>(t, f, s_w[w]);
@@ -734,22 +731,103 @@ __global__ __launch_bounds__(kStartBlock) void k_nbr_starts(const int32_t *__res
     }
 }
 
-// Slots into the CSR lists: thread (A, s) moves entry s of a list that fit
+// The same for at most kOneStartMax leaves by one workgroup in one launch: it
+// sums all counts first, then scans them.  16,384 leaves: 16 loads a thread,
+// beside a launch of 5 us.
+constexpr int64_t kOneStartMax = 16384;
+__global__ __launch_bounds__(1024) void k_nbr_starts_one(const int32_t *__restrict__ counts,
+                                                         const int32_t *__restrict__ segs, int64_t L, int64_t cap,
+                                                         int64_t *__restrict__ nbr_start,
+                                                         int64_t *__restrict__ totals) {
+    __shared__ int64_t s_w[2][16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int64_t all = 0, seg = 0;
+#pragma unroll 4
+    for (int64_t i = t; i < L; i += 1024) {
+        all += counts[i];
+        seg += segs[i];
+    }
+    all = wave_sum(all);
+    seg = wave_sum(seg);
+    if (lane == 0) {
+        s_w[0][w] = all;
+        s_w[1][w] = seg;
+    }
+    __syncthreads();
+    all = seg = 0;
+    for (int q = 0; q < 16; ++q) {
+        all += s_w[0][q];
+        seg += s_w[1][q];
+    }
+    if (t == 0) {
+        totals[0] = all;
+        totals[1] = seg;
+    }
+    if (all > cap) return;
+    if (t == 0) nbr_start[L] = all;
+    int64_t before = 0;
+    for (int64_t i0 = 0; i0 < L; i0 += 4096) {
+        const int64_t base = i0 + 4 * t;
+        int32_t v[4];
+        int64_t s = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = base + k < L ? counts[base + k] : 0;
+            s += v[k];
+        }
+        int64_t inc = s;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        __syncthreads();
+        if (lane == 63) s_w[0][w] = inc;
+        __syncthreads();
+        int64_t p = before + inc - s;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) p += s_w[0][q];
+            before += s_w[0][q];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (base + k < L) nbr_start[base + k] = p;
+            p += v[k];
+        }
+    }
+}
+
+// Slots into the CSR lists: thread t = (A, s) moves entry s of a list that fit
 // (and its image code, if slot_code is not null).  A heavy leaf's short list
-// is not in its slots; the fill writes it afterwards.
-__global__ void k_compact_slots(const int32_t *__restrict__ counts, const int32_t *__restrict__ slots,
-                                const int8_t *__restrict__ slot_code, const int64_t *__restrict__ totals,
-                                int64_t cap, const int64_t *__restrict__ nbr_start, int64_t L,
-                                int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+// is not in its slots; k_neighbors_heavy writes it afterwards.
+__device__ inline void compact_slot(int64_t t, const int32_t *__restrict__ counts, const int32_t *__restrict__ slots,
+                                    const int8_t *__restrict__ slot_code, const int64_t *__restrict__ nbr_start,
+                                    int64_t L, int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
     const int64_t A = t / kNbrSlots;
     const int sidx = static_cast<int>(t % kNbrSlots);
-    if (A >= L || totals[0] > cap) return;
+    if (A >= L) return;
     const int32_t c = counts[A];
     if (c <= kNbrSlots && sidx < c) {
         nbr_idx[nbr_start[A] + sidx] = slots[t];
         if (slot_code) nbr_shift[nbr_start[A] + sidx] = slot_code[t];
     }
+}
+
+// After the starts: the first g_slots workgroups move the slots, the others
+// search again for the lists over kNbrSlots entries.
+template <bool PER>
+__global__ __launch_bounds__(64 * kNbrWaves) void k_neighbors_finish(
+    NbrTree t, const int32_t *__restrict__ counts, const int32_t *__restrict__ slots,
+    const int8_t *__restrict__ slot_code, const int32_t *__restrict__ counters, const int32_t *__restrict__ heavy,
+    const int64_t *__restrict__ totals, int64_t cap, const int64_t *__restrict__ nbr_start, uint32_t g_slots,
+    int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
+    if (totals[0] > cap) return;
+    if (blockIdx.x < g_slots)
+        compact_slot(static_cast<int64_t>(blockIdx.x) * (64 * kNbrWaves) + threadIdx.x, counts, slots, slot_code,
+                     nbr_start, t.Lt, nbr_idx, nbr_shift);
+    else
+        fill_long_lists<PER>(t, blockIdx.x - g_slots, gridDim.x - g_slots, counters, heavy, nbr_start, nbr_idx,
+                             nbr_shift);
 }
 
 }  // namespace
@@ -792,36 +870,46 @@ p2p_status launch_neighbors(const uint64_t *leaf_key, const int8_t *leaf_level, 
                             const NbrScratch &ws, int64_t cap, int64_t *nbr_start, int32_t *nbr_idx,
                             int8_t *nbr_shift, hipStream_t s, const NbrTargets *tg) {
     const NbrTree t = make_tree(leaf_key, leaf_level, leaf_start, L, key_bits, inst_shift, dir, total_key_bits, tg);
-    const int64_t tiles = t.Lt > 0 ? (t.Lt + kStartTile - 1) / kStartTile : 1;
-    const int64_t span = (tiles + kStartGrid - 1) / kStartGrid * kStartTile;
-    const unsigned g_start = grid_for(t.Lt, static_cast<int>(span));
-    const unsigned g_leaf = grid_for(t.Lt, kNbrWaves), g_fill = g_leaf < kFillGrid ? g_leaf : kFillGrid;
-    const unsigned g_heavy = t.Lt < kHeavyGrid ? static_cast<unsigned>(t.Lt) : kHeavyGrid;
+    const unsigned g_leaf = grid_for(t.Lt, kNbrWaves);
+    // A list, and what is searched for it, holds no leaf twice in one image: few
+    // source leaves leave no leaf heavy, and fewer no list over its slots
+    const int64_t most = t.L * (ws.slot_code ? 27 : 1);
+    const unsigned g_fill = most <= kNbrSlots ? 0 : g_leaf < kFillGrid ? g_leaf : kFillGrid;
+    const unsigned g_heavy =
+        most <= kHeavyCands ? 0 : t.Lt < kHeavyGrid ? static_cast<unsigned>(t.Lt) : kHeavyGrid;
 #define P2P_NBR(PER)                                                                                              \
     k_neighbors_count<PER><<<g_leaf, 64 * kNbrWaves, 0, s>>>(t, ws.counts, ws.segs, ws.slots, ws.slot_code,      \
                                                              ws.counters, ws.heavy);                             \
     P2P_LAUNCH_CHECK();                                                                                           \
-    k_neighbors_heavy<kNbrCount, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                       \
-        t, ws.counts, ws.segs, ws.counters, ws.heavy, nullptr, 0, nullptr, nullptr, nullptr)
+    if (g_heavy > 0)                                                                                              \
+        k_neighbors_heavy<kNbrCount, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                   \
+            t, ws.counts, ws.segs, ws.counters, ws.heavy, nullptr, 0, nullptr, nullptr, nullptr)
     if (t.Lt > 0) {
         if (ws.slot_code) { P2P_NBR(true); } else { P2P_NBR(false); }
         P2P_LAUNCH_CHECK();
     }
 #undef P2P_NBR
-    k_nbr_sums<<<g_start, kStartBlock, 0, s>>>(ws.counts, ws.segs, t.Lt, span, ws.sums);
-    P2P_LAUNCH_CHECK();
-    k_nbr_starts<<<g_start, kStartBlock, 0, s>>>(ws.counts, t.Lt, span, ws.sums, cap, nbr_start, ws.totals);
+    if (t.Lt <= kOneStartMax) {
+        k_nbr_starts_one<<<1, 1024, 0, s>>>(ws.counts, ws.segs, t.Lt, cap, nbr_start, ws.totals);
+    } else {
+        const int64_t tiles = (t.Lt + kStartTile - 1) / kStartTile;
+        const int64_t span = (tiles + kStartGrid - 1) / kStartGrid * kStartTile;
+        const unsigned g = grid_for(t.Lt, static_cast<int>(span));
+        k_nbr_sums<<<g, kStartBlock, 0, s>>>(ws.counts, ws.segs, t.Lt, span, ws.sums);
+        P2P_LAUNCH_CHECK();
+        k_nbr_starts<<<g, kStartBlock, 0, s>>>(ws.counts, t.Lt, span, ws.sums, cap, nbr_start, ws.totals);
+    }
     P2P_LAUNCH_CHECK();
     if (t.Lt <= 0) return P2P_OK;
-    k_compact_slots<<<grid_for(t.Lt * kNbrSlots, 256), 256, 0, s>>>(ws.counts, ws.slots, ws.slot_code, ws.totals, cap,
-                                                                    nbr_start, t.Lt, nbr_idx, nbr_shift);
-    P2P_LAUNCH_CHECK();
+    const unsigned g_slots = grid_for(t.Lt * kNbrSlots, 64 * kNbrWaves);
 #define P2P_NBR(PER)                                                                                            \
-    k_neighbors_fill<PER><<<g_fill, 64 * kNbrWaves, 0, s>>>(t, ws.counters, ws.heavy, ws.totals, cap, nbr_start, \
-                                                            nbr_idx, nbr_shift);                                \
+    k_neighbors_finish<PER><<<g_slots + g_fill, 64 * kNbrWaves, 0, s>>>(                                        \
+        t, ws.counts, ws.slots, ws.slot_code, ws.counters, ws.heavy, ws.totals, cap, nbr_start, g_slots,        \
+        nbr_idx, nbr_shift);                                                                                    \
     P2P_LAUNCH_CHECK();                                                                                         \
-    k_neighbors_heavy<kNbrFill, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                      \
-        t, nullptr, nullptr, ws.counters, ws.heavy, ws.totals, cap, nbr_start, nbr_idx, nbr_shift)
+    if (g_heavy > 0)                                                                                            \
+        k_neighbors_heavy<kNbrFill, PER><<<g_heavy, 64 * kHeavyWaves, 0, s>>>(                                  \
+            t, nullptr, nullptr, ws.counters, ws.heavy, ws.totals, cap, nbr_start, nbr_idx, nbr_shift)
     if (ws.slot_code) { P2P_NBR(true); } else { P2P_NBR(false); }
 #undef P2P_NBR
     P2P_LAUNCH_CHECK();

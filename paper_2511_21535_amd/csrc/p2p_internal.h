@@ -69,6 +69,12 @@ size_t scan_ws_elems(int64_t n);
 template <class TI, class TO>
 p2p_status exclusive_scan(const TI *in, TO *out, int64_t n, TO *scratch, hipStream_t s);
 
+// What the tree steps find, cleared before them; max_level and n_leaves are
+// written by launch_leaf_write.
+struct TreeCounts {
+    int32_t bad, long_run, max_level, n_leaves;
+};
+
 // Pairs to be sorted: keys/vals hold them, tmp buffers of the same sizes take
 // the passes in turn (vals == nullptr at first: the values are 0..n-1, and
 // vals_tmp, vals_alt the two value buffers).
@@ -85,9 +91,12 @@ struct SortBufs {
 // Sorts by the key bits [lo, hi), stably.  Scratch: radix_hist_elems(n).
 p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s);
 size_t radix_hist_elems(int64_t n);
-// The same by whole keys, one launch, for as many pairs as fit.
+// The same by whole keys, one launch, for as many pairs as fit; it also writes
+// the tree's counts: bad if a key is kBadKey (no key of a point has its top bit
+// set), the others zero.
+constexpr uint64_t kBadKey = ~0ull;
 bool rank_sort_fits(int64_t n);
-p2p_status rank_sort_pairs(SortBufs &b, int64_t n, hipStream_t s);
+p2p_status rank_sort_pairs(SortBufs &b, int64_t n, TreeCounts *tc, hipStream_t s);
 // After a sort by the bits from lo up: runs of at most kRunMax equal upper
 // parts into the order of the whole key; a longer run is left and sets
 // *long_run.
@@ -99,11 +108,6 @@ p2p_status launch_particle_keys(const double *x, const double *y, const double *
                                 uint64_t *keys, int32_t *bad_flag, hipStream_t s);
 p2p_status launch_grid_keys(const int32_t *d_n_side, const int64_t *d_point_off, int32_t n_grids,
                             int bits, int64_t n, uint64_t *keys, hipStream_t s);
-// What the tree steps find, cleared before them; max_level and n_leaves are
-// written by launch_leaf_write.
-struct TreeCounts {
-    int32_t bad, long_run, max_level, n_leaves;
-};
 // Leaf level of every slot, kLeafFirst added where a leaf starts.  For each
 // kMarkBlock slots, leaf_counts receives the leaves that start in them and,
 // from kDeepShift up, their deepest level (one more entry for the total).

@@ -370,12 +370,18 @@ constexpr int64_t kRankSortMax = 8192;
 __global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__restrict__ kin,
                                                             const int32_t *__restrict__ vin,
                                                             uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
-                                                            int n) {
+                                                            int n, TreeCounts *__restrict__ tc) {
     __shared__ uint64_t s_key[kRankSortMax];
     __shared__ int s_cnt[kSortWaves][kRankKeys];
     const int tid = threadIdx.x, q = tid & (kRankKeys - 1), seg = tid / kRankKeys;
-    for (int j = tid; j < n; j += kSortThreads) s_key[j] = kin[j];
-    __syncthreads();
+    int bad = 0;
+    for (int j = tid; j < n; j += kSortThreads) {
+        const uint64_t k = kin[j];
+        bad |= k == kBadKey ? 1 : 0;
+        s_key[j] = k;
+    }
+    bad = __syncthreads_or(bad);
+    if (blockIdx.x == 0 && tid == 0) *tc = TreeCounts{bad != 0 ? 1 : 0, 0, 0, 0};
     const int i = blockIdx.x * kRankKeys + q;
     const uint64_t key = i < n ? s_key[i] : 0ull;
     int cnt = 0;
@@ -480,11 +486,11 @@ p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hi
 
 bool rank_sort_fits(int64_t n) { return n <= kRankSortMax; }
 
-p2p_status rank_sort_pairs(SortBufs &b, int64_t n, hipStream_t s) {
+p2p_status rank_sort_pairs(SortBufs &b, int64_t n, TreeCounts *tc, hipStream_t s) {
     if (n <= 0) return P2P_OK;
     if (!rank_sort_fits(n)) return fail(P2P_EINVAL, "rank sort: too many keys");
     k_rank_sort<<<grid_for(n, kRankKeys), kSortThreads, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp,
-                                                               static_cast<int>(n));
+                                                               static_cast<int>(n), tc);
     P2P_LAUNCH_CHECK();
     b.swap();
     return P2P_OK;

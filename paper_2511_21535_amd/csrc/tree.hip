@@ -31,8 +31,10 @@ __global__ void k_particle_keys(const double *__restrict__ x, const double *__re
         // x * 2^20 is exact; truncation of a non-negative value is floor
         c[d] = ok ? static_cast<uint32_t>(p[d] * 1048576.0) : 0u;
     }
-    if (!ok) atomicOr(bad, 1);
-    keys[i] = p2pd::morton3(c[0], c[1], c[2]);
+    // a point outside the domain: marked in its key for the sort by counting
+    // (bad == null), else in the counts
+    if (!ok && bad) atomicOr(bad, 1);
+    keys[i] = ok || bad ? p2pd::morton3(c[0], c[1], c[2]) : kBadKey;
 }
 
 __global__ void k_grid_keys(const int32_t *__restrict__ n_side, const int64_t *__restrict__ off,

@@ -70,7 +70,9 @@ def test_particles(name, periodic):
     assert nb.red_entries == int(occ[idx].sum())
 
 
-@pytest.mark.parametrize("sides", [[4], [4] * 9, [4, 8, 4, 12], [8] * 3, [16, 4]])
+# 512 boxes and 513: no leaf has more candidates than one wavefront takes, or may
+# have; 16,354 and 16,625: starts by one workgroup, or by many
+@pytest.mark.parametrize("sides", [[4], [4] * 9, [4, 8, 4, 12], [8] * 3, [16, 4], [16], [32], [32, 4], [100, 36], [100, 40]])
 def test_grids(sides):
     grids = [api.Grid(s, *W.grid_geometry(s)) for s in sides]
     print(f"case near lists grids {sides}", flush=True)
