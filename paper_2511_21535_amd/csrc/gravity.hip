@@ -8,8 +8,8 @@
 // partial sums of a target are reduced through LDS at the end.  Sources are staged
 // through LDS in tiles of 512:
 //   - redundant: one contiguous segment, read with coalesced loads;
-//   - gather: the near list is walked in chunks; every two successive staged
-//     rows are located by one search over the prefix of neighbour occupancies.
+//   - gather: the near list is walked in chunks; each staged row is located
+//     by a binary search over the prefix of neighbour occupancies.
 // Results are written straight to caller order through perm (the update
 // step).  No atomics: each output has one owner.
 //
@@ -58,8 +58,8 @@ constexpr int kGNbrChunk = 256;
 constexpr int kGFlush = 32;
 
 // Block-wide: loads one chunk of the near list of A into LDS (first sorted
-// slot of each neighbour, exclusive prefix of their occupancies -- the total
-// from nc on -- and, with PER, the images' shifts, two bits an axis).
+// slot of each neighbour, exclusive prefix of their occupancies and, with
+// PER, the image codes).
 // *s_self: the first chunk row of the entry (A, unshifted), the target leaf's
 // own rows, or -1 when the chunk does not hold it.
 template <bool PER>
@@ -78,7 +78,7 @@ __device__ int64_t g_load_nbr_chunk(const int32_t *__restrict__ leaf_start,
         int code = 13;
         if constexpr (PER) {
             code = nbr_shift[c0 + threadIdx.x];
-            s_code[threadIdx.x] = static_cast<int8_t>((code % 3) | (code / 3 % 3) << 2 | (code / 9) << 4);
+            s_code[threadIdx.x] = static_cast<int8_t>(code);
         }
         self = B == A && code == 13;
     }
@@ -105,14 +105,13 @@ __device__ int64_t g_load_nbr_chunk(const int32_t *__restrict__ leaf_start,
     return tot;
 }
 
-// The neighbour that holds chunk row p (< the total): the last with a prefix
-// of at most p.  top: the largest power of two below nc, or 0.  The trip count
-// is the same in every lane and no bound is tested (the prefixes from nc on are
-// the total).
-__device__ inline int g_find_nbr(const int64_t *s_pre, int top, int64_t p) {
-    int b = 0;
-    for (int step = top; step > 0; step >>= 1) b += s_pre[b + step] <= p ? step : 0;
-    return b;
+__device__ inline int g_find_nbr(const int64_t *s_pre, int nc, int64_t p) {
+    int lo = 0, hi = nc - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s_pre[mid] <= p) lo = mid; else hi = mid - 1;
+    }
+    return lo;
 }
 
 // Tile position given to `body` when the tile holds none of the target
@@ -120,8 +119,8 @@ __device__ inline int g_find_nbr(const int64_t *s_pre, int top, int64_t p) {
 constexpr int64_t kNoSelf = -(int64_t(1) << 40);
 
 // Walks the sources of leaf A tile by tile: after a barrier, `begin(n_tile)`,
-// then `stage(i, src_row, shift)` for the tile's sources i (shift: two bits an
-// axis, of use with PER only), a barrier, and `body(n_tile, self)`, where tile position
+// then `stage(i, src_row, image_code)` for the tile's sources i (code 13
+// unless PER), a barrier, and `body(n_tile, self)`, where tile position
 // self + r holds row r of A's own rows (the unshifted entry A of its list;
 // kNoSelf where no tile position does; the redundant layout takes it from
 // red_self, or none if red_self is null).  Must be called by the whole block.
@@ -141,7 +140,7 @@ __device__ void for_each_source_tile(int64_t A, const int64_t *__restrict__ red_
             const int nt = static_cast<int>(min<int64_t>(kGTile, ns - s0));
             __syncthreads();
             begin(nt);
-            for (int i = threadIdx.x; i < nt; i += kGBlock) stage(i, seg0 + s0 + i, 0);
+            for (int i = threadIdx.x; i < nt; i += kGBlock) stage(i, seg0 + s0 + i, 13);
             __syncthreads();
             body(nt, self >= 0 ? self - s0 : kNoSelf);
         }
@@ -153,23 +152,14 @@ __device__ void for_each_source_tile(int64_t A, const int64_t *__restrict__ red_
             const int64_t rows = g_load_nbr_chunk<PER>(leaf_start, nbr_idx, nbr_shift, A, c0, nc, s_pre, s_first,
                                                        s_code, s_w, s_self);
             const int64_t self = *s_self;
-            const int top = nc > 1 ? 1 << (31 - __builtin_clz(nc - 1)) : 0;
             for (int64_t s0 = 0; s0 < rows; s0 += kGTile) {
                 const int nt = static_cast<int>(min<int64_t>(kGTile, rows - s0));
                 __syncthreads();
                 begin(nt);
-                // two successive rows a thread: leaves are not empty, so the
-                // second is its neighbour's or the next one's
-                static_assert(kGTile == 2 * kGBlock, "two rows a thread");
-                const int i = 2 * static_cast<int>(threadIdx.x);
-                if (i < nt) {
+                for (int i = threadIdx.x; i < nt; i += kGBlock) {
                     const int64_t p = s0 + i;
-                    const int b = g_find_nbr(s_pre, top, p);
-                    stage(i, s_first[b] + (p - s_pre[b]), PER ? static_cast<int>(s_code[b]) : 0);
-                    if (i + 1 < nt) {
-                        const int b1 = b + (s_pre[b + 1] <= p + 1 ? 1 : 0);
-                        stage(i + 1, s_first[b1] + (p + 1 - s_pre[b1]), PER ? static_cast<int>(s_code[b1]) : 0);
-                    }
+                    const int b = g_find_nbr(s_pre, nc, p);
+                    stage(i, s_first[b] + (p - s_pre[b]), PER ? static_cast<int>(s_code[b]) : 13);
                 }
                 __syncthreads();
                 body(nt, self >= 0 ? self - s0 : kNoSelf);
@@ -178,12 +168,11 @@ __device__ void for_each_source_tile(int64_t A, const int64_t *__restrict__ red_
     }
 }
 
-// Source row of an image, placed at x + s in double; s + 1 is held in two bits
-// an axis.
+// Source row of an entry with image code c, placed at x + s in double.
 __device__ inline Row4d shifted(Row4d v, int c) {
-    v.x += static_cast<double>((c & 3) - 1);
-    v.y += static_cast<double>((c >> 2 & 3) - 1);
-    v.z += static_cast<double>((c >> 4) - 1);
+    v.x += static_cast<double>(c % 3 - 1);
+    v.y += static_cast<double>((c / 3) % 3 - 1);
+    v.z += static_cast<double>(c / 9 - 1);
     return v;
 }
 
@@ -199,38 +188,6 @@ __device__ inline void lane_split(int tc, int &G, int &t, int &g) {
     G = static_cast<int>((static_cast<float>(kGBlock) + 0.5f) * rtc);
     g = static_cast<int>((static_cast<float>(threadIdx.x) + 0.5f) * rtc);
     t = static_cast<int>(threadIdx.x) - g * tc;
-}
-
-// Per-target sums of the G partials that lane (t, g) left at s_red[c][g tc + t]
-// for component c, for 4 tc <= 256 and called by the whole block after a
-// barrier: lane (t, c) with c = tid / tc < 4 returns the sum of component c of
-// target t (it holds target t's row already).  Two steps, as a leaf of few
-// targets has many partials (256 / tc of them): the 256 / (4 tc) lanes of one
-// sum take about four partials each, then one lane adds theirs.  Up to kTwoStep
-// partials the two barriers cost more than one lane's sum: with two steps for
-// every leaf the redundant FP32-mixed pass of 2^21 points took 704 us, else 665
-// us; the periodic gather of 700,001 points 327 and 315 us (330 with no second
-// step at all and a search for each staged row).
-constexpr int kTwoStep = 16;
-__device__ inline double sum_partials(double (*s_red)[kGBlock], int tc, int G) {
-    int H, u, h;
-    lane_split(4 * tc, H, u, h);   // sum u = c tc + t, its h-th of H lanes
-    const float rtc = __builtin_amdgcn_rcpf(static_cast<float>(tc));
-    const int c = static_cast<int>((static_cast<float>(u) + 0.5f) * rtc), t = u - c * tc;
-    double s = 0.0;
-    if (h < H) {
-#pragma unroll 4
-        for (int q = h; q < G; q += H) s += s_red[c][q * tc + t];
-    }
-    __syncthreads();
-    double *part = &s_red[0][0];
-    part[threadIdx.x] = s;   // position u + 4 tc h
-    __syncthreads();
-    if (static_cast<int>(threadIdx.x) < 4 * tc) {
-#pragma unroll 4
-        for (int q = 1; q < H; ++q) s += part[threadIdx.x + 4 * tc * q];
-    }
-    return s;
 }
 
 // Centre of a particle leaf (exact in double: integers below 2^21 times 2^-20).
@@ -415,6 +372,11 @@ __device__ __forceinline__ void gravity_body(const GravityArgs &a) {
                                        a.nbr_shift, a.src_leaf_start, s_pre, s_first, s_code, s_w, &s_self,
                                        begin, stage, body);
 
+        // Per-target sums of the G partials, in the order q = 0..G-1.  Lanes
+        // with g >= G never accumulate and are never read.  When 4 tc <= 256,
+        // lane (t, g) with g < 4 sums component g of target t (it already
+        // holds target t's row), so the four sums of a target run in four
+        // lanes; otherwise lane t sums all four.
         __syncthreads();
         s_red[0][threadIdx.x] = p;
         s_red[1][threadIdx.x] = fx;
@@ -429,23 +391,18 @@ __device__ __forceinline__ void gravity_body(const GravityArgs &a) {
                 return tv.w * rsqrt(eps2);
         };
         if (4 * tc <= kGBlock) {
-            double s = 0.0;
-            if (G > kTwoStep) {
-                s = sum_partials(s_red, tc, G);
-            } else if (g < 4) {
-                for (int q = 0; q < G; ++q) s += s_red[g][q * tc + t];
-            }
             if (g < 4) {
+                double s = 0.0;
+                for (int q = 0; q < G; ++q) s += s_red[g][q * tc + t];
+                if constexpr (MIXED && !EPS0 && !REMOTE) {
+                    if (g == 0) s += self_phi();
+                }
                 double *out = g == 0 ? a.phi : g == 1 ? a.ax : g == 2 ? a.ay : a.az;
                 const int64_t i = a.perm[t0 + tc0 + t];
-                double v = s;
-                if constexpr (MIXED && !EPS0 && !REMOTE) {
-                    if (g == 0) v += self_phi();
-                }
                 if constexpr (REMOTE)
-                    out[i] += v;
+                    out[i] += s;
                 else
-                    out[i] = v;
+                    out[i] = s;
             }
         } else if (static_cast<int>(threadIdx.x) < tc) {
             double sp_ = 0.0, sx_ = 0.0, sy_ = 0.0, sz_ = 0.0;
@@ -516,7 +473,10 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(6))) vo
 // bytes a pair, has room for four by its LDS.  Its lane group g takes a run of
 // each tile, unrolled by two, and the pair's factor is collected by powers of
 // w: 2^18 clustered points 397 to 340 us against every G-th source and a factor
-// of 44 instructions.
+// of 44 instructions.  Two targets a lane, which halve the LDS reads, take 162
+// registers: 376 us.  The partial sums are added by a lane per target and
+// component, as in the forward kernels (leaf cap 16, 2^18 points, FP64 407 to
+// 311 us, FP32-mixed 501 to 252 us against a lane per target).
 template <bool PER, bool MIXED>
 __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
     GravityAdjointArgs a) {
@@ -666,13 +626,9 @@ __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
             return 0.0;
         };
         if (4 * tc <= kGBlock) {
-            double r = 0.0;
-            if (G > kTwoStep) {
-                r = sum_partials(s_red, tc, G);
-            } else if (g < 4) {
-                for (int q = 0; q < G; ++q) r += s_red[g][q * tc + t];
-            }
             if (g < 4) {
+                double r = 0.0;
+                for (int q = 0; q < G; ++q) r += s_red[g][q * tc + t];
                 double *out = g == 0 ? a.gm : g == 1 ? a.gx : g == 2 ? a.gy : a.gz;
                 out[a.perm[tr]] = g == 0 ? r + self_gm() : r;
             }
