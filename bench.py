@@ -1006,10 +1006,11 @@ def run_adjoint_helmholtz(wname, args):
     line["ms"] = {"forward": t_fwd / K * 1e3, "adjoint": t_adj / K * 1e3, "adjoint_fp32": t_adj32 / K * 1e3}
     line["rates"] = {"forward_plus_adjoint": value, "adjoint": pairs * K / t_adj, "adjoint_fp32": pairs * K / t_adj32}
     # both adjoints (A^T g = A g, A symmetric: the forward product on g) on the
-    # matrix cores with the target boxes as the columns, the complex multiply-add
-    # of a pair as three real products (6 flop executed; the 8-flop equivalent of
-    # the four-product form beside it): FP64 on the FP64 matrix instructions, FP32
-    # on the FP32 ones (a tile's offsets shared by two workgroups on this grid)
+    # matrix cores with the target boxes as the columns: FP64 on the FP64 matrix
+    # instructions, the complex multiply-add of a pair as three real products (6
+    # flop executed; the 8-flop equivalent of the four-product form beside it),
+    # FP32 on the BF16 ones by the three-way split (48 flop executed); a tile's
+    # offsets are shared by two workgroups on this grid
     a64 = 6.0 * pairs / (t_adj / K) / 1e12
     a32 = SPLIT_FLOP_PER_PAIR * pairs / (t_adj32 / K) / 1e12
     per_pair = ("6 flop per pair: the complex multiply-add as three real products "

@@ -1052,16 +1052,15 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
 // (many columns), the sorted copy of q (GATHER) and the partial results of
-// tiles whose offsets several workgroups share: only while the card has CUs to
-// spare (in FP64 at most half as many tiles as CUs, so no more than
-// kMaxSplitTiles on any card), so larger calls hold none.
-constexpr int32_t kMaxSplitTiles = 256;
+// tiles whose offsets several workgroups share: only while a card may have CUs
+// to spare (in FP64 two workgroups for up to kMaxSplitTiles tiles, more where
+// 256 CUs take them), so larger calls hold none.
 void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, int32_t **counter, char **sorted,
                     double2 **parts) {
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     *counter = h.wide ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
-    const int32_t share = h.fp64 ? (h.n_tiles <= kMaxSplitTiles ? 2 : 1) : h.wide ? 1 : helm_split_share(h.n_tiles);
+    const int32_t share = h.fp64 ? helm_cols64_share(h.n_tiles, 2 * kMaxSplitTiles) : h.wide ? 1 : helm_split_share(h.n_tiles);
     *parts = share > 1 ? ar.take<double2>(static_cast<size_t>(share) * n * h.nrhs) : nullptr;
 }
 

@@ -68,13 +68,15 @@ __global__ __launch_bounds__(256) void k_prep64(const double *__restrict__ kh_de
         out[static_cast<int64_t>(n_tables) * per + threadIdx.x] = make_double2(0.0, 0.0);
 }
 
-// A tile's 27 offsets may be shared by H workgroups (H = 2 on grids with at
-// most half as many tiles as CUs, so that twice the CUs work): wave w of part
-// p takes offsets o = 4 p + w + 4 H idx, the slots past the 27 offsets reading zero
-// rows.  With H = 2 each part stores its
+// A tile's 27 offsets may be shared by H = 2, 4 or 7 workgroups (as many as the
+// card has CUs for; a wavefront then takes four, two or one of them instead of
+// seven): wave w of part p takes offsets o = 4 p + w + 4 H idx, the slots past
+// the 27 offsets reading zero rows.  With H > 1 each part stores its
 // result in sorted order to parts[p][.] (coalesced), and k_join_parts adds
-// part 0 and part 1 and scatters the sum to the caller's order (FP64 atomic
-// additions at the scattered caller rows took 7 us more on a 48^3 grid).
+// the parts in order and scatters the sum to the caller's order (FP64 atomic
+// additions at the scattered caller rows took 7 us more on a 48^3 grid).  A
+// prepared call on a 32^3 grid, one right-hand side: 40 us with two workgroups
+// a tile, 26 us with seven.
 template <bool RED, bool CONJ, bool ONE, int H>
 __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     int key_bits, HelmTiles ht, HelmInline inl, int32_t nrhs, const int32_t *__restrict__ leaf_start,
@@ -214,12 +216,16 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
 
 // u[perm[s]][r] = parts[0][s][r] + parts[1][s][r] for every sorted row s and
 // right-hand side r (m = rows times right-hand sides).
-__global__ void k_join_parts(const double2 *__restrict__ parts, const int32_t *__restrict__ perm, int64_t m,
-                             int32_t nrhs, double2 *__restrict__ u) {
+__global__ void k_join_parts(const double2 *__restrict__ parts, int32_t share, const int32_t *__restrict__ perm,
+                             int64_t m, int32_t nrhs, double2 *__restrict__ u) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i >= m) return;
-    const double2 a = parts[i], b = parts[m + i];
-    const double2 v = make_double2(a.x + b.x, a.y + b.y);
+    double2 v = parts[i];
+    for (int p = 1; p < share; ++p) {
+        const double2 b = parts[p * m + i];
+        v.x += b.x;
+        v.y += b.y;
+    }
     if (nrhs == 1) {
         u[perm[i]] = v;
     } else {
@@ -240,16 +246,20 @@ static void launch_cols64(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const
         a.n * a.nrhs);
 }
 
+template <bool R, bool C, bool O>
+static void launch_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
+                        int32_t share, hipStream_t s) {
+    if (share == 7) launch_cols64<R, C, O, 7>(a, ht, inl, n_tiles, s);
+    else if (share == 4) launch_cols64<R, C, O, 4>(a, ht, inl, n_tiles, s);
+    else if (share == 2) launch_cols64<R, C, O, 2>(a, ht, inl, n_tiles, s);
+    else launch_cols64<R, C, O, 1>(a, ht, inl, n_tiles, s);
+}
+
 template <bool R, bool C>
 static void launch_cols(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
-                        bool split, hipStream_t s) {
-    if (a.nrhs == 1) {
-        if (split) launch_cols64<R, C, true, 2>(a, ht, inl, n_tiles, s);
-        else launch_cols64<R, C, true, 1>(a, ht, inl, n_tiles, s);
-    } else {
-        if (split) launch_cols64<R, C, false, 2>(a, ht, inl, n_tiles, s);
-        else launch_cols64<R, C, false, 1>(a, ht, inl, n_tiles, s);
-    }
+                        int32_t share, hipStream_t s) {
+    if (a.nrhs == 1) launch_cols<R, C, true>(a, ht, inl, n_tiles, share, s);
+    else launch_cols<R, C, false>(a, ht, inl, n_tiles, share, s);
 }
 
 p2p_status launch_prep64(const double *d_kh, const HelmInline &inl, int32_t n_tables, void *blocks, const void *q,
@@ -276,17 +286,17 @@ p2p_status launch_helmholtz_cols64(const HelmholtzMfmaArgs &a, const HelmTiles &
     int dev = 0, cus = 0;
     P2P_HIP(hipGetDevice(&dev));
     P2P_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // two workgroups per tile while that still fits on the card's CUs
-    const bool split = 2 * static_cast<int64_t>(n_tiles) <= cus && a.parts;
+    // as many workgroups per tile as still fit on the card's CUs
+    const int32_t share = a.parts ? helm_cols64_share(n_tiles, cus) : 1;
     const bool cj = a.conj != 0;
-    if (redundant) { if (cj) launch_cols<true, true>(a, ht, inl, n_tiles, split, s);
-                     else launch_cols<true, false>(a, ht, inl, n_tiles, split, s); }
-    else { if (cj) launch_cols<false, true>(a, ht, inl, n_tiles, split, s);
-           else launch_cols<false, false>(a, ht, inl, n_tiles, split, s); }
+    if (redundant) { if (cj) launch_cols<true, true>(a, ht, inl, n_tiles, share, s);
+                     else launch_cols<true, false>(a, ht, inl, n_tiles, share, s); }
+    else { if (cj) launch_cols<false, true>(a, ht, inl, n_tiles, share, s);
+           else launch_cols<false, false>(a, ht, inl, n_tiles, share, s); }
     P2P_LAUNCH_CHECK();
-    if (split) {
+    if (share > 1) {
         const int64_t m = a.n * a.nrhs;
-        k_join_parts<<<grid_for(m, 256), 256, 0, s>>>(a.parts, a.perm, m, a.nrhs, reinterpret_cast<double2 *>(a.u));
+        k_join_parts<<<grid_for(m, 256), 256, 0, s>>>(a.parts, share, a.perm, m, a.nrhs, reinterpret_cast<double2 *>(a.u));
         P2P_LAUNCH_CHECK();
     }
     return P2P_OK;

@@ -313,7 +313,7 @@ struct HelmholtzMfmaArgs {
     const double *inst_h;      // per instance: h (FP64 with uploaded parameters)
     int64_t n;                 // points
     double2 *parts;            // [share][n][nrhs] partial results in sorted order of tiles whose offsets
-                               // several workgroups share (two in FP64, helm_split_share in single precision)
+                               // several workgroups share (helm_cols64_share in FP64, else helm_split_share)
     int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies (many columns)
     const int32_t *inst_table; // per instance: table index
     const float *inst_scale;   // per instance: 1/h
@@ -352,6 +352,13 @@ p2p_status launch_prep64(const double *d_kh, const HelmInline &inl, int32_t n_ta
 p2p_status launch_split_prep(const double *d_kh, const HelmInline &inl, int32_t n_tables, int32_t copies,
                              int32_t nrhs, void *blocks, const void *q, const int32_t *perm, int64_t n, void *sorted,
                              hipStream_t s);
+// Workgroups that share the offsets of a tile in FP64 on a card of `cus` CUs;
+// as many as fit, of those that even out the offsets of four wavefronts each.
+constexpr int32_t kMaxSplitTiles = 256;
+inline int32_t helm_cols64_share(int64_t n_tiles, int64_t cus) {
+    const int64_t c = cus < 256 ? cus : 256;
+    return 7 * n_tiles <= c ? 7 : 4 * n_tiles <= c ? 4 : 2 * n_tiles <= cus && n_tiles <= kMaxSplitTiles ? 2 : 1;
+}
 // Workgroups that share the offsets of a half tile of the product for few
 // columns: as many as leave every CU of the card (256) at most one workgroup, up
 // to 4 (27 offsets over eight wavefronts each).  16^3 grid, 2 tiles: product 22

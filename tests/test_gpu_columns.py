@@ -36,7 +36,12 @@ CASES = [
     # two (up to 64) and not, one right-hand side and several
     ([16], [10], 1),
     ([48], [10], 1),
-    ([32], [10], 2),
+    ([32], [10], 2),                        # FP64: 64 tiles, four workgroups each
+    ([24], [10], 3),                        # FP64: 41 tiles, four; 36 and 37 tiles below: seven and four
+    ([12, 24], [10, 6], 2),
+    ([8, 20], [10, 10], 4),
+    ([8], [10], 72),
+    ([8], [10], 74),
     ([32], [10], 3),
     ([32], [10], 4),
     ([32], [10], 5),
