@@ -808,10 +808,10 @@ namespace {
 
 // Everything a Helmholtz evaluation derives from its arguments on the host:
 // the product (few columns, many columns, FP64), the launch shape, the distinct
-// k h values (one set of G blocks each), and the layout of the set-up buffer.  The set-up buffer (the plan)
-// holds the instances' parameters and the G blocks; helm_upload and helm_prep
-// fill it, either on every call (p2p_eval_helmholtz, in the workspace) or once
-// (p2p_helmholtz_prepare, in a caller buffer).
+// k h values (one set of G blocks each), and the layout of the set-up buffer.
+// The set-up buffer (the plan) holds the instances' parameters and the G blocks;
+// helm_upload and helm_prep fill it, either on every call (p2p_eval_helmholtz,
+// in the workspace) or once (p2p_helmholtz_prepare, in a caller buffer).
 constexpr int64_t kWideColumns = 24576;
 struct HelmSetup {
     p2p_precision prec;
@@ -1007,8 +1007,9 @@ p2p_status helm_check_call(const HelmSetup &h, const p2p_tree *tree, const p2p_n
 }
 
 // The evaluation: one launch for the G blocks (`fill`, else the set-up is a
-// filled plan) and the sorted copy of q (GATHER), then one product launch (the work queues' counters are zeroed first; in FP64 few tiles
-// add the join of the two halves of each tile).
+// filled plan) and the sorted copy of q (GATHER), then the product (many
+// columns: after the work queues' counters are zeroed; few tiles: followed by
+// the join of the parts of each tile).
 p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter, char *sorted, double2 *parts,
                     bool fill, const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
                     const void *q, void *u, int32_t conj, hipStream_t s) {

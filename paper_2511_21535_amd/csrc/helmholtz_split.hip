@@ -6,7 +6,7 @@
 // v_mfma_f32_32x32x16_bf16.  What is left out (m l, l m, l l) lies below
 // 2^-23 of the product, as one FP32 rounding does, while the sixteen terms an
 // instruction adds are rounded once instead of eight times: the error against
-// 64 bits of a 64^3 grid is 1.8e-7 where FP32 matrix instructions (three real
+// 64 bits of a 64^3 grid is 1.4e-7 where FP32 matrix instructions (three real
 // products per complex one) leave 2.2e-7.  A BF16 product takes a sixteenth of
 // the FP32 one's time, so six cost 0.38 of it.  Magnitudes below about 1e-33
 // lose their low parts to the subnormal range; infinities and NaN give NaN.
