@@ -220,7 +220,7 @@ struct ColLane {
     int32_t A0, boxes, box, rhs;
 };
 template <bool ONE>
-__device__ inline ColLane col_lane(const ColTile &t, int32_t nrhs, int li) {
+__host__ __device__ inline ColLane col_lane(const ColTile &t, int32_t nrhs, int li) {
     ColLane l;
     if constexpr (ONE) {
         l.A0 = t.leaf0 + static_cast<int32_t>(t.c0);
@@ -232,12 +232,18 @@ __device__ inline ColLane col_lane(const ColTile &t, int32_t nrhs, int li) {
         const int32_t r0 = static_cast<int32_t>(t.c0 - b0 * nrhs);   // < nrhs; r0 + 15 may pass 2^31
         l.A0 = t.leaf0 + static_cast<int32_t>(b0);
         l.boxes = static_cast<int32_t>((static_cast<int64_t>(r0) + t.cnt - 1) / nrhs) + 1;
-        const uint32_t c = static_cast<uint32_t>(r0) + static_cast<uint32_t>(min(li, t.cnt - 1));
+        const uint32_t c = static_cast<uint32_t>(r0) + static_cast<uint32_t>(li < t.cnt ? li : t.cnt - 1);
         l.box = static_cast<int32_t>(c / static_cast<uint32_t>(nrhs));
         l.rhs = static_cast<int32_t>(c - static_cast<uint32_t>(l.box) * static_cast<uint32_t>(nrhs));
     }
     return l;
 }
+
+// The right-hand side of a wavefront's first column where nrhs is a multiple of
+// 16 and its 16 columns are those of one box, from any lane's rhs.  A wavefront
+// past the tile's last column holds that column in every lane; from the start of
+// its group of 16 its loads stay inside the box's rows all the same.
+__host__ __device__ inline int32_t uni_first_rhs(int32_t rhs) { return rhs & ~15; }
 
 }  // namespace
 }  // namespace p2p

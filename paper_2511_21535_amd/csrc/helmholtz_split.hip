@@ -475,7 +475,7 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
             const float2 *qp = nullptr;
             int64_t qs = 0;
             Rsrc qr_;
-            const int rhs0 = __builtin_amdgcn_readfirstlane(cl.rhs);
+            const int rhs0 = __builtin_amdgcn_readfirstlane(uni_first_rhs(cl.rhs));
             const int voff = (8 * kq * nrhs + col) * static_cast<int>(sizeof(float2));
             auto rows_of = [&](int o) {
                 const int64_t row = sm.row[o * cap + cl.box];
