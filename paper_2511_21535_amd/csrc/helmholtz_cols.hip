@@ -17,12 +17,14 @@ namespace {
 // faces of the grid), so every column of an instruction shares the one G_o.
 // Bound by the matrix cores.  It replaced a vector kernel (a wave per box, G
 // from a table in LDS, one pass per right-hand side, bound by the LDS reads of
-// G): 32^3 grid, 8 right-hand sides, FP64: 545 to 56 us per product.
-// v_mfma_f64_16x16x4f64, complex as three real products; lane l supplies
+// G): 32^3 grid, 8 right-hand sides, FP64, forward and backward: 1109
+// to 136 us.
+// v_mfma_f64_16x16x4f64, complex as three real products (one right-hand side)
+// or four; lane l supplies
 // A[l%16][l/16] and B[l/16][l%16], and accumulator register r of lane l holds
 // row l/16 + 4 r (rows interleaved), column l%16.  A workgroup of 4 wavefronts
 // owns a tile; wave w takes the offsets o = w, w + 4, ... for all 64 targets
-// (four row tiles, 12 instructions per k-step of 4 sources) with a deep operand
+// (four row tiles, 12 or 16 instructions per k-step of 4 sources) with a deep operand
 // prefetch, and the four partial products are summed through LDS at the end.
 // The workgroup first maps every (offset, box) to the first row of its sources
 // -- the sorted rows of the neighbour box (gather) or its place in the target's
@@ -118,11 +120,23 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
             Qp = row >= 0 ? src + (row + kq) * nrhs + cl.rhs : zeros;
     };
     int64_t dst[4] = {0, 0, 0, 0};
-    // three real products per complex one: pa = sum Re G Re Q,
-    // pb = sum Im G Im Q, pc = sum (Re G +- Im G)(Re Q + Im Q), the sums formed per k-step
-    f64x4 pa[4], pb[4], pc[4];
+    // One right-hand side: three real products per complex one, pa = sum Re G Re Q,
+    // pb = sum Im G Im Q, pc = sum (Re G +- Im G)(Re Q + Im Q), the sums formed per
+    // k-step.  Several: four, pa and pc the real and the imaginary part: an
+    // imaginary part formed as pc - pa - pb carries the rounding of the real one,
+    // which a caller with real q and a small kh sees (kh 1e-4: 1.1e-12 of Im u,
+    // 3e-16 by four), and spreads an infinity of one part to the other.  They
+    // start anew at every offset and are added to sr and si behind it: a chain of
+    // 128 terms instead of up to 896 (32^3 grid, 8 right-hand sides: 9.4e-16
+    // without, 4.4e-16 with).
+    constexpr int NB = ONE ? 4 : 1, NC = ONE ? 1 : 4;
+    const f64x4 zero = f64x4{0.0, 0.0, 0.0, 0.0};
+    f64x4 pa[4], pb[NB], pc[4], sr[NC], si[NC];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) pa[rt] = pb[rt] = pc[rt] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int rt = 0; rt < 4; ++rt) {
+        pa[rt] = pc[rt] = zero;
+        pb[rt % NB] = sr[rt % NC] = si[rt % NC] = zero;
+    }
     {
         const double2 *Gs[NSL], *Qs[NSL];
 #pragma unroll
@@ -174,27 +188,53 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
                 __builtin_amdgcn_sched_barrier(0);
                 const double2(&gv)[4] = gbuf[st % (kColPrefG + 1)];
                 const double2 q = qbuf[st % (kColPrefQ + 1)];
-                const double qs = q.x + q.y;
+                if constexpr (ONE) {
+                    const double qs = q.x + q.y;
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt) {
-                    const double gs = CONJ ? gv[rt].x - gv[rt].y : gv[rt].x + gv[rt].y;
-                    pa[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].x, q.x, pa[rt], 0, 0, 0);
-                    pb[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].y, q.y, pb[rt], 0, 0, 0);
-                    pc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gs, qs, pc[rt], 0, 0, 0);
+                    for (int rt = 0; rt < 4; ++rt) {
+                        const double gs = CONJ ? gv[rt].x - gv[rt].y : gv[rt].x + gv[rt].y;
+                        pa[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].x, q.x, pa[rt], 0, 0, 0);
+                        pb[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].y, q.y, pb[rt], 0, 0, 0);
+                        pc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gs, qs, pc[rt], 0, 0, 0);
+                    }
+                } else {
+                    // Im G meets -Im q and Re q (G q), or Im q and -Re q (conj(G) q)
+                    const double nr = CONJ ? q.y : -q.y, ni = CONJ ? -q.x : q.x;
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) {
+                        pa[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].x, q.x, kk == 0 ? zero : pa[rt], 0, 0, 0);
+                        pc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].x, q.y, kk == 0 ? zero : pc[rt], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int rt = 0; rt < 4; ++rt) {
+                        pa[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].y, nr, pa[rt], 0, 0, 0);
+                        pc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(gv[rt].y, ni, pc[rt], 0, 0, 0);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (!ONE)
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt) {
+                    sr[rt] += pa[rt];
+                    si[rt] += pc[rt];
+                }
         }
     }
-    // U = G Q: Re = pa - pb, Im = pc - pa - pb; with CONJ (conj G): Re = pa + pb,
-    // Im = pc - pa + pb.  Wave w finishes row tile w from the four waves' partials, in
-    // wave order.
+    // Three products: U = G Q: Re = pa - pb, Im = pc - pa - pb; with CONJ (conj G):
+    // Re = pa + pb, Im = pc - pa + pb.  Wave w finishes row tile w from the four
+    // waves' partials, in wave order.
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            s_red[w][rt][0][r][lane] = CONJ ? pa[rt][r] + pb[rt][r] : pa[rt][r] - pb[rt][r];
-            s_red[w][rt][1][r][lane] = CONJ ? pc[rt][r] - pa[rt][r] + pb[rt][r] : pc[rt][r] - pa[rt][r] - pb[rt][r];
+            if constexpr (ONE) {
+                s_red[w][rt][0][r][lane] = CONJ ? pa[rt][r] + pb[rt][r] : pa[rt][r] - pb[rt][r];
+                s_red[w][rt][1][r][lane] = CONJ ? pc[rt][r] - pa[rt][r] + pb[rt][r] : pc[rt][r] - pa[rt][r] - pb[rt][r];
+            } else {
+                s_red[w][rt][0][r][lane] = sr[rt][r];
+                s_red[w][rt][1][r][lane] = si[rt][r];
+            }
         }
     __syncthreads();
     if (li < cnt) {

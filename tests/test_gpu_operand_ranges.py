@@ -1,0 +1,95 @@
+"""Helmholtz at the edges of the operands' range, each part of the result by
+itself: real and imaginary part of very different size, magnitudes near both
+ends of single precision, infinities.  The reference is the definition in numpy
+(long double, or the stated set of non-finite targets).
+
+Tolerances.  A part sums at most 2 x 1728 products in the working precision, in
+any order, of operands rounded once: within (3456 + 4) u of the sum of the
+products' magnitudes, u the unit roundoff."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_21535_amd import api
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+PI = np.longdouble("3.14159265358979323846264338327950288")
+U = {"fp64": 2.0 ** -53, "fp32": 2.0 ** -24, "fp32_plain": 2.0 ** -24}
+
+
+def _grid(side, kh):
+    """A grid of spacing 1, so that u is not scaled."""
+    t = api.Tree.build_grids([api.Grid(side, 1.0, kh)], device=DEV)
+    return t, t.neighbors()
+
+
+def _sum(side, kh, q, targets, conj=False):
+    """(u, sum of |terms|), each as real and imaginary part, at the targets; q complex or real, [n, nrhs]."""
+    ijk = np.stack([np.arange(side ** 3) % side, np.arange(side ** 3) // side % side, np.arange(side ** 3) // side ** 2], 1)
+    qr, qi = q.real.astype(np.longdouble), q.imag.astype(np.longdouble)
+    out = []
+    for i in targets:
+        near = np.all(np.abs(ijk // 4 - ijk[i] // 4) <= 1, axis=1)
+        near[i] = False
+        d = np.sqrt((((ijk[near] - ijk[i]) ** 2).sum(1)).astype(np.longdouble))
+        a = 1 / (4 * PI * d)
+        gr, gi = (a * np.cos(kh * d))[:, None], (a * np.sin(kh * d) * (-1 if conj else 1))[:, None]
+        x, y = qr[near], qi[near]
+        out.append(((gr * x - gi * y).sum(0), (gr * y + gi * x).sum(0),
+                    (abs(gr * x) + abs(gi * y)).sum(0), (abs(gr * y) + abs(gi * x)).sum(0)))
+    return [np.stack([o[k] for o in out]) for k in range(4)]
+
+
+def _check(u, ref, prec, floor=0.0):
+    tol = (2 * 1728 + 4) * U[prec]
+    for got, want, size in ((u.real, ref[0], ref[2]), (u.imag, ref[1], ref[3])):
+        err = np.abs(got.astype(np.longdouble) - want)
+        assert np.all(err <= tol * size + floor), float((err / (size + 1e-4000)).max())
+
+
+def _targets(side):
+    return np.unique(np.concatenate([np.arange(0, side ** 3, 61), [side ** 3 - 1]]))
+
+
+@pytest.mark.parametrize("nrhs", [2, 8, 17])
+@pytest.mark.parametrize("kh", [0.6, 1e-4, 1e-8])
+def test_fp64_parts_of_unequal_size(kh, nrhs):
+    """Real q and a small kh: Im u is kh times smaller than Re u, and as accurate."""
+    side = 12
+    print(f"case fp64 parts kh={kh} nrhs={nrhs}", flush=True)
+    t, nb = _grid(side, kh)
+    rng = np.random.default_rng(nrhs)
+    tg = _targets(side)
+    for q in (rng.standard_normal((side ** 3, nrhs)) + 0j, 1j * rng.standard_normal((side ** 3, nrhs))):
+        gq = torch.as_tensor(q, device=DEV)
+        red = api.restructure(t, nb, [gq], prec="fp64", nrhs=nrhs)
+        for u in (api.helmholtz(t, nb, gq, prec="fp64"),
+                  api.helmholtz(t, nb, None, layout="redundant", prec="fp64", red=red)):
+            _check(u.cpu().numpy()[tg], _sum(side, kh, q, tg), "fp64")
+        _check(api.helmholtz_adjoint(t, nb, gq, prec="fp64", conjugate=True).cpu().numpy()[tg],
+               _sum(side, kh, q, tg, conj=True), "fp64")
+
+
+def _near(side, i):
+    ijk = np.stack([np.arange(side ** 3) % side, np.arange(side ** 3) // side % side, np.arange(side ** 3) // side ** 2], 1)
+    near = np.all(np.abs(ijk // 4 - ijk[i] // 4) <= 1, axis=1)
+    return near
+
+
+@pytest.mark.parametrize("nrhs", [2, 32])
+def test_fp64_infinity_stays_an_infinity(nrhs):
+    """An infinite real part of one source: Re and Im of every other target it reaches are infinite, none NaN (G of the
+    point itself is zero), and targets of other boxes and columns are untouched."""
+    side, i = 16, 77
+    print(f"case fp64 infinity nrhs={nrhs}", flush=True)
+    t, nb = _grid(side, 0.6)
+    q = torch.randn(side ** 3, nrhs, dtype=torch.float64, device=DEV).to(torch.complex128)
+    q[i, 0] = complex(float("inf"), 0.0)
+    u = torch.view_as_real(api.helmholtz(t, nb, q, prec="fp64")).cpu().numpy()
+    near = _near(side, i)
+    other = near.copy()
+    other[i] = False
+    assert np.all(np.isinf(u[other, 0])) and np.all(np.isnan(u[i, 0]))
+    assert np.all(np.isfinite(u[~near])) and np.all(np.isfinite(u[:, 1:]))
