@@ -332,8 +332,8 @@ p2p_status p2p_eval_gravity_noalloc(const p2p_tree *tree, const p2p_nbrs *nbrs, 
  * (tile of columns) items in tree order from eight queues in one persistent
  * launch, one queue per XCD over a contiguous eighth of the items, a workgroup
  * whose own queue is empty taking from the others in turn (neighbouring boxes
- * meet in one XCD's L2).  Instances whose k h agree to 1e-12 share one set of
- * G blocks.  `tile` (host int32[4], may be NULL = default {4, 1, 32, 1}) is the
+ * meet in one XCD's L2).  Instances whose k h agree (to 1e-12; to one rounding in
+ * FP64 with several right-hand sides) share one set of G blocks.  `tile` (host int32[4], may be NULL = default {4, 1, 32, 1}) is the
  * launch shape of single-precision calls with nrhs a multiple of 32 (at most
  * 2^20) that the autotuner picked: tile[0] = 1, 2 or 4: workgroups of two (1,
  * 2) or four tiles of 32 columns, two wavefronts each; tile[1] = workgroups per

@@ -871,14 +871,19 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
         if ((h->rhs_tile != 32 && h->rhs_tile != 64) || nrhs % h->rhs_tile != 0)
             return fail(P2P_EINVAL, "tile[2] (RHS tile) must be 32 or 64 and divide nrhs");
     }
-    // distinct k h values share one set of unit-spacing G blocks (relative tolerance 1e-12)
+    // Instances share one set of unit-spacing G blocks where their k h differ by so
+    // little that the phases k h r (r < 12.2) agree to the precision: in FP64
+    // within one rounding of k h (one right-hand side: 1e-12 of it), in single
+    // precision within 1e-12 of it and 1e-10 in all.
+    const double rel = h->fp64 && nrhs > 1 ? 0x1p-52 : 1e-12, most = h->fp64 ? HUGE_VAL : 1e-10;
     h->itab.resize(n_grids);
     h->iscale.resize(n_grids);
     for (int32_t g = 0; g < n_grids; ++g) {
         const double kh = grids[g].k * grids[g].h;
+        const double near = std::fmin(rel * std::fmax(kh, 1e-300), most);
         int32_t t = -1;
         for (size_t j = 0; j < h->khs.size(); ++j)
-            if (std::fabs(h->khs[j] - kh) <= 1e-12 * std::fmax(std::fabs(kh), 1e-300) || h->khs[j] == kh) {
+            if (std::fabs(h->khs[j] - kh) <= near || h->khs[j] == kh) {
                 t = static_cast<int32_t>(j);
                 break;
             }

@@ -93,3 +93,17 @@ def test_fp64_infinity_stays_an_infinity(nrhs):
     other[i] = False
     assert np.all(np.isinf(u[other, 0])) and np.all(np.isnan(u[i, 0]))
     assert np.all(np.isfinite(u[~near])) and np.all(np.isfinite(u[:, 1:]))
+
+
+@pytest.mark.parametrize("prec,nrhs,kh,dk", [("fp64", 2, 40.0, 9e-13), ("fp32", 3, 3e7, 9e-13)])
+def test_media_that_differ_little(prec, nrhs, kh, dk):
+    """Two grids whose k h differ by less than 1e-12: each gets its own phases, as accurate as alone (the same bits)."""
+    print(f"case two media {prec} kh={kh}", flush=True)
+    side, khs = 8, (kh, kh * (1 + dk))
+    q = torch.randn(2 * side ** 3, nrhs, dtype=torch.complex128 if prec == "fp64" else torch.complex64, device=DEV)
+    both = api.Tree.build_grids([api.Grid(side, 1.0, k) for k in khs], device=DEV)
+    u = api.helmholtz(both, both.neighbors(), q, prec=prec)
+    for g, k in enumerate(khs):
+        t, nb = _grid(side, k)
+        part = slice(g * side ** 3, (g + 1) * side ** 3)
+        assert torch.equal(u[part], api.helmholtz(t, nb, q[part].contiguous(), prec=prec))
