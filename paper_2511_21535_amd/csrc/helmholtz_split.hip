@@ -406,6 +406,7 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
     const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
     const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, int32_t *__restrict__ counter,
     float2 *__restrict__ u) {
+    using S = typename std::conditional<COMP, double, float>::type;
     constexpr int NT = 128 * W, NL = kWideStage / NT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int32_t s_item;
@@ -534,14 +535,12 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
             const floatx4 zero = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int rt = 0; rt < 4; ++rt) re[rt] = im[rt] = zero;
-            constexpr int CN = COMP ? 4 : 1;
-            double cr[4][CN], ci[4][CN];
-            if constexpr (COMP) {
+            // the sums over the offsets, each offset's products starting anew
+            S cr[4][4], ci[4][4];
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt)
+            for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) cr[rt][r] = ci[rt][r] = 0.0;
-            }
+                for (int r = 0; r < 4; ++r) cr[rt][r] = ci[rt][r] = 0;
             auto mfma = [](const u32x4 &x, const u32x4 &y, const floatx4 &c) {
                 return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x),
                                                                __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
@@ -594,7 +593,7 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
                             const u32x4(&gc)[2] = g[pair % 3];
 #pragma unroll
                             for (int r = 2 - p; r >= 0; --r) {
-                                const bool fresh = COMP && ks == 0 && p == 2;
+                                const bool fresh = ks == 0 && p == 2;
                                 re[rt] = mfma(gc[0], qr[r], fresh ? zero : re[rt]);
                                 im[rt] = mfma(gc[0], qa[r], fresh ? zero : im[rt]);
                                 re[rt] = mfma(gc[1], qb[r], re[rt]);
@@ -608,15 +607,13 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
                     b1 = b2;
                     b2 = t;
                 }
-                if constexpr (COMP) {
 #pragma unroll
-                    for (int rt = 0; rt < 4; ++rt)
+                for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            cr[rt][r] += static_cast<double>(re[rt][r]);
-                            ci[rt][r] += static_cast<double>(im[rt][r]);
-                        }
-                }
+                    for (int r = 0; r < 4; ++r) {
+                        cr[rt][r] += static_cast<S>(re[rt][r]);
+                        ci[rt][r] += static_cast<S>(im[rt][r]);
+                    }
             }
             if (16 * w + col < ct.cnt) {
                 const int32_t t0 = sm.tstart[cl.box];
@@ -625,14 +622,7 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int64_t at = static_cast<int64_t>(perm[t0 + 16 * rt + 4 * kq + r]) * nrhs + cl.rhs;
-                        float x, y;
-                        if constexpr (COMP) {
-                            x = static_cast<float>(cr[rt][r] * ct.sc);
-                            y = static_cast<float>(ci[rt][r] * ct.sc);
-                        } else {
-                            x = re[rt][r] * ct.sc;
-                            y = im[rt][r] * ct.sc;
-                        }
+                        const float x = static_cast<float>(cr[rt][r] * ct.sc), y = static_cast<float>(ci[rt][r] * ct.sc);
                         u[at] = make_float2(x, CONJ ? -y : y);
                     }
             }

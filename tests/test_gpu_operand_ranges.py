@@ -107,3 +107,19 @@ def test_media_that_differ_little(prec, nrhs, kh, dk):
         t, nb = _grid(side, k)
         part = slice(g * side ** 3, (g + 1) * side ** 3)
         assert torch.equal(u[part], api.helmholtz(t, nb, q[part].contiguous(), prec=prec))
+
+
+@pytest.mark.parametrize("nrhs,tile", [(32, (4, 1, 32, 1)), (32, (2, 1, 32, 1)), (911, None)])
+def test_single_precision_sums_of_many_columns(nrhs, tile):
+    """prec "fp32_plain" keeps its sums in single precision: at most 24 roundings within an offset and 27 between them,
+    1.7e-7 of a sum of random terms as independent roundings; half as much again is allowed."""
+    side = 12
+    print(f"case plain sums nrhs={nrhs} tile={tile}", flush=True)
+    t, nb = _grid(side, 0.6)
+    rng = np.random.default_rng(nrhs)
+    q = (rng.standard_normal((side ** 3, nrhs)) + 1j * rng.standard_normal((side ** 3, nrhs))).astype(np.complex64)
+    tg = _targets(side)
+    ref = _sum(side, 0.6, q, tg)
+    u = api.helmholtz(t, nb, torch.as_tensor(q, device=DEV), prec="fp32_plain", tile=tile).cpu().numpy()[tg]
+    for got, want in ((u.real, ref[0]), (u.imag, ref[1])):
+        assert float(np.linalg.norm((got - want).astype(np.float64)) / np.linalg.norm(want.astype(np.float64))) <= 2.6e-7
