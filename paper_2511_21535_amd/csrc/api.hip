@@ -1038,6 +1038,7 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
     a.blocks = b.blocks;
     a.zeros = b.blocks + helm_block_elems(h);
+    a.kh = reinterpret_cast<const double *>(b.params + h.o_kh);
     a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
     a.n = n;
     a.parts = parts;

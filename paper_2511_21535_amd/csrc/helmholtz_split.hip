@@ -8,8 +8,10 @@
 // instruction adds are rounded once instead of eight times: the error against
 // 64 bits of a 64^3 grid is 1.4e-7 where FP32 matrix instructions (three real
 // products per complex one) leave 2.2e-7.  A BF16 product takes a sixteenth of
-// the FP32 one's time, so six cost 0.38 of it.  Magnitudes below about 1e-33
-// lose their low parts to the subnormal range; infinities and NaN give NaN.
+// the FP32 one's time, so six cost 0.38 of it.  The parts do not hold
+// what lies below 2^-133 (q of 1e-36 would be off by 1e-3), a value that rounds
+// to infinity in BF16, nor infinities.  A wavefront whose sums tell of one
+// forms them again on the FP32 matrix cores.
 #include <algorithm>
 #include <type_traits>
 
@@ -20,6 +22,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // The packed conversion as one instruction: from plain casts the compiler
@@ -34,11 +37,176 @@ __device__ inline float bf16_hi(uint32_t v) { return __uint_as_float(v & 0xffff0
 
 // Two values into their three BF16 parts, packed in pairs.  Each difference is
 // exact: what is left after rounding to 8 bits fits in the remaining 16.
-__device__ inline void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
-    h = bf16_pair(a, b);
+__device__ inline void split_rest(float a, float b, uint32_t h, uint32_t &m, uint32_t &l) {
     const float a1 = a - bf16_lo(h), b1 = b - bf16_hi(h);
     m = bf16_pair(a1, b1);
     l = bf16_pair(a1 - bf16_lo(m), b1 - bf16_hi(m));
+}
+__device__ inline void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
+    h = bf16_pair(a, b);
+    split_rest(a, b, h, m, l);
+}
+// The same, the bits of both values added to nz.  In one block with the
+// conversion: by itself the compiler puts the addition off and keeps the values in
+// their registers until then (20 more, with spills).
+__device__ inline void split_pair(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l, uint32_t &nz) {
+    asm("v_cvt_pk_bf16_f32 %0, %2, %3\n\tv_or3_b32 %1, %1, %2, %3" : "=&v"(h), "+v"(nz) : "v"(a), "v"(b));
+    split_rest(a, b, h, m, l);
+}
+// Im G = sin(kh r) / (4 pi r) below what the parts hold, at every distance
+__device__ inline bool unheld_kh(double kh) { return kh > 0.0 && kh < 0x1p-98; }
+
+// A wavefront's sums again on the FP32 matrix cores, which hold every FP32 value
+// and keep an infinite source to the targets that it reaches: over the offsets in
+// `offs`, G from its 148 values (formed here, s_g may be shared by the wavefronts
+// of one table), four real products per complex one, 32 sources at a time added
+// in double.  row[o * cap] is the first source row of this lane's column at offset
+// o; conj: the sums of conj(q), as in the products.  Functions of their own, so
+// that their registers do not count in the products.  With every wavefront taken
+// again (q of 1e-36) a prepared 64^3 call takes 79 us instead of 33, one of 20
+// right-hand sides on 44^3 448 us instead of 147.
+struct RedoSource {
+    const int64_t *row;
+    int cap;
+    const float2 *src, *zeros;
+    int32_t nrhs, rhs;
+    bool conj;
+    // rows of offset o: the first entry and the stride
+    __device__ const float2 *open(int o, int64_t &stride) const {
+        const int64_t first = row[o * cap];
+        stride = first >= 0 ? nrhs : 1;
+        return first >= 0 ? src + first * nrhs + rhs : zeros;
+    }
+};
+__device__ inline void green_values(double kh, float2 *s_g) {
+    for (int dd = threadIdx.x & 63; dd < kDistances; dd += 64) {
+        const double2 v = green(kh, dd);
+        s_g[dd] = make_float2(static_cast<float>(v.x), static_cast<float>(v.y));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// 32 columns, the targets 32 rt + 0..31: out[16][2][64] as k_helm_split_cols holds them.
+template <class S>
+__device__ __attribute__((noinline)) void redo_half_tile(uint32_t offs, double kh, float2 *s_g, RedoSource f, int rt,
+                                                         S *out) {
+    const int lane = threadIdx.x & 63, i = 32 * rt + (lane & 31), half = lane >> 5;
+    green_values(kh, s_g);
+    double sr[16], si[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sr[r] = si[r] = 0.0;
+    for (; offs != 0; offs &= offs - 1) {
+        const int o = __ffs(offs) - 1;
+        int64_t stride;
+        const float2 *q = f.open(o, stride) + half * stride;
+#pragma unroll 1
+        for (int s0 = 0; s0 < 64; s0 += 32) {
+            floatx16 re = floatx16{0}, im = floatx16{0};
+#pragma unroll 4
+            for (int s = s0 + half; s < s0 + 32; s += 2, q += 2 * stride) {
+                const float x = q->x, y = f.conj ? -q->y : q->y;
+                const float2 g = s_g[near_distance(o, s, i)];
+                re = __builtin_amdgcn_mfma_f32_32x32x2f32(g.x, x, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f32_32x32x2f32(g.x, y, im, 0, 0, 0);
+                re = __builtin_amdgcn_mfma_f32_32x32x2f32(g.y, -y, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f32_32x32x2f32(g.y, x, im, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sr[r] += static_cast<double>(re[r]);
+                si[r] += static_cast<double>(im[r]);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        out[(2 * r) * 64 + lane] = static_cast<S>(sr[r]);
+        out[(2 * r + 1) * 64 + lane] = static_cast<S>(si[r]);
+    }
+}
+// 16 columns, all 64 targets, stored (if this lane's column is one) to the
+// caller's rows row_of[target] of u, times sc.
+__device__ __attribute__((noinline)) void redo_columns(uint32_t offs, double kh, float2 *s_g, RedoSource f, bool mine,
+                                                       const int32_t *row_of, float sc, float2 *u) {
+    const int lane = threadIdx.x & 63, col = lane & 15, kq = lane >> 4;
+    green_values(kh, s_g);
+    double sr[16], si[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sr[r] = si[r] = 0.0;
+    for (; offs != 0; offs &= offs - 1) {
+        const int o = __ffs(offs) - 1;
+        int64_t stride;
+        const float2 *q = f.open(o, stride) + kq * stride;
+#pragma unroll 1
+        for (int s0 = 0; s0 < 64; s0 += 32) {
+            floatx4 re[4], im[4];
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) re[rt] = im[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+            for (int s = s0 + kq; s < s0 + 32; s += 4, q += 4 * stride) {
+                const float x = q->x, y = f.conj ? -q->y : q->y;
+#pragma unroll
+                for (int rt = 0; rt < 4; ++rt) {
+                    const float2 g = s_g[near_distance(o, s, 16 * rt + col)];
+                    re[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.x, x, re[rt], 0, 0, 0);
+                    im[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.x, y, im[rt], 0, 0, 0);
+                    re[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.y, -y, re[rt], 0, 0, 0);
+                    im[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(g.y, x, im[rt], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                sr[r] += static_cast<double>(re[r / 4][r % 4]);
+                si[r] += static_cast<double>(im[r / 4][r % 4]);
+            }
+        }
+    }
+    if (!mine) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float x = static_cast<float>(sr[r] * sc), y = static_cast<float>(si[r] * sc);
+        u[static_cast<int64_t>(row_of[16 * (r / 4) + 4 * kq + r % 4]) * f.nrhs + f.rhs] = make_float2(x, f.conj ? -y : y);
+    }
+}
+
+// Whether a wavefront's sums tell of values that the parts do not hold.  What lies
+// below 2^-133, the subnormal spacing of BF16, is lost, and a value that rounds to
+// infinity in BF16 leaves NaN; so a sum of at most 1728 products with |G| < 0.08 is
+// off by less than 2^-127, or NaN.  Sums of 2^-100 and more are good; smaller ones,
+// and columns of which every sum is zero, are not, unless they are sums of
+// nothing: nz_r and nz_i hold the bits of every Re q and Im q (a column's values
+// and sums lie in the 64 / C lanes l, l + C, ... that hold it; with kh = 0 the
+// parts do not mix).  A single zero is good: a target may be the only source, or
+// its terms cancel.
+struct SumBits {
+    uint32_t least = ~0u, most = 0;   // the least nonzero (less one) and the greatest of the magnitudes
+    __device__ void add(float x) {
+        const uint32_t b = __float_as_uint(x) & 0x7fffffffu;
+        least = min(least, b - 1u);
+        most = max(most, b);
+    }
+};
+template <int C, int NR, class S>
+__device__ inline bool sums_unheld(double kh, uint32_t nz_r, uint32_t nz_i, const S (&sr)[NR], const S (&si)[NR]) {
+    SumBits r, i;
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+        r.add(static_cast<float>(sr[k]));
+        i.add(static_cast<float>(si[k]));
+    }
+#pragma unroll
+    for (int d = C; d < 64; d <<= 1) {
+        nz_r |= __shfl_xor(nz_r, d, 64);
+        nz_i |= __shfl_xor(nz_i, d, 64);
+        r.most = max(r.most, static_cast<uint32_t>(__shfl_xor(r.most, d, 64)));
+        i.most = max(i.most, static_cast<uint32_t>(__shfl_xor(i.most, d, 64)));
+    }
+    const uint32_t mix = kh != 0.0 ? ~0u : 0u;
+    auto bad = [&](const SumBits &b, uint32_t nz) {
+        const bool small = b.most == 0 || b.least < ((127u - 100u) << 23) - 1u;
+        return (nz << 1) != 0 && (small || b.most >= (255u << 23));
+    };
+    return __ballot(bad(r, nz_r | (nz_i & mix)) || bad(i, nz_i | (nz_r & mix))) != 0 || unheld_kh(kh);
 }
 
 // G operands of the split products: for table t, copy c, box offset o and run
@@ -126,14 +294,15 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
     const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
-    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, float2 *__restrict__ u,
-    int32_t share, double2 *__restrict__ parts, int64_t entries) {
+    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, const double *__restrict__ kh_dev,
+    float2 *__restrict__ u, int32_t share, double2 *__restrict__ parts, int64_t entries) {
     using S = typename std::conditional<COMP, double, float>::type;
     __shared__ ColMap<kSplitCols> s_map;
     const ColMapView sm = s_map.view();
     // one right-hand side: until the sums, two tiles of Q rows in a wavefront's part
     __shared__ __attribute__((aligned(16))) S s_red[kSplitWaves][16][2][64];
     static_assert(sizeof(s_red[0]) >= 2 * 32 * 16 * sizeof(float2), "Q tiles do not fit");
+    __shared__ float2 s_g[kDistances];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int64_t item = p2pd::xcd_contiguous(blockIdx.x, gridDim.x);
@@ -237,6 +406,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
 #pragma unroll
         for (int p = 0; p < 6; ++p) g[p] = gp[(ks * 2 * 6 + p) * 64];
     };
+    uint32_t nz[2] = {0, 0};   // the bits of every Re q and Im q
     // the h, m, l parts of Re q and Im q (negated with CONJ)
     auto split_q = [&](const float (&v)[16], u32x4 (&q)[6]) {
 #pragma unroll
@@ -249,7 +419,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
                     b = -b;
                 }
                 uint32_t h, m, l;
-                split_pair(a, b, h, m, l);
+                split_pair(a, b, h, m, l, nz[c]);
                 q[3 * c][j] = h;
                 q[3 * c + 1][j] = m;
                 q[3 * c + 2][j] = l;
@@ -257,8 +427,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     };
     const floatx16 zero = floatx16{0};
     floatx16 pa = zero, pb = zero, pc = zero;   // sums of Re Re, Im Im, and Re Im + Im Re
-    constexpr int CN = COMP ? 16 : 1;
-    double cr[CN], ci[CN];
+    S cr[16], ci[16];
     if constexpr (COMP) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) cr[r] = ci[r] = 0.0;
@@ -319,15 +488,25 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
             }
         }
     }
+    if constexpr (!COMP) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            cr[r] = pa[r] - pb[r];
+            ci[r] = pc[r];
+        }
+    }
+    const double kh = table_kh(inl, kh_dev, ct.tab);
+    const bool again = sums_unheld<32>(kh, nz[0], nz[1], cr, ci);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        if constexpr (COMP) {
-            s_red[w][r][0][lane] = cr[r];
-            s_red[w][r][1][lane] = ci[r];
-        } else {
-            s_red[w][r][0][lane] = pa[r] - pb[r];
-            s_red[w][r][1][lane] = pc[r];
-        }
+        s_red[w][r][0][lane] = cr[r];
+        s_red[w][r][1][lane] = ci[r];
+    }
+    if (again) {
+        uint32_t offs = 0;
+        for (int slot = 0; slot < n_slots; ++slot) offs |= 1u << offset_of(slot);
+        const RedoSource f{sm.row + min(cl.box, cl.boxes - 1), kSplitCols, src, zeros, nrhs, cl.rhs, CONJ};
+        redo_half_tile<S>(offs, kh, s_g, f, rt, &s_red[w][0][0][0]);
     }
     __syncthreads();
     if (col < ct.cnt) {
@@ -393,7 +572,6 @@ __global__ __launch_bounds__(256) void k_join_split(const double2 *__restrict__ 
 // (neighbouring boxes meet in one XCD's L2), a workgroup whose own queue is
 // empty taking from the others in turn; counters only grow, so every workgroup
 // ends after at most eight misses.
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int kWideStage = 4 * 6 * 64;    // 16-byte operands of a stage: [run of eight sources][plane][target]
 
 typedef __amdgpu_buffer_rsrc_t Rsrc;
@@ -404,12 +582,13 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int64_t *__restrict__ nbr_start, const int32_t *__restrict__ nbr_idx,
     const int64_t *__restrict__ red_start, const int64_t *__restrict__ red_row, const float2 *__restrict__ src,
     const u32x4 *__restrict__ blocks, int32_t copies, const float2 *__restrict__ zeros,
-    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, int32_t *__restrict__ counter,
-    float2 *__restrict__ u) {
+    const int32_t *__restrict__ inst_table, const float *__restrict__ inst_scale, const double *__restrict__ kh_dev,
+    int32_t *__restrict__ counter, float2 *__restrict__ u) {
     using S = typename std::conditional<COMP, double, float>::type;
     constexpr int NT = 128 * W, NL = kWideStage / NT;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ int32_t s_item;
+    __shared__ float2 s_g[kDistances];
     u32x4 *const sg = reinterpret_cast<u32x4 *>(smem);
     const ColMapView sm = col_map_view(smem + 3 * kWideStage * sizeof(u32x4), cap);
     const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, kq = lane >> 4;
@@ -507,16 +686,17 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
                     v[2 * j + 1] = x.y;
                 }
             };
+            uint32_t nz_r = 0, nz_i = 0;   // the bits of every Re q and Im q
             // parts of Re q, Im q and -Im q
             auto split_q = [&](const float (&v)[16], u32x4 (&qr)[3], u32x4 (&qi)[3], u32x4 (&qn)[3]) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     uint32_t h, m, l;
-                    split_pair(v[4 * j], v[4 * j + 2], h, m, l);
+                    split_pair(v[4 * j], v[4 * j + 2], h, m, l, nz_r);
                     qr[0][j] = h;
                     qr[1][j] = m;
                     qr[2][j] = l;
-                    split_pair(v[4 * j + 1], v[4 * j + 3], h, m, l);
+                    split_pair(v[4 * j + 1], v[4 * j + 3], h, m, l, nz_i);
                     qi[0][j] = h;
                     qi[1][j] = m;
                     qi[2][j] = l;
@@ -536,11 +716,9 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
 #pragma unroll
             for (int rt = 0; rt < 4; ++rt) re[rt] = im[rt] = zero;
             // the sums over the offsets, each offset's products starting anew
-            S cr[4][4], ci[4][4];
+            S cr[16], ci[16];
 #pragma unroll
-            for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) cr[rt][r] = ci[rt][r] = 0;
+            for (int r = 0; r < 16; ++r) cr[r] = ci[r] = 0;
             auto mfma = [](const u32x4 &x, const u32x4 &y, const floatx4 &c) {
                 return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x),
                                                                __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
@@ -611,18 +789,25 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
                 for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        cr[rt][r] += static_cast<S>(re[rt][r]);
-                        ci[rt][r] += static_cast<S>(im[rt][r]);
+                        cr[4 * rt + r] += static_cast<S>(re[rt][r]);
+                        ci[4 * rt + r] += static_cast<S>(im[rt][r]);
                     }
             }
-            if (16 * w + col < ct.cnt) {
-                const int32_t t0 = sm.tstart[cl.box];
+            const double kh = table_kh(inl, kh_dev, ct.tab);
+            const bool again = sums_unheld<16>(kh, nz_r, nz_i, cr, ci);
+            const bool mine = 16 * w + col < ct.cnt;
+            const int32_t *const row_of = perm + sm.tstart[cl.box];
+            if (again) {
+                const RedoSource f{sm.row + cl.box, cap, src, zeros, nrhs, cl.rhs, CONJ};
+                redo_columns(present, kh, s_g, f, mine, row_of, ct.sc, u);
+            } else if (mine) {
 #pragma unroll
                 for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const int64_t at = static_cast<int64_t>(perm[t0 + 16 * rt + 4 * kq + r]) * nrhs + cl.rhs;
-                        const float x = static_cast<float>(cr[rt][r] * ct.sc), y = static_cast<float>(ci[rt][r] * ct.sc);
+                        const int64_t at = static_cast<int64_t>(row_of[16 * rt + 4 * kq + r]) * nrhs + cl.rhs;
+                        const float x = static_cast<float>(cr[4 * rt + r] * ct.sc),
+                                    y = static_cast<float>(ci[4 * rt + r] * ct.sc);
                         u[at] = make_float2(x, CONJ ? -y : y);
                     }
             }
@@ -662,7 +847,7 @@ static void launch_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const 
     k_helm_split_cols<R, C, M, O, SH><<<grid, 64 * kSplitWaves, 0, s>>>(                                        \
         a.key_bits, ht, inl, a.nrhs, a.leaf_start, a.leaf_key, a.perm, a.nbr_start, a.nbr_idx, a.red_start,     \
         a.red_row, a.src, reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,           \
-        a.inst_scale, a.u, share, a.parts, entries)
+        a.inst_scale, a.kh, a.u, share, a.parts, entries)
     if (share > 1) {
         P2P_SPLIT(true);
         k_join_split<<<grid_for(entries, 256), 256, 0, s>>>(a.parts, share, a.perm, entries, a.nrhs, a.u);
@@ -707,7 +892,7 @@ static p2p_status launch_wide(const HelmholtzMfmaArgs &a, const HelmTiles &ht, c
     k<<<grid, 128 * W, lds, s>>>(a.key_bits, ht, inl, a.nrhs, n_tiles, per_item, cap, a.leaf_start, a.leaf_key, a.perm,
                                 a.nbr_start, a.nbr_idx, a.red_start, a.red_row, a.src,
                                 reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,
-                                a.inst_scale, a.counter, a.u);
+                                a.inst_scale, a.kh, a.counter, a.u);
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }

@@ -311,6 +311,7 @@ struct HelmholtzMfmaArgs {
                                // and Im G at [n_tables][copies][27][8 runs of 8 src][6][64 tgt][8]
     const float2 *zeros;       // an absent neighbour's sources: 64 zero entries (double2) in FP64, else 63 + nrhs
     const double *inst_h;      // per instance: h (FP64 with uploaded parameters)
+    const double *kh;          // per table: k h (single precision with uploaded parameters)
     int64_t n;                 // points
     double2 *parts;            // [share][n][nrhs] partial results in sorted order of tiles whose offsets
                                // several workgroups share (helm_cols64_share in FP64, else helm_split_share)

@@ -123,3 +123,74 @@ def test_single_precision_sums_of_many_columns(nrhs, tile):
     u = api.helmholtz(t, nb, torch.as_tensor(q, device=DEV), prec="fp32_plain", tile=tile).cpu().numpy()[tg]
     for got, want in ((u.real, ref[0]), (u.imag, ref[1])):
         assert float(np.linalg.norm((got - want).astype(np.float64)) / np.linalg.norm(want.astype(np.float64))) <= 2.6e-7
+
+
+# single precision: few columns (one right-hand side, several, tiles shared and not), many columns by a launch shape
+# (16 right-hand sides of one box to a wavefront) and by their number (3 right-hand sides do not divide by 16)
+SINGLE = [(16, 1, None), (16, 3, None), (12, 33, None), (12, 32, (4, 1, 32, 1)), (12, 64, (2, 1, 64, 1)), (12, 911, None)]
+
+
+def _close(u, ref, side):
+    """Relative 2.6e-7 (see above) beside the roundings at the subnormal spacing, 2^-150 each, 2 x 1728 a part."""
+    for got, want in ((u.real, ref[0]), (u.imag, ref[1])):
+        err = np.linalg.norm((got.astype(np.longdouble) - want))
+        assert err <= 2.6e-7 * np.linalg.norm(want) + (2 * 1728 * want.size) ** 0.5 * 2.0 ** -150, float(err / np.linalg.norm(want))
+
+
+@pytest.mark.parametrize("side,nrhs,tile", SINGLE)
+@pytest.mark.parametrize("prec", ["fp32", "fp32_plain"])
+def test_small_and_large_magnitudes(side, nrhs, tile, prec):
+    t, nb = _grid(side, 0.6)
+    cols = np.unique(np.linspace(0, nrhs - 1, 24).astype(int))    # compared; nrhs // 2 among them
+    cols = np.union1d(cols, [nrhs // 2])
+    rng = np.random.default_rng(nrhs)
+    base = rng.standard_normal((side ** 3, nrhs)) + 1j * rng.standard_normal((side ** 3, nrhs))
+    tg = _targets(side)
+    ramp = 2.0 ** -(np.arange(side ** 3) // side ** 2 * (150.0 / side))[:, None]      # 1 to 2^-150 across the grid
+    huge = np.ones((side ** 3, nrhs))
+    huge[side ** 3 // 2, nrhs // 2] = 3.4e38 / abs(base[side ** 3 // 2, nrhs // 2])   # rounds up in BF16
+    for name, scale in [("2^-%d" % e, 2.0 ** -e) for e in (100, 108, 114, 120, 126, 136)] + [("ramp", ramp), ("huge", huge)]:
+        print(f"case magnitudes side={side} nrhs={nrhs} tile={tile} {prec} {name}", flush=True)
+        q = (base * scale).astype(np.complex64)
+        gq = torch.as_tensor(q if nrhs > 1 else q[:, 0].copy(), device=DEV)
+        ref = _sum(side, 0.6, q[:, cols], tg)
+        red = api.restructure(t, nb, [gq], prec=prec, nrhs=nrhs)
+        for u in (api.helmholtz(t, nb, gq, prec=prec, tile=tile),
+                  api.helmholtz(t, nb, None, layout="redundant", prec=prec, red=red, tile=tile)):
+            u = u.cpu().numpy().reshape(side ** 3, nrhs)[tg][:, cols]
+            _close(u, ref, side)
+            if name == "ramp":   # the targets far below the largest source, by themselves
+                for z in range(0, side, 4):
+                    low = (tg // side ** 2) // 4 == z // 4
+                    _close(u[low], [r[low] for r in ref], side)
+        if tile is None:
+            u = api.helmholtz_adjoint(t, nb, gq, prec=prec, conjugate=True).cpu().numpy().reshape(side ** 3, nrhs)[tg]
+            _close(u[:, cols], _sum(side, 0.6, q[:, cols], tg, conj=True), side)
+
+
+@pytest.mark.parametrize("side,nrhs,tile", SINGLE)
+def test_single_precision_infinity_stays_an_infinity(side, nrhs, tile):
+    print(f"case fp32 infinity side={side} nrhs={nrhs} tile={tile}", flush=True)
+    t, nb = _grid(side, 0.6)
+    i = 77
+    q = torch.view_as_complex(torch.randn(side ** 3, nrhs, 2, device=DEV))
+    q[i, 0] = complex(float("inf"), 0.0)
+    u = api.helmholtz(t, nb, q if nrhs > 1 else q[:, 0].contiguous(), prec="fp32", tile=tile)
+    u = torch.view_as_real(u).reshape(side ** 3, nrhs, 2).cpu().numpy()
+    near = _near(side, i)
+    other = near.copy()
+    other[i] = False
+    assert np.all(np.isinf(u[other, 0])) and np.all(np.isnan(u[i, 0]))
+    assert np.all(np.isfinite(u[~near])) and np.all(np.isfinite(u[:, 1:]))
+
+
+@pytest.mark.parametrize("side,nrhs,tile", SINGLE)
+def test_single_precision_tiny_kh(side, nrhs, tile):
+    """Im G of about 1e-34: real q, each part of u as accurate as the other."""
+    print(f"case fp32 tiny kh side={side} nrhs={nrhs} tile={tile}", flush=True)
+    t, nb = _grid(side, 1e-33)
+    q = np.random.default_rng(nrhs).standard_normal((side ** 3, nrhs)).astype(np.complex64)
+    tg = _targets(side)
+    u = api.helmholtz(t, nb, torch.as_tensor(q if nrhs > 1 else q[:, 0].copy(), device=DEV), prec="fp32", tile=tile)
+    cols = np.unique(np.linspace(0, nrhs - 1, 24).astype(int))
+    _close(u.cpu().numpy().reshape(side ** 3, nrhs)[tg][:, cols], _sum(side, 1e-33, q[:, cols], tg), side)
