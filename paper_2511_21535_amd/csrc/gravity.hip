@@ -468,15 +468,16 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(6))) vo
 // and rounded to float once per staged source, float pair terms summed at
 // most 32 at a time before they are added to double accumulators.
 // Five waves per SIMD: the FP32-mixed form then fits in 96 registers without
-// spills (15% faster than at four).  The FP64 form, bound by its instructions
-// (35 and a division-free reciprocal root a pair) and by the LDS reads of 64
-// bytes a pair, has room for four by its LDS.  Its lane group g takes a run of
-// each tile, unrolled by two, and the pair's factor is collected by powers of
-// w: 2^18 clustered points 397 to 340 us against every G-th source and a factor
-// of 44 instructions.  Two targets a lane, which halve the LDS reads, take 162
-// registers: 376 us.  The partial sums are added by a lane per target and
-// component, as in the forward kernels (leaf cap 16, 2^18 points, FP64 407 to
-// 311 us, FP32-mixed 501 to 252 us against a lane per target).
+// spills (15% faster than at four).  The FP64 form has room for four by its LDS,
+// and its pairs are unrolled by two: 2^18 clustered points 395 to 388 us.  Lane
+// group g takes every G-th source of a tile from the g-th on, a pair's terms are
+// formed before they are added, and the factor is as written above: a run of
+// successive sources per group and the factor collected by powers of w (35
+// instructions instead of 44) take 360 us, with an error against long double of
+// 4.7e-16 instead of 3.8e-16.  Two targets a lane, which halve the LDS reads, take
+// 162 registers: 376 us in that form.  The partial sums are added by a lane per
+// target and component, as in the forward kernels (leaf cap 16, 2^18 points, FP64
+// 420 to 319 us, FP32-mixed 501 to 252 us against a lane per target).
 template <bool PER, bool MIXED>
 __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
     GravityAdjointArgs a) {
@@ -525,8 +526,6 @@ __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
         // ga_j sum_k w^3 m_k: two running sums instead of a difference per pair
         // (FP64 over all sources; FP32_MIXED per group of at most kGFlush pairs)
         double s1x = 0.0, s1y = 0.0, s1z = 0.0, s2 = 0.0;
-        // FP64: the pair's factor is w^3 (m_k gp_j + m_j gp_k + w^2 (m_k 3 ga_j.d - 3 m_j ga_k.d))
-        const double gj3x = 3.0 * gj.y, gj3y = 3.0 * gj.z, gj3z = 3.0 * gj.w, mj3 = 3.0 * pj.w;
         // a periodic source image at x_k + s: both pair directions see the
         // same d = x_j - (x_k + s) (the reverse entry carries -s)
         auto stage = [&](int i, int64_t row, int code) {
@@ -570,25 +569,19 @@ __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
                     oz += fmaf(pj.w, f1z, fmaf(-gj.w, f2, fz));
                 }
             } else {
-                // lane group g takes the run [g chunk, (g + 1) chunk) of the
-                // tile; runs past its end are shorter, all in the last groups
-                const int chunk = (nt + G - 1) / G;
-                const int n = min(chunk, max(0, nt - g * chunk));
-                // the shortest run of the wavefront is its last active lane's
+                const int n = nt > g ? (nt - g + G - 1) / G : 0;
                 const int n_all = __builtin_amdgcn_readlane(n, 63 - __builtin_clzll(__ballot(true)));
-                // the step at the target's own row, whose pair is dropped
-                const int64_t pos = self + tc0 + t - static_cast<int64_t>(g) * chunk;
-                const int selfj = (pos >= 0 && pos < n) ? static_cast<int>(pos) : -1;
-                const Row4d *pp = s_p + g * chunk, *gp = s_g + g * chunk;
+                const int64_t pos = self + tc0 + t;
+                const int selfs = (pos >= 0 && pos < nt) ? static_cast<int>(pos) : -1;
+                const Row4d *pp = s_p + g, *gp = s_g + g;
                 auto pair = [&](const Row4d pk, const Row4d gk, bool own) {
                     const double dx = pj.x - pk.x, dy = pj.y - pk.y, dz = pj.z - pk.z;
                     double w = p2pd::rsqrt_normal(fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2))));
                     w = own ? 0.0 : w;
-                    const double w2 = w * w, w3 = w2 * w;
-                    const double gdj3 = fma(gj3x, dx, fma(gj3y, dy, gj3z * dz));
-                    const double gdk = fma(gk.y, dx, fma(gk.z, dy, gk.w * dz));
-                    const double near = fma(pk.w, gdj3, -(mj3 * gdk)), far = fma(pk.w, gj.x, pj.w * gk.x);
-                    const double cc = w3 * fma(w2, near, far);
+                    const double w3 = w * w * w, w5 = w3 * w * w;
+                    const double gdj = gj.y * dx + gj.z * dy + gj.w * dz;
+                    const double gdk = gk.y * dx + gk.z * dy + gk.w * dz;
+                    const double cc = pk.w * (gj.x * w3 + 3.0 * w5 * gdj) + pj.w * (gk.x * w3 - 3.0 * w5 * gdk);
                     ox = fma(cc, dx, ox);
                     oy = fma(cc, dy, oy);
                     oz = fma(cc, dz, oz);
@@ -596,15 +589,15 @@ __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
                     s1y = fma(w3, gk.z, s1y);
                     s1z = fma(w3, gk.w, s1z);
                     s2 = fma(w3, pk.w, s2);
-                    om = fma(w3, gdk, fma(-gk.x, w, om));
+                    om -= gk.x * w - w3 * gdk;
                 };
-                int j = 0;
-                for (; j + 2 <= n_all; j += 2) {
-                    const Row4d p0 = pp[j], g0 = gp[j], p1 = pp[j + 1], g1 = gp[j + 1];
-                    pair(p0, g0, j == selfj);
-                    pair(p1, g1, j + 1 == selfj);
+                int j = 0, s = g;
+                for (; j + 2 <= n_all; j += 2, s += 2 * G, pp += 2 * G, gp += 2 * G) {
+                    const Row4d p0 = pp[0], g0 = gp[0], p1 = pp[G], g1 = gp[G];
+                    pair(p0, g0, s == selfs);
+                    pair(p1, g1, s + G == selfs);
                 }
-                for (; j < n; ++j) pair(pp[j], gp[j], j == selfj);
+                for (; j < n; ++j, s += G, pp += G, gp += G) pair(pp[0], gp[0], s == selfs);
             }
         };
         for_each_source_tile<false, PER>(A, nullptr, nullptr, a.nbr_start, a.nbr_idx, a.nbr_shift, a.leaf_start,
