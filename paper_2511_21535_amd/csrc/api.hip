@@ -206,6 +206,21 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
     }
     if (tree->cap_leaves < 0) return fail(P2P_EINVAL, "cap_leaves < 0");
 
+    // Few keys are placed by counting.  More are sorted by the top kSortTop
+    // bits, then every run of equal top bits by a count of its keys: four
+    // passes instead of eight for 60-bit keys (the 2^21-point mixture 490 to 240
+    // us for the tree).  Where more than kRunMax points share their top bits (a
+    // cell of 2^-32 of the domain: a Plummer sphere of scale radius 0.005 from
+    // 2^18 points on, the mixture from 2^23) the leaf steps do nothing, the host
+    // learns of it with the counts, and the points of such runs are sorted among
+    // themselves: that sphere with 2^21 points 473 us (500 by eight passes), all
+    // points in a cube of edge 1e-4 434 (512), the mixture of 2^23 848 (1280).
+    // The boxes of a grid are full, so its runs hold up to 2^lo points: all
+    // passes unless those are short.
+    constexpr int kSortTop = 32;
+    const bool few = rank_sort_fits(n);   // the sort by counting writes the counts
+    const int below = sort_bits - kSortTop;
+    const int lo = few || below <= 0 || (!particles && (int64_t(1) << below) > kRunMax) ? 0 : below;
     Arena ar(ws);
     uint64_t *keys = ar.take<uint64_t>(n);
     uint64_t *keys_tmp = ar.take<uint64_t>(n);
@@ -215,6 +230,17 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
     uint8_t *pair_common = ar.take<uint8_t>(n);
     uint8_t *mark = ar.take<uint8_t>(n);
     int32_t *leaf_counts = ar.take<int32_t>(leaf_count_elems(n) + 1);
+    LongRuns lr{};
+    if (lo > 0) {
+        lr.runs = ar.take<int32_t>(run_blocks(n));
+        lr.slots = ar.take<int32_t>(run_blocks(n));
+        lr.run_off = ar.take<int64_t>(run_blocks(n) + 1);
+        lr.slot_off = ar.take<int64_t>(run_blocks(n) + 1);
+        lr.scan = ar.take<int64_t>(scan_ws_elems(run_blocks(n)));
+        lr.keys = ar.take<uint64_t>(n);
+        lr.vals = ar.take<int32_t>(n);
+        lr.slot = ar.take<int32_t>(n);
+    }
     TreeCounts *tc = ar.take<TreeCounts>(1);
     int32_t *d_nside = ar.take<int32_t>(particles ? 1 : n_grids);
     int64_t *d_off = ar.take<int64_t>(particles ? 1 : n_grids);
@@ -237,7 +263,6 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
         tree->max_level = 0;
         return P2P_OK;
     }
-    const bool few = rank_sort_fits(n);   // the sort by counting writes the counts
     if (!few) P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
     if (particles) {
         P2P_TRY(launch_particle_keys(x, y, z, n, keys, few ? nullptr : &tc->bad, s));
@@ -252,32 +277,23 @@ extern "C" p2p_status p2p_build_tree(const double *x, const double *y, const dou
         P2P_HIP(hipMemcpyAsync(d_off, off.data(), n_grids * sizeof(int64_t), hipMemcpyHostToDevice, s));
         P2P_TRY(launch_grid_keys(d_nside, d_off, n_grids, key_bits, n, keys, s));
     }
-    // Few keys are placed by counting.  More are sorted by the top kSortTop
-    // bits, then every run of equal top bits by a count of its keys: four
-    // passes instead of eight for 60-bit keys.  Points so close that more than
-    // kRunMax share their top bits (a cell of 2^-32 of the domain) set
-    // long_run, and the keys take all their passes.
-    constexpr int kSortTop = 32;
-    const int lo = sort_bits > kSortTop && !few ? sort_bits - kSortTop : 0;
     SortBufs sb{keys, keys_tmp, nullptr, vals, vals_tmp};
     if (few)
         P2P_TRY(rank_sort_pairs(sb, n, tc, s));
     else
         P2P_TRY(radix_sort_pairs(sb, n, lo, sort_bits, hist, s));
-    if (lo > 0) P2P_TRY(sort_runs(sb, n, lo, &tc->long_run, s));
+    if (lo > 0) P2P_TRY(sort_runs(sb, n, lo, tc, lr, s));
     TreeCounts host{};
-    for (bool full = lo == 0;; full = true) {
+    for (;;) {
         P2P_TRY(launch_leaf_levels(sb.keys, n, tree->kind, leaf_depth, particles ? leaf_cap : 0, pair_common, mark,
-                                   leaf_counts, s));
-        P2P_TRY(launch_leaf_write(sb.keys, sb.vals, mark, n, tree->kind, tree->cap_leaves, leaf_counts, tc,
+                                   leaf_counts, tc, s));
+        P2P_TRY(launch_leaf_write(sb.keys, sb.vals, mark, n, tree->kind, lr, tree->cap_leaves, leaf_counts, tc,
                                   tree->leaf_start, tree->leaf_key, tree->leaf_level, tree->perm, tree->iperm, s));
         P2P_HIP(hipMemcpyAsync(&host, tc, sizeof(host), hipMemcpyDeviceToHost, s));
         P2P_HIP(hipStreamSynchronize(s));
-        if (host.long_run == 0 || host.bad != 0 || full) break;
-        // equal keys are still in caller order: a full sort from here is stable
+        if (host.long_found == 0 || host.bad != 0) break;
         P2P_HIP(hipMemsetAsync(tc, 0, sizeof(TreeCounts), s));
-        P2P_TRY(radix_sort_pairs(sb, n, 0, lo, hist, s));
-        P2P_TRY(radix_sort_pairs(sb, n, lo, sort_bits, hist, s));
+        P2P_TRY(sort_long_runs(sb, n, lo, lr, host.long_runs, host.long_slots, hist, s));
     }
     const int64_t L = host.n_leaves;
     if (host.bad != 0) {

@@ -69,10 +69,11 @@ size_t scan_ws_elems(int64_t n);
 template <class TI, class TO>
 p2p_status exclusive_scan(const TI *in, TO *out, int64_t n, TO *scratch, hipStream_t s);
 
-// What the tree steps find, cleared before them; max_level and n_leaves are
-// written by launch_leaf_write.
+// What the tree steps find, cleared before them: long_found is set by sort_runs,
+// the others are written by launch_leaf_write: long_runs and long_slots (the runs
+// that sort_runs left, and their keys) if it is set, else max_level and n_leaves.
 struct TreeCounts {
-    int32_t bad, long_run, max_level, n_leaves;
+    int32_t bad, long_found, long_runs, long_slots, max_level, n_leaves;
 };
 
 // Pairs to be sorted: keys/vals hold them, tmp buffers of the same sizes take
@@ -88,7 +89,8 @@ struct SortBufs {
         vals_tmp = old;
     }
 };
-// Sorts by the key bits [lo, hi), stably.  Scratch: radix_hist_elems(n).
+// Sorts by the key bits [lo, hi), stably.  Scratch: radix_hist_elems(n), enough
+// for any number of keys up to n.
 p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s);
 size_t radix_hist_elems(int64_t n);
 // The same by whole keys, one launch, for as many pairs as fit; it also writes
@@ -98,10 +100,23 @@ constexpr uint64_t kBadKey = ~0ull;
 bool rank_sort_fits(int64_t n);
 p2p_status rank_sort_pairs(SortBufs &b, int64_t n, TreeCounts *tc, hipStream_t s);
 // After a sort by the bits from lo up: runs of at most kRunMax equal upper
-// parts into the order of the whole key; a longer run is left and sets
-// *long_run.
-constexpr int kRunMax = 64;
-p2p_status sort_runs(SortBufs &b, int64_t n, int lo, int32_t *long_run, hipStream_t s);
+// parts into the order of the whole key; a longer run is left.  For each kRunBlock
+// slots the runs that were left and begin there, and their slots, go to runs and
+// slots [run_blocks(n)].
+constexpr int kRunMax = 64, kRunBlock = 256;
+__host__ __device__ inline int64_t run_blocks(int64_t n) { return (n + kRunBlock - 1) / kRunBlock; }
+struct LongRuns {
+    int32_t *runs, *slots;           // [run_blocks(n)]
+    int64_t *run_off, *slot_off;     // [run_blocks(n) + 1]: their prefix sums, by sort_long_runs
+    int64_t *scan;                   // scan_ws_elems(run_blocks(n))
+    uint64_t *keys;                  // [n]
+    int32_t *vals, *slot;            // [n], [n]
+};
+p2p_status sort_runs(SortBufs &b, int64_t n, int lo, TreeCounts *tc, const LongRuns &lr, hipStream_t s);
+// The runs that sort_runs left (n_runs, n_slots keys in all) put in order: sorted by
+// (run, key) among themselves.  Scratch: the tmp buffers of b, and hist.
+p2p_status sort_long_runs(SortBufs &b, int64_t n, int lo, const LongRuns &lr, int32_t n_runs, int32_t n_slots,
+                          uint32_t *hist, hipStream_t s);
 
 // Tree construction steps (tree.hip).
 p2p_status launch_particle_keys(const double *x, const double *y, const double *z, int64_t n,
@@ -110,17 +125,19 @@ p2p_status launch_grid_keys(const int32_t *d_n_side, const int64_t *d_point_off,
                             int bits, int64_t n, uint64_t *keys, hipStream_t s);
 // Leaf level of every slot, kLeafFirst added where a leaf starts.  For each
 // kMarkBlock slots, leaf_counts receives the leaves that start in them and,
-// from kDeepShift up, their deepest level (one more entry for the total).
+// from kDeepShift up, their deepest level (one more entry for the total).  Nothing
+// is done while *tc tells of a long run.
 constexpr uint8_t kLeafFirst = 0x80;
 constexpr int kMarkBlock = 256, kDeepShift = 16;
 inline int64_t leaf_count_elems(int64_t n) { return (n + kMarkBlock - 1) / kMarkBlock; }
 p2p_status launch_leaf_levels(const uint64_t *skeys, int64_t n, int kind, int depth, int leaf_cap,
-                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, hipStream_t s);
+                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, const TreeCounts *tc,
+                              hipStream_t s);
 // Leaf arrays, perm and its inverse, unless the points are bad, a long run was
-// left or there are more than cap_leaves leaves; the number of leaves in any
-// case.
+// left (then only its counts are summed) or there are more than cap_leaves leaves;
+// the number of leaves in any case.
 p2p_status launch_leaf_write(const uint64_t *skeys, const int32_t *vals, const uint8_t *mark, int64_t n, int kind,
-                             int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
+                             const LongRuns &lr, int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
                              uint64_t *leaf_key, int8_t *leaf_level, int32_t *perm, int32_t *iperm, hipStream_t s);
 
 // Near lists (nbrs.hip).  Directory over the top bits of the leaf keys (dir:

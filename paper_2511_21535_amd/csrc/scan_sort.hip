@@ -1,6 +1,8 @@
 // Device-wide exclusive scan and stable LSD radix sort of (uint64 key, int32
 // value) pairs.  Both are plain data-movement primitives used by tree
 // binning, near-list construction and the restructure step.
+#include <algorithm>
+
 #include "p2p_internal.h"
 
 namespace p2p {
@@ -381,7 +383,7 @@ __global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__re
         s_key[j] = k;
     }
     bad = __syncthreads_or(bad);
-    if (blockIdx.x == 0 && tid == 0) *tc = TreeCounts{bad != 0 ? 1 : 0, 0, 0, 0};
+    if (blockIdx.x == 0 && tid == 0) *tc = TreeCounts{bad != 0 ? 1 : 0, 0, 0, 0, 0, 0};
     const int i = blockIdx.x * kRankKeys + q;
     const uint64_t key = i < n ? s_key[i] : 0ull;
     int cnt = 0;
@@ -401,40 +403,120 @@ __global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__re
     }
 }
 
+// A slot's run of equal bits from lo up, seen through a window of kRunMax keys on
+// either side of the workgroup's kRunBlock slots (LDS, no key past either end).
+__device__ inline void run_window(const uint64_t *__restrict__ k, int64_t n, uint64_t (&w)[kRunBlock + 2 * kRunMax]) {
+    const int64_t b = static_cast<int64_t>(blockIdx.x) * kRunBlock;
+    for (int i = threadIdx.x; i < kRunBlock + 2 * kRunMax; i += kRunBlock) {
+        const int64_t j = b - kRunMax + i;
+        w[i] = j >= 0 && j < n ? k[j] : ~0ull;   // no key has its top bit set
+    }
+    __syncthreads();
+}
+// Whether the run of window slot me holds more than kRunMax keys; else it is [a, e).
+__device__ inline bool run_is_long(const uint64_t (&w)[kRunBlock + 2 * kRunMax], int me, int lo, int &a, int &e) {
+    const uint64_t top = w[me] >> lo;
+    a = me;
+    e = me + 1;
+    // the same kRunMax slots away: long, without counting it
+    if ((w[me - kRunMax] >> lo) == top || (w[me + kRunMax] >> lo) == top) return true;
+    while ((w[a - 1] >> lo) == top) --a;   // both end inside the window
+    while ((w[e] >> lo) == top) ++e;
+    return e - a > kRunMax;
+}
+// Long slots of the workgroup before this thread's (rank) and in all (total); the
+// slots at which a long run begins, up to this one (begun) and in all (begins).
+struct RunRank {
+    int rank, total, begun, begins;
+};
+__device__ inline RunRank rank_long(bool is_long, bool begin) {
+    __shared__ int s_c[2][kRunBlock / 64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint64_t l = __ballot(is_long), f = __ballot(is_long && begin), below = lanes_below(lane);
+    if (lane == 0) {
+        s_c[0][wv] = __popcll(l);
+        s_c[1][wv] = __popcll(f);
+    }
+    __syncthreads();
+    RunRank r{static_cast<int>(__popcll(l & below)), 0, static_cast<int>(__popcll(f & (below | 1ull << lane))), 0};
+    for (int q = 0; q < kRunBlock / 64; ++q) {
+        if (q < wv) {
+            r.rank += s_c[0][q];
+            r.begun += s_c[1][q];
+        }
+        r.total += s_c[0][q];
+        r.begins += s_c[1][q];
+    }
+    return r;
+}
+
 // Keys sorted by their bits from lo up: puts every run of equal upper bits in
-// order of the whole key, ties in their present order.  A slot finds its run
-// in a window of kRunMax keys on either side, held in LDS, and counts its
-// place.  A run over kRunMax keys is left as it is, and *long_run is set.
-constexpr int kRunBlock = 256;
+// order of the whole key, ties in their present order: a slot counts its place
+// in its run.  A run over kRunMax keys is left as it is and counted.
 __global__ __launch_bounds__(kRunBlock) void k_sort_runs(const uint64_t *__restrict__ kin,
                                                          const int32_t *__restrict__ vin,
                                                          uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
-                                                         int64_t n, int lo, int32_t *__restrict__ long_run) {
+                                                         int64_t n, int lo, TreeCounts *__restrict__ tc, LongRuns lr) {
     __shared__ uint64_t w[kRunBlock + 2 * kRunMax];
-    const int64_t b = static_cast<int64_t>(blockIdx.x) * kRunBlock;
-    const int t = threadIdx.x;
-    for (int k = t; k < kRunBlock + 2 * kRunMax; k += kRunBlock) {
-        const int64_t j = b - kRunMax + k;
-        w[k] = j >= 0 && j < n ? kin[j] : ~0ull;   // no key has its top bit set
+    run_window(kin, n, w);
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kRunBlock + threadIdx.x;
+    const int me = threadIdx.x + kRunMax;
+    const uint64_t key = w[me];
+    bool is_long = false;
+    if (i < n) {
+        int a, e;
+        is_long = run_is_long(w, me, lo, a, e);
+        int64_t p = i;
+        if (!is_long) {
+            int r = a - me;
+            for (int j = a; j < e; ++j) r += w[j] < key || (w[j] == key && j < me) ? 1 : 0;
+            p = i + r;
+        }
+        kout[p] = key;
+        vout[p] = vin[i];
     }
-    __syncthreads();
-    const int64_t i = b + t;
-    if (i >= n) return;
-    const int me = t + kRunMax;
-    const uint64_t key = w[me], top = key >> lo;
-    int a = me, e = me + 1;
-    while (a > me - kRunMax && (w[a - 1] >> lo) == top) --a;
-    while (e <= me + kRunMax && (w[e] >> lo) == top) ++e;   // one key past the longest run on either side
-    int64_t p = i;
-    if (e - a <= kRunMax) {
-        int r = a - me;
-        for (int j = a; j < e; ++j) r += w[j] < key || (w[j] == key && j < me) ? 1 : 0;
-        p = i + r;
-    } else if (*long_run == 0) {
-        *long_run = 1;   // every writer writes the same
+    const RunRank r = rank_long(is_long, (w[me - 1] >> lo) != (key >> lo));
+    if (threadIdx.x == 0) {
+        lr.slots[blockIdx.x] = r.total;
+        lr.runs[blockIdx.x] = r.begins;
+        if (r.total != 0) tc->long_found = 1;   // every writer writes the same
     }
-    kout[p] = key;
-    vout[p] = vin[i];
+}
+
+// The keys of the runs that k_sort_runs left, in order: (number of the run, the
+// bits below lo), their values and slots.  The runs are numbered by their slots, so
+// the keys of a run stay within its slots when they are sorted.
+__global__ __launch_bounds__(kRunBlock) void k_gather_runs(const uint64_t *__restrict__ kin,
+                                                           const int32_t *__restrict__ vin, int64_t n, int lo,
+                                                           LongRuns lr) {
+    __shared__ uint64_t w[kRunBlock + 2 * kRunMax];
+    if (lr.slots[blockIdx.x] == 0) return;   // the same for the whole workgroup
+    run_window(kin, n, w);
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kRunBlock + threadIdx.x;
+    const int me = threadIdx.x + kRunMax;
+    const uint64_t key = w[me];
+    int a, e;
+    const bool is_long = i < n && run_is_long(w, me, lo, a, e);
+    const RunRank r = rank_long(is_long, (w[me - 1] >> lo) != (key >> lo));
+    if (is_long) {
+        const int64_t m = lr.slot_off[blockIdx.x] + r.rank;
+        const uint64_t run = static_cast<uint64_t>(lr.run_off[blockIdx.x] + r.begun - 1);
+        lr.keys[m] = run << lo | (key & ((1ull << lo) - 1ull));
+        lr.vals[m] = vin[i];
+        lr.slot[m] = static_cast<int32_t>(i);
+    }
+}
+
+// Sorted, back to the slots, each of which holds its run's upper bits.
+__global__ __launch_bounds__(kRunBlock) void k_scatter_runs(const uint64_t *__restrict__ ck,
+                                                            const int32_t *__restrict__ cv,
+                                                            const int32_t *__restrict__ slot, int32_t n_slots, int lo,
+                                                            uint64_t *__restrict__ keys, int32_t *__restrict__ vals) {
+    const int64_t m = static_cast<int64_t>(blockIdx.x) * kRunBlock + threadIdx.x;
+    if (m >= n_slots) return;
+    const int32_t i = slot[m];
+    keys[i] = keys[i] >> lo << lo | (ck[m] & ((1ull << lo) - 1ull));
+    vals[i] = cv[m];
 }
 
 // Three launches a pass (counts, scan, scatter), or two where the scatter's
@@ -470,7 +552,12 @@ p2p_status radix_pass(SortBufs &b, int64_t n, int shift, uint32_t *hist, hipStre
 
 }  // namespace
 
-size_t radix_hist_elems(int64_t n) { return static_cast<size_t>(256 * (n > 0 ? sort_tiles(n) : 1) + 256); }
+size_t radix_hist_elems(int64_t n) {
+    if (n <= 0) return 512;
+    // tiles of 1024 keys up to kSmallTileMax, of 4096 beyond: the most of any size up to n
+    const int64_t small = sort_tiles(n < kSmallTileMax ? n : kSmallTileMax);
+    return static_cast<size_t>(256 * std::max(small, sort_tiles(n)) + 256);
+}
 
 p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s) {
     if (n <= 0) return P2P_OK;
@@ -496,11 +583,28 @@ p2p_status rank_sort_pairs(SortBufs &b, int64_t n, TreeCounts *tc, hipStream_t s
     return P2P_OK;
 }
 
-p2p_status sort_runs(SortBufs &b, int64_t n, int lo, int32_t *long_run, hipStream_t s) {
+p2p_status sort_runs(SortBufs &b, int64_t n, int lo, TreeCounts *tc, const LongRuns &lr, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    k_sort_runs<<<grid_for(n, kRunBlock), kRunBlock, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp, n, lo, long_run);
+    k_sort_runs<<<grid_for(n, kRunBlock), kRunBlock, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp, n, lo, tc, lr);
     P2P_LAUNCH_CHECK();
     b.swap();
+    return P2P_OK;
+}
+
+p2p_status sort_long_runs(SortBufs &b, int64_t n, int lo, const LongRuns &lr, int32_t n_runs, int32_t n_slots,
+                          uint32_t *hist, hipStream_t s) {
+    if (n_runs <= 0) return P2P_OK;
+    P2P_TRY((exclusive_scan<int32_t, int64_t>(lr.slots, lr.slot_off, run_blocks(n), lr.scan, s)));
+    P2P_TRY((exclusive_scan<int32_t, int64_t>(lr.runs, lr.run_off, run_blocks(n), lr.scan, s)));
+    k_gather_runs<<<grid_for(n, kRunBlock), kRunBlock, 0, s>>>(b.keys, b.vals, n, lo, lr);
+    P2P_LAUNCH_CHECK();
+    SortBufs c{lr.keys, b.keys_tmp, lr.vals, b.vals_tmp, nullptr};
+    int hi = lo;
+    while ((int64_t(1) << (hi - lo)) < n_runs) ++hi;
+    P2P_TRY(radix_sort_pairs(c, n_slots, 0, hi, hist, s));
+    k_scatter_runs<<<grid_for(n_slots, kRunBlock), kRunBlock, 0, s>>>(c.keys, c.vals, lr.slot, n_slots, lo, b.keys,
+                                                                      b.vals);
+    P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 

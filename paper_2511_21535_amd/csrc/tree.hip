@@ -59,7 +59,9 @@ __device__ inline int common_digits(uint64_t a, uint64_t b) {
     return x == 0 ? 20 : (__clzll(static_cast<long long>(x)) - 4) / 3;
 }
 
-__global__ void k_pair_common(const uint64_t *__restrict__ sk, int64_t n, uint8_t *__restrict__ c) {
+__global__ void k_pair_common(const uint64_t *__restrict__ sk, int64_t n, uint8_t *__restrict__ c,
+                              const TreeCounts *__restrict__ tc) {
+    if (tc->long_found != 0) return;
     int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i + 1 < n) c[i] = static_cast<uint8_t>(common_digits(sk[i], sk[i + 1]));
 }
@@ -92,7 +94,8 @@ __device__ inline void leaf_mark(int64_t i, int64_t n, int l, bool first, uint8_
 // Adaptive levels for any leaf_cap > 0.
 __global__ void k_leaf_level_particles(const uint8_t *__restrict__ c, int64_t n, int depth,
                                        int leaf_cap, uint8_t *__restrict__ mark,
-                                       int32_t *__restrict__ leaf_counts) {
+                                       int32_t *__restrict__ leaf_counts, const TreeCounts *__restrict__ tc) {
+    if (tc->long_found != 0) return;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kMarkBlock + threadIdx.x;
     int l = depth;
     if (i < n) {
@@ -134,15 +137,18 @@ __global__ void k_leaf_level_particles(const uint8_t *__restrict__ c, int64_t n,
 __global__ __launch_bounds__(kMarkBlock) void k_leaf_level_ballot(const uint64_t *__restrict__ sk, int64_t n,
                                                                   int depth, int leaf_cap,
                                                                   uint8_t *__restrict__ mark,
-                                                                  int32_t *__restrict__ leaf_counts) {
+                                                                  int32_t *__restrict__ leaf_counts,
+                                                                  const TreeCounts *__restrict__ tc) {
     __shared__ int8_t cs[256 + 128];   // cs[k] = c[b - 64 + k], -1 past either end
     const int64_t b = static_cast<int64_t>(blockIdx.x) * 256;
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const bool skip = tc->long_found != 0;   // read beside the keys
     for (int k = t; k < 256 + 128; k += 256) {
         const int64_t j = b - 64 + k;
         cs[k] = (j >= 0 && j + 1 < n) ? static_cast<int8_t>(common_digits(sk[j], sk[j + 1])) : int8_t(-1);
     }
     __syncthreads();
+    if (skip) return;
     // this wave's window: c of slots (wave's first) - 64 + k, k < 192, in three registers
     const int c0 = cs[64 * wv + lane], c1 = cs[64 * wv + 64 + lane], c2 = cs[64 * wv + 128 + lane];
     const int sh = lane;   // the lane's own count c[i] sits at window bit 64 + lane
@@ -172,10 +178,12 @@ constexpr int kTileSlots = kMarkBlock;
 __global__ __launch_bounds__(kTileSlots) void k_leaf_level_tile(const uint64_t *__restrict__ sk, int64_t n,
                                                                   int depth, int leaf_cap,
                                                                   uint8_t *__restrict__ mark,
-                                                                  int32_t *__restrict__ leaf_counts) {
+                                                                  int32_t *__restrict__ leaf_counts,
+                                                                  const TreeCounts *__restrict__ tc) {
     extern __shared__ int8_t cs[];   // cs[k] = c[b - leaf_cap + k], k < kTileSlots + 2 leaf_cap
     const int64_t b = static_cast<int64_t>(blockIdx.x) * kTileSlots;
     const int t = threadIdx.x, w = kTileSlots + 2 * leaf_cap;
+    if (tc->long_found != 0) return;
     for (int k = t; k < w; k += kTileSlots) {
         const int64_t j = b - leaf_cap + k;
         cs[k] = (j >= 0 && j + 1 < n) ? static_cast<int8_t>(common_digits(sk[j], sk[j + 1])) : int8_t(-1);
@@ -205,7 +213,9 @@ __global__ __launch_bounds__(kTileSlots) void k_leaf_level_tile(const uint64_t *
 
 __global__ __launch_bounds__(kMarkBlock) void k_leaf_flag_grids(const uint64_t *__restrict__ sk, int64_t n,
                                                                 uint8_t *__restrict__ mark, int box_level,
-                                                                int32_t *__restrict__ leaf_counts) {
+                                                                int32_t *__restrict__ leaf_counts,
+                                                                const TreeCounts *__restrict__ tc) {
+    if (tc->long_found != 0) return;
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kMarkBlock + threadIdx.x;
     leaf_mark(i, n, box_level, i < n && (i == 0 || (sk[i] >> 6) != (sk[i - 1] >> 6)), mark, leaf_counts);
 }
@@ -258,12 +268,40 @@ constexpr int kLeafTile = kWriteBlock * kWriteItems;
 template <bool SCANNED>
 __global__ __launch_bounds__(kWriteBlock) void k_leaf_write(
     const uint64_t *__restrict__ sk, const int32_t *__restrict__ vals, const uint8_t *__restrict__ mark, int64_t n,
-    int kind, int64_t cap_leaves, const int32_t *__restrict__ leaf_counts, int64_t nb, TreeCounts *__restrict__ tc,
+    int kind, LongRuns lr, int64_t cap_leaves, const int32_t *__restrict__ leaf_counts, int64_t nb,
+    TreeCounts *__restrict__ tc,
     int32_t *__restrict__ leaf_start, uint64_t *__restrict__ leaf_key, int8_t *__restrict__ leaf_level,
     int32_t *__restrict__ perm, int32_t *__restrict__ iperm) {
     constexpr int W = kWriteBlock / 64;
     __shared__ int32_t s_w[4][W];
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (tc->long_found != 0) {
+        if (blockIdx.x != 0) return;
+        int32_t r = 0, k = 0;
+        for (int64_t q = t; q < run_blocks(n); q += kWriteBlock) {
+            r += lr.runs[q];
+            k += lr.slots[q];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            r += __shfl_xor(r, o, 64);
+            k += __shfl_xor(k, o, 64);
+        }
+        if (lane == 0) {
+            s_w[0][w] = r;
+            s_w[1][w] = k;
+        }
+        __syncthreads();
+        if (t == 0) {
+            for (int q = 1; q < W; ++q) {
+                r += s_w[0][q];
+                k += s_w[1][q];
+            }
+            tc->long_runs = r;
+            tc->long_slots = k;
+        }
+        return;
+    }
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kLeafTile;
     const int64_t b = i0 / kMarkBlock;   // the first count of this workgroup's slots
     // this thread's slots are consecutive
@@ -321,7 +359,7 @@ __global__ __launch_bounds__(kWriteBlock) void k_leaf_write(
         tc->n_leaves = L;
         if (!SCANNED) tc->max_level = deep;
     }
-    if (tc->bad != 0 || tc->long_run != 0 || L > cap_leaves) return;
+    if (tc->bad != 0 || L > cap_leaves) return;
     if (blockIdx.x == 0 && t == 0) leaf_start[L] = static_cast<int32_t>(n);
 #pragma unroll
     for (int k = 0; k < kWriteItems; ++k)
@@ -361,29 +399,30 @@ p2p_status launch_grid_keys(const int32_t *d_n_side, const int64_t *d_point_off,
 }
 
 p2p_status launch_leaf_levels(const uint64_t *skeys, int64_t n, int kind, int depth, int leaf_cap,
-                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, hipStream_t s) {
+                              uint8_t *pair_common, uint8_t *mark, int32_t *leaf_counts, const TreeCounts *tc,
+                              hipStream_t s) {
     if (n <= 0) return P2P_OK;
     const unsigned g = grid_for(n, kMarkBlock);
     if (kind == P2P_TREE_PARTICLES && leaf_cap <= 64) {
-        k_leaf_level_ballot<<<g, kMarkBlock, 0, s>>>(skeys, n, depth, leaf_cap, mark, leaf_counts);
+        k_leaf_level_ballot<<<g, kMarkBlock, 0, s>>>(skeys, n, depth, leaf_cap, mark, leaf_counts, tc);
     } else if (kind == P2P_TREE_PARTICLES && leaf_cap <= kTileCap) {
         k_leaf_level_tile<<<g, kMarkBlock, kTileSlots + 2 * leaf_cap, s>>>(skeys, n, depth, leaf_cap, mark,
-                                                                           leaf_counts);
+                                                                           leaf_counts, tc);
     } else if (kind == P2P_TREE_PARTICLES) {
         if (n > 1) {
-            k_pair_common<<<grid_for(n - 1, 256), 256, 0, s>>>(skeys, n, pair_common);
+            k_pair_common<<<grid_for(n - 1, 256), 256, 0, s>>>(skeys, n, pair_common, tc);
             P2P_LAUNCH_CHECK();
         }
-        k_leaf_level_particles<<<g, kMarkBlock, 0, s>>>(pair_common, n, depth, leaf_cap, mark, leaf_counts);
+        k_leaf_level_particles<<<g, kMarkBlock, 0, s>>>(pair_common, n, depth, leaf_cap, mark, leaf_counts, tc);
     } else {
-        k_leaf_flag_grids<<<g, kMarkBlock, 0, s>>>(skeys, n, mark, depth, leaf_counts);
+        k_leaf_flag_grids<<<g, kMarkBlock, 0, s>>>(skeys, n, mark, depth, leaf_counts, tc);
     }
     P2P_LAUNCH_CHECK();
     return P2P_OK;
 }
 
 p2p_status launch_leaf_write(const uint64_t *skeys, const int32_t *vals, const uint8_t *mark, int64_t n, int kind,
-                             int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
+                             const LongRuns &lr, int64_t cap_leaves, int32_t *leaf_counts, TreeCounts *tc, int32_t *leaf_start,
                              uint64_t *leaf_key, int8_t *leaf_level, int32_t *perm, int32_t *iperm, hipStream_t s) {
     if (n <= 0) return P2P_OK;
     // beyond this many counts (4M slots) their sum in every workgroup costs more than one launch that scans them
@@ -391,12 +430,12 @@ p2p_status launch_leaf_write(const uint64_t *skeys, const int32_t *vals, const u
     const int64_t nb = leaf_count_elems(n);
     const unsigned g = grid_for(n, kLeafTile);
     if (nb <= kSumCounts) {
-        k_leaf_write<false><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, cap_leaves, leaf_counts, nb, tc,
+        k_leaf_write<false><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, lr, cap_leaves, leaf_counts, nb, tc,
                                                       leaf_start, leaf_key, leaf_level, perm, iperm);
     } else {
         k_leaf_scan<<<1, 1024, 0, s>>>(leaf_counts, nb, tc);
         P2P_LAUNCH_CHECK();
-        k_leaf_write<true><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, cap_leaves, leaf_counts, nb, tc,
+        k_leaf_write<true><<<g, kWriteBlock, 0, s>>>(skeys, vals, mark, n, kind, lr, cap_leaves, leaf_counts, nb, tc,
                                                      leaf_start, leaf_key, leaf_level, perm, iperm);
     }
     P2P_LAUNCH_CHECK();
