@@ -352,7 +352,9 @@ p2p_status p2p_eval_helmholtz(const p2p_tree *tree, const p2p_nbrs *nbrs, const 
  * reused by every box and every call).  A plan holds, in a caller-owned device
  * buffer, what p2p_eval_helmholtz otherwise rebuilds on every call: the
  * instances' parameters, the G blocks of every distinct k h built in double
- * precision (rounded to single on the FP32 paths).  Host struct. */
+ * precision (rounded to single on the FP32 paths).  With more than 4096
+ * distinct k h it holds the parameters, and a call forms the blocks in its
+ * workspace in groups, as p2p_eval_helmholtz does.  Host struct. */
 typedef struct {
     void *buf;            /* in: device buffer, 256-byte aligned; NULL asks for the size */
     size_t bytes;         /* in: size of buf; out (buf == NULL): bytes needed */

@@ -828,6 +828,21 @@ namespace {
 // The set-up buffer (the plan) holds the instances' parameters and the G blocks;
 // helm_upload and helm_prep fill it, either on every call (p2p_eval_helmholtz,
 // in the workspace) or once (p2p_helmholtz_prepare, in a caller buffer).
+//
+// A set of G blocks takes 1.33 MB (single precision) or 1.77 MB.  A call holds at
+// most kCallTables of them, a plan kPlanTables: instances of more distinct k h are
+// taken in groups of successive ones, each group's blocks formed before its product
+// in the place of the last group's.  A plan of more holds the parameters only and
+// forms blocks as a call does.  A group is to fill the card: 1000 grids of side 16
+// with a k h each, one right-hand side, take 1.62 ms in groups of 128, 1.11 of 256,
+// 512 and all at once (1.48 by the FP32 products, 0.9 GB); of side 8 with 3
+// right-hand sides 0.79 ms and 350 MB (0.98 ms by the vector kernel, which held
+// 148 values a grid; FP64 1.16 against 1.02).
+constexpr int32_t kCallTables = 256, kPlanTables = 4096;
+struct HelmGroup {
+    int32_t g0, g1;      // instances
+    int32_t t0, tables;  // its k h values in khs
+};
 constexpr int64_t kWideColumns = 24576;
 struct HelmSetup {
     p2p_precision prec;
@@ -836,9 +851,11 @@ struct HelmSetup {
     int waves_per_wg = 4, wg_per_cu = 1, rhs_tile = 32, copies = 1;
     // 32-column tiles per workgroup of the product for many columns
     int tiles_per_wg() const { return waves_per_wg == 4 ? 4 : 2; }
-    int32_t n_grids = 0, n_tables = 0, n_tiles = 0;
-    std::vector<double> khs;
-    std::vector<int32_t> itab;
+    int32_t n_grids = 0, n_tables = 0, n_tiles = 0;   // n_tables: the most of a group
+    bool resident = true;                             // a plan holds the blocks
+    std::vector<HelmGroup> groups;
+    std::vector<double> khs;                          // group by group
+    std::vector<int32_t> itab;                        // of an instance, in its group
     std::vector<float> iscale;
     std::vector<int32_t> first;   // first tile, then first box, of each instance (and the totals)
     size_t o_kh = 0, o_itab = 0, o_isc = 0, o_first = 0, param_bytes = 0;
@@ -852,7 +869,7 @@ struct HelmSetupBufs {
 };
 
 p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision prec, const p2p_grid *grids,
-                      int32_t n_grids, int32_t nrhs, const int32_t *tile, HelmSetup *h) {
+                      int32_t n_grids, int32_t nrhs, const int32_t *tile, bool plan, HelmSetup *h) {
     P2P_TRY(check_tree(tree));
     if (tree->kind != P2P_TREE_GRIDS) return fail(P2P_EINVAL, "Helmholtz needs a grid tree");
     P2P_TRY(check_nbrs(tree, nbrs));
@@ -894,23 +911,33 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     const double rel = h->fp64 && nrhs > 1 ? 0x1p-52 : 1e-12, most = h->fp64 ? HUGE_VAL : 1e-10;
     h->itab.resize(n_grids);
     h->iscale.resize(n_grids);
-    for (int32_t g = 0; g < n_grids; ++g) {
-        const double kh = grids[g].k * grids[g].h;
-        const double near = std::fmin(rel * std::fmax(kh, 1e-300), most);
-        int32_t t = -1;
-        for (size_t j = 0; j < h->khs.size(); ++j)
-            if (std::fabs(h->khs[j] - kh) <= near || h->khs[j] == kh) {
-                t = static_cast<int32_t>(j);
-                break;
+    auto group = [&](int32_t limit) {   // false if a group is full and plan is set
+        h->groups.assign(1, HelmGroup{0, 0, 0, 0});
+        h->khs.clear();
+        for (int32_t g = 0; g < n_grids; ++g) {
+            const double kh = grids[g].k * grids[g].h;
+            const double near = std::fmin(rel * std::fmax(kh, 1e-300), most);
+            int32_t t0 = h->groups.back().t0, t = t0;
+            const int32_t end = static_cast<int32_t>(h->khs.size());
+            while (t < end && !(std::fabs(h->khs[t] - kh) <= near || h->khs[t] == kh)) ++t;
+            if (t == end) {
+                if (end - t0 == limit) {
+                    if (plan && limit > kCallTables) return false;
+                    h->groups.push_back(HelmGroup{g, g, end, 0});
+                    t0 = end;
+                }
+                h->khs.push_back(kh);
+                ++h->groups.back().tables;
             }
-        if (t < 0) {
-            t = static_cast<int32_t>(h->khs.size());
-            h->khs.push_back(kh);
+            h->itab[g] = t - t0;
+            h->iscale[g] = static_cast<float>(1.0 / grids[g].h);
+            h->groups.back().g1 = g + 1;
         }
-        h->itab[g] = t;
-        h->iscale[g] = static_cast<float>(1.0 / grids[g].h);
-    }
-    h->n_tables = static_cast<int32_t>(h->khs.size());
+        return true;
+    };
+    h->resident = plan && group(kPlanTables / h->copies);
+    if (!h->resident) group(kCallTables / h->copies);
+    for (const HelmGroup &q : h->groups) h->n_tables = q.tables > h->n_tables ? q.tables : h->n_tables;
     // every box of a grid instance is a leaf, instances in order
     int64_t boxes = 0, tiles = 0;
     const int64_t cb = h->fp64 ? kHelmColBoxes : kHelmSplitCols * (h->wide ? h->tiles_per_wg() : 1);
@@ -929,7 +956,7 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     // each instance, the column tiles) travel in one copy: each small copy
     // costs a blit launch, a sizeable part of a call on a small grid
     h->o_kh = 8 * static_cast<size_t>(n_grids);
-    h->o_itab = h->o_kh + 8 * static_cast<size_t>(h->n_tables);
+    h->o_itab = h->o_kh + 8 * h->khs.size();
     h->o_isc = h->o_itab + 4 * static_cast<size_t>(n_grids);
     h->o_first = h->o_isc + 4 * static_cast<size_t>(n_grids);
     h->param_bytes = h->o_first + 4 * h->first.size();
@@ -954,18 +981,23 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     return P2P_OK;
 }
 
-// Size of the G blocks in float2.
-size_t helm_block_elems(const HelmSetup &h) {
-    const size_t sets = static_cast<size_t>(h.n_tables) * h.copies * 27;
+// Size of the G blocks of n_tables sets in float2.
+size_t helm_block_elems(const HelmSetup &h, int32_t n_tables) {
+    const size_t sets = static_cast<size_t>(n_tables) * h.copies * 27;
     if (h.fp64) return sets * 4096 * 2;                                 // double2
     return sets * 8 * 6 * 64 * 2;                                       // 16-byte operands
 }
 
-HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h) {
+// The G blocks of a group and the zero entries after them.
+float2 *helm_take_blocks(Arena &ar, const HelmSetup &h) {
+    return ar.take<float2>(helm_block_elems(h, h.n_tables) + (h.fp64 ? 128 : 63 + static_cast<size_t>(h.nrhs)));
+}
+
+// A plan's buffer, or the set-up part of a call's workspace.
+HelmSetupBufs helm_take(Arena &ar, const HelmSetup &h, bool plan) {
     HelmSetupBufs b;
     b.params = ar.take<char>(h.param_bytes);
-    // the G blocks and the zero entries after them
-    b.blocks = ar.take<float2>(helm_block_elems(h) + (h.fp64 ? 128 : 63 + static_cast<size_t>(h.nrhs)));
+    if (!plan || h.resident) b.blocks = helm_take_blocks(ar, h);
     return b;
 }
 
@@ -978,7 +1010,7 @@ p2p_status helm_upload(const HelmSetup &h, const HelmSetupBufs &b, const p2p_gri
     if (!h.inline_params) {
         std::vector<char> hp(h.param_bytes);
         for (int32_t g = 0; g < h.n_grids; ++g) std::memcpy(hp.data() + 8 * g, &grids[g].h, 8);
-        std::memcpy(hp.data() + h.o_kh, h.khs.data(), 8 * static_cast<size_t>(h.n_tables));
+        std::memcpy(hp.data() + h.o_kh, h.khs.data(), 8 * h.khs.size());
         std::memcpy(hp.data() + h.o_itab, h.itab.data(), 4 * static_cast<size_t>(h.n_grids));
         std::memcpy(hp.data() + h.o_isc, h.iscale.data(), 4 * static_cast<size_t>(h.n_grids));
         std::memcpy(hp.data() + h.o_first, h.first.data(), 4 * h.first.size());
@@ -988,12 +1020,12 @@ p2p_status helm_upload(const HelmSetup &h, const HelmSetupBufs &b, const p2p_gri
     return P2P_OK;
 }
 
-// The launch before the product: the G blocks if `fill` (else the plan holds
+// The launch before a group's product: its G blocks if `fill` (else the plan holds
 // them), and q into sorted order unless `sorted` is null.
-p2p_status helm_prep(const HelmSetup &h, const HelmSetupBufs &b, bool fill, const p2p_tree *tree, const void *q,
-                     char *sorted, hipStream_t s) {
-    const double *d_kh = reinterpret_cast<const double *>(b.params + h.o_kh);
-    const int32_t n_tables = fill ? h.n_tables : 0;
+p2p_status helm_prep(const HelmSetup &h, const HelmSetupBufs &b, const HelmGroup &grp, bool fill, const p2p_tree *tree,
+                     const void *q, char *sorted, hipStream_t s) {
+    const double *d_kh = reinterpret_cast<const double *>(b.params + h.o_kh) + grp.t0;
+    const int32_t n_tables = fill ? grp.tables : 0;
     if (h.fp64) return launch_prep64(d_kh, h.inl, n_tables, b.blocks, q, tree->perm, tree->n, h.nrhs, sorted, s);
     // many columns: the copy is large enough for a launch of its own with the widest units
     P2P_TRY(launch_split_prep(d_kh, h.inl, n_tables, h.copies, h.nrhs, b.blocks, q, tree->perm, tree->n,
@@ -1027,10 +1059,10 @@ p2p_status helm_check_call(const HelmSetup &h, const p2p_tree *tree, const p2p_n
     return P2P_OK;
 }
 
-// The evaluation: one launch for the G blocks (`fill`, else the set-up is a
-// filled plan) and the sorted copy of q (GATHER), then the product (many
-// columns: after the work queues' counters are zeroed; few tiles: followed by
-// the join of the parts of each tile).
+// The evaluation, for each group: one launch for its G blocks (`fill`, else the
+// set-up is a filled plan) and, with the first, the sorted copy of q (GATHER), then
+// the product (many columns: after the work queues' counters are zeroed; few tiles:
+// followed by the join of the parts of each tile).
 p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter, char *sorted, double2 *parts,
                     bool fill, const p2p_tree *tree, const p2p_nbrs *nbrs, const p2p_redundant *red, p2p_layout layout,
                     const void *q, void *u, int32_t conj, hipStream_t s) {
@@ -1039,7 +1071,6 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     const int64_t n = tree->n;
     const int32_t nrhs = h.nrhs;
     const bool tiled = redundant && red->grain > 1;
-    P2P_TRY(helm_prep(h, b, fill, tree, q, redundant ? nullptr : sorted, s));
     const int32_t *d_itab = reinterpret_cast<const int32_t *>(b.params + h.o_itab);
     const float *d_iscale = reinterpret_cast<const float *>(b.params + h.o_isc);
     HelmholtzMfmaArgs a{};
@@ -1053,8 +1084,6 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.red_row = tiled ? red->red_row : nullptr;
     a.src = redundant ? static_cast<const float2 *>(red->planes[0]) : reinterpret_cast<const float2 *>(sorted);
     a.blocks = b.blocks;
-    a.zeros = b.blocks + helm_block_elems(h);
-    a.kh = reinterpret_cast<const double *>(b.params + h.o_kh);
     a.inst_h = h.inline_params ? nullptr : reinterpret_cast<const double *>(b.params);
     a.n = n;
     a.parts = parts;
@@ -1067,10 +1096,21 @@ p2p_status helm_run(const HelmSetup &h, const HelmSetupBufs &b, int32_t *counter
     a.copies = h.copies;
     a.counter = counter;
     const int32_t *first = reinterpret_cast<const int32_t *>(b.params + h.o_first);
-    const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids};
-    if (h.fp64) return launch_helmholtz_cols64(a, ht, h.inl, h.n_tiles, redundant, s);
-    if (!h.wide) return launch_helmholtz_split_cols(a, ht, h.inl, h.n_tiles, redundant, s);
-    return launch_helmholtz_split(a, ht, h.inl, h.n_tiles, redundant, h.tiles_per_wg(), h.wg_per_cu, h.rhs_tile, s);
+    for (const HelmGroup &grp : h.groups) {
+        const bool leads = &grp == h.groups.data();
+        P2P_TRY(helm_prep(h, b, grp, fill, tree, q, redundant || !leads ? nullptr : sorted, s));
+        a.zeros = b.blocks + helm_block_elems(h, grp.tables);
+        a.kh = reinterpret_cast<const double *>(b.params + h.o_kh) + grp.t0;
+        const HelmTiles ht{first, first + h.n_grids + 1, h.n_grids, h.first[grp.g0]};
+        const int32_t n_tiles = h.first[grp.g1] - h.first[grp.g0];
+        if (h.fp64)
+            P2P_TRY(launch_helmholtz_cols64(a, ht, h.inl, n_tiles, redundant, s));
+        else if (!h.wide)
+            P2P_TRY(launch_helmholtz_split_cols(a, ht, h.inl, n_tiles, redundant, s));
+        else
+            P2P_TRY(launch_helmholtz_split(a, ht, h.inl, n_tiles, redundant, h.tiles_per_wg(), h.wg_per_cu, h.rhs_tile, s));
+    }
+    return P2P_OK;
 }
 
 // Per-call scratch of an evaluation beside the set-up: the eight queue counters
@@ -1083,7 +1123,8 @@ void helm_take_call(Arena &ar, const HelmSetup &h, int64_t n, bool redundant, in
     const size_t csize = h.fp64 ? sizeof(double2) : sizeof(float2);
     *counter = h.wide ? ar.take<int32_t>(64) : nullptr;
     *sorted = redundant ? nullptr : ar.take<char>(static_cast<size_t>(n) * h.nrhs * csize);
-    const int32_t share = h.fp64 ? helm_cols64_share(h.n_tiles, 2 * kMaxSplitTiles) : h.wide ? 1 : helm_split_share(h.n_tiles);
+    const int32_t share = h.groups.size() > 1 || h.wide ? 1
+                          : h.fp64 ? helm_cols64_share(h.n_tiles, 2 * kMaxSplitTiles) : helm_split_share(h.n_tiles);
     *parts = share > 1 ? ar.take<double2>(static_cast<size_t>(share) * n * h.nrhs) : nullptr;
 }
 
@@ -1093,10 +1134,10 @@ p2p_status helmholtz_common(const p2p_tree *tree, const p2p_nbrs *nbrs, const p2
                             const int32_t *tile, void *ws, size_t *ws_bytes, hipStream_t s) {
     if (!ws_bytes) return fail(P2P_EINVAL, "ws_bytes must not be NULL");
     HelmSetup h;
-    P2P_TRY(helm_setup(tree, nbrs, prec, grids, n_grids, nrhs, tile, &h));
+    P2P_TRY(helm_setup(tree, nbrs, prec, grids, n_grids, nrhs, tile, false, &h));
     if (layout != P2P_GATHER && layout != P2P_REDUNDANT) return fail(P2P_EINVAL, "bad layout");
     Arena ar(ws);
-    const HelmSetupBufs b = helm_take(ar, h);
+    const HelmSetupBufs b = helm_take(ar, h, false);
     int32_t *counter;
     char *sorted;
     double2 *parts;
@@ -1163,9 +1204,9 @@ extern "C" p2p_status p2p_helmholtz_prepare(const p2p_tree *tree, const p2p_nbrs
     set_error("");
     if (!plan) return fail(P2P_EINVAL, "plan is NULL");
     HelmSetup h;
-    P2P_TRY(helm_setup(tree, nbrs, prec, grids, n_grids, nrhs, tile, &h));
+    P2P_TRY(helm_setup(tree, nbrs, prec, grids, n_grids, nrhs, tile, true, &h));
     Arena ar(plan->buf);
-    const HelmSetupBufs b = helm_take(ar, h);
+    const HelmSetupBufs b = helm_take(ar, h, true);
     if (!plan->buf) {
         plan->bytes = ar.used;
         return P2P_OK;
@@ -1175,7 +1216,7 @@ extern "C" p2p_status p2p_helmholtz_prepare(const p2p_tree *tree, const p2p_nbrs
                                     std::to_string(plan->bytes));
     if ((reinterpret_cast<uintptr_t>(plan->buf) & 255u) != 0) return fail(P2P_EINVAL, "plan->buf must be 256-byte aligned");
     P2P_TRY(helm_upload(h, b, grids, as_stream(stream)));
-    P2P_TRY(helm_prep(h, b, true, tree, nullptr, nullptr, as_stream(stream)));
+    if (h.resident) P2P_TRY(helm_prep(h, b, h.groups[0], true, tree, nullptr, nullptr, as_stream(stream)));
     plan->prec = prec;
     plan->nrhs = nrhs;
     plan->tile[0] = h.waves_per_wg;
@@ -1198,20 +1239,21 @@ extern "C" p2p_status p2p_eval_helmholtz_prepared(const p2p_tree *tree, const p2
     if (layout != P2P_GATHER && layout != P2P_REDUNDANT) return fail(P2P_EINVAL, "bad layout");
     HelmSetup h;
     P2P_TRY(helm_setup(tree, nbrs, static_cast<p2p_precision>(plan->prec), grids, n_grids, plan->nrhs,
-                       plan->tiled ? plan->tile : nullptr, &h));
+                       plan->tiled ? plan->tile : nullptr, true, &h));
     if (helm_fingerprint(h, tree, nbrs, grids) != plan->fingerprint)
         return fail(P2P_EINVAL, "plan was prepared for another tree, grid set, precision, nrhs or tile");
     Arena pa(plan->buf);
-    const HelmSetupBufs b = helm_take(pa, h);
+    HelmSetupBufs b = helm_take(pa, h, true);
     if (plan->bytes < pa.used) return fail(P2P_EINVAL, "plan->bytes smaller than the set-up");
     Arena ar(ws);
+    if (!h.resident) b.blocks = helm_take_blocks(ar, h);
     int32_t *counter;
     char *sorted;
     double2 *parts;
     helm_take_call(ar, h, tree->n, layout == P2P_REDUNDANT, &counter, &sorted, &parts);
     p2p_status st;
     if (ws_query(ws, ws_bytes, ar, &st)) return st;
-    return helm_run(h, b, counter, sorted, parts, false, tree, nbrs, red, layout, q, u, 0, as_stream(stream));
+    return helm_run(h, b, counter, sorted, parts, !h.resident, tree, nbrs, red, layout, q, u, 0, as_stream(stream));
 }
 
 // ------------------------------------------------------------- adjoint ----

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t b = static_cast<int32_t>(blockIdx.x) / H, part = static_cast<int32_t>(blockIdx.x) % H;
-    const ColTile ct = col_tile<kColBoxes>(inl, ht, nrhs, inst_table, nullptr, inst_h, b);
+    const ColTile ct = col_tile<kColBoxes>(inl, ht, nrhs, inst_table, nullptr, inst_h, ht.tile0 + b);
     const int32_t cnt = ct.cnt, tab = ct.tab;
     const double sc64 = ct.sc64;
     const int li = lane & 15, kq = lane >> 4;

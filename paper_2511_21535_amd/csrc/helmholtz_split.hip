@@ -313,7 +313,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) __attribute__((amdgpu_waves_per_e
     }
     const int rt = static_cast<int>(item & 1);
     const ColTile ct = col_tile<kSplitCols>(inl, ht, nrhs, inst_table, inst_scale, nullptr,
-                                            static_cast<int32_t>(item >> 1));
+                                            ht.tile0 + static_cast<int32_t>(item >> 1));
     const int col = lane & 31, half = lane >> 5;
     const ColLane cl = col_lane<ONE>(ct, nrhs, col);
     col_map<RED, 64 * kSplitWaves>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start,
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
         if (tid == 0) ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
         const int32_t tile_end = static_cast<int32_t>(min<int64_t>((item + int64_t(1)) * per_item, n_tiles));
         for (int32_t tile = item * per_item; tile < tile_end; ++tile) {
-            const ColTile ct = col_tile<32 * W>(inl, ht, nrhs, inst_table, inst_scale, nullptr, tile);
+            const ColTile ct = col_tile<32 * W>(inl, ht, nrhs, inst_table, inst_scale, nullptr, ht.tile0 + tile);
             const ColLane cl = col_lane<false>(ct, nrhs, 16 * w + col);
             __syncthreads();   // the map and the stages of the tile before are no longer read
             col_map<RED, NT>(sm, key_bits, cl.A0, cl.boxes, leaf_start, leaf_key, nbr_start, nbr_idx, red_start,
@@ -840,7 +840,7 @@ p2p_status launch_split_prep(const double *d_kh, const HelmInline &inl, int32_t 
 template <bool R, bool C, bool M, bool O>
 static void launch_split(const HelmholtzMfmaArgs &a, const HelmTiles &ht, const HelmInline &inl, int32_t n_tiles,
                          hipStream_t s) {
-    const int32_t share = helm_split_share(n_tiles);
+    const int32_t share = a.parts ? helm_split_share(n_tiles) : 1;
     const int64_t entries = a.n * a.nrhs;
     const unsigned grid = 2u * static_cast<unsigned>(n_tiles) * static_cast<unsigned>(share);
 #define P2P_SPLIT(SH)                                                                                           \

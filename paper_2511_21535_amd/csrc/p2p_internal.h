@@ -330,7 +330,7 @@ struct HelmholtzMfmaArgs {
     const double *inst_h;      // per instance: h (FP64 with uploaded parameters)
     const double *kh;          // per table: k h (single precision with uploaded parameters)
     int64_t n;                 // points
-    double2 *parts;            // [share][n][nrhs] partial results in sorted order of tiles whose offsets
+    double2 *parts;            // null (nothing shared) or [share][n][nrhs] partial results in sorted order of tiles whose offsets
                                // several workgroups share (helm_cols64_share in FP64, else helm_split_share)
     int32_t copies;            // copies of each table; workgroup w reads copy (w / 8) % copies (many columns)
     const int32_t *inst_table; // per instance: table index
@@ -350,6 +350,7 @@ struct HelmTiles {
     const int32_t *tile_first;              // first column tile of each instance, [n_grids + 1]
     const int32_t *leaf_first;              // first box (leaf) of each instance, [n_grids + 1]
     int32_t n_grids;
+    int32_t tile0;                          // the launch's first tile
 };
 struct HelmInline {
     int32_t n_grids;
