@@ -843,7 +843,6 @@ struct HelmGroup {
     int32_t g0, g1;      // instances
     int32_t t0, tables;  // its k h values in khs
 };
-constexpr int64_t kWideColumns = 24576;
 struct HelmSetup {
     p2p_precision prec;
     int32_t nrhs;
@@ -881,14 +880,27 @@ p2p_status helm_setup(const p2p_tree *tree, const p2p_nbrs *nbrs, p2p_precision 
     h->nrhs = nrhs;
     h->n_grids = n_grids;
     h->fp64 = prec == P2P_FP64;
-    // Single precision: from kWideColumns columns on, the product that stages G
-    // in LDS for many columns; below, the one that splits the offsets of 32
-    // columns over eight wavefronts and both row tiles over two workgroups,
-    // which fills the card with fewer columns: 16,384 columns 80-99 us against
-    // 134-138 us, 32,768 columns 174 against 150 us per call.  A launch shape is
-    // for the former.
-    const int64_t columns = tree->n_leaves * static_cast<int64_t>(nrhs);
-    h->wide = !h->fp64 && (tile || columns >= kWideColumns);
+    // Single precision: the product that stages G in LDS for many columns, a
+    // workgroup per CU with 128 columns, or the one that splits the offsets of 32
+    // columns over eight wavefronts and both row tiles over two workgroups, which
+    // fills the card with fewer.  The former takes about the same for every round of
+    // 256 tiles, full or not, the latter a time in proportion to the columns, so
+    // the rounds have to be full to three quarters, several rounds with several
+    // right-hand sides (whose rows the former reads without gaps) to three fifths.
+    // A prepared call with one right-hand side: 24,389 columns 164 us (few) against
+    // 181 (many), 27,000 180 both, 32,768 207 against 184, 35,937 232 against 319,
+    // 46,656 300 against 315, 54,872 347 against 318, 64,000 397 against 332; with
+    // several: 24,334 162 against 156, 26,620 172 against 150, 34,300 182 against
+    // 257, 39,366 262 against 278 (redundant layout 308 against 278), 46,875 312
+    // against 274.  A launch shape is for the former.
+    int64_t columns = 0, wide_tiles = 0;
+    for (int32_t g = 0; g < n_grids; ++g) {
+        const int64_t nb = grids[g].n_side / 4, c = nb * nb * nb * nrhs;
+        columns += c;
+        wide_tiles += (c + 127) / 128;
+    }
+    const int64_t rounds = (wide_tiles + 255) / 256;
+    h->wide = !h->fp64 && (tile || 20 * columns >= (rounds == 1 || nrhs == 1 ? 15 : 12) * rounds * 256 * 128);
     if (tile) {
         if (h->fp64 || nrhs % 32 != 0 || nrhs > (1 << 20))
             return fail(P2P_EINVAL, "tile applies to single precision with nrhs a multiple of 32 up to 2^20");

@@ -153,7 +153,8 @@ __device__ inline ColMapView col_map_view(void *base, int cap) {
 // Fills m for the cnt boxes from leaf A0; called by the whole workgroup (T threads), ends with a
 // barrier.  Each column's list start, key, segment start and first target row
 // come in one round of loads; then the entries, two per thread with their
-// loads issued together: at most 27 per box, so one round covers a tile.
+// loads issued together: at most 27 per box, so a round of 2 T covers the tiles of
+// up to 32 boxes; one of 128 (many columns, one right-hand side) takes four.
 template <bool RED, int T>
 __device__ void col_map(const ColMapView &m, int key_bits, int32_t A0, int32_t cnt, const int32_t *__restrict__ leaf_start,
                         const uint64_t *__restrict__ leaf_key, const int64_t *__restrict__ nbr_start,

@@ -596,12 +596,17 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
     const int xcd = static_cast<int>(blockIdx.x & 7);
     const int64_t items = (n_tiles + per_item - 1) / per_item;
     auto slice = [&](int x) { return items * x / 8; };
-    // thread 0: `ticket` is drawn at the start of an item and looked at after it
+    // thread 0: the next ticket is drawn at the start of an item and looked at after
+    // it while its queue holds more items than there are workgroups to an XCD;
+    // towards the end it would keep an item from a workgroup that is free sooner (a
+    // launch of 203 items by 203 workgroups took two rounds, 260 us instead of 150)
     int sl = 0;
+    bool drawn = true;
     int32_t ticket = tid == 0 ? atomicAdd(&counter[xcd], 1) : 0;
     for (;;) {
         if (tid == 0) {
             int32_t it = -1;
+            if (!drawn) ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
             for (;;) {
                 const int x = (xcd + sl) & 7;
                 if (slice(x) + ticket < slice(x + 1)) {
@@ -616,7 +621,10 @@ __global__ __launch_bounds__(128 * W) __attribute__((amdgpu_waves_per_eu(2))) vo
         __syncthreads();
         const int32_t item = __builtin_amdgcn_readfirstlane(s_item);
         if (item < 0) break;
-        if (tid == 0) ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
+        if (tid == 0) {
+            drawn = slice(((xcd + sl) & 7) + 1) - item > gridDim.x / 8 + 1;
+            if (drawn) ticket = atomicAdd(&counter[(xcd + sl) & 7], 1);
+        }
         const int32_t tile_end = static_cast<int32_t>(min<int64_t>((item + int64_t(1)) * per_item, n_tiles));
         for (int32_t tile = item * per_item; tile < tile_end; ++tile) {
             const ColTile ct = col_tile<32 * W>(inl, ht, nrhs, inst_table, inst_scale, nullptr, ht.tile0 + tile);
@@ -885,10 +893,13 @@ static p2p_status launch_wide(const HelmholtzMfmaArgs &a, const HelmTiles &ht, c
                               int32_t n_tiles, int32_t per_item, unsigned grid, hipStream_t s) {
     // boxes a tile of 32 W columns can touch
     const int32_t cap = static_cast<int32_t>(std::min<int64_t>(32 * W, (32 * W + static_cast<int64_t>(a.nrhs) - 2) / a.nrhs + 1));
-    const size_t lds = 3 * kWideStage * sizeof(u32x4) + col_map_bytes(cap);
+    constexpr size_t ring = 3 * kWideStage * sizeof(u32x4);
+    const size_t lds = ring + col_map_bytes(cap);
     auto *k = k_helm_split<W, R, C, M, U>;
+    // the largest a launch can need: the attribute belongs to the kernel, and threads
+    // with other right-hand sides set it between each other's set and launch
     P2P_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                static_cast<int>(lds)));
+                                static_cast<int>(ring + col_map_bytes(32 * W))));
     k<<<grid, 128 * W, lds, s>>>(a.key_bits, ht, inl, a.nrhs, n_tiles, per_item, cap, a.leaf_start, a.leaf_key, a.perm,
                                 a.nbr_start, a.nbr_idx, a.red_start, a.red_row, a.src,
                                 reinterpret_cast<const u32x4 *>(a.blocks), a.copies, a.zeros, a.inst_table,
