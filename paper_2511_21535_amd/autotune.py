@@ -6,7 +6,7 @@ in memory (the pattern redundancy factor), and the fewest copies within 2% of
 the fastest time are kept.  Each candidate is timed on the
 actual problem with HIP events (one warm-up, then the median of `reps` calls)
 and the fastest is cached in a JSON file keyed by device name, grid sizes,
-nrhs and layout.  The cache path is
+nrhs, layout, precision and the kernel's revision.  The cache path is
 $P2P_AUTOTUNE_CACHE, else ~/.cache/p2p_mi355x_autotune.json.
 """
 from __future__ import annotations
@@ -21,6 +21,10 @@ import torch
 from . import api
 
 CANDIDATES = [(w, c, r) for w in (1, 2, 4) for c in (1, 2, 3, 4, 6, 8) for r in (32, 64)]
+# Stands in the cache key: raised whenever the kernel or the meaning of a shape's
+# entries changes, so that shapes tuned for another kernel are measured again
+# (2: the BF16 product, whose first entry counts pairs of wavefronts).
+REVISION = 2
 # copies of the G blocks (the pattern redundancy factor), tuned on the best shape
 COPIES = (1, 2, 4, 8)
 # a copy count is kept over a smaller one only if it is faster by more than this
@@ -36,7 +40,7 @@ def problem_key(tree: api.Tree, nrhs: int, layout: str, prec: str = "fp32") -> s
     dev = torch.cuda.get_device_name(tree.leaf_start.device)
     sizes = ",".join(str(g.n_side) for g in tree.grids)
     h = hashlib.sha1(sizes.encode()).hexdigest()[:16]
-    return f"{dev}|grids={len(tree.grids)}:{h}|nrhs={nrhs}|{layout}|{prec}"
+    return f"{dev}|grids={len(tree.grids)}:{h}|nrhs={nrhs}|{layout}|{prec}|rev={REVISION}"
 
 
 def _load_cache() -> Dict[str, dict]:
