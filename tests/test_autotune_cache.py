@@ -34,3 +34,9 @@ def test_own_entries_are_kept(monkeypatch, tmp_path):
     (key,) = cache
     tile, _ = _tune(monkeypatch, tmp_path, {key: {"tile": [4, 2, 32, 1], "ms": {}}})
     assert tile == (4, 2, 32, 1)
+
+
+def test_no_launch_is_timed_twice():
+    """Four tiles of 32 columns to a workgroup with a first entry of 4, else two."""
+    shapes = [(4 if w == 4 else 2, c, r) for w, c, r in autotune.CANDIDATES]
+    assert len(set(shapes)) == len(shapes)
