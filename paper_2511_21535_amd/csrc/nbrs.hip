@@ -127,7 +127,6 @@ __device__ inline NbrLeaf nbr_leaf(const NbrTree &t, int64_t A) {
 // the candidates of the ranges before it, its image code (PER).
 struct NbrRanges {
     int32_t lo, pre, code;
-    int K;           // ranges, the same in every lane
     int32_t total;   // candidates, the same in every lane
 };
 
@@ -230,8 +229,7 @@ __device__ NbrRanges order_ranges(bool valid, int32_t lo, int32_t hi, int code, 
     if (tail) s[1][at] = hi;
     wave_sync();
     NbrRanges r;
-    r.K = __popcll(heads);
-    const bool in = lane < r.K;
+    const bool in = lane < __popcll(heads);
     r.lo = in ? s[0][lane] : 0;
     r.code = PER && in ? s[2][lane] : 13;
     const int32_t len = in ? s[1][lane] - r.lo : 0;
@@ -520,7 +518,7 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void k_neighbors_heavy(
     const int64_t *__restrict__ nbr_start, int32_t *__restrict__ nbr_idx, int8_t *__restrict__ nbr_shift) {
     __shared__ int32_t s_r[3][64];                // the ranges: first leaf, prefix, image code
     __shared__ int32_t s_mark[kHeavyWaves][64];
-    __shared__ int32_t s_meta[2];                 // K, total
+    __shared__ int32_t s_total;
     __shared__ int32_t s_cnt[kHeavyWaves];        // listed chunks, then adjacent candidates, per wavefront
     __shared__ int32_t s_occ[kHeavyWaves];        // points of the adjacent candidates (COUNT)
     __shared__ int32_t s_chunk[kSegChunks];
@@ -537,18 +535,14 @@ __global__ __launch_bounds__(64 * kHeavyWaves) void k_neighbors_heavy(
             s_r[0][lane] = r0.lo;
             s_r[1][lane] = r0.pre;
             s_r[2][lane] = r0.code;
-            if (lane == 0) {
-                s_meta[0] = r0.K;
-                s_meta[1] = r0.total;
-            }
+            if (lane == 0) s_total = r0.total;
         }
         __syncthreads();
         NbrRanges r;
         r.lo = s_r[0][lane];
         r.pre = s_r[1][lane];
         r.code = s_r[2][lane];
-        r.K = __builtin_amdgcn_readfirstlane(s_meta[0]);
-        r.total = __builtin_amdgcn_readfirstlane(s_meta[1]);
+        r.total = __builtin_amdgcn_readfirstlane(s_total);
         const int32_t nch = (r.total + kChunk - 1) / kChunk;
         const int64_t out0 = MODE == kNbrFill ? nbr_start[A] : 0;
         int32_t written = 0, occ_sum = 0;

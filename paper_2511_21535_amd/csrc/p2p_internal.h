@@ -93,7 +93,7 @@ struct SortBufs {
 // for any number of keys up to n.
 p2p_status radix_sort_pairs(SortBufs &b, int64_t n, int lo, int hi, uint32_t *hist, hipStream_t s);
 size_t radix_hist_elems(int64_t n);
-// The same by whole keys, one launch, for as many pairs as fit; it also writes
+// The same by whole keys, one launch, for as many pairs as fit whose values are 0..n-1; it also writes
 // the tree's counts: bad if a key is kBadKey (no key of a point has its top bit
 // set), the others zero.
 constexpr uint64_t kBadKey = ~0ull;

@@ -671,18 +671,10 @@ p2p_status launch_tile_copy(const void *q, int64_t row_bytes, const int32_t *lea
     }
 }
 
-template p2p_status launch_permute_rows<double>(const double *, const int32_t *, int64_t, int64_t,
-                                                double *, hipStream_t);
 template p2p_status launch_permute_rows<float2>(const float2 *, const int32_t *, int64_t, int64_t,
                                                 float2 *, hipStream_t);
 template p2p_status launch_permute_rows<double2>(const double2 *, const int32_t *, int64_t, int64_t,
                                                  double2 *, hipStream_t);
-template p2p_status launch_copy_segments<double>(const double *, int64_t, const int32_t *,
-                                                 const int64_t *, const int32_t *, const int64_t *,
-                                                 int64_t, double *, bool, hipStream_t, BoxSegments);
-template p2p_status launch_copy_segments<float>(const float *, int64_t, const int32_t *,
-                                                const int64_t *, const int32_t *, const int64_t *,
-                                                int64_t, float *, bool, hipStream_t, BoxSegments);
 template p2p_status launch_copy_segments<float2>(const float2 *, int64_t, const int32_t *,
                                                  const int64_t *, const int32_t *, const int64_t *,
                                                  int64_t, float2 *, bool, hipStream_t, BoxSegments);

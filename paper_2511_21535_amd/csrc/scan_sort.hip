@@ -153,8 +153,6 @@ p2p_status exclusive_scan(const TI *in, TO *out, int64_t n, TO *scratch, hipStre
     return P2P_OK;
 }
 
-template p2p_status exclusive_scan<int32_t, int32_t>(const int32_t *, int32_t *, int64_t, int32_t *,
-                                                     hipStream_t);
 template p2p_status exclusive_scan<int32_t, int64_t>(const int32_t *, int64_t *, int64_t, int64_t *,
                                                      hipStream_t);
 template p2p_status exclusive_scan<int64_t, int64_t>(const int64_t *, int64_t *, int64_t, int64_t *,
@@ -362,15 +360,14 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     }
 }
 
-// Few pairs: every key's place is the number of keys before it (smaller, or
-// equal and earlier).  A workgroup holds all keys in LDS and places 16 of
+// Few keys (the values are the positions): every key's place is the number of
+// keys before it (smaller, or equal and earlier).  A workgroup holds all keys in LDS and places 16 of
 // them, 64 threads counting for each; n <= kRankSortMax.  4096 keys: 9 us; one
 // workgroup sorting them in LDS by four passes and their runs took 23 us, the
 // 24 launches of eight radix passes 170 us.
 constexpr int kRankKeys = 16;
 constexpr int64_t kRankSortMax = 8192;
 __global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__restrict__ kin,
-                                                            const int32_t *__restrict__ vin,
                                                             uint64_t *__restrict__ kout, int32_t *__restrict__ vout,
                                                             int n, TreeCounts *__restrict__ tc) {
     __shared__ uint64_t s_key[kRankSortMax];
@@ -399,7 +396,7 @@ __global__ __launch_bounds__(kSortThreads) void k_rank_sort(const uint64_t *__re
         int p = 0;
         for (int w = 0; w < kSortWaves; ++w) p += s_cnt[w][q];
         kout[p] = key;
-        vout[p] = vin ? vin[i] : i;
+        vout[p] = i;
     }
 }
 
@@ -575,9 +572,9 @@ bool rank_sort_fits(int64_t n) { return n <= kRankSortMax; }
 
 p2p_status rank_sort_pairs(SortBufs &b, int64_t n, TreeCounts *tc, hipStream_t s) {
     if (n <= 0) return P2P_OK;
-    if (!rank_sort_fits(n)) return fail(P2P_EINVAL, "rank sort: too many keys");
-    k_rank_sort<<<grid_for(n, kRankKeys), kSortThreads, 0, s>>>(b.keys, b.vals, b.keys_tmp, b.vals_tmp,
-                                                               static_cast<int>(n), tc);
+    if (!rank_sort_fits(n) || b.vals) return fail(P2P_EINVAL, "rank sort: too many keys, or values of their own");
+    k_rank_sort<<<grid_for(n, kRankKeys), kSortThreads, 0, s>>>(b.keys, b.keys_tmp, b.vals_tmp, static_cast<int>(n),
+                                                               tc);
     P2P_LAUNCH_CHECK();
     b.swap();
     return P2P_OK;
