@@ -72,13 +72,12 @@ SLOTS_PER_PAIR_MIXED = 3 + 3 + 2 + 3 + 1 + 3        # = 15
 # third-order refinement step to full precision).
 SLOTS_PER_PAIR_FP64 = 3 + 3 + 3 + 1 + 3 + 6         # = 19
 # Gravity adjoint per pair, the VALU instructions hipcc emits in the pair
-# loop without its loop control: FP64 29 arithmetic + 6 for the reciprocal
+# loop without its loop control: FP64 33 arithmetic + 6 for the reciprocal
 # square root (as in the forward count); FP32-mixed 34, with v_rsq_f32 at
 # half rate (one more slot).  The term w^3 (m_j ga_k - m_k ga_j) is summed as
 # two running sums (m_j sum w^3 ga_k - ga_j sum w^3 m_k), which took 8 of the
-# 41 and 42 instructions a per-pair difference needed; in FP64 the pair's
-# factor is collected by powers of w, which took 4 more.
-SLOTS_PER_PAIR_ADJ_FP64 = 29 + 6                     # = 35
+# 41 and 42 instructions a per-pair difference needed.
+SLOTS_PER_PAIR_ADJ_FP64 = 33 + 6                     # = 39
 SLOTS_PER_PAIR_ADJ_MIXED = 34 + 1                    # = 35
 FP32_MFMA_PEAK_TFLOPS = 157.3                        # dense FP32 matrix (published)
 FP64_VALU_PEAK_TFLOPS = 78.6                         # FP64 vector (published)
@@ -1020,7 +1019,7 @@ def run_adjoint_helmholtz(wname, args):
                         "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": a64 / FP64_MFMA_PEAK_TFLOPS,
                         "traffic": None, "algorithmic_per_pair": per_pair,
                         "achieved_8flop_equivalent": a64 * 8.0 / 6.0,
-                        "timed": "the whole adjoint call (sorted copy, G blocks, cleared output, product)"}
+                        "timed": "the whole adjoint call (G blocks and sorted copy, product, join of a tile's parts)"}
     line["roofline_fp32"] = {
         "bound": "mfma", "kernel": "k_helm_split_cols", "achieved": a32, "peak": BF16_MFMA_PEAK_TFLOPS,
         "unit": "TFLOP/s", "frac": a32 / BF16_MFMA_PEAK_TFLOPS, "algorithmic_per_pair": SPLIT_PER_PAIR,

@@ -473,11 +473,13 @@ __global__ __launch_bounds__(kGBlock) __attribute__((amdgpu_waves_per_eu(6))) vo
 // group g takes every G-th source of a tile from the g-th on, a pair's terms are
 // formed before they are added, and the factor is as written above: a run of
 // successive sources per group and the factor collected by powers of w (35
-// instructions instead of 44) take 360 us, with an error against long double of
+// instructions a pair instead of 39) take 360 us, with an error against long double of
 // 4.7e-16 instead of 3.8e-16.  Two targets a lane, which halve the LDS reads, take
 // 162 registers: 376 us in that form.  The partial sums are added by a lane per
 // target and component, as in the forward kernels (leaf cap 16, 2^18 points, FP64
-// 420 to 319 us, FP32-mixed 501 to 252 us against a lane per target).
+// 420 to 319 us, FP32-mixed 501 to 252 us against a lane per target).  By the
+// counters the vector units issue 0.66 of the time and the LDS reads 0.26 of it; the
+// rest the four wavefronts of a SIMD wait, for LDS, a tile's rows and its barriers.
 template <bool PER, bool MIXED>
 __global__ __launch_bounds__(kGBlock, MIXED ? 5 : 4) void k_gravity_adjoint(
     GravityAdjointArgs a) {

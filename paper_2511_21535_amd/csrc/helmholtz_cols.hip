@@ -17,8 +17,8 @@ namespace {
 // faces of the grid), so every column of an instruction shares the one G_o.
 // Bound by the matrix cores.  It replaced a vector kernel (a wave per box, G
 // from a table in LDS, one pass per right-hand side, bound by the LDS reads of
-// G): 32^3 grid, 8 right-hand sides, FP64, forward and backward: 1109
-// to 136 us.
+// G): 32^3 grid, 8 right-hand sides, FP64, forward and backward:
+// 1109 to 136 us.
 // v_mfma_f64_16x16x4f64, complex as three real products (one right-hand side)
 // or four; lane l supplies
 // A[l%16][l/16] and B[l/16][l%16], and accumulator register r of lane l holds
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
 #pragma unroll
         for (int st = 0; st < kColPrefQ; ++st) load_q(st);
         // the rows of the four targets this lane stores at the end: caller-order
-        // rows, or sorted rows in this part's half of `parts`
+        // rows, or sorted rows of this workgroup's part
         if (li < cnt) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -254,8 +254,8 @@ __global__ __launch_bounds__(64 * kColWaves) void k_helm_mfma_cols64(
     }
 }
 
-// u[perm[s]][r] = parts[0][s][r] + parts[1][s][r] for every sorted row s and
-// right-hand side r (m = rows times right-hand sides).
+// u[perm[s]][r] = the sum of parts[p][s][r] over the `share` parts, in order, for
+// every sorted row s and right-hand side r (m = rows times right-hand sides).
 __global__ void k_join_parts(const double2 *__restrict__ parts, int32_t share, const int32_t *__restrict__ perm,
                              int64_t m, int32_t nrhs, double2 *__restrict__ u) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;

@@ -553,19 +553,19 @@ __global__ __launch_bounds__(256) void k_join_split(const double2 *__restrict__ 
 // (v_mfma_f32_16x16x32_bf16): each Q value is then split once per target box,
 // and 32 accumulator and 64 FP64-sum registers leave room for two wavefronts
 // per SIMD, one of which splits, adds and waits while the other multiplies.
-// On the 128-grid, 64-RHS batch the product takes 20.8 ms, 1.27 PFLOP/s of BF16
-// products with the matrix cores busy 0.62 of the cycles at 2.05 GHz (FP32
-// matrix instructions: 26.4 ms).  A wavefront per SIMD with 64 x 32 results and
-// three real products per complex one issues a quarter fewer matrix
-// instructions, but its vector work, eight instructions per matrix instruction,
-// hides behind nothing: 22.3 ms.  Row tiles of 32 over twice the wavefronts
-// split every Q value twice: 24.1 ms.
+// On the 128-grid, 64-RHS batch the product takes 22.0 ms, 1.20 PFLOP/s of BF16
+// products (FP32 matrix instructions: 26.4 ms); under the profiler the matrix cores
+// are busy 0.58 of the cycles at 1.85 GHz.  Compared at 20.8 ms, before the checks
+// of the sums: a wavefront per SIMD with 64 x 32 results and three real products
+// per complex one issues a quarter fewer matrix instructions, but its vector work,
+// eight instructions per matrix instruction, hides behind nothing: 22.3 ms.  Row
+// tiles of 32 over twice the wavefronts split every Q value twice: 24.1 ms.
 // G is staged 32 sources at a time through three LDS buffers: the stage after
 // next is written behind a stage's one barrier and its loads are issued a stage
 // earlier, so a barrier waits for the slowest wavefront only.  The barrier
 // stands at the middle of the stage for the first W wavefronts and at its start
 // for the others, so that the two of a SIMD do not split at the same time
-// (21.6 ms with all at the middle).  G parts are read from LDS two plane pairs
+// (21.6 ms with all at the middle, 20.8 so).  G parts are read from LDS two plane pairs
 // ahead of their products.
 // Items (one tile, or two with 64 right-hand sides per wave) are taken in tree
 // order from eight queues, one per XCD over a contiguous eighth of them
