@@ -183,16 +183,18 @@ def peaks():
     print(json.dumps(res), flush=True)
 
 
-def pmc_traffic(kernel, workload, source):
+def pmc_traffic(kernel, workload, source, tiles=None):
     """HBM bytes per launch of `kernel` on `workload`, from the FETCH_SIZE and
     WRITE_SIZE counter summary kept in profiles/<kernel>_<workload>_hbm_counters.md,
     each counter scaled by what it reads for a plain copy of known size.  The
     summary records the SHA-256 of the kernel's source file when the counters
-    were taken; if that file has changed since, or there is no summary, the
-    traffic is unknown (None)."""
+    were taken; if that file has changed since, or there is no summary (for
+    this many tiles per workgroup, where the launch has them), the traffic is
+    unknown (None)."""
     path = os.path.join(ROOT, "profiles", f"{kernel}_{workload}_hbm_counters.md")
     try:
-        rec = next(json.loads(l.split("record:", 1)[1]) for l in open(path) if l.startswith("record:"))
+        recs = [json.loads(l.split("record:", 1)[1]) for l in open(path) if l.startswith("record:")]
+        rec = next(c for c in recs if c.get("tiles_per_workgroup") == tiles)
     except (OSError, StopIteration, ValueError):
         return None
     with open(os.path.join(ROOT, "paper_2511_21535_amd", "csrc", source), "rb") as f:
@@ -792,7 +794,8 @@ def run_helmholtz(wname, args):
         # redundant rows read once, results written once (complex64), G operands read once
         alg_bytes = S_red * 8 + tree.n * 8 + 27 * 4096 * 12
     ach = flops / t_dom / 1e12
-    traffic = pmc_traffic(kern, wname, src)
+    # tiles of 32 columns per workgroup: tile[0] = 1 and 2 launch the same shape
+    traffic = pmc_traffic(kern, wname, src, tiles=(4 if tile[0] == 4 else 2) if mfma else None)
     roof.update({"kernel": kern, "achieved": ach, "unit": "TFLOP/s", "frac": ach / roof["peak"],
                  "traffic": traffic["bytes"] if traffic else None,
                  "traffic_detail": dict(traffic, algorithmic_bytes=alg_bytes) if traffic else None,

@@ -555,7 +555,7 @@ __global__ __launch_bounds__(256) void k_join_split(const double2 *__restrict__ 
 // per SIMD, one of which splits, adds and waits while the other multiplies.
 // On the 128-grid, 64-RHS batch the product takes 22.0 ms, 1.20 PFLOP/s of BF16
 // products (FP32 matrix instructions: 26.4 ms); under the profiler the matrix cores
-// are busy 0.58 of the cycles at 1.85 GHz.  Compared at 20.8 ms, before the checks
+// are busy 0.60 of the cycles at 1.71 GHz.  Compared at 20.8 ms, before the checks
 // of the sums: a wavefront per SIMD with 64 x 32 results and three real products
 // per complex one issues a quarter fewer matrix instructions, but its vector work,
 // eight instructions per matrix instruction, hides behind nothing: 22.3 ms.  Row
